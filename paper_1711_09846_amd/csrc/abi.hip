@@ -194,6 +194,7 @@ pbt_status make_plan(const pbt_config* c, Plan* pl) {
     if (c->workload == PBT_WL_A2C) pl->o_stage[k++] = w.take(P * 12 * 4);
   }
   pl->fused_small = false;
+  pl->step_scratch_bytes = 0;
   pl->eval_chunk = 0;
   if (gan) {
     if (!bf16 || !adam) return fail(nullptr, PBT_EUNSUPPORTED, "the GAN workload is built for bf16 compute with Adam");
@@ -220,6 +221,8 @@ pbt_status make_plan(const pbt_config* c, Plan* pl) {
                   "fp32 compute is built only for networks whose weights, optimiser state and one mini-batch of "
                   "activations fit the 160 KB LDS of a compute unit; use bf16 compute for larger ones");
     pl->fused_small = true;
+    pl->step_scratch_bytes = w.off;   // (the score's partial sums are no part of a step's working memory)
+    pl->o_evalrow = w.take((size_t)P * fused_small_eval_parts(c->n_eval) * 4);
   } else {
     for (int l = 0; l < L; ++l) {
       const bool head = l == L - 1;
@@ -256,6 +259,7 @@ pbt_status make_plan(const pbt_config* c, Plan* pl) {
     pl->o_evalrow = w.take((size_t)P * c->n_eval * 4);
   }
   pl->scratch_bytes = w.off;
+  if (!pl->step_scratch_bytes) pl->step_scratch_bytes = w.off;
   return PBT_OK;
 }
 
@@ -591,7 +595,6 @@ pbt_status pbt_step(pbt_handle* h, const void* const* d_inputs, int32_t n_inputs
     fill_fused(h, &fa);
     fa.x = x; fa.y = y; fa.n_rows = h->cfg.n_train;
     fa.step0 = (uint32_t)step_index; fa.n_steps = n_steps;
-    fused_small_plan(fa, false);
     PBT_LAUNCH(h, PBT_K_FUSED_STEP, s, fused_small_step(fa, s));
     return PBT_OK;
   }
@@ -605,9 +608,9 @@ pbt_status pbt_step(pbt_handle* h, const void* const* d_inputs, int32_t n_inputs
 pbt_status pbt_step_static(pbt_handle* h, const void* const* d_inputs, int32_t n_inputs, int64_t step_index, int32_t n_steps,
                            void* hip_stream) {
   if (!h) return fail(nullptr, PBT_EINVAL, "handle is NULL");
-  if (h->plan.scratch_bytes > STATIC_SCRATCH_BYTES)
+  if (h->plan.step_scratch_bytes > STATIC_SCRATCH_BYTES)
     return fail(h, PBT_ENOMEM, "pbt_step_static: this configuration needs %zu bytes of working memory, the library's static array holds %zu; use pbt_step",
-                h->plan.scratch_bytes, (size_t)STATIC_SCRATCH_BYTES);
+                h->plan.step_scratch_bytes, (size_t)STATIC_SCRATCH_BYTES);
   char* ptr = nullptr;
   hipError_t e = static_scratch_ptr(&ptr);
   if (e != hipSuccess) return fail(h, PBT_EDEVICE, "pbt_step_static: looking up the static working memory failed: %s", hipGetErrorString(e));
@@ -644,8 +647,7 @@ pbt_status pbt_eval(pbt_handle* h, const void* const* d_inputs, int32_t n_inputs
     FusedSmallArgs fa;
     fill_fused(h, &fa);
     fa.x = x; fa.y = y; fa.n_rows = h->cfg.n_eval;
-    fused_small_plan(fa, true);
-    PBT_HIP(h, fused_small_eval(fa, s));
+    PBT_HIP(h, fused_small_eval(fa, h->sc<float>(h->plan.o_evalrow), s));
     return PBT_OK;
   }
   return eval_bf16(h, x, y, s);

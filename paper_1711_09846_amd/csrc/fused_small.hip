@@ -8,6 +8,7 @@
 // along the features" access patterns are free of bank conflicts.
 #include "common.h"
 #include "internal.h"
+#include "optim_math.h"
 #include "philox.h"
 
 namespace pbt {
@@ -211,11 +212,517 @@ __global__ __launch_bounds__(FS_THREADS) void fused_small_step_kernel(FusedSmall
   }
 }
 
-hipError_t fused_small_step(const FusedSmallArgs& a, hipStream_t s) {
-  const size_t bytes = (size_t)a.lds_total * sizeof(float);
+// ---- tiled form ------------------------------------------------------------------------------------------------
+// The same step with every contraction on the matrix cores (v_mfma_f32_16x16x4_f32: fp32 operands and accumulation).
+// What bounds the plain form below is LDS reads (two per multiply-add) and wavefronts that wait for each other's and the
+// data rows' latencies: 63 us per step of a 32-64-4 network with 64 rows.  Here an operand is read once per 16
+// multiply-adds, every array is padded to whole 16 x 16 blocks (so no loop has a remainder), four wavefronts of their own
+// fetch the rows of step s + 1 while the other eight compute step s, and phases that do not depend on each other share a
+// barrier interval: 2 L barriers per step of an L-layer network.  6.3 us per step (50 steps in one launch: 3.13 -> 0.31 ms);
+// what is left is instruction issue and LDS latency of the chain fragment -> MFMA -> activation -> fragment of each
+// interval.  The optimiser and the number of layers are template parameters: as branches inside the element loops they cost
+// a third of the time, and with the rows' loads in the computing wavefronts every loop waited for them.
+// LDS pitch of a padded array: 16-wide blocks plus 4 floats.  Pitch / 4 is odd, so the 16 rows x 4 columns of a fragment
+// whose lanes walk down rows fall on 64 different banks; one whose lanes walk along a row reads runs of 16.
+__host__ __device__ inline int fs_pad(int w) { return (w + 15) & ~15; }
+__host__ __device__ inline int fs_pitch(int w) { return fs_pad(w) + 4; }
+
+constexpr int FT_WAVES = 8, FT_LOADERS = 4;   // wavefronts that compute, wavefronts that fetch
+constexpr int FT_THREADS = (FT_WAVES + FT_LOADERS) * 64;
+constexpr int FT_EVAL_ROWS = 64;    // held-out rows per workgroup: four wavefronts of 16 rows each
+
+size_t fused_tiled_plan(FusedSmallArgs& a, bool for_eval) {
+  int off = 0;
+  for (int l = 0; l < a.n_layers; ++l) {
+    a.lt_w[l] = off; off += fs_pad(a.dims[l]) * fs_pitch(a.dims[l + 1]);
+    a.lt_b[l] = off; off += fs_pad(a.dims[l + 1]);
+  }
+  if (for_eval) {
+    int maxp = 0;
+    for (int l = 0; l <= a.n_layers; ++l) maxp = fs_pitch(a.dims[l]) > maxp ? fs_pitch(a.dims[l]) : maxp;
+    a.lt_pitch = maxp;
+    a.lt_a[0] = off; off += FT_EVAL_ROWS * maxp;
+    a.lt_a[1] = off; off += FT_EVAL_ROWS * maxp;
+    a.lt_total = off;
+    return (size_t)off * sizeof(float);
+  }
+  a.lt_s0 = off; off += (int)a.stride;
+  a.lt_s1 = off; if (a.optimizer == 1) off += (int)a.stride;
+  const int rows = fs_pad(a.B);
+  a.lt_x[0] = off; off += rows * fs_pitch(a.dims[0]);
+  a.lt_x[1] = off; off += rows * fs_pitch(a.dims[0]);
+  for (int l = 0; l < a.n_layers; ++l) {
+    a.lt_a[l + 1] = off; if (l + 1 < a.n_layers) off += rows * fs_pitch(a.dims[l + 1]);
+    a.lt_d[l] = off; off += rows * fs_pitch(a.dims[l + 1]);   // z (GELU), logits, then the gradient with respect to z
+  }
+  a.lt_y = off; off += 2 * rows;
+  a.lt_rowloss = off; off += rows;
+  a.lt_sc = off; off += 4;
+  a.lt_total = off;
+  if (rows * a.dims[0] > 65535) return SIZE_MAX;   // (ft_div's range)
+  a.lt_inv_d0 = (uint32_t)(((1ull << 32) + a.dims[0] - 1) / a.dims[0]);
+  return (size_t)off * sizeof(float);
+}
+
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// One 16 x 16 block of A B over k < KP (a multiple of 16: the padding is zero in at least one operand).  pa / pb point at
+// the lane's first element (row or column lane % 16, k = lane / 16); sa / sb are the steps along k.  Result: column
+// lane % 16, rows 4 (lane / 16) + e.
+// colsum: sums of B's columns as a by-product.  The operands of the next 16 k are on their way while one 16 is multiplied (past the end the last ones again: loads that
+// are issued always let the compiler wait for the older ones only).
+template <bool COLSUM>
+__device__ __forceinline__ f32x4_t ft_block(const float* pa, int sa, const float* pb, int sb, int KP, f32x4_t& colsum) {
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  float x[2][4], y[2][4];
+  auto fetch = [&](int q, int k) {
+    k = min(k, KP - 16);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { x[q][j] = pa[(k + 4 * j) * sa]; y[q][j] = pb[(k + 4 * j) * sb]; }
+  };
+  auto multiply = [&](int q) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[q][j], y[q][j], acc, 0, 0, 0);
+    if (COLSUM) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) colsum = __builtin_amdgcn_mfma_f32_16x16x4f32(1.f, y[q][j], colsum, 0, 0, 0);
+    }
+  };
+  fetch(0, 0);
+  for (int k = 0;;) {
+    fetch(1, k + 16);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(0);
+    if ((k += 16) >= KP) break;
+    fetch(0, k + 16);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(1);
+    if ((k += 16) >= KP) break;
+  }
+  return acc;
+}
+__device__ __forceinline__ f32x4_t ft_block(const float* pa, int sa, const float* pb, int sb, int KP) {
+  f32x4_t unused = {0.f, 0.f, 0.f, 0.f};
+  return ft_block<false>(pa, sa, pb, sb, KP, unused);
+}
+// LDS written before is visible behind it; loads from memory stay in flight (a __syncthreads would wait for them)
+__device__ __forceinline__ void ft_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// the value of the lane whose number differs in bit 0 (bit 1): within four lanes, without LDS
+__device__ __forceinline__ float ft_xor(float v, int bit) {
+  const int x = __float_as_int(v);
+  return __int_as_float(bit == 1 ? __builtin_amdgcn_update_dpp(x, x, 0xB1, 0xF, 0xF, false) : __builtin_amdgcn_update_dpp(x, x, 0x4E, 0xF, 0xF, false));
+}
+__device__ __forceinline__ int ft_xor(int v, int bit) { return __float_as_int(ft_xor(__int_as_float(v), bit)); }
+
+// Softmax cross-entropy of 16 rows whose logits sit in LDS (written by this wavefront): four lanes per row, classes in
+// turn.  Same split as fs_loss: the largest term apart, softmax_y - 1 as minus the sum of the others.  grad: the
+// gradient replaces the logits (rows from nrows on get zeros).
+__device__ __forceinline__ void ft_loss16(float* lg_rows, int pitch, int C, const int* y, int nrows, float* rowloss, bool grad, float gscale) {
+  const int lane = threadIdx.x & 63, r = lane >> 2, q = lane & 3;
+  float* lg = lg_rows + r * pitch;
+  const bool live = r < nrows;
+  const int yb = live ? y[r] : 0;
+  float v[8], mx = -INFINITY;
+  int cm = 1 << 20;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    if (4 * j >= C) break;
+    const int c = q + 4 * j;
+    v[j] = c < C ? lg[c] : -INFINITY;
+    if (c < C && (v[j] > mx || j == 0)) { mx = v[j]; cm = c; }
+  }
+#pragma unroll
+  for (int o = 1; o < 3; ++o) {
+    const float m2 = ft_xor(mx, o);
+    const int c2 = ft_xor(cm, o);
+    if (m2 > mx || (m2 == mx && c2 < cm)) { mx = m2; cm = c2; }
+  }
+  float rest = 0.f, others = 0.f, ly = 0.f;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    if (4 * j >= C) break;
+    const int c = q + 4 * j;
+    ly += c == yb ? v[j] : 0.f;
+    v[j] = c == cm ? 1.f : c < C ? expf(v[j] - mx) : 0.f;
+    rest += c == cm ? 0.f : v[j];
+    others += c == yb ? 0.f : v[j];
+  }
+#pragma unroll
+  for (int o = 1; o < 3; ++o) {
+    rest += ft_xor(rest, o);
+    others += ft_xor(others, o);
+    ly += ft_xor(ly, o);
+  }
+  if (rowloss && q == 0) rowloss[r] = live ? log1pf(rest) + (mx - ly) : 0.f;
+  if (grad) {
+    const float inv = 1.f / (1.f + rest);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (4 * j >= C) break;
+      const int c = q + 4 * j;
+      if (c < C) lg[c] = live ? (c == yb ? -others * inv : v[j] * inv) * gscale : 0.f;
+    }
+  }
+}
+
+// e / d for 0 <= e < 65536, inv = ceil(2^32 / d) (d > 1; 2^32 / 1 does not fit and is taken as 0)
+__device__ __forceinline__ int ft_div(int e, uint32_t inv) { return inv ? (int)__umulhi((uint32_t)e, inv) : e; }
+
+// Block numbers wave, wave + FT_WAVES, ... of a grid with `rows` block rows, as (row, column)
+struct FtWalk {
+  int row, col, rows;
+  __device__ __forceinline__ void start(int first, int n) {
+    rows = n; row = first; col = 0;
+    settle();
+  }
+  __device__ __forceinline__ void settle() { while (row >= rows) { row -= rows; ++col; } }
+  __device__ __forceinline__ void next() { row += FT_WAVES; settle(); }
+};
+
+__device__ __forceinline__ void ft_act4(float* v, int kind) {
+  switch (kind) {
+    case ACT_RELU:
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
+      break;
+    case ACT_LEAKY_RELU:
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.2f * v[e];
+      break;
+    case ACT_GELU:
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = act_fwd(v[e], ACT_GELU);
+      break;
+    case ACT_TANH:
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = tanhf(v[e]);
+      break;
+    default: break;
+  }
+}
+// act'(z), from z for GELU, else from the activation (v holds the one or the other)
+__device__ __forceinline__ void ft_act4_bwd(float* v, int kind) {
+  switch (kind) {
+    case ACT_RELU:
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? 1.f : 0.f;
+      break;
+    case ACT_LEAKY_RELU:
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? 1.f : 0.2f;
+      break;
+    case ACT_GELU:
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = act_bwd(v[e], ACT_GELU);
+      break;
+    case ACT_TANH:
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = 1.f - v[e] * v[e];
+      break;
+    default:
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = 1.f;
+  }
+}
+
+// Rows and labels of one step's mini-batch (Philox domain 1) into LDS, by the FT_LOADERS wavefronts: each takes its share of
+// the rows, a lane draws the number of one row, then all lanes run over the rows' elements, eight loads at a time.
+__device__ __forceinline__ void ft_load_batch(const FusedSmallArgs& a, int member, uint32_t step, float* X, int px, int* y, int loader) {
+  const int lane = threadIdx.x & 63, B = a.B, d0 = a.dims[0];
+  const int share = (B + FT_LOADERS - 1) / FT_LOADERS, rbeg = loader * share, rend = min(B, rbeg + share);
+  for (int r0 = rbeg; r0 < rend; r0 += 64) {
+    const int rows = min(64, rend - r0), n = rows * d0;
+    int src = 0;
+    if (lane < rows) {
+      src = (int)philox_bounded(philox4x32_10(step, (uint32_t)member, DOMAIN_BATCH, (uint32_t)(r0 + lane), (uint32_t)a.seed, (uint32_t)(a.seed >> 32)).x, (uint32_t)a.n_rows);
+      y[r0 + lane] = a.y[src];
+    }
+    for (int e0 = 0; e0 < n; e0 += 512) {
+      float v[8];
+      int at[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int e = min(e0 + 64 * j + lane, n - 1), r = ft_div(e, a.lt_inv_d0), c = e - r * d0;   // (past the end: the last element again)
+        at[j] = (r0 + r) * px + c;
+        v[j] = a.x[(int64_t)__shfl(src, r) * d0 + c];
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) X[at[j]] = v[j];
+    }
+  }
+}
+
+// NL: number of layers when it is known (its loops are unrolled and what they read of the argument block stays in scalar
+// registers), 0: any.  OPT: optimiser.
+template <int NL, int OPT>
+__global__ __launch_bounds__(FT_THREADS) void fused_tiled_step_kernel(FusedSmallArgs a) {
+  extern __shared__ float lds[];
+  const int i = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int fr = lane & 15, fg = lane >> 4;   // fragment row / column, group of four rows (or k offset)
+  const int64_t base = (int64_t)i * a.stride;
+  const int L = NL ? NL : a.n_layers, B = a.B, d0 = a.dims[0], RB = fs_pad(B) / 16, px = fs_pitch(d0);
+  int* const ytab = reinterpret_cast<int*>(lds + a.lt_y);
+  for (int j = tid; j < a.lt_total; j += FT_THREADS) lds[j] = 0.f;   // every padding element stays zero (or finite where no result uses it)
+  __syncthreads();
+  for (int l = 0; l < L; ++l) {
+    const int N = a.dims[l + 1], KN = a.dims[l] * N, p = fs_pitch(N);
+    for (int e = tid; e < KN; e += FT_THREADS) {
+      const int k = e / N;
+      lds[a.lt_w[l] + k * p + (e - k * N)] = a.W32[base + a.w_off[l] + e];
+    }
+    for (int e = tid; e < N; e += FT_THREADS) lds[a.lt_b[l] + e] = a.W32[base + a.b_off[l] + e];
+  }
+  for (int e = tid; e < (int)a.stride; e += FT_THREADS) {
+    lds[a.lt_s0 + e] = a.S0[base + e];
+    if (OPT == OPT_ADAM) lds[a.lt_s1 + e] = a.S1[base + e];
+  }
+  const float* h = a.H + (int64_t)i * a.n_hyper;
+  const float lr = h[a.col_lr];
+  const float b1 = (OPT == OPT_ADAM && a.col_beta1 >= 0) ? h[a.col_beta1] : a.c0;
+  const float wd = (OPT == OPT_ADAM && a.col_wd >= 0) ? h[a.col_wd] : a.c3;
+  const int t0 = a.t[i];
+  const float gscale = 1.f / (float)B;
+  float last_loss = 0.f;
+
+  if (wave >= FT_WAVES) {
+    // the fetching wavefronts: step s + 1's rows, labels and bias corrections go into the half of the double buffers that
+    // step s does not read; they meet the others at every barrier
+    for (int s = -1; s < a.n_steps; ++s) {
+      const int nxt = (s + 1) & 1;
+      if (s + 1 < a.n_steps) {
+        if (OPT == OPT_ADAM && tid - FT_WAVES * 64 < 2)   // 1 / (1 - beta^t)
+          lds[a.lt_sc + 2 * nxt + lane] = 1.f / (1.f - powf(lane == 0 ? b1 : a.c1, (float)(t0 + s + 2)));
+        ft_load_batch(a, i, a.step0 + (uint32_t)(s + 1), lds + a.lt_x[nxt], px, ytab + nxt * RB * 16, wave - FT_WAVES);
+      }
+      if (s < 0) __syncthreads();
+      else
+        for (int k = 0; k < 2 * L; ++k) ft_barrier();
+    }
+  } else {
+    // optimiser on n (at most 4) parameters: w[e * wp] in LDS, p + e * pp in the member's vector
+    auto update4 = [&](float* w, int wp, int p, int pp, const f32x4_t g, int n, const float* sc, bool last) {
+      float wv[4], s0[4], s1[4];
+      float* const S0 = lds + a.lt_s0 + p;
+      float* const S1 = lds + a.lt_s1 + p;
+      // (parameters past the n-th are read, inside the workgroup's LDS, and not written)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        wv[e] = w[e * wp];
+        s0[e] = S0[e * pp];
+        if (OPT == OPT_ADAM) s1[e] = S1[e * pp];
+      }
+      const float bc1 = OPT == OPT_ADAM ? sc[0] : 1.f, bc2 = OPT == OPT_ADAM ? sc[1] : 1.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (OPT == OPT_SGD_MOMENTUM) {
+          s0[e] = a.c0 * s0[e] + g[e];
+          wv[e] = wv[e] - lr * s0[e];
+        } else if (OPT == OPT_ADAM) {
+          s0[e] = b1 * s0[e] + (1.f - b1) * g[e];
+          s1[e] = a.c1 * s1[e] + (1.f - a.c1) * g[e] * g[e];
+          wv[e] = wv[e] - lr * ((s0[e] * bc1) / (sqrtf(s1[e] * bc2) + a.c2) + wd * wv[e]);
+        } else {
+          s0[e] = a.c0 * s0[e] + (1.f - a.c0) * g[e] * g[e];
+          wv[e] = wv[e] - lr * g[e] / sqrtf(s0[e] + a.c1);
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (e < n) {
+          w[e * wp] = wv[e];
+          S0[e * pp] = s0[e];
+          if (OPT == OPT_ADAM) S1[e * pp] = s1[e];
+          if (last) a.G[base + p + e * pp] = g[e];
+        }
+    };
+    // gradient and update of a 16 x 16 block of W_l; the blocks of the first block row also form the bias gradient of their
+    // columns (column sums of dz: a product with ones, from the operands that are there anyway)
+    auto weight_unit = [&](int l, int kb, int nb, const float* in, int pin, const float* sc, bool last) {
+      const int K = a.dims[l], N = a.dims[l + 1], pn = fs_pitch(N), n = nb * 16 + fr, k = kb * 16 + 4 * fg;
+      f32x4_t bsum = {0.f, 0.f, 0.f, 0.f};
+      const float* const pa = in + fg * pin + kb * 16 + fr;
+      const float* const pb = lds + a.lt_d[l] + fg * pn + n;
+      const f32x4_t acc = kb == 0 ? ft_block<true>(pa, pin, pb, pn, RB * 16, bsum) : ft_block(pa, pin, pb, pn, RB * 16);
+      if (k < K && n < N) update4(lds + a.lt_w[l] + k * pn + n, pn, a.w_off[l] + k * N + n, N, acc, K - k, sc, last);
+      if (kb == 0 && fg == 0 && n < N) update4(lds + a.lt_b[l] + n, 0, a.b_off[l] + n, 0, bsum, 1, sc, last);
+    };
+    __syncthreads();
+    for (int s = 0; s < a.n_steps; ++s) {
+      const int cur = s & 1;
+      const bool last = s == a.n_steps - 1;
+      const float* X = lds + a.lt_x[cur];
+      const float* sc = lds + a.lt_sc + 2 * cur;
+      FtWalk w;
+#pragma unroll
+      for (int l = 0; l < L; ++l) {
+        const int KP = fs_pad(a.dims[l]), N = a.dims[l + 1], pk = fs_pitch(a.dims[l]), pn = fs_pitch(N), NB = fs_pad(N) / 16;
+        const float* in = l == 0 ? X : lds + a.lt_a[l];
+        if (l < L - 1) {
+          for (w.start(wave, RB); w.col < NB; w.next()) {
+            const int n = w.col * 16 + fr, o = (w.row * 16 + 4 * fg) * pn + n;
+            const float bias = lds[a.lt_b[l] + n];
+            const f32x4_t acc = ft_block(in + (w.row * 16 + fr) * pk + fg, 1, lds + a.lt_w[l] + fg * pn + n, pn, KP);
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = acc[e] + bias;
+            if (a.act == ACT_GELU) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) lds[a.lt_d[l] + o + e * pn] = v[e];
+            }
+            ft_act4(v, a.act);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) lds[a.lt_a[l + 1] + o + e * pn] = v[e];
+          }
+        } else {
+          for (int rb = wave; rb < RB; rb += FT_WAVES) {
+            for (int nb = 0; nb < NB; ++nb) {
+              const int n = nb * 16 + fr, o = (rb * 16 + 4 * fg) * pn + n;
+              const float bias = lds[a.lt_b[l] + n];
+              const f32x4_t acc = ft_block(in + (rb * 16 + fr) * pk + fg, 1, lds + a.lt_w[l] + fg * pn + n, pn, KP);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) lds[a.lt_d[l] + o + e * pn] = acc[e] + bias;
+            }
+            // (written and read by the same wavefront: in order, no barrier)
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            ft_loss16(lds + a.lt_d[l] + rb * 16 * pn, pn, N, ytab + (cur * RB + rb) * 16, B - rb * 16, last ? lds + a.lt_rowloss + rb * 16 : nullptr,
+                      true, gscale);
+          }
+        }
+        ft_barrier();
+      }
+      if (last && wave == 0) last_loss = fs_sum_rowloss(lds + a.lt_rowloss, B) / (float)B;
+      // backward: the input gradient of layer l shares an interval with the weight gradient of layer l + 1
+#pragma unroll
+      for (int l = L - 1; l >= 0; --l) {
+        int left = wave;   // number of this wavefront's next unit in what follows
+        if (l > 0) {
+          const int K = a.dims[l], N = a.dims[l + 1], pn = fs_pitch(N), pk = fs_pitch(K), KB = fs_pad(K) / 16;
+          for (w.start(wave, RB); w.col < KB; w.next()) {   // dz_{l-1} = (dz_l W_l^T) * act'
+            const int o = (w.row * 16 + 4 * fg) * pk + w.col * 16 + fr;
+            float* d = lds + a.lt_d[l - 1] + o;
+            const float* from = a.act == ACT_GELU ? d : lds + a.lt_a[l] + o;
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = from[e * pk];
+            const f32x4_t acc = ft_block(lds + a.lt_d[l] + (w.row * 16 + fr) * pn + fg, 1, lds + a.lt_w[l] + (w.col * 16 + fr) * pn + fg, 1, fs_pad(N));
+            ft_act4_bwd(v, a.act);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) d[e * pk] = acc[e] * v[e];
+            left += FT_WAVES;
+          }
+          left -= RB * KB;
+        }
+        if (l + 1 < L) {
+          const int NB = fs_pad(a.dims[l + 2]) / 16, KB = fs_pad(a.dims[l + 1]) / 16;
+          for (w.start(left, NB); w.col < KB; w.next()) { weight_unit(l + 1, w.col, w.row, lds + a.lt_a[l + 1], fs_pitch(a.dims[l + 1]), sc, last); left += FT_WAVES; }
+          left -= NB * KB;
+        }
+        if (l == 0) {
+          const int NB = fs_pad(a.dims[1]) / 16, KB = fs_pad(d0) / 16;
+          for (w.start(left, NB); w.col < KB; w.next()) weight_unit(0, w.col, w.row, X, px, sc, last);
+        }
+        ft_barrier();
+      }
+    }
+  }
+  __syncthreads();
+  for (int l = 0; l < L; ++l) {
+    const int N = a.dims[l + 1], KN = a.dims[l] * N, p = fs_pitch(N);
+    for (int e = tid; e < KN; e += FT_THREADS) {
+      const int k = e / N;
+      a.W32[base + a.w_off[l] + e] = lds[a.lt_w[l] + k * p + (e - k * N)];
+    }
+    for (int e = tid; e < N; e += FT_THREADS) a.W32[base + a.b_off[l] + e] = lds[a.lt_b[l] + e];
+  }
+  for (int e = tid; e < (int)a.stride; e += FT_THREADS) {
+    a.S0[base + e] = lds[a.lt_s0 + e];
+    if (OPT == OPT_ADAM) a.S1[base + e] = lds[a.lt_s1 + e];
+  }
+  if (tid == 0) {
+    a.t[i] = t0 + a.n_steps;
+    a.loss[i] = last_loss;
+  }
+}
+
+template <int OPT>
+static void (*ft_step_kernel(int n_layers))(FusedSmallArgs) {
+  return n_layers == 2 ? fused_tiled_step_kernel<2, OPT> : n_layers == 3 ? fused_tiled_step_kernel<3, OPT> : fused_tiled_step_kernel<0, OPT>;
+}
+
+// (1024 rows x 8 members: 506 -> 18 us with the sum over workgroups, against one workgroup per member that walks all rows.)
+// eval: every workgroup takes 64 held-out rows of one member (blockIdx.x), a wavefront 16 of them through all layers on
+// its own; the workgroup's sum of row losses goes to part[member][blockIdx.x].
+__global__ __launch_bounds__(256) void fused_tiled_eval_kernel(FusedSmallArgs a, float* __restrict__ part) {
+  extern __shared__ float lds[];
+  __shared__ int ylds[FT_EVAL_ROWS];
+  __shared__ float rowloss[FT_EVAL_ROWS];
+  const int i = blockIdx.y, r0 = blockIdx.x * FT_EVAL_ROWS, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int fr = lane & 15, fg = lane >> 4, L = a.n_layers, d0 = a.dims[0];
+  const int64_t base = (int64_t)i * a.stride;
+  const int nrows = min(FT_EVAL_ROWS, a.n_rows - r0);
+  for (int l = 0; l < L; ++l) {
+    const int K = a.dims[l], N = a.dims[l + 1], p = fs_pitch(N), NP = fs_pad(N), total = fs_pad(K) * NP;
+    for (int e = tid; e < total; e += 256) {   // (with the padding)
+      const int k = e / NP, n = e - k * NP;
+      lds[a.lt_w[l] + k * p + n] = k < K && n < N ? a.W32[base + a.w_off[l] + k * N + n] : 0.f;
+    }
+    for (int n = tid; n < NP; n += 256) lds[a.lt_b[l] + n] = n < N ? a.W32[base + a.b_off[l] + n] : 0.f;
+  }
+  const int p = a.lt_pitch, D = fs_pad(d0);
+  for (int e = tid; e < FT_EVAL_ROWS * D; e += 256) {
+    const int r = e / D, c = e - r * D;
+    lds[a.lt_a[0] + r * p + c] = r < nrows && c < d0 ? a.x[(int64_t)(r0 + r) * d0 + c] : 0.f;
+  }
+  if (tid < FT_EVAL_ROWS) ylds[tid] = tid < nrows ? a.y[r0 + tid] : 0;
+  __syncthreads();
+  for (int l = 0; l < L; ++l) {
+    const int KP = fs_pad(a.dims[l]), N = a.dims[l + 1], pn = fs_pitch(N), NB = fs_pad(N) / 16;
+    const float* in = lds + a.lt_a[l & 1] + wave * 16 * p;
+    float* out = lds + a.lt_a[(l + 1) & 1] + wave * 16 * p;
+    for (int nb = 0; nb < NB; ++nb) {
+      const int n = nb * 16 + fr;
+      const f32x4_t acc = ft_block(in + fr * p + fg, 1, lds + a.lt_w[l] + fg * pn + n, pn, KP);
+      const float bias = lds[a.lt_b[l] + n];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float z = acc[e] + bias;
+        out[(4 * fg + e) * p + n] = l < L - 1 ? act_fwd(z, a.act) : z;
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  ft_loss16(lds + a.lt_a[L & 1] + wave * 16 * p, p, a.dims[L], ylds + wave * 16, nrows - wave * 16, rowloss + wave * 16, false, 0.f);
+  __syncthreads();
+  if (wave == 0) {
+    const float t = wave_sum(rowloss[lane]);
+    if (lane == 0) part[(int64_t)i * gridDim.x + blockIdx.x] = t;
+  }
+}
+
+static hipError_t set_lds(const void* kernel, size_t bytes) {
   if (bytes > FUSED_SMALL_MAX_LDS) return hipErrorInvalidValue;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_small_step_kernel),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
+// The tiled form whenever its padded arrays fit a compute unit; the plain form (no padding, no double buffers) is left for
+// networks that fill the LDS nearly to the last byte.
+hipError_t fused_small_step(FusedSmallArgs a, hipStream_t s) {
+  const size_t tiled = fused_tiled_plan(a, false);
+  if (tiled <= FUSED_SMALL_MAX_LDS) {
+    auto kernel = a.optimizer == OPT_SGD_MOMENTUM ? ft_step_kernel<OPT_SGD_MOMENTUM>(a.n_layers)
+                  : a.optimizer == OPT_ADAM ? ft_step_kernel<OPT_ADAM>(a.n_layers) : ft_step_kernel<OPT_RMSPROP>(a.n_layers);
+    hipError_t e = set_lds(reinterpret_cast<const void*>(kernel), tiled);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3(a.P), dim3(FT_THREADS), tiled, s, a);
+    return hipGetLastError();
+  }
+  const size_t bytes = fused_small_plan(a, false);
+  hipError_t e = set_lds(reinterpret_cast<const void*>(fused_small_step_kernel), bytes);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(fused_small_step_kernel, dim3(a.P), dim3(FS_THREADS), bytes, s, a);
   return hipGetLastError();
@@ -249,11 +756,20 @@ __global__ __launch_bounds__(FS_THREADS) void fused_small_eval_kernel(FusedSmall
   if (tid == 0) a.score[i] = -total / (float)a.n_rows;
 }
 
-hipError_t fused_small_eval(const FusedSmallArgs& a, hipStream_t s) {
-  const size_t bytes = (size_t)a.lds_total * sizeof(float);
-  if (bytes > FUSED_SMALL_MAX_LDS) return hipErrorInvalidValue;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_small_eval_kernel),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+int fused_small_eval_parts(int n_rows) { return (n_rows + FT_EVAL_ROWS - 1) / FT_EVAL_ROWS; }
+// part: P x fused_small_eval_parts(n_rows) floats of working memory
+hipError_t fused_small_eval(FusedSmallArgs a, float* part, hipStream_t s) {
+  const size_t tiled = fused_tiled_plan(a, true);
+  if (tiled <= FUSED_SMALL_MAX_LDS - 1024) {   // (1 KB for the kernel's static arrays)
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_tiled_eval_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)tiled);
+    if (e != hipSuccess) return e;
+    const int parts = fused_small_eval_parts(a.n_rows);
+    hipLaunchKernelGGL(fused_tiled_eval_kernel, dim3(parts, a.P), dim3(256), tiled, s, a, part);
+    e = hipGetLastError();
+    return e != hipSuccess ? e : row_reduce(part, parts, a.P, parts, -1.f / (float)a.n_rows, a.score, 1, s);
+  }
+  const size_t bytes = fused_small_plan(a, true);
+  hipError_t e = set_lds(reinterpret_cast<const void*>(fused_small_eval_kernel), bytes);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(fused_small_eval_kernel, dim3(a.P), dim3(FS_THREADS), bytes, s, a);
   return hipGetLastError();

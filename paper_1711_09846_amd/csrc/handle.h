@@ -78,7 +78,7 @@ struct Plan {
   size_t o_act[PBT_MAX_DIMS], o_z[PBT_MAX_DIMS], o_dz[PBT_MAX_DIMS];
   size_t o_evalx, o_evala[2], o_evalrow;
   size_t o_stage[6];  // tournament exploit: staging rows of the copied arrays
-  size_t scratch_bytes;
+  size_t scratch_bytes, step_scratch_bytes;   // all of d_scratch; the part a step needs
   int eval_chunk;
   bool fused_small;  // fp32: the whole step runs in one LDS-resident kernel
   int col_lr, col_beta1, col_wd;

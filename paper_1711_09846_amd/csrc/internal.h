@@ -213,11 +213,15 @@ struct FusedSmallArgs {
   uint32_t step0; int n_steps; uint64_t seed;
   // LDS carve-up in floats, filled by fused_small_plan()
   int lds_w, lds_s0, lds_s1, lds_a[16], lds_z[16], lds_dz[2], lds_rowloss, lds_y, lds_total;
+  // the same for the tiled form (arrays padded to whole 16 x 16 blocks)
+  int lt_w[16], lt_b[16], lt_s0, lt_s1, lt_x[2], lt_a[17], lt_d[16], lt_y, lt_rowloss, lt_sc, lt_pitch, lt_total;
+  uint32_t lt_inv_d0;
 };
 // Fills the lds_* fields; returns the dynamic LDS bytes needed (for_eval: no state, no gradients).
 size_t fused_small_plan(FusedSmallArgs& a, bool for_eval);
 constexpr size_t FUSED_SMALL_MAX_LDS = 160 * 1024;
-hipError_t fused_small_step(const FusedSmallArgs& a, hipStream_t s);
-hipError_t fused_small_eval(const FusedSmallArgs& a, hipStream_t s);
+hipError_t fused_small_step(FusedSmallArgs a, hipStream_t s);
+int fused_small_eval_parts(int n_rows);   // partial sums per member of fused_small_eval
+hipError_t fused_small_eval(FusedSmallArgs a, float* part, hipStream_t s);
 
 }  // namespace pbt

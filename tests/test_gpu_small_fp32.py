@@ -1,0 +1,43 @@
+"""The LDS-resident fp32 step and score at sizes where a tile can go wrong: widths, batches and held-out sets just below, at
+and above multiples of 16, one layer to four, one input, and a network too large for the padded arrays (plain form)."""
+import numpy as np
+import pytest
+
+from paper_1711_09846_amd import binding, workloads as W
+from tests.harness import Pair
+
+pytestmark = pytest.mark.gpu
+
+SGD, ADAM, RMS = W.OPT_SGD_MOMENTUM, W.OPT_ADAM, W.OPT_RMSPROP
+CONST = {SGD: dict(momentum=0.9), ADAM: dict(beta1=0.9, beta2=0.999, eps=1e-8), RMS: dict(rho=0.99, eps=1e-5)}
+SHAPES = [
+    # dims, batch, held-out rows, activation, optimiser
+    ([1, 16, 2], 1, 1, W.ACT_RELU, SGD),
+    ([11, 71, 20, 5], 17, 65, W.ACT_TANH, RMS),
+    ([16, 32, 32], 16, 64, W.ACT_LEAKY_RELU, ADAM),
+    ([17, 3], 33, 100, W.ACT_NONE, SGD),
+    ([33, 15, 48, 9, 7], 63, 63, W.ACT_GELU, RMS),
+    ([64, 96, 10], 31, 129, W.ACT_GELU, SGD),
+    ([40, 50, 17], 128, 200, W.ACT_RELU, SGD),      # 157 KB unpadded, 174 KB padded
+]
+
+
+@pytest.mark.parametrize("dims,batch,n_eval,act,opt", SHAPES, ids=lambda v: str(v))
+def test_step_and_score_against_the_oracle(dims, batch, n_eval, act, opt):
+    """Three steps from the same start, then the score.  fp32 sums of at most 128 products of O(1) terms: 128 x 2^-24 = 8e-6
+    at worst per sum, a few 1e-7 as a rule; 2e-5 leaves room for three chained layers and steps.  Adam and RMSProp divide by
+    the root of near-zero mean squares in the first steps: 2e-4 there.  Losses near 1: same bound."""
+    wl = W.MLP_SMALL.replace(P=3, dims=dims, batch=batch, n_eval=n_eval, n_train=500, n_trunc=1, act=act, optimizer=opt, n_classes=dims[-1],
+                             opt_const=CONST[opt], priors=[("log", 1e-3, 1e-2)])
+    pair = Pair(wl)
+    pair.gpu.step(pair.d_train, 0)
+    pair.gpu.step(pair.d_train, 1, n_steps=2)
+    for s in range(3):
+        loss = pair.step_ref(s)
+    tol = 2e-5 if opt == SGD else 2e-4
+    assert pair.scalar_errors(pair.gpu.get(binding.ARR_LOSS), loss, 1e-2) <= tol
+    assert pair.tensor_errors(binding.ARR_W32, "theta") <= tol
+    assert pair.tensor_errors(binding.ARR_OPT0, "s0") <= tol
+    assert np.all(pair.gpu.get(binding.ARR_T) == 3)
+    pair.gpu.eval(pair.d_eval)
+    assert pair.scalar_errors(pair.gpu.get(binding.ARR_SCORE), pair.eval_ref(), 1e-2) <= tol
