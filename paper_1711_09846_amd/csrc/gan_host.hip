@@ -36,53 +36,83 @@ __global__ __launch_bounds__(256) void wgan_interpolate_kernel(bf16_t* __restric
 // critic (rows = 3B): loss[2 i] = mean out[B..2B) - mean out[0..B) (the penalty is added later), and the
 // gradient of the outputs: -1/B on the real rows, +1/B on the generated rows, 1 on the interpolated rows (which
 // starts the input-gradient pass).  generator (rows = B): loss[2 i + 1] = -mean out, gradient -1/B.
+// The outputs are brought into LDS by all threads and added in row order from there: one thread that read them
+// from memory one after the other (128 bytes apart) was the whole kernel, 30 us for B = 64 against 5.
 __global__ __launch_bounds__(256) void wgan_head_kernel(const float* __restrict__ out, int B, int rows, int generator,
                                                         bf16_t* __restrict__ dlogits, float* __restrict__ loss) {
-  const int i = blockIdx.x;
+  extern __shared__ float col[];  // [generator ? B : 2 B] the outputs that enter the loss
+  const int i = blockIdx.x, n = generator ? B : 2 * B;
+  const float* __restrict__ o = out + (int64_t)i * rows * 32;
+  for (int r = threadIdx.x; r < n; r += blockDim.x) col[r] = o[(int64_t)r * 32];
   for (int r = threadIdx.x; r < rows; r += blockDim.x) {
     const float d = generator ? -1.f / (float)B : r < B ? -1.f / (float)B : r < 2 * B ? 1.f / (float)B : 1.f;
     uint4* __restrict__ row = reinterpret_cast<uint4*>(dlogits + ((int64_t)i * rows + r) * 32);
     row[0] = make_uint4((uint32_t)f2bf(d), 0u, 0u, 0u);
     row[1] = row[2] = row[3] = make_uint4(0u, 0u, 0u, 0u);
   }
+  __syncthreads();
   if (threadIdx.x == 0) {
-    const float* __restrict__ o = out + (int64_t)i * rows * 32;
     double real = 0.0, fake = 0.0;
     if (generator) {
-      for (int r = 0; r < B; ++r) fake += (double)o[r * 32];
+#pragma unroll 8
+      for (int r = 0; r < B; ++r) fake += (double)col[r];
       loss[2 * i + 1] = (float)(-fake / (double)B);
     } else {
-      for (int r = 0; r < B; ++r) real += (double)o[r * 32];
-      for (int r = B; r < 2 * B; ++r) fake += (double)o[r * 32];
+#pragma unroll 8
+      for (int r = 0; r < B; ++r) { real += (double)col[r]; fake += (double)col[B + r]; }
       loss[2 * i] = (float)(fake / (double)B - real / (double)B);
     }
   }
 }
 
-// One workgroup per member.  g: the critic's input gradient on the interpolated rows, float [P][B][D].
-// penalty = weight * mean_r (|g_r| - 1)^2 is added to loss[2 i]; c_r = (2 weight / B) (|g_r| - 1) / |g_r| g_r,
-// the gradient of the penalty with respect to g_r, goes (bf16) to rows 2B .. 3B-1 of the critic's input
-// buffer, where the weight-gradient contraction of the first layer finds it.  Row norms are summed in double,
-// lanes in a fixed butterfly order, rows in order.
-__global__ __launch_bounds__(256) void wgan_penalty_kernel(const float* __restrict__ g, int B, int D, float weight,
-                                                           bf16_t* __restrict__ X, float* __restrict__ loss) {
+// One workgroup per member, a wavefront per row.  g: the critic's input gradient on the interpolated rows, float
+// [P][B][D] (D a multiple of 8).  penalty = weight * mean_r (|g_r| - 1)^2 is added to loss[2 i];
+// c_r = (2 weight / B) (|g_r| - 1) / |g_r| g_r, the gradient of the penalty with respect to g_r, goes (bf16) to
+// rows 2B .. 3B-1 of the critic's input buffer, where the weight-gradient contraction of the first layer finds it.
+// Row norms are summed in double, lanes in a fixed butterfly order, rows in order.
+// Bound by memory latency (6 MB in all for 32 members of 64 x 784): each wavefront reads its row once, as 16-byte
+// loads that are all in flight together, and keeps up to PEN_VEC * 256 elements in registers between the norm and
+// the scaling (longer rows read the rest again).  With four wavefronts per member, 4-byte loads and a second pass
+// over memory the kernel took 106 us at those sizes, now 12.
+constexpr int PEN_VEC = 4;
+__global__ __launch_bounds__(1024) void wgan_penalty_kernel(const float* __restrict__ g, int B, int D, float weight,
+                                                            bf16_t* __restrict__ X, float* __restrict__ loss) {
   extern __shared__ double sq[];  // [B] squared deviations
   const int i = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
   for (int r = wave; r < B; r += waves) {
     const float* __restrict__ gr = g + ((int64_t)i * B + r) * D;
+    float4 v[PEN_VEC];
+#pragma unroll
+    for (int u = 0; u < PEN_VEC; ++u) {
+      const int c = (u * 64 + lane) * 4;
+      v[u] = c < D ? *reinterpret_cast<const float4*>(gr + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
     double acc = 0.0;
-    for (int c = lane; c < D; c += 64) acc += (double)gr[c] * (double)gr[c];
+#pragma unroll
+    for (int u = 0; u < PEN_VEC; ++u)
+      acc += ((double)v[u].x * (double)v[u].x + (double)v[u].y * (double)v[u].y) + ((double)v[u].z * (double)v[u].z + (double)v[u].w * (double)v[u].w);
+    for (int c = PEN_VEC * 256 + lane; c < D; c += 64) acc += (double)gr[c] * (double)gr[c];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
     const double norm = sqrt(acc);
     const double scale = (2.0 * (double)weight / (double)B) * ((norm - 1.0) / norm);
     bf16_t* __restrict__ xr = X + ((int64_t)i * 3 * B + 2 * B + r) * D;
-    for (int c = lane; c < D; c += 64) xr[c] = d2bf(scale * (double)gr[c]);
+#pragma unroll
+    for (int u = 0; u < PEN_VEC; ++u) {
+      const int c = (u * 64 + lane) * 4;
+      if (c < D) {
+        const uint32_t lo = (uint32_t)d2bf(scale * (double)v[u].x) | (uint32_t)d2bf(scale * (double)v[u].y) << 16;
+        const uint32_t hi = (uint32_t)d2bf(scale * (double)v[u].z) | (uint32_t)d2bf(scale * (double)v[u].w) << 16;
+        *reinterpret_cast<uint2*>(xr + c) = make_uint2(lo, hi);
+      }
+    }
+    for (int c = PEN_VEC * 256 + lane; c < D; c += 64) xr[c] = d2bf(scale * (double)gr[c]);
     if (lane == 0) sq[r] = (norm - 1.0) * (norm - 1.0);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     double total = 0.0;
+#pragma unroll 8
     for (int r = 0; r < B; ++r) total += sq[r];
     loss[2 * i] = (float)((double)loss[2 * i] + (double)weight * total / (double)B);
   }
@@ -219,7 +249,7 @@ static pbt_status gan_step_wgan(pbt_handle* h, const float* train_x, uint32_t st
     if ((st = forward(h, dnet, Ld - 1, R, b.dA, b.dZ, nullptr, 0, s)) != PBT_OK) return st;
     PBT_LAUNCH(h, PBT_K_HEAD, s, head_fwd_loss(b.dA[Ld - 1], (int64_t)R * Kh, W16 + p.lay.w_off[head], S, W32 + p.lay.b_off[head], S,
                                                nullptr, 0, P, R, Kh, 1, 0.f, -2, nullptr, hout, 0, s));
-    hipLaunchKernelGGL(wgan_head_kernel, dim3(P), dim3(256), 0, s, hout, B, R, 0, dlogits, loss);
+    hipLaunchKernelGGL(wgan_head_kernel, dim3(P), dim3(256), (size_t)2 * B * sizeof(float), s, hout, B, R, 0, dlogits, loss);
     PBT_HIP(h, hipGetLastError());
     // input gradients of every layer on all 3B rows (no weight gradients yet), down to g = dz_0 W_0^T on the interpolated rows
     PBT_LAUNCH(h, PBT_K_HEAD, s, head_dgrad(dlogits, W16 + p.lay.w_off[head], S, b.dZ[Ld - 2], b.ddZ[Ld - 2], P, R, Kh, 1, dnet.hidden_act, s));
@@ -229,7 +259,7 @@ static pbt_status gan_step_wgan(pbt_handle* h, const float* train_x, uint32_t st
       GemmOperands o{b.ddZ[0] + (int64_t)2 * B * N0, N0, (int64_t)R * N0, false, W16 + p.lay.w_off[first], N0, S, true, B, D, N0, P};
       PBT_LAUNCH(h, PBT_K_GEMM_DGRAD, s, gemm_store_f32(o, gin, D, (int64_t)B * D, s));
     }
-    hipLaunchKernelGGL(wgan_penalty_kernel, dim3(P), dim3(256), (size_t)B * sizeof(double), s, gin, B, D, c.gp_weight, b.dA[0], loss);
+    hipLaunchKernelGGL(wgan_penalty_kernel, dim3(P), dim3(1024), (size_t)B * sizeof(double), s, gin, B, D, c.gp_weight, b.dA[0], loss);
     PBT_HIP(h, hipGetLastError());
     // c_{l+1} = (c_l W_l) * act'(z_l) on the interpolated rows, written over those rows of the next layer's input
     for (int l = 0; l < Ld - 1; ++l) {
@@ -263,7 +293,7 @@ static pbt_status gan_step_wgan(pbt_handle* h, const float* train_x, uint32_t st
   if ((st = forward(h, dnet, Ld - 1, B, dA, b.dZ, nullptr, 0, s)) != PBT_OK) return st;
   PBT_LAUNCH(h, PBT_K_HEAD, s, head_fwd_loss(dA[Ld - 1], (int64_t)B * Kh, W16 + p.lay.w_off[head], S, W32 + p.lay.b_off[head], S,
                                              nullptr, 0, P, B, Kh, 1, 0.f, -2, nullptr, hout, 0, s));
-  hipLaunchKernelGGL(wgan_head_kernel, dim3(P), dim3(256), 0, s, hout, B, B, 1, dlogits, loss);
+  hipLaunchKernelGGL(wgan_head_kernel, dim3(P), dim3(256), (size_t)B * sizeof(float), s, hout, B, B, 1, dlogits, loss);
   PBT_HIP(h, hipGetLastError());
   PBT_LAUNCH(h, PBT_K_HEAD, s, head_dgrad(dlogits, W16 + p.lay.w_off[head], S, b.dZ[Ld - 2], b.ddZ[Ld - 2], P, B, Kh, 1, dnet.hidden_act, s));
   if ((st = backward(h, dnet, Ld - 1, B, dA, b.dZ, b.ddZ, false, nullptr, b.gZ[gnet.L - 1], b.gdZ[gnet.L - 1], gnet.out_act, s)) != PBT_OK) return st;
