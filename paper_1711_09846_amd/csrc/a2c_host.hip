@@ -155,6 +155,10 @@ __global__ void a2c_score_kernel(const float* __restrict__ hist, int P, float* _
   score[i] = (float)(acc / (double)m);
 }
 
+// scratch of the one-kernel unroll (below), in elements per member
+static int64_t a2c_packed_elems(const pbt_config* c);
+static int64_t a2c_draw_count(const pbt_config* c);
+
 pbt_status a2c_check_and_plan(const pbt_config* c, Plan* pl, Carver* w) {
   A2CPlan& a = pl->a2c;
   const int L = c->n_layers;
@@ -192,6 +196,9 @@ pbt_status a2c_check_and_plan(const pbt_config* c, Plan* pl, Carver* w) {
     a.o_lat = w->take((size_t)P * c->batch * c->latent_dim * 8);
     for (int l = 1; l < L; ++l) a.o_ga[l] = w->take((size_t)P * c->batch * c->dims[l] * 2);
     a.o_gout = w->take((size_t)P * c->batch * 32 * 4);
+    // the one-kernel unroll: weights as matrix fragments, draws made ahead
+    a.o_packed = w->take((size_t)(P * a2c_packed_elems(c)) * 2);
+    a.o_draws = w->take((size_t)(P * a2c_draw_count(c)) * 8);
   }
   return PBT_OK;
 }
@@ -405,299 +412,437 @@ __global__ __launch_bounds__(256) void a2c_env_observe_kernel(EnvArgs a, int t) 
   }
 }
 
-// ---- the whole unroll of one member in one kernel -------------------------------------------------------------
-// One workgroup per member runs the T + 1 rounds of (transition and action draw, observation, policy) back to
-// back: latents, the round's observations and the hidden activations stay in LDS, the member's bf16 weights are
-// streamed through LDS a 64-deep slab at a time (fetched with eight neighbouring lanes on 128 contiguous bytes,
-// transposed on the way in through a lane exchange, the next slab's loads in flight while this one is multiplied),
-// and every layer is a 32 x N x K product on the matrix cores with the trajectories as one 32-row block.  The same
-// arithmetic as the kernels above and the batched GEMMs (bf16 operands, float accumulation, bias and activation in
-// float, activations rounded to bf16 between layers, float head outputs); sums run in a different order.
-// Shapes: at most 32 trajectories, observation width a multiple of 64, hidden widths 64, 128 or 256, at most 32
-// head outputs.
+// ---- the whole unroll in one kernel -----------------------------------------------------------------------------
+// The T + 1 rounds of (action draw and transition, observation, policy) of a member's trajectories run back to back;
+// trajectories do not interact, so a member is cut into `parts` workgroups of `rows` trajectories, as many as fill the
+// chip's compute units.  The same arithmetic as the kernels above and the batched GEMMs (bf16 operands, float
+// accumulation, bias and activation in float, activations rounded to bf16 between layers, float head outputs); sums
+// run in a different order.
+// What a round waits for is latency, so nothing in it touches memory for longer than it must:
+//  - the weights are packed once per unroll into MFMA fragments (a2c_pack_weights_kernel: 16 columns x 32 k, lane l's 16
+//    bytes at 16 l, zeros past the matrix), so a wavefront fetches an operand with one contiguous 1 KB load and no LDS.  The
+//    first layer (the large one) stays in registers for the whole unroll as far as they go; what remains of it and the later
+//    layers are requested ahead of the barrier or the layer before them.
+//  - every draw that does not depend on the policy (latent noise, reward noise, the uniforms of the action draw; all in
+//    double) is made ahead by a kernel that fills the chip (a2c_env_noise_kernel) and fetched one round ahead.
+//  - the observation noise is drawn here, four trajectories per thread: a run of four components of C is read from LDS
+//    once for all of them (16 bytes per lane; read 4 bytes at a time at a stride of 16 it was the LDS that bounded this).
+//  - the action draw and the latent transition of a trajectory belong to one half-wavefront (lane = action, then latent
+//    component): exchanges instead of barriers.
+// 128 members, 32 trajectories of 20 steps, 512-256-256-19: 427 us, and 31 + 9 for the packing and the draws ahead, against
+// 1197 us as one workgroup per member that streamed its weights through LDS in every round.
+// Shapes: observation width and hidden widths multiples of 8, hidden widths up to 256, up to three hidden layers, at
+// most 32 head outputs, and what rollout_cut() finds to fit LDS.
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 ro_frag_t;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float ro_acc_t;
-constexpr int RO_WP = 64 + 4;     // LDS pitch (elements) of a transposed weight slab [N][64]
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float ro_acc_t;
 constexpr int RO_MAX_HIDDEN = 3;
-constexpr int RO_THREADS = 512;   // 8 wavefronts: with one workgroup per compute unit, two per SIMD to overlap each other's latencies
+constexpr int RO_MAX_WIDTH = 256;
+constexpr int RO_THREADS = 512;   // 8 wavefronts, two per SIMD: 256 registers per lane
+constexpr int RO_WAVES = RO_THREADS / 64;
+constexpr int RO_KB0 = 12;        // k-blocks of 32 of the first layer that stay in registers: 96 per lane (16 made the compiler spill),
+constexpr int RO_KT0 = 4;         // and those that are requested again in every round, ahead of the barrier before the layer
+constexpr int RO_PART_PITCH = 36; // floats per row of the head's partial sums
+
+__host__ __device__ inline int ro_kblocks(int K) { return (K + 31) / 32; }
+__host__ __device__ inline int ro_nblocks(int N) { return 2 * ((N + 31) / 32); }   // column blocks of 16, padded to 32 columns
+inline int64_t ro_packed_elems(const int32_t* dims, int L) {
+  int64_t n = 0;
+  for (int l = 0; l < L; ++l) n += (int64_t)ro_nblocks(dims[l + 1]) * ro_kblocks(dims[l]) * 512;
+  return n;
+}
+// draws made ahead, in doubles per member: latent noise [T][B][nz] in stream order, z_0, reward noise, uniforms
+struct RoDraws { int64_t o_zeta, o_z0, o_rew, o_u, count; };
+__host__ __device__ inline RoDraws ro_draws(int B, int T, int nz) {
+  RoDraws d;
+  d.o_zeta = 0;
+  d.o_z0 = d.o_zeta + ((int64_t)B * T * nz + 3) / 4 * 4;
+  d.o_rew = d.o_z0 + ((int64_t)B * nz + 3) / 4 * 4;
+  d.o_u = d.o_rew + ((int64_t)B * T + 3) / 4 * 4;
+  d.count = d.o_u + ((int64_t)B * T + 3) / 4 * 4;
+  return d;
+}
+
+// grid (Philox counters of a member / 256, P): one thread per counter, four doubles each
+__global__ __launch_bounds__(256) void a2c_env_noise_kernel(EnvArgs a, double* __restrict__ draws) {
+  const int i = blockIdx.y;
+  const RoDraws o = ro_draws(a.B, a.T, a.nz);
+  const int64_t item = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (item >= o.count / 4) return;
+  double v[4];
+  if (item >= o.o_u / 4) {          // one counter per transition, its first word
+    const uint32_t c = (uint32_t)(item - o.o_u / 4) * 4;
+    for (int q = 0; q < 4; ++q) v[q] = philox_unit(philox4x32_10(a.step, (uint32_t)i, DOMAIN_ENV + 2, c + q, a.k0, a.k1).x);
+  } else if (item >= o.o_rew / 4) {
+    env_normal4(a.step, i, DOMAIN_ENV + 3, (uint32_t)(item - o.o_rew / 4), a.k0, a.k1, v);
+  } else if (item >= o.o_z0 / 4) {
+    env_normal4(a.step, i, DOMAIN_ENV + 0, (uint32_t)(item - o.o_z0 / 4), a.k0, a.k1, v);
+  } else {
+    env_normal4(a.step, i, DOMAIN_ENV + 4, (uint32_t)item, a.k0, a.k1, v);
+  }
+  double2* __restrict__ p = reinterpret_cast<double2*>(draws + i * o.count + item * 4);
+  p[0] = make_double2(v[0], v[1]);
+  p[1] = make_double2(v[2], v[3]);
+}
 
 struct RolloutArgs {
   EnvArgs e;
   const bf16_t* W16; const float* W32; int64_t stride;
-  int n_hidden, act, hmax;
+  bf16_t* packed; int64_t packed_stride;   // [P] fragments of all layers, layer l from packed_off[l]
+  double* draws;                           // [P][ro_draws().count]
+  int n_hidden, act, hmax, rows;           // rows: trajectories per workgroup
   int dims[RO_MAX_HIDDEN + 2];
-  int64_t w_off[RO_MAX_HIDDEN + 1], b_off[RO_MAX_HIDDEN + 1];
+  int64_t w_off[RO_MAX_HIDDEN + 1], b_off[RO_MAX_HIDDEN + 1], packed_off[RO_MAX_HIDDEN + 1];
 };
 
-// Wt[n][k] (pitch RO_WP) = W[k0 + k][n] for k < 64, n < N: rows of N contiguous values in memory.  A thread
-// holds N / 32 pieces of 16 bytes; piece `it` is row (it % 512) / 8, columns 64 (it / 512) + 8 (it % 8) ...
-struct RoStaged { uint4 v[4]; };
-template <int N>
-__device__ __forceinline__ void ro_fetch(const bf16_t* __restrict__ W, int k0, RoStaged& r) {
+// grid (32-column blocks of all layers together, k-blocks of the deepest layer / 2, P); 32 columns x 64 k of W[K][N] (rows of N) go
+// through LDS and leave as fragments: block (nb, kb), lane l: column 16 nb + l % 16, k = 32 kb + 8 (l / 16) ...
+__global__ __launch_bounds__(256) void a2c_pack_weights_kernel(RolloutArgs a) {
+  __shared__ bf16_t tile[64 * 34];
+  const int i = blockIdx.z;
+  int l = 0, cb = blockIdx.x;
+  while (cb >= ro_nblocks(a.dims[l + 1]) / 2) cb -= ro_nblocks(a.dims[l++ + 1]) / 2;
+  const int K = a.dims[l], N = a.dims[l + 1], KB = ro_kblocks(K);
+  const int k0 = blockIdx.y * 64;
+  if (k0 >= K) return;
+  const bf16_t* __restrict__ W = a.W16 + (int64_t)i * a.stride + a.w_off[l];
+  // (element loads: N = the head's width need not be a multiple of anything)
 #pragma unroll
-  for (int j = 0; j < N / 64; ++j) {
-    const int it = threadIdx.x + RO_THREADS * j;
-    r.v[j] = *reinterpret_cast<const uint4*>(W + (int64_t)(k0 + ((it & 511) >> 3)) * N + 64 * (it >> 9) + 8 * (it & 7));
+  for (int u = 0; u < 8; ++u) {
+    const int x = u * 256 + threadIdx.x, k = x >> 5, n = x & 31;
+    tile[k * 34 + n] = k0 + k < K && cb * 32 + n < N ? W[(int64_t)(k0 + k) * N + cb * 32 + n] : (bf16_t)0;
   }
-}
-template <int N>
-__device__ __forceinline__ void ro_put(const RoStaged& r, bf16_t* Wt) {
+  __syncthreads();
+  const int f = threadIdx.x >> 6, lane = threadIdx.x & 63;   // four fragments: column block f & 1, k-block f >> 1
+  const int kb = blockIdx.y * 2 + (f >> 1), nb = cb * 2 + (f & 1);
+  if (kb >= KB) return;
+  const bf16_t* __restrict__ src = tile + ((f >> 1) * 32 + 8 * (lane >> 4)) * 34 + (f & 1) * 16 + (lane & 15);
+  uint32_t w[4];
 #pragma unroll
-  for (int j = 0; j < N / 64; ++j) {
-    const int it = threadIdx.x + RO_THREADS * j;
-    const int row = (it & 511) >> 3, n0 = 64 * (it >> 9) + 8 * (it & 7), odd = row & 1;
-    const uint4 v = r.v[j];
-    // lanes 8 apart hold rows k and k ^ 1: they exchange halves so that each writes four (k, k + 1) pairs
-    const uint32_t g0 = __shfl_xor(odd ? v.x : v.z, 8), g1 = __shfl_xor(odd ? v.y : v.w, 8);
-    const uint32_t e0 = odd ? g0 : v.x, e1 = odd ? g1 : v.y, o0 = odd ? v.z : g0, o1 = odd ? v.w : g1;
-    uint32_t* out = reinterpret_cast<uint32_t*>(Wt) + (n0 + 4 * odd) * (RO_WP / 2) + (row >> 1);
-    out[0] = (e0 & 0xffffu) | (o0 << 16);
-    out[RO_WP / 2] = (e0 >> 16) | (o0 & 0xffff0000u);
-    out[2 * (RO_WP / 2)] = (e1 & 0xffffu) | (o1 << 16);
-    out[3 * (RO_WP / 2)] = (e1 >> 16) | (o1 & 0xffff0000u);
-  }
-}
-__device__ __forceinline__ ro_frag_t ro_wfrag(const bf16_t* Wt, int n, int c, int hf) {
-  const bf16_t* p = Wt + n * RO_WP + 16 * c + 8 * hf;   // 8-byte aligned
-  const uint2 lo = *reinterpret_cast<const uint2*>(p), hi = *reinterpret_cast<const uint2*>(p + 4);
-  const uint4 v = make_uint4(lo.x, lo.y, hi.x, hi.y);
-  return __builtin_bit_cast(ro_frag_t, v);
+  for (int q = 0; q < 4; ++q) w[q] = (uint32_t)src[2 * q * 34] | (uint32_t)src[(2 * q + 1) * 34] << 16;
+  *reinterpret_cast<uint4*>(a.packed + i * a.packed_stride + a.packed_off[l] + (((int64_t)nb * KB + kb) * 64 + lane) * 8) =
+      make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// out[r][n] = act(sum_k in[r][k] W[k][n] + b[n]) for the 32 rows in LDS; N in {64, 128, 256}, K a multiple of 64
-template <int N>
-__device__ __forceinline__ void ro_dense(const bf16_t* in, int pin, int K, const bf16_t* __restrict__ W, const float* __restrict__ bias,
-                                         int act, bf16_t* out, int pout, bf16_t* Wt) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, lr = lane & 31, hf = lane >> 5;
-  const bool mine = w < N / 32;   // wavefront w owns columns 32 w .. 32 w + 31
-  ro_acc_t acc;
+__device__ __forceinline__ ro_acc_t ro_mfma(uint4 w, uint4 x, ro_acc_t acc) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(ro_frag_t, w), __builtin_bit_cast(ro_frag_t, x), acc, 0, 0, 0);
+}
+// Wavefront w owns the column blocks w and w + 8 of a layer.  The weight fragment is the MFMA's first operand: a lane holds, of
+// row (trajectory) lane % 16, the columns 16 nb + 4 (lane / 16) ... + 3.
+template <int KB>
+struct RoFrags { uint4 v[2][KB > 0 ? KB : 1]; };
+// (blocks the layer does not have are read as its last one and not multiplied: no branch around a load)
+template <int KB>
+__device__ __forceinline__ void ro_fetch(int tid, const bf16_t* __restrict__ frags, int kb0, int kblocks, int nblocks, RoFrags<KB>& r) {
+  const int lane = tid & 63, w = tid >> 6;
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-  // Three register sets: the slabs k0 + 64 and k0 + 128 are on their way while slab k0 is written to LDS and
-  // multiplied (one workgroup per compute unit: nothing else hides the memory latency).  Every slab step issues
-  // the same loads, past the end of W's rows too (the last slab again, never multiplied), so that the number of
-  // loads in flight at each wait is known when the kernel is compiled; with conditional loads every wait was for
-  // all of them, i.e. a full memory latency per slab.
-  const int last = K - 64;
-  RoStaged st[3];
-  ro_fetch<N>(W, 0, st[0]);
-  ro_fetch<N>(W, min(64, last), st[1]);
-  ro_fetch<N>(W, min(128, last), st[2]);
-  auto slab = [&](RoStaged& r, int k0) {
-    ro_put<N>(r, Wt);
-    __syncthreads();
-    ro_fetch<N>(W, min(k0 + 192, last), r);
-    if (mine && k0 < K) {
+  for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const ro_frag_t af = *reinterpret_cast<const ro_frag_t*>(in + lr * pin + k0 + 16 * c + 8 * hf);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ro_wfrag(Wt, 32 * w + lr, c, hf), af, acc, 0, 0, 0);
+    for (int kb = 0; kb < KB; ++kb) {
+      r.v[j][kb] = *reinterpret_cast<const uint4*>(frags + ((min(w + 8 * j, nblocks - 1) * kblocks + min(kb0 + kb, kblocks - 1)) * 64 + lane) * 8);
+    }
+}
+// out = act(in W + b) for MB blocks of 16 rows in LDS.  k-blocks past those handed in (observations wider than 512) are
+// fetched as they are needed.  Columns N .. of the last 32 get zeros (their weights are zero), which the next layer's padded k reads.
+template <int MB, int KB, int KT>
+__device__ __forceinline__ void ro_dense(int tid, const bf16_t* in, int pin, int K, int N, const RoFrags<KB>& wf, const RoFrags<KT>& wt, const bf16_t* __restrict__ frags,
+                                         const float* __restrict__ bias, int act, bf16_t* out, int pout) {
+  const int lane = tid & 63, w = tid >> 6, lr = lane & 15, q = lane >> 4;
+  const int kblocks = ro_kblocks(K), nblocks = ro_nblocks(N);
+  if (w >= nblocks) return;
+  const bool second = w + 8 < nblocks;
+  float4 b[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int n0 = 16 * (w + 8 * j) + 4 * q;
+    b[j] = n0 < N ? *reinterpret_cast<const float4*>(bias + n0) : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  ro_acc_t acc[MB][2];
+#pragma unroll
+  for (int m = 0; m < MB; ++m)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[m][j] = ro_acc_t{0.f, 0.f, 0.f, 0.f};
+  auto block = [&](int kb, const uint4& f0, const uint4& f1) {
+    if (kb < kblocks) {
+#pragma unroll
+      for (int m = 0; m < MB; ++m) {
+        const uint4 x = *reinterpret_cast<const uint4*>(in + (16 * m + lr) * pin + 32 * kb + 8 * q);
+        acc[m][0] = ro_mfma(f0, x, acc[m][0]);
+        if (second) acc[m][1] = ro_mfma(f1, x, acc[m][1]);
       }
     }
-    __syncthreads();
   };
-  for (int k0 = 0; k0 < K; k0 += 192) {
-    slab(st[0], k0);
-    slab(st[1], k0 + 64);
-    slab(st[2], k0 + 128);
-  }
-  // accumulator register e of lane (lr, hf): row lr, column 32 w + 8 (e / 4) + 4 hf + e % 4
-  if (mine) {
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int n0 = 32 * w + 8 * g + 4 * hf;
-      const float4 b = *reinterpret_cast<const float4*>(bias + n0);
-      const float a0 = act_fwd(acc[4 * g] + b.x, act), a1 = act_fwd(acc[4 * g + 1] + b.y, act);
-      const float a2 = act_fwd(acc[4 * g + 2] + b.z, act), a3 = act_fwd(acc[4 * g + 3] + b.w, act);
-      *reinterpret_cast<uint2*>(out + lr * pout + n0) = make_uint2(f2bf_pair(a0, a1), f2bf_pair(a2, a3));
+  for (int kb = 0; kb < KB; ++kb) block(kb, wf.v[0][kb], wf.v[1][kb]);
+#pragma unroll
+  for (int kb = 0; kb < KT; ++kb) block(KB + kb, wt.v[0][kb], wt.v[1][kb]);
+  for (int kb = KB + KT; kb < kblocks; ++kb) {
+    const uint4 w0 = *reinterpret_cast<const uint4*>(frags + (((int64_t)w * kblocks + kb) * 64 + lane) * 8);
+    const uint4 w1 = second ? *reinterpret_cast<const uint4*>(frags + (((int64_t)(w + 8) * kblocks + kb) * 64 + lane) * 8) : make_uint4(0, 0, 0, 0);
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+      const uint4 x = *reinterpret_cast<const uint4*>(in + (16 * m + lr) * pin + 32 * kb + 8 * q);
+      acc[m][0] = ro_mfma(w0, x, acc[m][0]);
+      acc[m][1] = ro_mfma(w1, x, acc[m][1]);
     }
   }
-  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    if (j == 1 && !second) break;
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+      const float a0 = act_fwd(acc[m][j][0] + b[j].x, act), a1 = act_fwd(acc[m][j][1] + b[j].y, act);
+      const float a2 = act_fwd(acc[m][j][2] + b[j].z, act), a3 = act_fwd(acc[m][j][3] + b[j].w, act);
+      *reinterpret_cast<uint2*>(out + (16 * m + lr) * pout + 16 * (w + 8 * j) + 4 * q) = make_uint2(f2bf_pair(a0, a1), f2bf_pair(a2, a3));
+    }
+  }
 }
 
-// hout[r][c] = sum_k in[r][k] W[k][c] + b[c] for c < C <= 32 (float): the whole K x C matrix is staged at once
-__device__ __forceinline__ void ro_head(const bf16_t* in, int pin, int K, const bf16_t* __restrict__ W, const float* __restrict__ bias, int C,
-                                        float* hout, bf16_t* Wt) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, lr = lane & 31, hf = lane >> 5;
-  const int pw = K + 8;
-  for (int e = threadIdx.x; e < 32 * K; e += RO_THREADS) {
-    const int c = e / K, k = e - c * K;
-    Wt[c * pw + k] = c < C ? W[(int64_t)k * C + c] : (bf16_t)0;
-  }
-  __syncthreads();
-  // the eight wavefronts share the contraction (k-blocks of 16 in turn); partial sums are added in wavefront order
-  ro_acc_t acc;
+// The observations of round t, RG trajectories per thread: to memory (the update reads them) and to X0 (the policy's
+// input).  The sum C z runs in float (the result is stored as bf16; the latents themselves stay in double).
+template <int RG>
+__device__ __forceinline__ void ro_observe(int tid, const EnvArgs& e, int i, int t, int r0, int rows, const float* Ct, const float* zf, int zpitch,
+                                           bf16_t* X0, int px) {
+  const int d = e.d, runs = d / 4, groups = (rows + RG - 1) / RG;
+  for (int item = tid; item < groups * runs; item += RO_THREADS) {
+    const int grp = item / runs, j0 = 4 * (item - grp * runs);
+    float acc[RG][4];
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-  for (int kb = w; kb < K / 16; kb += RO_THREADS / 64) {
-    const ro_frag_t af = *reinterpret_cast<const ro_frag_t*>(in + lr * pin + 16 * kb + 8 * hf);
-    const ro_frag_t wf = *reinterpret_cast<const ro_frag_t*>(Wt + lr * pw + 16 * kb + 8 * hf);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, af, acc, 0, 0, 0);
-  }
-  __syncthreads();   // the staged weights are not needed any more: their space takes the partial sums
-  float* part = reinterpret_cast<float*>(Wt);   // [8][32][33]
+    for (int s = 0; s < RG; ++s)
 #pragma unroll
-  for (int e = 0; e < 16; ++e) part[(w * 32 + lr) * 33 + 8 * (e / 4) + 4 * hf + e % 4] = acc[e];
-  __syncthreads();
-  for (int e = threadIdx.x; e < 32 * 32; e += RO_THREADS) {
-    const int r = e >> 5, c = e & 31;
-    float sum = part[r * 33 + c];
-    for (int v = 1; v < RO_THREADS / 64; ++v) sum += part[(32 * v + r) * 33 + c];
-    hout[e] = sum + (c < C ? bias[c] : 0.f);
+      for (int q = 0; q < 4; ++q) acc[s][q] = 0.f;
+    for (int k = 0; k < e.nz; ++k) {
+      const float4 c = *reinterpret_cast<const float4*>(Ct + k * d + j0);
+#pragma unroll
+      for (int s = 0; s < RG; ++s) {
+        const float zk = zf[k * zpitch + grp * RG + s];
+        acc[s][0] = fmaf(c.x, zk, acc[s][0]); acc[s][1] = fmaf(c.y, zk, acc[s][1]);
+        acc[s][2] = fmaf(c.z, zk, acc[s][2]); acc[s][3] = fmaf(c.w, zk, acc[s][3]);
+      }
+    }
+    const float noise_obs = (float)e.env.noise[0];
+#pragma unroll
+    for (int s = 0; s < RG; ++s) {
+      const int r = grp * RG + s;
+      if (r < rows) {
+        const int64_t row = (int64_t)(r0 + r) * (e.T + 1) + t;
+        float v[4], o[4];
+        env_normal4_f32(e.step, i, DOMAIN_ENV + 1, (uint32_t)((row * d + j0) >> 2), e.k0, e.k1, v);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = fmaf(noise_obs, v[q], acc[s][q]);
+        const uint2 packed = make_uint2(f2bf_pair(o[0], o[1]), f2bf_pair(o[2], o[3]));
+        *reinterpret_cast<uint2*>(e.obs + ((int64_t)i * e.rows + row) * d + j0) = packed;
+        *reinterpret_cast<uint2*>(X0 + r * px + j0) = packed;
+      }
+    }
   }
-  __syncthreads();
 }
 
-// bytes of the kernel's LDS ahead of the 16-byte aligned activation buffers
-__host__ __device__ inline size_t ro_front_bytes(int nz, int n_act, int d) {
-  const size_t b = (size_t)(2 * 32 * nz + nz * nz + nz * n_act + nz) * 8 + (size_t)(nz * (d + 1) + 32 * nz + 32 * 32 + 32) * 4;
-  return (b + 15) & ~(size_t)15;
+// LDS of the kernel, in this order: doubles: latents (two copies of [rb][nz]), A transposed, B, w of the latent system, the next
+// round's latent noise [rb][nz], uniforms and reward noise [rb]; then, each 16-byte aligned, floats: C transposed [nz][d], the
+// round's latents [nz][rb], the head's partial sums [8][rb][36]; then bf16: observations and two activation buffers [rb][width + 8].
+struct RoLds { size_t o_Ct, o_zf, o_part, o_x, bytes; };
+__host__ __device__ inline RoLds ro_lds_layout(int rb, int nz, int n_act, int d, int hmax) {
+  RoLds o;
+  const size_t doubles = (size_t)3 * rb * nz + (size_t)nz * nz + (size_t)nz * n_act + nz + 2 * rb;
+  o.o_Ct = (doubles * 8 + 15) & ~(size_t)15;
+  o.o_zf = o.o_Ct + (size_t)nz * d * 4;
+  o.o_part = o.o_zf + (size_t)nz * rb * 4;
+  o.o_x = o.o_part + (size_t)RO_WAVES * rb * RO_PART_PITCH * 4;
+  o.bytes = o.o_x + (size_t)rb * (32 * ro_kblocks(d) + 8) * 2 + (size_t)2 * rb * (32 * ro_kblocks(hmax) + 8) * 2;
+  return o;
 }
+
+// grid (parts, P); MB blocks of 16 trajectories
+template <int MB>
 __global__ __launch_bounds__(RO_THREADS) void a2c_rollout_kernel(RolloutArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char ro_lds[];
+  constexpr int RB = 16 * MB;
   const EnvArgs& e = a.e;
-  const int i = blockIdx.x, nz = e.nz, B = e.B, T = e.T, d = e.d, n_act = e.n_act;
-  // LDS.  doubles: latents (two copies), A, B, w of the latent system; floats: C transposed (kept for the whole
-  // unroll), the round's latents, head outputs; actions; then, 16-byte aligned, the observations, two activation
-  // buffers and the weight slab (which doubles as scratch of the action draw and of the head)
-  double* zs = reinterpret_cast<double*>(ro_lds);                 // [2][32][nz]
-  double* As = zs + 2 * 32 * nz;                                  // [nz][nz]
-  double* Bs = As + nz * nz;                                      // [nz][n_act]
+  const int i = blockIdx.y, nz = e.nz, T = e.T, d = e.d, n_act = e.n_act;
+  const int r0 = blockIdx.x * a.rows, rows = min(a.rows, e.B - r0);
+  const RoLds o = ro_lds_layout(RB, nz, n_act, d, a.hmax);
+  double* zs = reinterpret_cast<double*>(ro_lds);                 // [2][RB][nz]
+  double* At = zs + 2 * RB * nz;                                  // [nz][nz], transposed
+  double* Bs = At + nz * nz;                                      // [nz][n_act]
   double* ws = Bs + nz * n_act;                                   // [nz]
-  float* Ct = reinterpret_cast<float*>(ws + nz);                  // [nz][d + 1]
-  float* zf = Ct + nz * (d + 1);                                  // [32][nz]
-  float* hout = zf + 32 * nz;                                     // [32][32]
-  int* action = reinterpret_cast<int*>(hout + 32 * 32);           // [32]
-  bf16_t* X0 = reinterpret_cast<bf16_t*>(ro_lds + ro_front_bytes(nz, n_act, d));   // [32][d + 8]
-  bf16_t* XA = X0 + 32 * (d + 8);                                 // [32][hmax + 8]
-  bf16_t* XB = XA + 32 * (a.hmax + 8);
-  bf16_t* Wt = XB + 32 * (a.hmax + 8);                            // [256][RO_WP]
-  double* ex = reinterpret_cast<double*>(Wt);                     // [32][32] during the action draw
-  const bf16_t* W16 = a.W16 + (int64_t)i * a.stride;
+  double* zeta = ws + nz;                                         // [RB][nz]
+  double* us = zeta + RB * nz;                                    // [RB]
+  double* rns = us + RB;                                          // [RB]
+  float* Ct = reinterpret_cast<float*>(ro_lds + o.o_Ct);          // [nz][d]
+  float* zf = reinterpret_cast<float*>(ro_lds + o.o_zf);          // [nz][RB]
+  float* part = reinterpret_cast<float*>(ro_lds + o.o_part);      // [8][RB][36]
+  const int px = 32 * ro_kblocks(d) + 8, ph = 32 * ro_kblocks(a.hmax) + 8;
+  bf16_t* X0 = reinterpret_cast<bf16_t*>(ro_lds + o.o_x);         // [RB][px]
+  bf16_t* XA = X0 + RB * px;                                      // [RB][ph]
+  bf16_t* XB = XA + RB * ph;
+  const bf16_t* packed = a.packed + (int64_t)i * a.packed_stride;
   const float* W32 = a.W32 + (int64_t)i * a.stride;
-  if (threadIdx.x == 0) e.t_count[i] += 1;
-  for (int x = threadIdx.x; x < nz * nz; x += RO_THREADS) As[x] = e.env.A[x];
+  const RoDraws od = ro_draws(e.B, T, nz);
+  const double* draws = a.draws + i * od.count;
+  RoFrags<RO_KB0> w0;
+  ro_fetch<RO_KB0>(threadIdx.x, packed + a.packed_off[0], 0, ro_kblocks(d), ro_nblocks(a.dims[1]), w0);
+  // the head: its two column blocks of the k-block this wavefront contributes
+  const int Kh = a.dims[a.n_hidden], C = a.dims[a.n_hidden + 1], kbh = ro_kblocks(Kh);
+  uint4 wh[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    wh[j] = make_uint4(0, 0, 0, 0);
+    if ((int)threadIdx.x >> 6 < kbh)
+      wh[j] = *reinterpret_cast<const uint4*>(packed + a.packed_off[a.n_hidden] + (((int64_t)j * kbh + (threadIdx.x >> 6)) * 64 + (threadIdx.x & 63)) * 8);
+  }
+  const float head_bias = (int)(threadIdx.x & 31) < C ? W32[a.b_off[a.n_hidden] + (threadIdx.x & 31)] : 0.f;
+  if (threadIdx.x == 0 && blockIdx.x == 0) e.t_count[i] += 1;
+  for (int x = threadIdx.x; x < nz * nz; x += RO_THREADS) At[(x % nz) * nz + x / nz] = e.env.A[x];
   for (int x = threadIdx.x; x < nz * n_act; x += RO_THREADS) Bs[x] = e.env.B[x];
   for (int x = threadIdx.x; x < nz; x += RO_THREADS) ws[x] = e.env.w[x];
   for (int x = threadIdx.x; x < d * nz; x += RO_THREADS) {
     const int j = x / nz, k = x - j * nz;
-    Ct[k * (d + 1) + j] = (float)e.env.C[x];
+    Ct[k * d + j] = (float)e.env.C[x];
   }
-  const double noise_obs = e.env.noise[0], noise_rew = e.env.noise[1], noise_lat = e.env.noise[2];
-  // rows past the last trajectory stay zero in every activation buffer
-  for (int x = threadIdx.x; x < 32 * (d + 8) / 2; x += RO_THREADS) reinterpret_cast<uint32_t*>(X0)[x] = 0u;
-  const int quads = (nz + 3) / 4;
+  const double noise_rew = e.env.noise[1], noise_lat = e.env.noise[2];
+  // rows past the last trajectory and columns past the last component stay zero in the observation buffer
+  for (int x = threadIdx.x; x < RB * px / 2; x += RO_THREADS) reinterpret_cast<uint32_t*>(X0)[x] = 0u;
+  for (int x = threadIdx.x; x < nz * RB; x += RO_THREADS) zf[x] = 0.f;
   __syncthreads();
   for (int t = 0; t <= T; ++t) {
-    const int tt = t - 1;
-    double* zo = zs + (t & 1) * 32 * nz;          // latents before this round's transition
-    double* zn_ = zs + ((t + 1) & 1) * 32 * nz;   // and after
-    if (t > 0) {
-      // a_{t-1} from the head outputs: the exponentials with one thread per (trajectory, action), then the
-      // cumulative distribution with one thread per trajectory
-      for (int x = threadIdx.x; x < B * 32; x += RO_THREADS) {
-        const int r = x >> 5, c = x & 31;
-        const float* lg = hout + r * 32;
-        float mx = -INFINITY;
-        for (int q = 0; q < n_act; ++q) mx = fmaxf(mx, lg[q]);
-        ex[x] = c < n_act ? exp((double)lg[c] - (double)mx) : 0.0;
-      }
-      __syncthreads();
-      for (int r = threadIdx.x; r < B; r += RO_THREADS) {
-        double se = 0.0;
-        for (int c = 0; c < n_act; ++c) se += ex[r * 32 + c];
-        const double u = philox_unit(philox4x32_10(e.step, i, DOMAIN_ENV + 2, (uint32_t)(r * T + tt), e.k0, e.k1).x);
-        double cdf = 0.0;
-        int act = 0;
-        for (int c = 0; c < n_act; ++c) { cdf += ex[r * 32 + c] / se; act += cdf <= u ? 1 : 0; }
-        act = act < n_act - 1 ? act : n_act - 1;
-        double rw = 0.0;
-        for (int k = 0; k < nz; ++k) rw += ws[k] * zo[r * nz + k];
-        rw += noise_rew * env_normal(e.step, i, DOMAIN_ENV + 3, (uint32_t)(r * T + tt), e.k0, e.k1);
-        e.act[((int64_t)i * B + r) * T + tt] = act;
-        e.rew[((int64_t)i * B + r) * T + tt] = (float)rw;
-        action[r] = act;
-      }
-      __syncthreads();
-    }
-    const uint32_t domain = t == 0 ? DOMAIN_ENV + 0 : DOMAIN_ENV + 4;
-    for (int item = threadIdx.x; item < B * quads; item += RO_THREADS) {
-      const int r = item / quads, k0 = (item - r * quads) * 4;
-      const uint32_t e0 = (uint32_t)((t == 0 ? r : r * T + tt) * nz + k0);
-      double v[4];
-      if ((e0 & 3u) == 0) {
-        env_normal4(e.step, i, domain, e0 >> 2, e.k0, e.k1, v);
-      } else {
-        for (int q = 0; q < 4; ++q) v[q] = env_normal(e.step, i, domain, e0 + q, e.k0, e.k1);
-      }
-      for (int q = 0; q < 4 && k0 + q < nz; ++q) {
-        const int k = k0 + q;
-        double zv = v[q];
-        if (t > 0) {
-          double acc = 0.0;
-          for (int j = 0; j < nz; ++j) acc += As[k * nz + j] * zo[r * nz + j];
-          zv = acc + Bs[k * n_act + action[r]] + noise_lat * v[q];
+    // (the thread's index, made opaque once per round: otherwise the compiler computes every address of a round ahead of
+    // the loop and keeps them in registers that the weights need)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int tt = t - 1, lane = tid & 63, w = tid >> 6;
+    double* zo = zs + (t & 1) * RB * nz;          // latents before this round's transition
+    double* zn = zs + ((t + 1) & 1) * RB * nz;    // and after
+    // a half-wavefront per trajectory: a_{t-1} from the head outputs (lane = action), then z_t (lane = component)
+    for (int r = tid >> 5; r < rows; r += RO_THREADS / 32) {
+      const int c = tid & 31;
+      int action = 0;
+      if (t > 0) {
+        float lg = part[r * RO_PART_PITCH + c];
+        for (int v = 1; v < kbh; ++v) lg += part[(v * RB + r) * RO_PART_PITCH + c];
+        lg += head_bias;
+        float mx = c < n_act ? lg : -INFINITY;
+#pragma unroll
+        for (int off = 16; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 32));
+        const double ex = c < n_act ? exp((double)lg - (double)mx) : 0.0;
+        double se = ex;
+#pragma unroll
+        for (int off = 16; off > 0; off >>= 1) se += __shfl_xor(se, off, 32);
+        double cdf = ex / se;
+#pragma unroll
+        for (int off = 1; off < 32; off <<= 1) {
+          const double below = __shfl_up(cdf, off, 32);
+          if (c >= off) cdf += below;
         }
-        zn_[r * nz + k] = zv;
-        zf[r * nz + k] = (float)zv;
+        const uint64_t passed = __ballot(c < n_act && cdf <= us[r]);
+        action = __popc((uint32_t)(lane & 32 ? passed >> 32 : passed));
+        action = action < n_act - 1 ? action : n_act - 1;
+        if (c == 0) e.act[((int64_t)i * e.B + r0 + r) * T + tt] = action;
+      }
+      for (int k = c; k < nz; k += 32) {
+        double zv;
+        if (t == 0) {
+          zv = draws[od.o_z0 + (int64_t)(r0 + r) * nz + k];
+        } else {
+          double acc = 0.0;
+          for (int j = 0; j < nz; ++j) acc += At[j * nz + k] * zo[r * nz + j];
+          zv = acc + Bs[k * n_act + action] + noise_lat * zeta[r * nz + k];
+        }
+        zn[r * nz + k] = zv;
+        zf[k * RB + r] = (float)zv;
       }
     }
     __syncthreads();
-    // observations of round t: to memory (the update reads them) and to X0 (the policy's input).  The sum C z runs
-    // in float (the result is stored as bf16; the latents themselves stay in double from round to round).
-    {
-      const int runs = d / 4;
-      for (int item = threadIdx.x; item < B * runs; item += RO_THREADS) {
-        const int r = item / runs, g = item - r * runs, j0 = 4 * g;
-        const int64_t row = (int64_t)r * (T + 1) + t;
-        float v[4];
-        env_normal4_f32(e.step, i, DOMAIN_ENV + 1, (uint32_t)((row * d + j0) >> 2), e.k0, e.k1, v);
-        float acc[4] = {0.f, 0.f, 0.f, 0.f};
-        for (int k = 0; k < nz; ++k) {
-          const float zk = zf[r * nz + k];
+    // next round's draws are requested, this round's reward is booked and the observations are made while they arrive
+    double next_zeta[4], next_u = 0.0, next_rn = 0.0;
+    const int n_zeta = t < T ? rows * nz : 0;     // (at most 32 x 64 = 4 per thread)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) acc[q] = fmaf(Ct[k * (d + 1) + j0 + q], zk, acc[q]);
-        }
-        float o[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) o[q] = fmaf((float)noise_obs, v[q], acc[q]);
-        const uint2 packed = make_uint2(f2bf_pair(o[0], o[1]), f2bf_pair(o[2], o[3]));
-        *reinterpret_cast<uint2*>(e.obs + ((int64_t)i * e.rows + row) * d + j0) = packed;
-        *reinterpret_cast<uint2*>(X0 + r * (d + 8) + j0) = packed;
-      }
-      __syncthreads();
+    for (int q = 0; q < 4; ++q) {
+      const int x = q * RO_THREADS + tid;
+      next_zeta[q] = 0.0;
+      if (x < n_zeta) { const int r = x / nz; next_zeta[q] = draws[od.o_zeta + ((int64_t)(r0 + r) * T + t) * nz + (x - r * nz)]; }
     }
+    if (t < T && tid < rows) {
+      next_u = draws[od.o_u + (int64_t)(r0 + tid) * T + t];
+      next_rn = draws[od.o_rew + (int64_t)(r0 + tid) * T + t];
+    }
+    if (t > 0 && tid < rows) {
+      const int r = tid;
+      double rw = 0.0;
+      for (int k = 0; k < nz; ++k) rw += ws[k] * zo[r * nz + k];
+      rw += noise_rew * rns[r];
+      e.rew[((int64_t)i * e.B + r0 + r) * T + tt] = (float)rw;
+    }
+    // (as many trajectories per thread as leave every thread something to do)
+    if (rows * (d / 4) >= 4 * RO_THREADS) ro_observe<4>(tid, e, i, t, r0, rows, Ct, zf, RB, X0, px);
+    else if (rows * (d / 4) >= 2 * RO_THREADS) ro_observe<2>(tid, e, i, t, r0, rows, Ct, zf, RB, X0, px);
+    else ro_observe<1>(tid, e, i, t, r0, rows, Ct, zf, RB, X0, px);
     if (t == T) break;
-    // the policy on the round's observations
-    const bf16_t* in = X0;
-    int pin = d + 8, K = d;
-    for (int l = 0; l < a.n_hidden; ++l) {
-      bf16_t* out = l & 1 ? XB : XA;
-      const int N = a.dims[l + 1];
-      if (N == 256) ro_dense<256>(in, pin, K, W16 + a.w_off[l], W32 + a.b_off[l], a.act, out, a.hmax + 8, Wt);
-      else if (N == 128) ro_dense<128>(in, pin, K, W16 + a.w_off[l], W32 + a.b_off[l], a.act, out, a.hmax + 8, Wt);
-      else ro_dense<64>(in, pin, K, W16 + a.w_off[l], W32 + a.b_off[l], a.act, out, a.hmax + 8, Wt);
-      in = out; pin = a.hmax + 8; K = a.dims[l + 1];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int x = q * RO_THREADS + tid;
+      if (x < n_zeta) zeta[x] = next_zeta[q];
     }
-    ro_head(in, pin, K, W16 + a.w_off[a.n_hidden], W32 + a.b_off[a.n_hidden], a.dims[a.n_hidden + 1], hout, Wt);
+    if (tid < rows) { us[tid] = next_u; rns[tid] = next_rn; }
+    // the policy on the round's observations
+    RoFrags<RO_KT0> wt;
+    ro_fetch<RO_KT0>(tid, packed + a.packed_off[0], RO_KB0, ro_kblocks(d), ro_nblocks(a.dims[1]), wt);
+    __syncthreads();
+    ro_dense<MB, RO_KB0, RO_KT0>(tid, X0, px, d, a.dims[1], w0, wt, packed + a.packed_off[0], W32 + a.b_off[0], a.act, XA, ph);
+    RoFrags<RO_MAX_WIDTH / 32> wl;
+    if (a.n_hidden > 1) ro_fetch<RO_MAX_WIDTH / 32>(tid, packed + a.packed_off[1], 0, ro_kblocks(a.dims[1]), ro_nblocks(a.dims[2]), wl);
+    __syncthreads();
+    bf16_t* in = XA;
+    bf16_t* out = XB;
+    for (int l = 1; l < a.n_hidden; ++l) {
+      ro_dense<MB, RO_MAX_WIDTH / 32, 0>(tid, in, ph, a.dims[l], a.dims[l + 1], wl, RoFrags<0>{}, packed + a.packed_off[l], W32 + a.b_off[l], a.act, out, ph);
+      if (l + 1 < a.n_hidden)
+        ro_fetch<RO_MAX_WIDTH / 32>(tid, packed + a.packed_off[l + 1], 0, ro_kblocks(a.dims[l + 1]), ro_nblocks(a.dims[l + 2]), wl);
+      __syncthreads();
+      bf16_t* x = in; in = out; out = x;
+    }
+    // the head: the wavefronts share the contraction, the partial sums are added in wavefront order by the action draw
+    if (w < kbh) {
+      const int lr = lane & 15, q = lane >> 4;
+#pragma unroll
+      for (int m = 0; m < MB; ++m) {
+        const uint4 x = *reinterpret_cast<const uint4*>(in + (16 * m + lr) * ph + 32 * w + 8 * q);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const ro_acc_t acc = ro_mfma(wh[j], x, ro_acc_t{0.f, 0.f, 0.f, 0.f});
+          *reinterpret_cast<float4*>(part + (w * RB + 16 * m + lr) * RO_PART_PITCH + 16 * j + 4 * q) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        }
+      }
+    }
+    __syncthreads();
   }
 }
 
-// LDS of the kernel above for a shape, 0 if the shape is not covered
-static size_t rollout_lds_bytes(const pbt_config& c) {
-  const int L = c.n_layers, d = c.dims[0], C = c.dims[L];
-  if (c.batch > 32 || d % 64 || L - 1 < 1 || L - 1 > RO_MAX_HIDDEN || C > 32) return 0;
+// How a population is cut into workgroups, 0 parts if the shape is not covered.  One workgroup occupies a compute unit
+// (registers), so a member gets as many as the chip has left for it, down to four trajectories each (below that the
+// per-round latencies are all there is); never more than 32 trajectories, and 16 where 32 do not fit LDS.
+struct RoCut { int parts, rows; size_t lds; };
+static RoCut rollout_cut(const pbt_config& c) {
+  const int L = c.n_layers, d = c.dims[0], C = c.dims[L], B = c.batch;
+  const RoCut none{0, 0, 0};
+  if (d % 8 || L - 1 < 1 || L - 1 > RO_MAX_HIDDEN || C > 32 || c.latent_dim > 64) return none;
   int hmax = 0;
   for (int l = 1; l < L; ++l) {
-    if (c.dims[l] != 64 && c.dims[l] != 128 && c.dims[l] != 256) return 0;
+    if (c.dims[l] > RO_MAX_WIDTH || c.dims[l] % 8) return none;
     hmax = c.dims[l] > hmax ? c.dims[l] : hmax;
   }
-  const size_t wt = (size_t)256 * RO_WP * 2;   // also holds the head's [32][K + 8] bf16 and its 8 x 32 x 33 partial sums
-  if ((size_t)32 * (hmax + 8) * 2 > wt || (size_t)(RO_THREADS / 64) * 32 * 33 * 4 > wt) return 0;
-  if ((size_t)32 * 32 * 8 > wt) return 0;      // (and the exponentials of the action draw)
-  const size_t bytes = ro_front_bytes(c.latent_dim, C - 1, d) + (size_t)32 * (d + 8) * 2 + (size_t)2 * 32 * (hmax + 8) * 2 + wt;
-  return bytes <= 160 * 1024 ? bytes : 0;
+  auto lds_of = [&](int rows) { return ro_lds_layout(rows > 16 ? 32 : 16, c.latent_dim, C - 1, d, hmax).bytes; };
+  constexpr size_t LDS_MAX = 160 * 1024;
+  int parts = 256 / c.P;
+  parts = parts > (B + 3) / 4 ? (B + 3) / 4 : parts;
+  parts = parts < (B + 31) / 32 ? (B + 31) / 32 : parts;
+  int rows = (B + parts - 1) / parts;
+  if (rows > 16 && lds_of(rows) > LDS_MAX) { parts = (B + 15) / 16; rows = (B + parts - 1) / parts; }
+  if (lds_of(rows) > LDS_MAX) return none;
+  return RoCut{(B + rows - 1) / rows, rows, lds_of(rows)};
 }
+
+static int64_t a2c_packed_elems(const pbt_config* c) { return rollout_cut(*c).parts ? ro_packed_elems(c->dims, c->n_layers) : 0; }
+static int64_t a2c_draw_count(const pbt_config* c) { return rollout_cut(*c).parts ? ro_draws(c->batch, c->unroll, c->latent_dim).count : 0; }
 
 // Pushes the unroll's return (mean over trajectories of the summed rewards, in double, trajectories in order)
 // into the member's history ring.
@@ -737,15 +882,30 @@ pbt_status a2c_step_on_policy(pbt_handle* h, const A2CEnv& env, uint32_t step, h
   float* gout = h->sc<float>(a.o_gout);
   EnvArgs ea{env, c.latent_dim, C - 1, d, B, T, R, step, (uint32_t)c.seed, (uint32_t)(c.seed >> 32), h->sc<double>(a.o_lat), gout,
              h->sc<int32_t>(a.o_act), h->sc<float>(a.o_rew), obs, h->st<int32_t>(p.o_t)};
-  if (const size_t lds = rollout_lds_bytes(c)) {
+  if (const RoCut cut = rollout_cut(c); cut.parts) {
     RolloutArgs ra{};
-    ra.e = ea; ra.W16 = W16; ra.W32 = W32; ra.stride = S; ra.n_hidden = L - 1; ra.act = c.act; ra.hmax = 0;
+    ra.e = ea; ra.W16 = W16; ra.W32 = W32; ra.stride = S; ra.n_hidden = L - 1; ra.act = c.act; ra.rows = cut.rows;
+    ra.packed = h->sc<bf16_t>(a.o_packed); ra.packed_stride = ro_packed_elems(c.dims, L); ra.draws = h->sc<double>(a.o_draws);
+    int64_t off = 0;
+    int col_blocks = 0, kmax = 0;
     for (int l = 0; l <= L; ++l) ra.dims[l] = c.dims[l];
     for (int l = 1; l < L; ++l) ra.hmax = c.dims[l] > ra.hmax ? c.dims[l] : ra.hmax;
-    for (int l = 0; l < L; ++l) { ra.w_off[l] = p.lay.w_off[l]; ra.b_off[l] = p.lay.b_off[l]; }
-    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(a2c_rollout_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    PBT_HIP(h, attr);
-    hipLaunchKernelGGL(a2c_rollout_kernel, dim3(P), dim3(RO_THREADS), lds, s, ra);
+    for (int l = 0; l < L; ++l) {
+      ra.w_off[l] = p.lay.w_off[l]; ra.b_off[l] = p.lay.b_off[l]; ra.packed_off[l] = off;
+      off += (int64_t)ro_nblocks(c.dims[l + 1]) * ro_kblocks(c.dims[l]) * 512;
+      col_blocks += ro_nblocks(c.dims[l + 1]) / 2;
+      kmax = c.dims[l] > kmax ? c.dims[l] : kmax;
+    }
+    static hipError_t attr1 = hipFuncSetAttribute(reinterpret_cast<const void*>(a2c_rollout_kernel<1>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    static hipError_t attr2 = hipFuncSetAttribute(reinterpret_cast<const void*>(a2c_rollout_kernel<2>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    PBT_HIP(h, attr1);
+    PBT_HIP(h, attr2);
+    hipLaunchKernelGGL(a2c_pack_weights_kernel, dim3(col_blocks, (kmax + 63) / 64, P), dim3(256), 0, s, ra);
+    PBT_HIP(h, hipGetLastError());
+    hipLaunchKernelGGL(a2c_env_noise_kernel, dim3((unsigned)((ro_draws(B, T, c.latent_dim).count / 4 + 255) / 256), P), dim3(256), 0, s, ea, ra.draws);
+    PBT_HIP(h, hipGetLastError());
+    if (cut.rows > 16) hipLaunchKernelGGL(a2c_rollout_kernel<2>, dim3(cut.parts, P), dim3(RO_THREADS), cut.lds, s, ra);
+    else hipLaunchKernelGGL(a2c_rollout_kernel<1>, dim3(cut.parts, P), dim3(RO_THREADS), cut.lds, s, ra);
     PBT_HIP(h, hipGetLastError());
     hipLaunchKernelGGL(a2c_push_return_kernel, dim3(P), dim3(64), 0, s, h->sc<float>(a.o_rew), B, T, h->st<float>(p.o_hist));
     PBT_HIP(h, hipGetLastError());

@@ -46,6 +46,7 @@ struct A2CPlan {
   // on-policy generation: latent states (double [P][batch][latent_dim]), the policy's hidden activations and
   // head outputs for one time step ([P][batch][width])
   size_t o_lat, o_ga[PBT_MAX_DIMS], o_gout;
+  size_t o_packed, o_draws;   // the one-kernel unroll's packed weights and the draws made ahead of it
 };
 
 struct TfBlockOff { int64_t ln1g, ln1b, wqkv, bqkv, wo, bo, ln2g, ln2b, w1, b1, w2, b2; };

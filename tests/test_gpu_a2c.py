@@ -230,3 +230,46 @@ def test_a2c_on_policy_full_size_steps():
     sc = _eval(g)
     assert len(set(sc.tolist())) > 100 and n_differ <= 0.01 * n_choices
     print("a2c on-policy full size:", {k: float("%.3g" % v) for k, v in worst.items()}, "choices differing:", n_differ, "of", n_choices, flush=True)
+
+
+@pytest.mark.parametrize("P,dims,batch,unroll,latent", [
+    (3, [40, 264, 24, 9], 5, 4, 4),            # a hidden width past the one-kernel unroll: the kernels of one round each
+    (2, [584, 256, 8, 32], 6, 4, 7),           # more k-blocks than are kept in registers, the widest head
+    (100, [72, 40, 19], 36, 3, 5),             # 18 trajectories per workgroup: two blocks of 16 rows; one hidden layer
+    (2, [64, 24, 200, 136, 5], 33, 4, 1),      # three hidden layers of ragged widths, nine workgroups of four and fewer
+    (130, [512, 256, 256, 19], 32, 2, 16),     # one workgroup of 32 per member
+    (2, [512, 256, 256, 3], 32, 3, 64),        # the largest latent system
+])
+def test_a2c_unroll_at_the_edges_of_its_kernels(P, dims, batch, unroll, latent):
+    """The unroll where its cut into workgroups, row blocks and fragments has remainders: observations and rewards
+    replayed by the oracle along the GPU's actions, choices that differ only next to an edge of the cdf (criteria of
+    the free-running test above), and the step taken on it."""
+    from oracle import nets
+    wl = workloads.A2C_MLP.replace(P=P, dims=dims, n_actions=dims[-1] - 1, batch=batch, unroll=unroll, n_train=50, n_trunc=1, latent=latent,
+                                   on_policy=1, priors=[("log", 1e-4, 2e-3), ("log", 1e-4, 1e-2)])
+    sample = sorted({0, P // 2, P - 1})
+    pair = A2CPair(wl, ref_members=sample)
+    g = pair.gpu
+    n_choices = n_differ = 0
+    for s in range(2):
+        before = {i: [(W.copy(), b.copy()) for W, b in pair.oa.params_of(pair.ref[i])] for i in sample}
+        g.step(pair.d_pool, s)
+        for i in sample:
+            obs_g, act_g, rew_g = pair.gpu_unroll(i)
+            assert act_g.min() >= 0 and act_g.max() < wl.n_actions
+            obs_o, act_o, rew_o, margin = pair.env_mod.rollout(pair.spec, pair.env, before[i], i, s, forced_actions=act_g)
+            differ = act_o != act_g
+            assert np.all(margin[differ] < 1e-3)
+            n_choices += act_g.size
+            n_differ += int(differ.sum())
+            obs_o16 = nets.round_bf16(obs_o.astype(np.float64))
+            off = obs_o16 != obs_g
+            assert np.all(np.abs(obs_o16 - obs_g)[off] <= np.maximum(2.0 ** -7 * np.abs(obs_g)[off], 2e-6)) and np.mean(off) <= 1e-3
+            assert float(np.max(np.abs(rew_o.astype(np.float64) - rew_g))) <= 1e-5
+        loss_ref = pair.step_ref(s)
+        loss = g.get(binding.ARR_LOSS)[sample]
+        assert float(np.max(np.abs(loss - loss_ref) / np.maximum(np.abs(loss_ref), FLOOR))) <= TOL_BF16
+        for i in sample:
+            assert pair.member_errors(i, binding.ARR_W32, "theta")[0] <= TOL_BF16
+        _hist_equal(pair, sample)
+    assert n_differ <= max(1, 0.01 * n_choices)
