@@ -30,7 +30,8 @@ __device__ __forceinline__ bf16x8_t load_frag(const bf16_t* p, bool valid) {
   return *reinterpret_cast<bf16x8_t*>(&v);
 }
 
-// grid (ceil(rows / 32), P); dynamic LDS = 32 * (K + 8) bf16 + 4 * 32 * 33 floats
+// grid (workgroups per member, P); dynamic LDS = C rows of K + 8 bf16 (rounded up to 16 bytes) + 4 * 32 * 33 floats.  A workgroup
+// takes the blocks of 32 rows blockIdx.x, blockIdx.x + gridDim.x, ...: the weights are staged once for all of them.
 __global__ __launch_bounds__(256) void head_fwd_loss_kernel(const bf16_t* __restrict__ A, int64_t sa,
                                                             const bf16_t* __restrict__ W16, int64_t sw,
                                                             const float* __restrict__ bias, int64_t sbias,
@@ -40,22 +41,27 @@ __global__ __launch_bounds__(256) void head_fwd_loss_kernel(const bf16_t* __rest
                                                             float* __restrict__ rowloss, int64_t srowloss) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int pitch = K + 8;
-  bf16_t* Wt = reinterpret_cast<bf16_t*>(smem);                                  // [32][K + 8], rows >= C unused
-  float* Lg = reinterpret_cast<float*>(smem + (size_t)HEAD_NP * pitch * 2);      // [4 wavefronts][32][33]
+  bf16_t* Wt = reinterpret_cast<bf16_t*>(smem);                                  // [C][K + 8]
+  float* Lg = reinterpret_cast<float*>(smem + (size_t)C * pitch * 2);            // [4 wavefronts][32][33]; K + 8 is a multiple of 8
   const int i = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r_lane = blockIdx.x * HEAD_FWD_ROWS + (lane & 31);
   const int kq = (lane >> 5) * 8;
-  const bf16_t* __restrict__ arow = A + (int64_t)i * sa + (int64_t)r_lane * K + kq;
-  const bool row_ok = r_lane < rows;
-  // the first rows' fragments are requested before the weights are staged
+  const bf16_t* __restrict__ arow;
+  bool row_ok;
+  // the first rows' fragments are requested before the weights are staged, a later block's before the one ahead of it is finished
   constexpr int AHEAD = 8;
   bf16x8_t af[AHEAD];
+  auto request_rows = [&](int block) {
+    const int r_lane = block * HEAD_FWD_ROWS + (lane & 31);
+    arow = A + (int64_t)i * sa + (int64_t)r_lane * K + kq;
+    row_ok = r_lane < rows;
 #pragma unroll
-  for (int j = 0; j < AHEAD; ++j) {
-    const int k0 = (wave + 4 * j) * 16;
-    af[j] = load_frag(arow + k0, row_ok && k0 + kq + 8 <= K);
-  }
+    for (int j = 0; j < AHEAD; ++j) {
+      const int k0 = (wave + 4 * j) * 16;
+      af[j] = load_frag(arow + k0, row_ok && k0 + kq + 8 <= K);
+    }
+  };
+  request_rows(blockIdx.x);
   // stage W[K][C] transposed; rows >= C of the 32-wide class tile are never read (their lanes use zeros)
   const bf16_t* __restrict__ W = W16 + (int64_t)i * sw;
   if ((reinterpret_cast<uintptr_t>(W) & 15) == 0) {
@@ -78,6 +84,7 @@ __global__ __launch_bounds__(256) void head_fwd_loss_kernel(const bf16_t* __rest
   __syncthreads();
 
   const bf16_t* brow = Wt + (lane & 31) * pitch + kq;
+  for (int block = blockIdx.x; block * HEAD_FWD_ROWS < rows; block += gridDim.x) {
   f32x16_t acc;
 #pragma unroll
   for (int e = 0; e < 16; ++e) acc[e] = 0.f;
@@ -100,6 +107,7 @@ __global__ __launch_bounds__(256) void head_fwd_loss_kernel(const bf16_t* __rest
   for (int e = 0; e < 16; ++e)
     Lg[(wave * 32 + 8 * (e / 4) + 4 * (lane >> 5) + (e % 4)) * 33 + (lane & 31)] = acc[e];
   __syncthreads();
+  if ((block + (int)gridDim.x) * HEAD_FWD_ROWS < rows) request_rows(block + gridDim.x);
   // partial sums of the four wavefronts, added in wavefront order
   for (int e = threadIdx.x; e < 32 * 32; e += 256) {
     const int o = (e >> 5) * 33 + (e & 31);
@@ -108,7 +116,7 @@ __global__ __launch_bounds__(256) void head_fwd_loss_kernel(const bf16_t* __rest
   __syncthreads();
 
   if (threadIdx.x < HEAD_FWD_ROWS) {
-    const int r = blockIdx.x * HEAD_FWD_ROWS + threadIdx.x;
+    const int r = block * HEAD_FWD_ROWS + threadIdx.x;
     if (r < rows) {
       const float* __restrict__ b = bias + (int64_t)i * sbias;
       float* lg = Lg + threadIdx.x * 33;
@@ -160,18 +168,26 @@ __global__ __launch_bounds__(256) void head_fwd_loss_kernel(const bf16_t* __rest
       }
     }
   }
+  __syncthreads();  // the logits are read before the next block's go there
+  }
 }
 
 hipError_t head_fwd_loss(const bf16_t* A, int64_t sa, const bf16_t* W16, int64_t sw, const float* bias, int64_t sbias,
                          const int32_t* labels, int64_t sy, int P, int rows, int K, int C, float gscale, int n_pos,
                          bf16_t* dlogits, float* rowloss, int64_t srowloss, hipStream_t s) {
   if (C > HEAD_NP || C < 1 || K % 8 || (n_pos >= 0 && C != 1)) return hipErrorInvalidValue;
-  const size_t lds = (size_t)HEAD_NP * (K + 8) * 2 + (size_t)4 * 32 * 33 * 4;
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
+  // (LDS for the C rows of weights that exist, not the tile's 32: with 10 classes over 1024 features four workgroups fit a compute
+  // unit instead of one)
+  const size_t lds = (size_t)C * (K + 8) * 2 + (size_t)4 * 32 * 33 * 4;
+  if ((size_t)HEAD_NP * (K + 8) * 2 + (size_t)4 * 32 * 33 * 4 > 160 * 1024) return hipErrorInvalidValue;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(head_fwd_loss_kernel),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  dim3 grid((rows + HEAD_FWD_ROWS - 1) / HEAD_FWD_ROWS, P);
+  // Enough workgroups to fill the chip four deep; past that each takes several row blocks, because staging the weights costs as much
+  // as a few blocks (8192 held-out rows of 64 members, K = 1024: 619 us with a workgroup per block, 242 now, most of it the
+  // activations' 1.07 GB).
+  const int blocks = (rows + HEAD_FWD_ROWS - 1) / HEAD_FWD_ROWS, fill = (1024 + P - 1) / P;
+  dim3 grid(blocks < fill ? blocks : fill, P);
   hipLaunchKernelGGL(head_fwd_loss_kernel, grid, dim3(256), lds, s, A, sa, W16, sw, bias, sbias, labels, sy, rows, K, C,
                      gscale, n_pos, dlogits, rowloss, srowloss);
   return hipGetLastError();

@@ -5,6 +5,7 @@
 #include "internal.h"
 #include "optim_math.h"
 #include "philox.h"
+#include "row_sum.h"
 
 namespace pbt {
 
@@ -103,20 +104,19 @@ hipError_t gather_batch(const float* train_x, const int32_t* train_y, int n_trai
   return hipGetLastError();
 }
 
-// Per-member reduction of per-row values with wavefront shuffles: lane l adds rows l, l+64, ...
-// in order, then a butterfly over the 64 lanes.
-__global__ __launch_bounds__(64) void row_reduce_kernel(const float* __restrict__ rowval, int64_t srow, int rows,
-                                                        float scale, float* __restrict__ out, int out_stride) {
+// Per-member reduction of per-row values: thread l adds rows l, l + n, ... in order (n threads), a butterfly over the
+// lanes, then the wavefronts in order.  Up to 1024 rows one wavefront does it; more rows (held-out sets) are latency-bound in
+// one (8192 rows: 46 us, 32768 in perplexity_score: 187 us), so sixteen share them there, eight loads of each thread in flight (5 and 6 us).
+__global__ __launch_bounds__(1024) void row_reduce_kernel(const float* __restrict__ rowval, int64_t srow, int rows,
+                                                          float scale, float* __restrict__ out, int out_stride) {
+  __shared__ float wsum[16];
   const int i = blockIdx.x;
-  const float* __restrict__ p = rowval + (int64_t)i * srow;
-  float acc = 0.f;
-  for (int r = threadIdx.x; r < rows; r += 64) acc += p[r];
-  acc = wave_sum(acc);
+  const float acc = member_row_sum(rowval + (int64_t)i * srow, rows, wsum);
   if (threadIdx.x == 0) out[(int64_t)i * out_stride] = acc * scale;
 }
 hipError_t row_reduce(const float* rowval, int64_t srow, int P, int rows, float scale, float* out, int out_stride,
                       hipStream_t s) {
-  hipLaunchKernelGGL(row_reduce_kernel, dim3(P), dim3(64), 0, s, rowval, srow, rows, scale, out, out_stride);
+  hipLaunchKernelGGL(row_reduce_kernel, dim3(P), dim3(row_sum_threads(rows)), 0, s, rowval, srow, rows, scale, out, out_stride);
   return hipGetLastError();
 }
 
@@ -193,9 +193,12 @@ __global__ __launch_bounds__(256) void latent_normal_kernel(bf16_t* __restrict__
   const int64_t blk = (int64_t)blockIdx.x * 256 + threadIdx.x;  // block of 4 elements
   if (blk * 4 >= per_member) return;
   const u32x4 w = philox4x32_10(c0, (uint32_t)i, domain, (uint32_t)blk, k0, k1);
-  const double r1 = sqrt(-2.0 * log(philox_unit(w.x))), a1 = 6.283185307179586476925 * philox_unit(w.y);
-  const double r2 = sqrt(-2.0 * log(philox_unit(w.z))), a2 = 6.283185307179586476925 * philox_unit(w.w);
-  const double v[4] = {r1 * cos(a1), r1 * sin(a1), r2 * cos(a2), r2 * sin(a2)};
+  // (cos and sin of 2 pi u through sincospi(2 u): no reduction of a large argument modulo pi)
+  const double r1 = sqrt(-2.0 * log(philox_unit(w.x))), r2 = sqrt(-2.0 * log(philox_unit(w.z)));
+  double s1, c1, s2, c2;
+  sincospi(2.0 * philox_unit(w.y), &s1, &c1);
+  sincospi(2.0 * philox_unit(w.w), &s2, &c2);
+  const double v[4] = {r1 * c1, r1 * s1, r2 * c2, r2 * s2};
   bf16_t* __restrict__ o = out + (int64_t)i * per_member + blk * 4;
 #pragma unroll
   for (int e = 0; e < 4; ++e)
@@ -237,16 +240,30 @@ hipError_t gather_rows(const float* train_x, int n_train, int d, int P, int B, i
   return hipGetLastError();
 }
 
-// one wavefront per row: lanes stride over the row, butterfly sum
+// one wavefront per row: lanes stride over the row, 16 bytes at a time where rows are aligned for it (2 bytes at a time a
+// load instruction moved 128 bytes: 47 us for 65536 rows of 784, 20 now), butterfly sum
 __global__ __launch_bounds__(256) void row_sqnorm_kernel(const bf16_t* __restrict__ X, int64_t n_rows, int d,
                                                          float* __restrict__ out) {
   const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= n_rows) return;
   const bf16_t* __restrict__ p = X + r * d;
   float acc = 0.f;
-  for (int c = threadIdx.x & 63; c < d; c += 64) {
-    const float v = bf2f(p[c]);
-    acc = fmaf(v, v, acc);
+  if ((d & 7) == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0) {
+    for (int c = (threadIdx.x & 63) * 8; c < d; c += 512) {
+      const uint4 x = *reinterpret_cast<const uint4*>(p + c);
+      const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float lo = __uint_as_float(w[q] << 16), hi = __uint_as_float(w[q] & 0xffff0000u);
+        acc = fmaf(lo, lo, acc);
+        acc = fmaf(hi, hi, acc);
+      }
+    }
+  } else {
+    for (int c = threadIdx.x & 63; c < d; c += 64) {
+      const float v = bf2f(p[c]);
+      acc = fmaf(v, v, acc);
+    }
   }
   acc = wave_sum(acc);
   if ((threadIdx.x & 63) == 0) out[r] = acc;

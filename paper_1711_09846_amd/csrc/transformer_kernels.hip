@@ -13,6 +13,7 @@
 #include "common.h"
 #include "internal.h"
 #include "philox.h"
+#include "row_sum.h"
 #include "dropout.h"
 
 namespace pbt {
@@ -933,16 +934,15 @@ hipError_t tf_scatter_rows(const float* src, int P, int rows, float* dst, int64_
   return hipGetLastError();
 }
 
-// score[i] = -exp(mean of rowloss[i][:])   (perplexity, negated), one wavefront per member
-__global__ __launch_bounds__(64) void perplexity_kernel(const float* __restrict__ rowloss, int rows, float* __restrict__ score) {
+// score[i] = -exp(mean of rowloss[i][:])   (perplexity, negated), one workgroup per member
+__global__ __launch_bounds__(1024) void perplexity_kernel(const float* __restrict__ rowloss, int rows, float* __restrict__ score) {
+  __shared__ float wsum[16];
   const int i = blockIdx.x;
-  float acc = 0.f;
-  for (int r = threadIdx.x; r < rows; r += 64) acc += rowloss[(int64_t)i * rows + r];
-  acc = wave_sum(acc);
+  const float acc = member_row_sum(rowloss + (int64_t)i * rows, rows, wsum);
   if (threadIdx.x == 0) score[i] = -expf(acc / (float)rows);
 }
 hipError_t perplexity_score(const float* rowloss, int P, int rows, float* score, hipStream_t s) {
-  hipLaunchKernelGGL(perplexity_kernel, dim3(P), dim3(64), 0, s, rowloss, rows, score);
+  hipLaunchKernelGGL(perplexity_kernel, dim3(P), dim3(row_sum_threads(rows)), 0, s, rowloss, rows, score);
   return hipGetLastError();
 }
 
