@@ -232,6 +232,7 @@ static pbt_status a2c_update(pbt_handle* h, hipStream_t s) {
   {
     // (the bias gradient, column sums of dout, is a by-product of the same launch)
     GemmOperands wg{A[L - 1], Kh, (int64_t)R * Kh, true, dout, 32, (int64_t)R * 32, false, Kh, C, R, P};
+    wg.b_cols = 32;
     wg.colsum = G + p.lay.b_off[L - 1]; wg.colsum_stride = S;
     PBT_LAUNCH(h, PBT_K_HEAD, s, gemm_store_f32(wg, G + p.lay.w_off[L - 1], C, S, s));
   }

@@ -352,6 +352,7 @@ pbt_status step_bf16(pbt_handle* h, const float* train_x, const int32_t* train_y
     // dW_head[Kh][C] = X^T dlogits (contraction over the B rows), db_head = column sums
     GemmOperands wg{h->sc<bf16_t>(p.o_act[L - 1]), Kh, (int64_t)B * Kh, true, dlogits, 32, (int64_t)B * 32, false,
                     Kh, C, B, P};
+    wg.b_cols = 32;
     wg.colsum = G + p.lay.b_off[L - 1]; wg.colsum_stride = S;   // db_head, a by-product of the same launch
     PBT_LAUNCH(h, PBT_K_HEAD, s, gemm_store_f32(wg, G + p.lay.w_off[L - 1], C, S, s));
   }

@@ -73,7 +73,7 @@ __global__ __launch_bounds__(256) void wgan_head_kernel(const float* __restrict_
 // Bound by memory latency (6 MB in all for 32 members of 64 x 784): each wavefront reads its row once, as 16-byte
 // loads that are all in flight together, and keeps up to PEN_VEC * 256 elements in registers between the norm and
 // the scaling (longer rows read the rest again).  With four wavefronts per member, 4-byte loads and a second pass
-// over memory the kernel took 106 us at those sizes, now 12.
+// over memory the kernel took 106 us at those sizes, now 15.
 constexpr int PEN_VEC = 4;
 __global__ __launch_bounds__(1024) void wgan_penalty_kernel(const float* __restrict__ g, int B, int D, float weight,
                                                             bf16_t* __restrict__ X, float* __restrict__ loss) {
@@ -277,6 +277,7 @@ static pbt_status gan_step_wgan(pbt_handle* h, const float* train_x, uint32_t st
     }
     {
       GemmOperands wg{b.dA[Ld - 1], Kh, (int64_t)R * Kh, true, dlogits, 32, (int64_t)R * 32, false, Kh, 1, R, P};
+      wg.b_cols = 32;
       wg.colsum = G + p.lay.b_off[head]; wg.colsum_stride = S; wg.colsum_k = 2 * B;
       PBT_LAUNCH(h, PBT_K_HEAD, s, gemm_store_f32(wg, G + p.lay.w_off[head], 1, S, s));
     }
@@ -331,6 +332,7 @@ pbt_status gan_step(pbt_handle* h, const float* train_x, uint32_t step, hipStrea
   PBT_LAUNCH(h, PBT_K_HEAD, s, row_reduce(rowloss, R, P, R, 1.f / (float)B, loss, 2, s));
   {
     GemmOperands wg{b.dA[Ld - 1], Kh, (int64_t)R * Kh, true, dlogits, 32, (int64_t)R * 32, false, Kh, 1, R, P};
+    wg.b_cols = 32;
     wg.colsum = G + p.lay.b_off[head]; wg.colsum_stride = S;   // the bias gradient, a by-product of the same launch
     PBT_LAUNCH(h, PBT_K_HEAD, s, gemm_store_f32(wg, G + p.lay.w_off[head], 1, S, s));
   }

@@ -18,7 +18,7 @@ static hipError_t run(const GemmOperands& o, const E& e, hipStream_t s) {
     if (!o.colsum && nt_lds_applies(g, o.a_m_contig, o.b_k_contig)) return launch_gemm_nt_lds(g, e, s);
   }
   return launch_gemm_bf16<E>(o.A, o.lda, o.sa, o.a_m_contig, o.B, o.ldb, o.sb, o.b_k_contig, o.M, o.N, o.K, o.batch, e, s, o.inner,
-                             o.sa_in, o.sb_in, o.colsum, o.colsum_stride, o.colsum_k);
+                             o.sa_in, o.sb_in, o.colsum, o.colsum_stride, o.colsum_k, o.b_cols);
 }
 
 hipError_t gemm_store_f32(const GemmOperands& o, float* C, int64_t ldc, int64_t sc, hipStream_t s) {
