@@ -391,8 +391,10 @@ pbt_status gan_eval(pbt_handle* h, const float* eval_x, hipStream_t s) {
   const float inv2d = 1.f / (2.f * (float)D);
   int txx = 0, tyy = 0, txy = 0;
   GemmOperands xx{X, D, (int64_t)E * D, false, X, D, (int64_t)E * D, true, E, E, D, P};
+  xx.symmetric = 1;
   PBT_HIP(h, gemm_rbf_sum(xx, nx, E, nx, E, inv2d, h->sc<float>(g.o_pxx), &txx, s));
   GemmOperands yy{Y, D, 0, false, Y, D, 0, true, E, E, D, 1};
+  yy.symmetric = 1;
   PBT_HIP(h, gemm_rbf_sum(yy, ny, 0, ny, 0, inv2d, h->sc<float>(g.o_pyy), &tyy, s));
   GemmOperands xy{X, D, (int64_t)E * D, false, Y, D, 0, true, E, E, D, P};
   PBT_HIP(h, gemm_rbf_sum(xy, nx, E, ny, 0, inv2d, h->sc<float>(g.o_pxy), &txy, s));

@@ -18,7 +18,7 @@ static hipError_t run(const GemmOperands& o, const E& e, hipStream_t s) {
     if (!o.colsum && nt_lds_applies(g, o.a_m_contig, o.b_k_contig)) return launch_gemm_nt_lds(g, e, s);
   }
   return launch_gemm_bf16<E>(o.A, o.lda, o.sa, o.a_m_contig, o.B, o.ldb, o.sb, o.b_k_contig, o.M, o.N, o.K, o.batch, e, s, o.inner,
-                             o.sa_in, o.sb_in, o.colsum, o.colsum_stride, o.colsum_k, o.b_cols);
+                             o.sa_in, o.sb_in, o.colsum, o.colsum_stride, o.colsum_k, o.b_cols, o.symmetric);
 }
 
 hipError_t gemm_store_f32(const GemmOperands& o, float* C, int64_t ldc, int64_t sc, hipStream_t s) {
@@ -56,8 +56,9 @@ hipError_t gemm_rbf_sum(const GemmOperands& o, const float* na, int64_t sna, con
                         float* partial, int* tiles, hipStream_t s) {
   // tile count as launch_gemm_bf16 will choose it (the caller sizes `partial` with gemm_rbf_tiles, an upper bound)
   const TileShape t = tile_shape(choose_tile(o.M, o.N, o.K, o.batch));
-  *tiles = ((o.M + t.bm - 1) / t.bm) * ((o.N + t.bn - 1) / t.bn);
-  return run(o, EpiRbfSum{na, sna, nb, snb, inv2d, partial, 0.f}, s);
+  const int tm = (o.M + t.bm - 1) / t.bm, tn = (o.N + t.bn - 1) / t.bn;
+  *tiles = !o.symmetric ? tm * tn : t.bm == t.bn ? upper_tiles<1, 1>(tm, tn) : upper_tiles<2, 1>(tm, tn);
+  return run(o, EpiRbfSum{na, sna, nb, snb, inv2d, partial, 0.f, 0}, s);
 }
 int gemm_rbf_tiles(int M, int N, int) {
   return ((M + 127) / 128) * ((N + 63) / 64);  // the smallest tile gives the most partial sums

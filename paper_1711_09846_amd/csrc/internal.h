@@ -19,6 +19,7 @@ struct GemmOperands {
   float* colsum = nullptr;       // optional by-product: colsum[b * colsum_stride + n] = sum_k B[k][n]
   int64_t colsum_stride = 0;
   int colsum_k = -1;             // the column sums run over k < colsum_k only (-1: over all of K)
+  int symmetric = 0;             // gemm_rbf_sum only: A and B are the same rows
   int b_cols = 0;                // N-contiguous B whose rows are zero from column N up to this one (0: not known)
 };
 hipError_t gemm_store_f32(const GemmOperands& o, float* C, int64_t ldc, int64_t sc, hipStream_t s);
