@@ -33,6 +33,12 @@ hipError_t gemm_store_bf16_heads(const GemmOperands& o, bf16_t* C, int64_t ldc, 
 hipError_t gemm_bias_f32(const GemmOperands& o, const float* bias, int64_t sbias, float* C, int64_t ldc, int64_t sc, hipStream_t s) {
   return run(o, EpiBiasF32{bias, sbias, C, ldc, sc}, s);
 }
+int gemm_head_piece(int M, int N, int K, int batch) { return tile_shape(choose_tile(M, N, K, batch)).bn == 64 ? 32 : 64; }
+hipError_t gemm_head_stats(const GemmOperands& o, const float* bias, int64_t sbias, const int32_t* targets, float2* stats, float* target_logit,
+                           int pieces, hipStream_t s) {
+  if (o.a_m_contig || o.b_k_contig) return hipErrorInvalidValue;
+  return run(o, EpiHeadStats{bias, sbias, targets, stats, target_logit, o.M, pieces}, s);
+}
 hipError_t gemm_bias_act(const GemmOperands& o, const float* bias, int64_t sbias, bf16_t* Z, bf16_t* Aout, int64_t ld,
                          int64_t so, int act, hipStream_t s, const DropSite& site) {
   if (!site.record) return run(o, EpiBiasAct{bias, sbias, Z, Aout, ld, so, act}, s);

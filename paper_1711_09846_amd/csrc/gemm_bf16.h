@@ -209,6 +209,7 @@ __host__ __device__ inline int upper_tiles(int tiles_m, int tiles_n) {
 }
 
 struct EpiRbfSum;
+struct EpiHeadStats;
 
 template <int BM, int BN, int GEMM_BK, int WM, int WN, bool A_MCONTIG, bool B_KCONTIG, bool DOUBLE_BUF, class Epilogue>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, Epilogue epi) {
@@ -441,7 +442,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, Epi
         const int m = m0 + wm * (BM / WM) + i * 32 + row, n = n0 + wn * WCOLS + col;
         const float4 lo = *reinterpret_cast<const float4*>(Cw + row * CPITCH + col);
         const float4 hi = *reinterpret_cast<const float4*>(Cw + row * CPITCH + col + 4);
-        if (m < g.M && n < g.N) {
+        if constexpr (std::is_same_v<Epilogue, EpiHeadStats>) {
+          const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+          epi.template apply_row<RUNS>(m, n, v, m < g.M ? min(max(g.N - n, 0), 8) : 0, colv);
+        } else if (m < g.M && n < g.N) {
           const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
           if constexpr (Epilogue::HAS_COLS) epi.apply8(member, m, n, v, g.N - n < 8 ? g.N - n : 8, colv);
           else if constexpr (Epilogue::HAS_RUNDATA) epi.apply8(member, m, n, v, g.N - n < 8 ? g.N - n : 8, rund[q]);
@@ -563,6 +567,63 @@ struct EpiBiasF32 {
 #pragma unroll
       for (int e = 0; e < 8; ++e)
         if (e < count) dst[e] = v[e] + b[e];
+    }
+  }
+};
+
+// The same output layer where only the cross-entropy is wanted (held-out loss): the float logits stay in registers.  Of every row
+// and piece of 8 RUNS columns (64, or 32 with the narrow tile) the largest logit m and the sum of exp(logit - m) go to
+// stats[row][piece], the target's logit to target_logit[row]; a later pass puts a row's pieces together.  16 members x 4096 rows x 8192
+// logits: writing and re-reading 2.1 GB of logits cost 1161 + 388 us per
+// chunk, this 940 + 25.
+struct EpiHeadStats {
+  static constexpr bool HAS_FINISH = false;
+  static constexpr bool PREFETCH = false;
+  static constexpr bool COLSUM = false;
+  static constexpr bool HAS_COLS = true;
+  static constexpr bool HAS_RUNDATA = false;
+  static constexpr int LAYOUTS = 1;
+  struct Fetched {};
+  struct RunData {};
+  const float* bias;
+  int64_t sbias;
+  const int32_t* targets;   // [batch][M]
+  float2* stats;            // [batch][M][pieces]
+  float* target_logit;      // [batch][M]
+  int M, pieces;
+  __device__ __forceinline__ void begin(int member) {
+    bias += (int64_t)member * sbias;
+    targets += (int64_t)member * M;
+    stats += (int64_t)member * M * pieces;
+    target_logit += (int64_t)member * M;
+  }
+  __device__ __forceinline__ void load_cols(int n, int N, float* b) const {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) b[e] = n + e < N ? bias[n + e] : 0.f;
+  }
+  // every lane of the wavefront, RUNS neighbouring lanes on one row; count 0: nothing of this run lies inside C
+  template <int RUNS>
+  __device__ __forceinline__ void apply_row(int m, int n, const float* v, int count, const float* b) const {
+    float l[8], mx = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      l[e] = v[e] + b[e];
+      if (e < count) mx = fmaxf(mx, l[e]);
+    }
+#pragma unroll
+    for (int off = 1; off < RUNS; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    const float base = mx == -INFINITY ? 0.f : mx;   // (a piece of nothing but -inf has the sum 0)
+    float se = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) se += e < count ? expf(l[e] - base) : 0.f;
+#pragma unroll
+    for (int off = 1; off < RUNS; off <<= 1) se += __shfl_xor(se, off, 64);
+    if (count > 0) {
+      const int y = targets[m] - n;
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (y == e && e < count) target_logit[m] = l[e];
+      if (n % (8 * RUNS) == 0) stats[(int64_t)m * pieces + n / (8 * RUNS)] = make_float2(mx, se);
     }
   }
 };

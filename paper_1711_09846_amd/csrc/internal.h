@@ -28,6 +28,13 @@ hipError_t gemm_store_bf16(const GemmOperands& o, bf16_t* C, int64_t ldc, int64_
 hipError_t gemm_store_bf16_heads(const GemmOperands& o, bf16_t* C, int64_t ldc, int64_t sc, int64_t sc_in, hipStream_t s);
 // C (float) = acc + bias
 hipError_t gemm_bias_f32(const GemmOperands& o, const float* bias, int64_t sbias, float* C, int64_t ldc, int64_t sc, hipStream_t s);
+// the logits acc + bias of an output layer reduced to what a row's cross-entropy needs: per row and piece of gemm_head_piece() columns
+// {largest logit, sum of exp(logit - largest)} in stats[batch][M][pieces], the target's logit in target_logit[batch][M]
+int gemm_head_piece(int M, int N, int K, int batch);
+hipError_t gemm_head_stats(const GemmOperands& o, const float* bias, int64_t sbias, const int32_t* targets, float2* stats, float* target_logit,
+                           int pieces, hipStream_t s);
+// out[i * out_stride + r] = cross-entropy of row r of member i from those
+hipError_t xent_from_stats(const float2* stats, const float* target_logit, int P, int rows, int pieces, float* out, int64_t out_stride, hipStream_t s);
 // z = acc + bias; Z (may be null) <- z, Aout <- act(z); both [batch][M][ld] bf16 with batch stride so
 struct DropArgs {  // where a kernel finds the member's dropout rate and the Philox counter base
   const float* H; int n_hyper; int col;  // column of H holding the rate, -1 = no dropout
@@ -181,7 +188,6 @@ size_t dropout_mask_bytes(int P, int64_t per_member);
 hipError_t xent_rows(const float* logits, const int32_t* targets, int P, int rows, int V, const float* H, int n_hyper, int col_ls,
                      int use_ls, float gscale, bf16_t* dlogits, float* rowloss, hipStream_t s);
 hipError_t perplexity_score(const float* rowloss, int P, int rows, float* score, hipStream_t s);
-hipError_t tf_scatter_rows(const float* src, int P, int rows, float* dst, int64_t dst_stride, int64_t offset, hipStream_t s);
 
 struct ExploitArgs {
   float* score; const float* score_override; float* H; int32_t* t; int32_t* order; int32_t* donor; int32_t* parent;

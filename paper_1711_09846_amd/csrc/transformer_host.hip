@@ -163,12 +163,15 @@ pbt_status forward(const Ctx& x, const int32_t* pool, int n_pool, uint32_t c0, i
     TF_TRY(dense(x, fd, D.f, D.d, b.w2, b.b2, nullptr, tmp_d, PBT_ACT_NONE));
     PBT_HIP(h, dropout_apply(tmp_d, hmid, x.P, per_d, dr, 4 * l + 3, hout, x.s, nullptr, x.sc<uint16_t>(t.o_mask[l][2])));
   }
-  bf16_t* uf = x.sc<bf16_t>(t.o_uf);
   if (!x.fused_bwd)
-    PBT_HIP(h, layernorm_fwd(x.sc<bf16_t>(t.o_h[D.L]), x.P, x.n, D.d, x.W32, x.S_, t.lnfg, t.lnfb, uf, x.sc<float>(t.o_meanf), x.sc<float>(t.o_rstdf), x.s));
-  GemmOperands o{uf, D.d, (int64_t)x.n * D.d, false, x.W16 + t.whead, D.V, x.S_, false, x.n, D.V, D.d, x.P};
-  PBT_LAUNCH(h, PBT_K_GEMM_FWD, x.s, gemm_bias_f32(o, x.W32 + t.bhead, x.S_, x.sc<float>(t.o_logits), D.V, (int64_t)x.n * D.V, x.s));
+    PBT_HIP(h, layernorm_fwd(x.sc<bf16_t>(t.o_h[D.L]), x.P, x.n, D.d, x.W32, x.S_, t.lnfg, t.lnfb, x.sc<bf16_t>(t.o_uf), x.sc<float>(t.o_meanf), x.sc<float>(t.o_rstdf), x.s));
   return PBT_OK;
+}
+
+// The output layer on the final LayerNorm's rows.
+GemmOperands head_operands(const Ctx& x) {
+  const TfPlan& t = x.h->plan.tf;
+  return GemmOperands{x.sc<bf16_t>(t.o_uf), x.D.d, (int64_t)x.n * x.D.d, false, x.W16 + t.whead, x.D.V, x.S_, false, x.n, x.D.V, x.D.d, x.P};
 }
 
 Ctx make_ctx(pbt_handle* h, int Bc, hipStream_t s) {
@@ -285,6 +288,7 @@ pbt_status tf_step(pbt_handle* h, const int32_t* pool, uint32_t step, hipStream_
   TF_TRY(forward(x, pool, c.n_train, step, 1, 1));
   float* rowloss = x.sc<float>(t.o_rowloss);
   bf16_t* dl = x.sc<bf16_t>(t.o_dlogits);
+  PBT_LAUNCH(h, PBT_K_GEMM_FWD, s, gemm_bias_f32(head_operands(x), x.W32 + t.bhead, x.S_, x.sc<float>(t.o_logits), D.V, (int64_t)x.n * D.V, s));
   PBT_HIP(h, xent_rows(x.sc<float>(t.o_logits), x.sc<int32_t>(t.o_targets), x.P, x.n, D.V, h->st<float>(p.o_hyper), c.n_hyper, t.col_ls, 1,
                        1.f / (float)x.n, dl, rowloss, s));
   PBT_LAUNCH(h, PBT_K_HEAD, s, row_reduce(rowloss, x.n, x.P, x.n, 1.f / (float)x.n, h->st<float>(p.o_loss), 1, s));
@@ -363,16 +367,19 @@ pbt_status tf_eval(pbt_handle* h, const int32_t* eval_tokens, hipStream_t s) {
   const TfPlan& t = h->plan.tf;
   const int S = c.tf_seq;
   float* evalrow = h->sc<float>(t.o_evalrow);
-  // chunks of `batch` sequences; per-row losses of chunk k go to a [n_chunks][P][rows] staging area
-  // whose per-member rows are summed by the perplexity kernel in a fixed order
+  // chunks of `batch` sequences; their per-row losses go to [P][n_eval * S], whose rows the perplexity kernel sums in a fixed order
   if (c.n_eval % c.batch) return fail(h, PBT_EUNSUPPORTED, "n_eval must be a multiple of batch");
   const int chunks = c.n_eval / c.batch;
   for (int k = 0; k < chunks; ++k) {
     const Ctx x = make_ctx(h, c.batch, s);
     TF_TRY(forward(x, eval_tokens + (int64_t)k * c.batch * (S + 1), c.batch, 0u, 0, 0));
-    PBT_HIP(h, xent_rows(x.sc<float>(t.o_logits), x.sc<int32_t>(t.o_targets), x.P, x.n, c.tf_vocab, h->st<float>(h->plan.o_hyper), c.n_hyper, -1, 0,
-                         0.f, nullptr, x.sc<float>(t.o_rowloss), s));
-    PBT_HIP(h, tf_scatter_rows(x.sc<float>(t.o_rowloss), x.P, x.n, evalrow, (int64_t)c.n_eval * S, (int64_t)k * x.n, s));
+    // only the rows' cross-entropy is wanted, so the logits are never written; their buffer holds what is kept of them
+    const GemmOperands o = head_operands(x);
+    const int width = gemm_head_piece(o.M, o.N, o.K, o.batch), pieces = (o.N + width - 1) / width;
+    float2* stats = x.sc<float2>(t.o_logits);
+    float* target_logit = x.sc<float>(t.o_logits) + (int64_t)2 * x.P * x.n * pieces;   // (2 pieces + 1 <= V: V is a multiple of 8)
+    PBT_LAUNCH(h, PBT_K_GEMM_FWD, s, gemm_head_stats(o, x.W32 + t.bhead, x.S_, x.sc<int32_t>(t.o_targets), stats, target_logit, pieces, s));
+    PBT_HIP(h, xent_from_stats(stats, target_logit, x.P, x.n, pieces, evalrow + (int64_t)k * x.n, (int64_t)c.n_eval * S, s));
   }
   PBT_HIP(h, perplexity_score(evalrow, c.P, c.n_eval * S, h->st<float>(h->plan.o_score), s));
   return PBT_OK;

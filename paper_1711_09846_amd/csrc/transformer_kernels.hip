@@ -923,14 +923,23 @@ hipError_t xent_rows(const float* logits, const int32_t* targets, int P, int row
   return hipGetLastError();
 }
 
-// dst[i][offset + r] = src[i][r]: collects the per-row losses of one eval chunk
-__global__ void scatter_rows_kernel(const float* __restrict__ src, int rows, float* __restrict__ dst, int64_t dst_stride, int64_t offset) {
-  const int i = blockIdx.y;
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < rows) dst[(int64_t)i * dst_stride + offset + r] = src[(int64_t)i * rows + r];
+// Cross-entropy of a row from its pieces (gemm_head_stats): log-sum-exp of them minus the target's logit.  One wavefront per row, lanes
+// over the pieces in order, butterfly sums.
+__global__ __launch_bounds__(256) void xent_from_stats_kernel(const float2* __restrict__ stats, const float* __restrict__ target_logit, int rows,
+                                                              int pieces, float* __restrict__ out, int64_t out_stride) {
+  const int i = blockIdx.y, r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (r >= rows) return;
+  const float2* __restrict__ p = stats + ((int64_t)i * rows + r) * pieces;
+  float mx = -INFINITY;
+  for (int k = lane; k < pieces; k += 64) mx = fmaxf(mx, p[k].x);
+  mx = wave_max(mx);
+  float se = 0.f;
+  for (int k = lane; k < pieces; k += 64) { const float2 x = p[k]; se += x.y * expf(x.x - mx); }
+  se = wave_sum(se);
+  if (lane == 0) out[i * out_stride + r] = mx + logf(se) - target_logit[(int64_t)i * rows + r];
 }
-hipError_t tf_scatter_rows(const float* src, int P, int rows, float* dst, int64_t dst_stride, int64_t offset, hipStream_t s) {
-  hipLaunchKernelGGL(scatter_rows_kernel, dim3((rows + 255) / 256, P), dim3(256), 0, s, src, rows, dst, dst_stride, offset);
+hipError_t xent_from_stats(const float2* stats, const float* target_logit, int P, int rows, int pieces, float* out, int64_t out_stride, hipStream_t s) {
+  hipLaunchKernelGGL(xent_from_stats_kernel, dim3((rows + 3) / 4, P), dim3(256), 0, s, stats, target_logit, rows, pieces, out, out_stride);
   return hipGetLastError();
 }
 
