@@ -14,9 +14,9 @@ namespace pbt {
 namespace {
 
 struct Dim { int V, d, H, dh, f, S, L; };
-// LayerNorm, dropout and residual steps ride on neighbouring kernels when a row fits the fused kernels' registers
-// and the keep-bit records are whole bytes per row
-bool tf_fused_elementwise(const pbt_config& c) { return c.tf_d_model <= 2048 && c.tf_d_model % 16 == 0 && c.tf_d_ff % 16 == 0; }
+// LayerNorm, dropout and residual steps ride on neighbouring kernels when a row fits the fused kernels' registers (widths are multiples
+// of 8, so the keep-bit records are whole bytes per run of eight, and rows of 8 per member keep them 16-bit aligned between members)
+bool tf_fused_elementwise(const pbt_config& c) { return c.tf_d_model <= 2048; }
 Dim dim_of(const pbt_config& c) { return Dim{c.tf_vocab, c.tf_d_model, c.tf_heads, c.tf_d_model / c.tf_heads, c.tf_d_ff, c.tf_seq, c.n_layers}; }
 
 struct Ctx {
@@ -36,9 +36,13 @@ pbt_status dense(const Ctx& x, const bf16_t* in, int K, int N, int64_t w, int64_
 // A small weight matrix over many rows (the attention output projection: 512 x 512 from 4096 rows) gives 256 x 256 tiles
 // to a quarter of the compute units, and smaller tiles spend the long contraction on loop overhead (12 % of the MFMA peak):
 // its contraction is cut into WGRAD_PARTS pieces, each a tile of its own, and the pieces are added up in order afterwards.
+// The same where the whole population's 128 x 64 tiles do not fill the compute units once (small models: 6 members, 192 x 776 from
+// 720 rows): a tile there is one serial chain of slabs, 21 us, and a quarter of the chain plus the addition is 13.
 constexpr int WGRAD_PARTS = 4;
 bool wgrad_in_parts(int P, int rows, int K, int N) {
-  return (int64_t)((K + 255) / 256) * ((N + 255) / 256) * P <= 64 && K >= 256 && N >= 256 && N % 4 == 0 && ((int64_t)K * N) % 4 == 0 &&
+  if (N % 4 || ((int64_t)K * N) % 4) return false;
+  if ((int64_t)((K + 127) / 128) * ((N + 63) / 64) * P <= 256) return rows % WGRAD_PARTS == 0 && rows >= WGRAD_PARTS * 64;
+  return (int64_t)((K + 255) / 256) * ((N + 255) / 256) * P <= 64 && K >= 256 && N >= 256 &&
          rows % (WGRAD_PARTS * 64) == 0 && rows / WGRAD_PARTS >= 1024;
 }
 // G[w] = in^T dout, G[b] = column sums of dout

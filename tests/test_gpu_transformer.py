@@ -111,6 +111,16 @@ def test_transformer_reduced_weight_gradient_in_parts():
     print("transformer weight gradient in parts:", {k: float("%.3g" % v) for k, v in worst.items()}, flush=True)
 
 
+@pytest.mark.parametrize("seq,batch", [(72, 10), (32, 8)])
+def test_transformer_small_population_weight_gradient_in_parts(seq, batch):
+    """Few small members: every weight gradient's contraction is cut in four (180 rows each, no whole slab among the
+    remainder; 64 rows each, the fewest), widths that are multiples of 8 and not of 16."""
+    wl = _reduced(P=2, vocab=136, d_model=40, heads=5, d_ff=104, n_blocks=1, seq=seq, batch=batch, n_train=16, n_eval=batch)
+    pair = TransformerPair(wl, H=np.array([[1e-3, 0.1, 0.05], [5e-4, 0.0, 0.0]], dtype=np.float32))
+    # (the bounds of the two tests above, for their reason)
+    _teacher_forced(pair, range(2), range(2), tol_grad=2 * TOL_GRAD_SMALL, tol_w=2 * TOL_GRAD_SMALL)
+
+
 def test_transformer_free_running_eval_and_exploit():
     pair = TransformerPair(_reduced(P=4))
     g, P = pair.gpu, 4
