@@ -1,5 +1,5 @@
 // Causal self-attention of one (member, sequence, head) per workgroup, forward and backward, for sequences of
-// at most 128 positions and 64-wide heads: the S x S score, probability and gradient matrices live in MFMA
+// at most 128 positions (a multiple of 8) and heads of width W = 64 or 32: the S x S score, probability and gradient matrices live in MFMA
 // accumulators and never reach memory.  This is the attention of the transformer whose `step` the population
 // runs (Section 3, Eq. 2 of the PBT paper; Section 4.2 for the workload).
 //
@@ -9,6 +9,11 @@
 //             dQ = q(ds K), dK = q(ds^T Q), dV = q(pd^T dO)
 // keep = 0 or the member's 1 / (1 - rate), drawn by the forward pass (one Philox block per four consecutive
 // keys of a query) and left behind as one bit per (query, key) for the backward pass, which recomputes s and p.
+//
+// A sequence that does not fill its last block of 32 positions is padded with zero rows in LDS.  A padded key lies past every
+// real query, so the causal mask already hides it; a padded query's result is not stored, and its zero dO makes its ds and its
+// share of dK and dV zero.  72 positions, 32-wide heads, 6 members x
+// 10 sequences x 6 heads: 30 us per block forward and backward, against 64 for products and softmax as kernels of their own.
 //
 // Layout.  v_mfma_f32_32x32x16_bf16(X, Y, acc): lane l supplies row l % 32 of X and of Y, eight consecutive
 // contraction indices each (chosen by l / 32); afterwards acc[e] of lane l is the product for X row
@@ -34,48 +39,58 @@ namespace {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 frag_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float acc_t;
 
-constexpr int DH = ATTN_FUSED_HEAD, SMAX = ATTN_FUSED_MAX_SEQ;
-constexpr int TP = SMAX + 4;   // LDS pitch (elements) of a transposed [DH][S] operand: rows 2 banks apart
+constexpr int SMAX = ATTN_FUSED_MAX_SEQ;
+constexpr int TP = SMAX + 4;   // LDS pitch (elements) of a transposed [W][S] operand: rows 2 banks apart
 
 __device__ __forceinline__ float round_bf16(float x) { return bf2f(f2bf(x)); }
 __device__ __forceinline__ float bf_lo(uint32_t pair) { return __uint_as_float(pair << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t pair) { return __uint_as_float(pair & 0xffff0000u); }
 
 // ---- operands in LDS ------------------------------------------------------------------------------------
-// Every operand (Q, K, V or dO of one head: S rows of DH values, 128 bytes each, `pitch` apart in memory) is
-// fetched once with eight neighbouring lanes on a row, 16 bytes each -- read straight from memory in the MFMA
+// Every operand (Q, K, V or dO of one head: S rows of W values, 2 W bytes each, `pitch` apart in memory) is
+// fetched once with W / 8 neighbouring lanes on a row, 16 bytes each -- read straight from memory in the MFMA
 // operand pattern, a wavefront's load touches 32 rows and the L1 takes 64 separate accesses for it, which is
 // what bounded these kernels -- and then written to LDS either as rows (the X / Y operand of a product that
-// contracts over DH) or transposed (the X operand of a product that contracts over positions).
-struct Staged { uint4 v[SMAX * 8 / 256]; };
-__device__ __forceinline__ void fetch_rows(const bf16_t* __restrict__ src, int64_t pitch, int S, Staged& r) {
+// contracts over W) or transposed (the X operand of a product that contracts over positions).
+template <int W> struct Staged { uint4 v[SMAX * (W / 8) / 256]; };
+template <int W>
+__device__ __forceinline__ void fetch_rows(const bf16_t* __restrict__ src, int64_t pitch, int S, Staged<W>& r) {
 #pragma unroll
-  for (int j = 0; j < SMAX * 8 / 256; ++j) {
+  for (int j = 0; j < SMAX * (W / 8) / 256; ++j) {
     const int it = threadIdx.x + 256 * j;
-    const int row = min(it >> 3, S - 1);   // (past the operand: the last row again, never used)
-    r.v[j] = *reinterpret_cast<const uint4*>(src + (int64_t)row * pitch + (it & 7) * 8);
+    const int row = min(it / (W / 8), S - 1);   // (past the operand: the last row again, replaced by zeros)
+    r.v[j] = *reinterpret_cast<const uint4*>(src + (int64_t)row * pitch + (it % (W / 8)) * 8);
+  }
+#pragma unroll
+  for (int j = 0; j < SMAX * (W / 8) / 256; ++j)
+    if ((int)(threadIdx.x + 256 * j) / (W / 8) >= S) r.v[j] = make_uint4(0u, 0u, 0u, 0u);
+}
+// rows of W values, unpadded; the 16-byte chunks of a row are permuted by the row's index so that the 16 rows
+// an operand read touches per cycle spread over all banks
+template <int W>
+__device__ __forceinline__ int row_offset(int row, int chunk) {
+  return row * W + (((chunk ^ (row >> (W == 64 ? 1 : 2))) & (W / 8 - 1)) << 3);
+}
+// rows: whole blocks of 32
+template <int W>
+__device__ __forceinline__ void put_rows(const Staged<W>& r, int rows, bf16_t* lds) {
+#pragma unroll
+  for (int j = 0; j < SMAX * (W / 8) / 256; ++j) {
+    const int it = threadIdx.x + 256 * j;
+    if (it < rows * (W / 8)) *reinterpret_cast<uint4*>(lds + row_offset<W>(it / (W / 8), it % (W / 8))) = r.v[j];
   }
 }
-// rows of DH values, unpadded; the 16-byte chunks of a row are permuted by the row's index so that the 32 rows
-// an operand read touches spread over all banks
-__device__ __forceinline__ int row_offset(int row, int chunk) { return row * DH + (((chunk ^ (row >> 1)) & 7) << 3); }
-__device__ __forceinline__ void put_rows(const Staged& r, int S, bf16_t* lds) {
-#pragma unroll
-  for (int j = 0; j < SMAX * 8 / 256; ++j) {
-    const int it = threadIdx.x + 256 * j;
-    if (it < S * 8) *reinterpret_cast<uint4*>(lds + row_offset(it >> 3, it & 7)) = r.v[j];
-  }
-}
-// lds[c * TP + row] = operand[row][c].  Lanes 8 apart hold neighbouring rows: they exchange half of their chunk
+// lds[c * TP + row] = operand[row][c].  Lanes W / 8 apart hold neighbouring rows: they exchange half of their chunk
 // so that each writes four 4-byte pairs (row, row + 1) instead of eight 2-byte values.
-__device__ __forceinline__ void put_transposed(const Staged& r, int S, bf16_t* lds) {
+template <int W>
+__device__ __forceinline__ void put_transposed(const Staged<W>& r, int rows, bf16_t* lds) {
 #pragma unroll
-  for (int j = 0; j < SMAX * 8 / 256; ++j) {
+  for (int j = 0; j < SMAX * (W / 8) / 256; ++j) {
     const int it = threadIdx.x + 256 * j;
-    if (it >= S * 8) break;   // (uniform over the workgroup: S * 8 is a multiple of 256)
-    const int row = it >> 3, cc = it & 7, odd = row & 1;
+    if (it >= rows * (W / 8)) break;   // (uniform over a wavefront: 32 rows are two or four of them)
+    const int row = it / (W / 8), cc = it % (W / 8), odd = row & 1;
     const uint4 v = r.v[j];
-    const uint32_t g0 = __shfl_xor(odd ? v.x : v.z, 8), g1 = __shfl_xor(odd ? v.y : v.w, 8);
+    const uint32_t g0 = __shfl_xor(odd ? v.x : v.z, W / 8), g1 = __shfl_xor(odd ? v.y : v.w, W / 8);
     // the even row's and the odd row's four values of columns 8 cc + i0 .. + 3
     const uint32_t e0 = odd ? g0 : v.x, e1 = odd ? g1 : v.y, o0 = odd ? v.z : g0, o1 = odd ? v.w : g1;
     uint32_t* out = reinterpret_cast<uint32_t*>(lds) + (8 * cc + 4 * odd) * (TP / 2) + (row >> 1);
@@ -92,13 +107,14 @@ __device__ __forceinline__ acc_t zero_acc() {
   for (int e = 0; e < 16; ++e) a[e] = 0.f;
   return a;
 }
-// X rows (row xrow of xl) . Y rows (row yrow of yl) over the DH values, both stored as rows
+// X rows (row xrow of xl) . Y rows (row yrow of yl) over the W values, both stored as rows
+template <int W>
 __device__ __forceinline__ acc_t product_dh(const bf16_t* xl, int xrow, const bf16_t* yl, int yrow, int hf) {
   acc_t a = zero_acc();
 #pragma unroll
-  for (int c = 0; c < DH / 16; ++c)
-    a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const frag_t*>(xl + row_offset(xrow, 2 * c + hf)),
-                                                *reinterpret_cast<const frag_t*>(yl + row_offset(yrow, 2 * c + hf)), a, 0, 0, 0);
+  for (int c = 0; c < W / 16; ++c)
+    a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const frag_t*>(xl + row_offset<W>(xrow, 2 * c + hf)),
+                                                *reinterpret_cast<const frag_t*>(yl + row_offset<W>(yrow, 2 * c + hf)), a, 0, 0, 0);
   return a;
 }
 // X operand for a product whose contraction index runs over the registers of an accumulator block: rows of a
@@ -114,26 +130,27 @@ __device__ __forceinline__ frag_t packed_frag(const uint32_t* pairs, int half) {
   const uint4 u = make_uint4(pairs[4 * half], pairs[4 * half + 1], pairs[4 * half + 2], pairs[4 * half + 3]);
   return __builtin_bit_cast(frag_t, u);
 }
-// A wavefront's 32 x DH result (two accumulator blocks: lane = row, registers = runs of four columns), rounded,
-// to memory rows `pitch` apart.  Written straight from the accumulators every store would touch 32 rows with 8
+// A wavefront's 32 x W result (W / 32 accumulator blocks: lane = row, registers = runs of four columns), rounded,
+// to memory rows `pitch` apart, of which the first n exist.  Written straight from the accumulators every store would touch 32 rows with 8
 // bytes each; instead the block goes through the wavefront's own 32 rows of an LDS operand region it no longer
-// needs (rows first .. first + 31 of `region`, which no other wavefront reads) and leaves as whole 128-byte rows.
+// needs (rows first .. first + 31 of `region`, which no other wavefront reads) and leaves as whole rows.
 // LDS operations of one wavefront execute in order, so no barrier is involved.
-__device__ __forceinline__ void store_rows(const acc_t* acc, bf16_t* region, int first, int lane, bf16_t* __restrict__ dst, int64_t pitch) {
+template <int W>
+__device__ __forceinline__ void store_rows(const acc_t* acc, bf16_t* region, int first, int n, int lane, bf16_t* __restrict__ dst, int64_t pitch) {
   const int lr = lane & 31, hf = lane >> 5;
 #pragma unroll
-  for (int nb = 0; nb < 2; ++nb)
+  for (int nb = 0; nb < W / 32; ++nb)
 #pragma unroll
     for (int g = 0; g < 4; ++g)
-      *reinterpret_cast<uint2*>(region + row_offset(first + lr, 4 * nb + g) + 4 * hf) =
+      *reinterpret_cast<uint2*>(region + row_offset<W>(first + lr, 4 * nb + g) + 4 * hf) =
           make_uint2(f2bf_pair(acc[nb][4 * g], acc[nb][4 * g + 1]), f2bf_pair(acc[nb][4 * g + 2], acc[nb][4 * g + 3]));
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int row = (lane >> 3) + 8 * j, cc = lane & 7;
-    *reinterpret_cast<uint4*>(dst + (int64_t)row * pitch + 8 * cc) = *reinterpret_cast<const uint4*>(region + row_offset(first + row, cc));
+  for (int j = 0; j < W / 16; ++j) {
+    const int row = lane / (W / 8) + 512 / W * j, cc = lane % (W / 8);
+    if (row < n) *reinterpret_cast<uint4*>(dst + (int64_t)row * pitch + 8 * cc) = *reinterpret_cast<const uint4*>(region + row_offset<W>(first + row, cc));
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -159,12 +176,13 @@ __device__ __forceinline__ float keep_or_zero(uint32_t word, int k, float x) {
 // exp(v - max) for the scores of wavefront w's queries (lane's query t = 32 w + lane % 32) against key blocks
 // 0 .. w, in the accumulator layout (register e of block kb: key 32 kb + 8 (e / 4) + 4 hf + e % 4; 0 for keys
 // past the query), the row maximum and 1 / row sum.  Kr, Qr: K and Q as rows in LDS.
+template <int W>
 __device__ __forceinline__ void softmax_rows(const bf16_t* Kr, const bf16_t* Qr, int w, int lr, int hf, float scale, float (*p)[16], float& mx, float& inv) {
   mx = -INFINITY;
 #pragma unroll
   for (int kb = 0; kb < 4; ++kb) {
     if (kb > w) break;
-    const acc_t s = product_dh(Kr, 32 * kb + lr, Qr, 32 * w + lr, hf);
+    const acc_t s = product_dh<W>(Kr, 32 * kb + lr, Qr, 32 * w + lr, hf);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       p[kb][e] = round_bf16(s[e]) * scale;
@@ -189,25 +207,26 @@ __device__ __forceinline__ void softmax_rows(const bf16_t* Kr, const bf16_t* Qr,
 
 }  // namespace
 
+template <int W>
 __global__ __launch_bounds__(256) void attention_fwd_kernel(const bf16_t* __restrict__ qkv, AttnDims a, DropArgs dr, int site,
                                                             bf16_t* __restrict__ o, uint32_t* __restrict__ record) {
-  __shared__ __attribute__((aligned(16))) bf16_t Kr[SMAX * DH];
-  __shared__ __attribute__((aligned(16))) bf16_t Qr[SMAX * DH];
-  __shared__ __attribute__((aligned(16))) bf16_t Vt[DH * TP];
+  __shared__ __attribute__((aligned(16))) bf16_t Kr[SMAX * W];
+  __shared__ __attribute__((aligned(16))) bf16_t Qr[SMAX * W];
+  __shared__ __attribute__((aligned(16))) bf16_t Vt[W * TP];
   const int member = blockIdx.y, b = blockIdx.x / a.H, h = blockIdx.x % a.H;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, lr = lane & 31, hf = lane >> 5;
-  const int NB = a.S / 32;
+  const int NB = (a.S + 31) / 32;
   const int64_t row0 = ((int64_t)member * a.Bc + b) * a.S;          // first row of this sequence
   const int64_t pitch = 3 * (int64_t)a.d;
-  const bf16_t* Q = qkv + row0 * pitch + h * DH;
+  const bf16_t* Q = qkv + row0 * pitch + h * W;
   {
-    Staged q, k, v;
+    Staged<W> q, k, v;
     fetch_rows(Q, pitch, a.S, q);
     fetch_rows(Q + a.d, pitch, a.S, k);
     fetch_rows(Q + 2 * a.d, pitch, a.S, v);
-    put_rows(q, a.S, Qr);
-    put_rows(k, a.S, Kr);
-    put_transposed(v, a.S, Vt);
+    put_rows(q, 32 * NB, Qr);
+    put_rows(k, 32 * NB, Kr);
+    put_transposed(v, 32 * NB, Vt);
   }
   __syncthreads();
   if (w >= NB) return;
@@ -217,9 +236,11 @@ __global__ __launch_bounds__(256) void attention_fwd_kernel(const bf16_t* __rest
 
   float p[4][16];
   float mx, inv;
-  softmax_rows(Kr, Qr, w, lr, hf, a.scale, p, mx, inv);
+  softmax_rows<W>(Kr, Qr, w, lr, hf, a.scale, p, mx, inv);
 
-  acc_t oacc[2] = {zero_acc(), zero_acc()};
+  acc_t oacc[W / 32];
+#pragma unroll
+  for (int nb = 0; nb < W / 32; ++nb) oacc[nb] = zero_acc();
 #pragma unroll
   for (int kb = 0; kb < 4; ++kb) {
     if (kb > w) break;
@@ -242,39 +263,40 @@ __global__ __launch_bounds__(256) void attention_fwd_kernel(const bf16_t* __rest
     for (int half = 0; half < 2; ++half) {
       const frag_t pf = packed_frag(pd, half);
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
+      for (int nb = 0; nb < W / 32; ++nb)
         oacc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(transposed_frag(Vt, 32 * nb + lr, kb, half, hf), pf, oacc[nb], 0, 0, 0);
     }
   }
-  store_rows(oacc, Qr, 32 * w, lane, o + (row0 + 32 * w) * a.d + h * DH, a.d);   // (only this wavefront reads its queries' rows of Qr)
+  store_rows<W>(oacc, Qr, 32 * w, a.S - 32 * w, lane, o + (row0 + 32 * w) * a.d + h * W, a.d);   // (only this wavefront reads its queries' rows of Qr)
 }
 
 // Backward, first kernel: queries on lanes.  Row statistics, ds, dQ.  K and Q occupy two LDS regions for the
 // scores, V and dO (fetched at the start, held in registers meanwhile) the same two for dpd.  What has to stay
 // live across the key blocks is kept as packed bf16, which is what pq and dpd are anyway.
+template <int W>
 __global__ __launch_bounds__(256, 3) void attention_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO, AttnDims a, DropArgs dr,
                                                                   const uint32_t* __restrict__ record, bf16_t* __restrict__ dqkv, float* __restrict__ stats) {
-  __shared__ __attribute__((aligned(16))) bf16_t Xr[SMAX * DH];   // K, then V
-  __shared__ __attribute__((aligned(16))) bf16_t Yr[SMAX * DH];   // Q, then dO
-  __shared__ __attribute__((aligned(16))) bf16_t Kt[DH * TP];
+  __shared__ __attribute__((aligned(16))) bf16_t Xr[SMAX * W];   // K, then V
+  __shared__ __attribute__((aligned(16))) bf16_t Yr[SMAX * W];   // Q, then dO
+  __shared__ __attribute__((aligned(16))) bf16_t Kt[W * TP];
   const int member = blockIdx.y, b = blockIdx.x / a.H, h = blockIdx.x % a.H;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, lr = lane & 31, hf = lane >> 5;
-  const int NB = a.S / 32;
+  const int NB = (a.S + 31) / 32;
   const int64_t row0 = ((int64_t)member * a.Bc + b) * a.S;
   const int64_t pitch = 3 * (int64_t)a.d;
-  const bf16_t* Q = qkv + row0 * pitch + h * DH;
-  const bf16_t* dOh = dO + row0 * a.d + h * DH;
+  const bf16_t* Q = qkv + row0 * pitch + h * W;
+  const bf16_t* dOh = dO + row0 * a.d + h * W;
   const int t = 32 * w + lr;
-  Staged v, g;
+  Staged<W> v, g;
   {
-    Staged q, k;
+    Staged<W> q, k;
     fetch_rows(Q, pitch, a.S, q);
     fetch_rows(Q + a.d, pitch, a.S, k);
     fetch_rows(Q + 2 * a.d, pitch, a.S, v);
     fetch_rows(dOh, a.d, a.S, g);
-    put_rows(q, a.S, Yr);
-    put_rows(k, a.S, Xr);
-    put_transposed(k, a.S, Kt);
+    put_rows(q, 32 * NB, Yr);
+    put_rows(k, 32 * NB, Xr);
+    put_transposed(k, 32 * NB, Kt);
   }
   const DropRate rate = drop_rate(dr.H, dr.n_hyper, dr.col, member, dr.active);
   uint32_t words[4] = {0u, 0u, 0u, 0u};
@@ -288,7 +310,7 @@ __global__ __launch_bounds__(256, 3) void attention_bwd_dq_kernel(const bf16_t* 
   uint32_t pq[4][8];
   if (w < NB) {
     float p[4][16];
-    softmax_rows(Xr, Yr, w, lr, hf, a.scale, p, mx, inv);
+    softmax_rows<W>(Xr, Yr, w, lr, hf, a.scale, p, mx, inv);
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
       if (kb > w) break;
@@ -297,8 +319,8 @@ __global__ __launch_bounds__(256, 3) void attention_bwd_dq_kernel(const bf16_t* 
     }
   }
   __syncthreads();   // every wavefront is done with K and Q
-  put_rows(v, a.S, Xr);
-  put_rows(g, a.S, Yr);
+  put_rows(v, 32 * NB, Xr);
+  put_rows(g, 32 * NB, Yr);
   __syncthreads();
   if (w >= NB) return;
   // (pq is zero for keys past the query, so dp needs no mask of its own: those terms vanish from the sum and from ds)
@@ -307,7 +329,7 @@ __global__ __launch_bounds__(256, 3) void attention_bwd_dq_kernel(const bf16_t* 
 #pragma unroll
   for (int kb = 0; kb < 4; ++kb) {
     if (kb > w) break;
-    const acc_t gacc = product_dh(Xr, 32 * kb + lr, Yr, t, hf);
+    const acc_t gacc = product_dh<W>(Xr, 32 * kb + lr, Yr, t, hf);
 #pragma unroll
     for (int e = 0; e < 16; e += 2) {
       dpd[kb][e / 2] = f2bf_pair(gacc[e], gacc[e + 1]);
@@ -322,7 +344,9 @@ __global__ __launch_bounds__(256, 3) void attention_bwd_dq_kernel(const bf16_t* 
     float* st = stats + stat_index(a, member, b, h);
     st[t] = mx; st[SMAX + t] = inv; st[2 * SMAX + t] = dot;
   }
-  acc_t dq[2] = {zero_acc(), zero_acc()};
+  acc_t dq[W / 32];
+#pragma unroll
+  for (int nb = 0; nb < W / 32; ++nb) dq[nb] = zero_acc();
 #pragma unroll
   for (int kb = 0; kb < 4; ++kb) {
     if (kb > w) break;
@@ -337,34 +361,35 @@ __global__ __launch_bounds__(256, 3) void attention_bwd_dq_kernel(const bf16_t* 
     for (int half = 0; half < 2; ++half) {
       const frag_t sf = packed_frag(ds, half);
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
+      for (int nb = 0; nb < W / 32; ++nb)
         dq[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(transposed_frag(Kt, 32 * nb + lr, kb, half, hf), sf, dq[nb], 0, 0, 0);
     }
   }
-  store_rows(dq, Yr, 32 * w, lane, dqkv + (row0 + 32 * w) * pitch + h * DH, pitch);   // (only this wavefront reads its queries' rows of Yr)
+  store_rows<W>(dq, Yr, 32 * w, a.S - 32 * w, lane, dqkv + (row0 + 32 * w) * pitch + h * W, pitch);   // (only this wavefront reads its queries' rows of Yr)
 }
 
 // Backward, second kernel: keys on lanes (wavefront w owns keys 32 w .. 32 w + 31), queries on registers.
 // dK, dV.  Q and K occupy two LDS regions for the transposed scores, dO and V the same two for dpd^T.
+template <int W>
 __global__ __launch_bounds__(256, 2) void attention_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dO, AttnDims a, DropArgs dr,
                                                                    const uint32_t* __restrict__ record, const float* __restrict__ stats,
                                                                    bf16_t* __restrict__ dqkv) {
-  __shared__ __attribute__((aligned(16))) bf16_t Xr[SMAX * DH];   // Q, then dO
-  __shared__ __attribute__((aligned(16))) bf16_t Yr[SMAX * DH];   // K, then V
-  __shared__ __attribute__((aligned(16))) bf16_t Qt[DH * TP];
-  __shared__ __attribute__((aligned(16))) bf16_t dOt[DH * TP];
+  __shared__ __attribute__((aligned(16))) bf16_t Xr[SMAX * W];   // Q, then dO
+  __shared__ __attribute__((aligned(16))) bf16_t Yr[SMAX * W];   // K, then V
+  __shared__ __attribute__((aligned(16))) bf16_t Qt[W * TP];
+  __shared__ __attribute__((aligned(16))) bf16_t dOt[W * TP];
   __shared__ __attribute__((aligned(16))) float st[3 * SMAX];     // row maximum, 1 / row sum, sum_keys dp pq of every query
   __shared__ __attribute__((aligned(16))) uint32_t rec[SMAX * 4]; // keep bits: [query][key block]
   const int member = blockIdx.y, b = blockIdx.x / a.H, h = blockIdx.x % a.H;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, lr = lane & 31, hf = lane >> 5;
-  const int NB = a.S / 32;
+  const int NB = (a.S + 31) / 32;
   const int64_t row0 = ((int64_t)member * a.Bc + b) * a.S;
   const int64_t pitch = 3 * (int64_t)a.d;
-  const bf16_t* Q = qkv + row0 * pitch + h * DH;
-  const bf16_t* dOh = dO + row0 * a.d + h * DH;
-  Staged v, g;
+  const bf16_t* Q = qkv + row0 * pitch + h * W;
+  const bf16_t* dOh = dO + row0 * a.d + h * W;
+  Staged<W> v, g;
   {
-    Staged q, k;
+    Staged<W> q, k;
     fetch_rows(Q, pitch, a.S, q);
     fetch_rows(Q + a.d, pitch, a.S, k);
     fetch_rows(Q + 2 * a.d, pitch, a.S, v);
@@ -374,10 +399,10 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dkv_kernel(const bf16_t*
       reinterpret_cast<float4*>(st)[threadIdx.x] = reinterpret_cast<const float4*>(stats + stat_index(a, member, b, h))[threadIdx.x];
     if (threadIdx.x < SMAX)
       reinterpret_cast<uint4*>(rec)[threadIdx.x] = reinterpret_cast<const uint4*>(record + record_index(a, member, b, h, 0, 0))[threadIdx.x];
-    put_rows(q, a.S, Xr);
-    put_rows(k, a.S, Yr);
-    put_transposed(q, a.S, Qt);
-    put_transposed(g, a.S, dOt);
+    put_rows(q, 32 * NB, Xr);
+    put_rows(k, 32 * NB, Yr);
+    put_transposed(q, 32 * NB, Qt);
+    put_transposed(g, 32 * NB, dOt);
   }
   const DropRate rate = drop_rate(dr.H, dr.n_hyper, dr.col, member, dr.active);
   __syncthreads();
@@ -388,22 +413,24 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dkv_kernel(const bf16_t*
     for (int qb = 0; qb < 4; ++qb) {
       if (qb < w) continue;
       if (qb >= NB) break;
-      const acc_t s = product_dh(Xr, 32 * qb + lr, Yr, key, hf);
+      const acc_t s = product_dh<W>(Xr, 32 * qb + lr, Yr, key, hf);
 #pragma unroll
       for (int e = 0; e < 16; e += 2) sv[qb][e / 2] = f2bf_pair(s[e], s[e + 1]);
     }
   }
   __syncthreads();   // every wavefront is done with Q and K
-  put_rows(g, a.S, Xr);
-  put_rows(v, a.S, Yr);
+  put_rows(g, 32 * NB, Xr);
+  put_rows(v, 32 * NB, Yr);
   __syncthreads();
   if (w >= NB) return;
-  acc_t dk[2] = {zero_acc(), zero_acc()}, dv[2] = {zero_acc(), zero_acc()};
+  acc_t dk[W / 32], dv[W / 32];
+#pragma unroll
+  for (int nb = 0; nb < W / 32; ++nb) { dk[nb] = zero_acc(); dv[nb] = zero_acc(); }
 #pragma unroll
   for (int qb = 0; qb < 4; ++qb) {
     if (qb < w) continue;
     if (qb >= NB) break;
-    const acc_t gacc = product_dh(Xr, 32 * qb + lr, Yr, key, hf);
+    const acc_t gacc = product_dh<W>(Xr, 32 * qb + lr, Yr, key, hf);
     uint32_t pd[8], ds[8];
 #pragma unroll
     for (int gq = 0; gq < 4; ++gq) {
@@ -429,19 +456,19 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dkv_kernel(const bf16_t*
     for (int half = 0; half < 2; ++half) {
       const frag_t pf = packed_frag(pd, half), sf = packed_frag(ds, half);
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb) {
+      for (int nb = 0; nb < W / 32; ++nb) {
         dv[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(transposed_frag(dOt, 32 * nb + lr, qb, half, hf), pf, dv[nb], 0, 0, 0);
         dk[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(transposed_frag(Qt, 32 * nb + lr, qb, half, hf), sf, dk[nb], 0, 0, 0);
       }
     }
   }
-  bf16_t* krows = dqkv + (row0 + 32 * w) * pitch + a.d + h * DH;
-  store_rows(dk, Yr, 32 * w, lane, krows, pitch);   // (only this wavefront reads its keys' rows of Yr)
-  store_rows(dv, Yr, 32 * w, lane, krows + a.d, pitch);
+  bf16_t* krows = dqkv + (row0 + 32 * w) * pitch + a.d + h * W;
+  store_rows<W>(dk, Yr, 32 * w, a.S - 32 * w, lane, krows, pitch);   // (only this wavefront reads its keys' rows of Yr)
+  store_rows<W>(dv, Yr, 32 * w, a.S - 32 * w, lane, krows + a.d, pitch);
 }
 
 bool attention_fused_applies(int d_model, int heads, int seq) {
-  return heads > 0 && d_model / heads == DH && d_model % heads == 0 && seq % 32 == 0 && seq >= 32 && seq <= SMAX;
+  return heads > 0 && d_model % heads == 0 && (d_model / heads == 64 || d_model / heads == 32) && seq % 8 == 0 && seq >= 8 && seq <= SMAX;
 }
 size_t attention_record_bytes(int P, int Bc, int heads) { return (size_t)P * Bc * heads * SMAX * 4 * 4; }
 size_t attention_stats_bytes(int P, int Bc, int heads) { return (size_t)P * Bc * heads * 3 * SMAX * 4; }
@@ -449,17 +476,20 @@ size_t attention_stats_bytes(int P, int Bc, int heads) { return (size_t)P * Bc *
 hipError_t attention_fwd(const bf16_t* qkv, int P, int Bc, int S, int d, int H, float scale, const DropArgs& dr, int site, bf16_t* o,
                          uint32_t* record, hipStream_t s) {
   if (!attention_fused_applies(d, H, S) || d % 8) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(attention_fwd_kernel, dim3(Bc * H, P), dim3(256), 0, s, qkv, AttnDims{d, H, S, Bc, scale}, dr, site, o, record);
+  auto kernel = d / H == 64 ? attention_fwd_kernel<64> : attention_fwd_kernel<32>;
+  hipLaunchKernelGGL(kernel, dim3(Bc * H, P), dim3(256), 0, s, qkv, AttnDims{d, H, S, Bc, scale}, dr, site, o, record);
   return hipGetLastError();
 }
 hipError_t attention_bwd(const bf16_t* qkv, const bf16_t* dO, int P, int Bc, int S, int d, int H, float scale, const DropArgs& dr,
                          const uint32_t* record, float* stats, bf16_t* dqkv, hipStream_t s) {
   if (!attention_fused_applies(d, H, S) || d % 8 || !record || !stats) return hipErrorInvalidValue;
   const AttnDims a{d, H, S, Bc, scale};
-  hipLaunchKernelGGL(attention_bwd_dq_kernel, dim3(Bc * H, P), dim3(256), 0, s, qkv, dO, a, dr, record, dqkv, stats);
+  auto dq_kernel = d / H == 64 ? attention_bwd_dq_kernel<64> : attention_bwd_dq_kernel<32>;
+  auto dkv_kernel = d / H == 64 ? attention_bwd_dkv_kernel<64> : attention_bwd_dkv_kernel<32>;
+  hipLaunchKernelGGL(dq_kernel, dim3(Bc * H, P), dim3(256), 0, s, qkv, dO, a, dr, record, dqkv, stats);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(attention_bwd_dkv_kernel, dim3(Bc * H, P), dim3(256), 0, s, qkv, dO, a, dr, record, stats, dqkv);
+  hipLaunchKernelGGL(dkv_kernel, dim3(Bc * H, P), dim3(256), 0, s, qkv, dO, a, dr, record, stats, dqkv);
   return hipGetLastError();
 }
 

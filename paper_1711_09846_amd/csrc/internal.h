@@ -172,7 +172,7 @@ hipError_t wgrad_combine(const float* part, const float* colpart, int n_parts, i
 // (queries, keys, values side by side, heads side by side inside each); o, dO: [P][Bc*S][d]; dqkv like qkv.
 // The forward pass leaves the keep bits of its dropout site in `record` (attention_record_bytes; null = not
 // wanted); the backward pass (two kernels: dQ, then dK and dV) needs them and attention_stats_bytes of scratch.
-constexpr int ATTN_FUSED_HEAD = 64, ATTN_FUSED_MAX_SEQ = 128;
+constexpr int ATTN_FUSED_MAX_SEQ = 128;
 bool attention_fused_applies(int d_model, int heads, int seq);
 size_t attention_record_bytes(int P, int Bc, int heads);
 size_t attention_stats_bytes(int P, int Bc, int heads);

@@ -121,6 +121,18 @@ def test_transformer_small_population_weight_gradient_in_parts(seq, batch):
     _teacher_forced(pair, range(2), range(2), tol_grad=2 * TOL_GRAD_SMALL, tol_w=2 * TOL_GRAD_SMALL)
 
 
+@pytest.mark.parametrize("width,seq", [(32, 72), (32, 128), (32, 8), (64, 40), (64, 120)])
+def test_transformer_one_kernel_attention_of_padded_sequences(width, seq):
+    """Both head widths, and sequences that end inside a block of 32 positions (or fill all four)."""
+    wl = _reduced(P=2, vocab=64, d_model=3 * width, heads=3, d_ff=72, n_blocks=1, seq=seq, batch=3, n_train=16, n_eval=3)
+    pair = TransformerPair(wl, H=np.array([[1e-3, 0.0, 0.0], [5e-4, 0.3, 0.05]], dtype=np.float32))
+    # (the bounds of the one-kernel attention test above, for its reason)
+    _teacher_forced(pair, range(2), range(2), tol_grad=2 * TOL_GRAD_SMALL, tol_w=2 * TOL_GRAD_SMALL)
+    pair.gpu.eval(pair.d_eval)
+    sc, sc_ref = pair.gpu.get(binding.ARR_SCORE), pair.eval_ref()
+    assert np.max(np.abs(sc - sc_ref) / np.abs(sc_ref)) <= TOL_BF16, (sc, sc_ref)
+
+
 def test_transformer_free_running_eval_and_exploit():
     pair = TransformerPair(_reduced(P=4))
     g, P = pair.gpu, 4
