@@ -54,10 +54,12 @@ enum { ACT_NONE = 0, ACT_RELU = 1, ACT_GELU = 2, ACT_LEAKY_RELU = 3, ACT_TANH = 
 // erf(x) = 1 - (a1 t + ... + a5 t^5) exp(-x^2), t = 1/(1 + p x), x >= 0 (Abramowitz & Stegun
 // 7.1.26, |error| <= 1.5e-7), with x = |z|/sqrt(2) so that exp(-x^2) = exp(-z^2/2) is also what
 // phi(z) needs.  About a dozen instructions instead of a library erff call per element, which
-// matters in GEMM epilogues that touch 8 million elements per layer.
+// matters in GEMM epilogues that touch 8 million elements per layer (the correctly rounded reciprocal was a third of it: held-out pass
+// of the wide MLPs 2.86 -> 2.66 ms without, the same error, 2.7e-7 at most against double).
 __device__ __forceinline__ void normal_cdf_pdf(float z, float& cdf, float& pdf) {
-  const float x = fabsf(z) * 0.70710678118654752f;
-  const float t = __frcp_rn(fmaf(0.3275911f, x, 1.f));
+  // (clamped where exp(-x^2) is long zero, so that the reciprocal's argument is finite: one Newton step on the estimate, not a division)
+  const float x = fminf(fabsf(z) * 0.70710678118654752f, 1e9f);
+  const float q = fmaf(0.3275911f, x, 1.f), t0 = __builtin_amdgcn_rcpf(q), t = fmaf(fmaf(-q, t0, 1.f), t0, t0);
   const float e = __expf(-x * x);
   float poly = fmaf(1.061405429f, t, -1.453152027f);
   poly = fmaf(poly, t, 1.421413741f);
