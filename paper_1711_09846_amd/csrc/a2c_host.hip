@@ -531,7 +531,7 @@ struct RolloutArgs {
 // grid (32-column blocks of all layers together, k-blocks of the deepest layer / 2, P); 32 columns x 64 k of W[K][N] (rows of N) go
 // through LDS and leave as fragments: block (nb, kb), lane l: column 16 nb + l % 16, k = 32 kb + 8 (l / 16) ...
 __global__ __launch_bounds__(256) void a2c_pack_weights_kernel(RolloutArgs a) {
-  __shared__ bf16_t tile[64 * 34];
+  __shared__ __attribute__((aligned(16))) bf16_t tile[64 * 34];
   const int i = blockIdx.z;
   int l = 0, cb = blockIdx.x;
   while (cb >= ro_nblocks(a.dims[l + 1]) / 2) cb -= ro_nblocks(a.dims[l++ + 1]) / 2;
@@ -539,11 +539,19 @@ __global__ __launch_bounds__(256) void a2c_pack_weights_kernel(RolloutArgs a) {
   const int k0 = blockIdx.y * 64;
   if (k0 >= K) return;
   const bf16_t* __restrict__ W = a.W16 + (int64_t)i * a.stride + a.w_off[l];
-  // (element loads: N = the head's width need not be a multiple of anything)
+  // 16 bytes per thread (four neighbouring lanes on a row's 32 columns) where rows are whole groups of eight, which all but the head's are
+  if (N % 8 == 0) {
+    const int k = threadIdx.x >> 2, n = (threadIdx.x & 3) * 8;
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (k0 + k < K && cb * 32 + n < N) v = *reinterpret_cast<const uint4*>(W + (int64_t)(k0 + k) * N + cb * 32 + n);
+    uint32_t* t = reinterpret_cast<uint32_t*>(tile + k * 34 + n);
+    t[0] = v.x; t[1] = v.y; t[2] = v.z; t[3] = v.w;
+  } else {
 #pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    const int x = u * 256 + threadIdx.x, k = x >> 5, n = x & 31;
-    tile[k * 34 + n] = k0 + k < K && cb * 32 + n < N ? W[(int64_t)(k0 + k) * N + cb * 32 + n] : (bf16_t)0;
+    for (int u = 0; u < 8; ++u) {
+      const int x = u * 256 + threadIdx.x, k = x >> 5, n = x & 31;
+      tile[k * 34 + n] = k0 + k < K && cb * 32 + n < N ? W[(int64_t)(k0 + k) * N + cb * 32 + n] : (bf16_t)0;
+    }
   }
   __syncthreads();
   const int f = threadIdx.x >> 6, lane = threadIdx.x & 63;   // four fragments: column block f & 1, k-block f >> 1
