@@ -67,7 +67,7 @@ hipError_t gemm_rbf_sum(const GemmOperands& o, const float* na, int64_t sna, con
   return run(o, EpiRbfSum{na, sna, nb, snb, inv2d, partial, 0.f, 0}, s);
 }
 int gemm_rbf_tiles(int M, int N, int) {
-  return ((M + 127) / 128) * ((N + 63) / 64);  // the smallest tile gives the most partial sums
+  return ((M + 63) / 64) * ((N + 63) / 64);  // the smallest tile gives the most partial sums
 }
 
 }  // namespace pbt

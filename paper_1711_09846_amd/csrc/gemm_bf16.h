@@ -850,15 +850,17 @@ struct EpiOptimizer {
 
 // Tile shapes.  128x128 tiles (four wavefronts, three workgroups per compute unit) unless that leaves
 // the 256 compute units with fewer than four workgroups each to hide latency with; then 128x64.
+// Products of at most 64 rows, or with too few of those for the compute units, take 64x64 tiles.
 // Long contractions of large matrices take 256x256 tiles (eight wavefronts of 128x64, LDS slabs
 // double-buffered, one workgroup per compute unit): the L2 -> LDS traffic per flop halves, which
 // lifts the steady-state rate from about 880 to 1100 TFLOP/s (measured, 4096 x 2048 x K, batch 16);
 // a tile's fixed cost (first loads, epilogue) is no longer hidden by other workgroups on the compute
 // unit, so short contractions stay with 128x128.
-enum GemmTile { TILE_128x64 = 0, TILE_128x128, TILE_256x256 };
+enum GemmTile { TILE_128x64 = 0, TILE_128x128, TILE_256x256, TILE_64x64 };
 struct TileShape { int bm, bn; };
 inline TileShape tile_shape(GemmTile t) {
   switch (t) {
+    case TILE_64x64: return {64, 64};
     case TILE_128x64: return {128, 64};
     case TILE_256x256: return {256, 256};
     default: return {128, 128};
@@ -875,7 +877,11 @@ inline GemmTile choose_tile(int M, int N, int K, int batch) {
   if (K >= 1024 && M > 128 && N > 128 && tile_count(M, N, batch, 256, 256) >= CUS * 3 / 4) return TILE_256x256;
   // (double-buffered 128x128 and 128x64 variants were tried for the long, narrow weight gradients (K >= 2048 with at
   // most two tiles per compute unit) and for all 128x128 launches: no change for the former, 3 % slower for the latter)
-  // (a column or ten of them, the output layers' weight gradients, waste less of 64 columns than of 128: 21 members 15.4 -> 9 us)
+  // Half a 128-row tile would be clamped rows (a GAN's 64-row batches), or its tiles leave compute units idle: the GAN step
+  // 525 -> 500 us, 21 members with batches of 75 and ragged widths 129 -> 116, six small transformers 620 -> 602.
+  if (M <= 64 || tile_count(M, N, batch, 128, 64) < CUS) return TILE_64x64;
+  // (a column or ten of them, the output layers' weight gradients, waste less of 64 columns than of 128: 15.4 -> 8.4 us for 21 members
+  // with this and the 64-row tile)
   if (tile_count(M, N, batch, 128, 128) < 4 * CUS || N <= 64) return TILE_128x64;
   return TILE_128x128;
 }
@@ -982,6 +988,7 @@ hipError_t launch_gemm_bf16(const bf16_t* A, int64_t lda, int64_t sa, bool a_m_c
   g.b_cols = b_cols > N ? b_cols : N;
   switch (choose_tile(M, N, K, batch)) {
     case TILE_256x256: return launch_gemm_tile<256, 256, 64, 2, 4, true, Epilogue>(g, a_m_contig, b_k_contig, epi, stream);
+    case TILE_64x64: return launch_gemm_tile<64, 64, 64, 2, 2, false, Epilogue>(g, a_m_contig, b_k_contig, epi, stream);
     case TILE_128x64: return launch_gemm_tile<128, 64, 64, 2, 2, false, Epilogue>(g, a_m_contig, b_k_contig, epi, stream);
     default: return launch_gemm_tile<128, 128, 64, 2, 2, false, Epilogue>(g, a_m_contig, b_k_contig, epi, stream);
   }
