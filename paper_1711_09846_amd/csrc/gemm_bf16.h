@@ -877,9 +877,10 @@ inline GemmTile choose_tile(int M, int N, int K, int batch) {
   if (K >= 1024 && M > 128 && N > 128 && tile_count(M, N, batch, 256, 256) >= CUS * 3 / 4) return TILE_256x256;
   // (double-buffered 128x128 and 128x64 variants were tried for the long, narrow weight gradients (K >= 2048 with at
   // most two tiles per compute unit) and for all 128x128 launches: no change for the former, 3 % slower for the latter)
-  // Half a 128-row tile would be clamped rows (a GAN's 64-row batches), or its tiles leave compute units idle: the GAN step
-  // 525 -> 500 us, 21 members with batches of 75 and ragged widths 129 -> 116, six small transformers 620 -> 602.
-  if (M <= 64 || tile_count(M, N, batch, 128, 64) < CUS) return TILE_64x64;
+  // Half a 128-row tile would be clamped rows (a GAN's 64-row batches), or its tiles are fewer than two per compute unit: the GAN step
+  // 525 -> 487 us (500 with the line at one per compute unit), 21 members with batches of 75 and ragged widths 129 -> 116, six small
+  // transformers 620 -> 584 (602); populations of the wide MLP and the actor-critic lie above the line.
+  if (M <= 64 || tile_count(M, N, batch, 128, 64) < 2 * CUS) return TILE_64x64;
   // (a column or ten of them, the output layers' weight gradients, waste less of 64 columns than of 128: 15.4 -> 8.4 us for 21 members
   // with this and the 64-row tile)
   if (tile_count(M, N, batch, 128, 128) < 4 * CUS || N <= 64) return TILE_128x64;
