@@ -463,7 +463,7 @@ __global__ __launch_bounds__(256) void a2c_env_observe_kernel(EnvArgs a, int t) 
 //    once for all of them (16 bytes per lane; read 4 bytes at a time at a stride of 16 it was the LDS that bounded this).
 //  - the action draw and the latent transition of a trajectory belong to one half-wavefront (lane = action, then latent
 //    component): exchanges instead of barriers.
-// 128 members, 32 trajectories of 20 steps, 512-256-256-19: 356 us, and 31 + 9 for the packing and the draws ahead, against
+// 128 members, 32 trajectories of 20 steps, 512-256-256-19: 356 us, and 31 (2-byte loads; less now) + 9 for the packing and the draws ahead, against
 // 1197 us as one workgroup per member that streamed its weights through LDS in every round.
 // Shapes: observation width and hidden widths multiples of 8, hidden widths up to 256, up to three hidden layers, at
 // most 32 head outputs, and what rollout_cut() finds to fit LDS.

@@ -8,7 +8,7 @@
 // The A operand of v_mfma_f32_32x32x16_bf16 (row = lane % 32, eight consecutive k per lane) is exactly
 // a 16-byte global load of a K-contiguous row, so the large operand never passes through LDS; only
 // the small weight matrix is staged there (transposed to K-contiguous, which is what the B operand
-// needs).  Forward: a workgroup owns 32 rows and its four wavefronts share the contraction (wavefront
+// needs).  Forward: a workgroup owns blocks of 32 rows and its four wavefronts share the contraction (wavefront
 // w takes the k-blocks of 16 with index = w mod 4, so that together they read whole 128-byte lines
 // of a row); the partial sums are added in wavefront order.  Backward: a wavefront owns 32 rows and
 // passes its 32x64 block through LDS so that memory sees 16-byte accesses of whole 128-byte rows.
