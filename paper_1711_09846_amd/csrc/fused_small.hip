@@ -314,10 +314,16 @@ __device__ __forceinline__ float ft_xor(float v, int bit) {
   return __int_as_float(bit == 1 ? __builtin_amdgcn_update_dpp(x, x, 0xB1, 0xF, 0xF, false) : __builtin_amdgcn_update_dpp(x, x, 0x4E, 0xF, 0xF, false));
 }
 __device__ __forceinline__ int ft_xor(int v, int bit) { return __float_as_int(ft_xor(__int_as_float(v), bit)); }
+// the value of the first of each four lanes
+__device__ __forceinline__ int ft_first(int v) { return __builtin_amdgcn_update_dpp(v, v, 0x00, 0xF, 0xF, false); }
+__device__ __forceinline__ float ft_first(float v) { return __int_as_float(ft_first(__float_as_int(v))); }
 
 // Softmax cross-entropy of 16 rows whose logits sit in LDS (written by this wavefront): four lanes per row, classes in
 // turn.  Same split as fs_loss: the largest term apart, softmax_y - 1 as minus the sum of the others.  grad: the
 // gradient replaces the logits (rows from nrows on get zeros).
+// Class 0 starts as the largest and only a larger logit takes its place, as in fs_loss: a NaN there stays and is the row's maximum, a
+// NaN elsewhere never becomes it and turns the sum of the others into NaN, so a row with a NaN logit has a NaN loss and NaN
+// gradients whatever the class.  The four lanes have to agree on the maximum for that; the first one, which holds class 0, decides.
 __device__ __forceinline__ void ft_loss16(float* lg_rows, int pitch, int C, const int* y, int nrows, float* rowloss, bool grad, float gscale) {
   const int lane = threadIdx.x & 63, r = lane >> 2, q = lane & 3;
   float* lg = lg_rows + r * pitch;
@@ -330,7 +336,7 @@ __device__ __forceinline__ void ft_loss16(float* lg_rows, int pitch, int C, cons
     if (4 * j >= C) break;
     const int c = q + 4 * j;
     v[j] = c < C ? lg[c] : -INFINITY;
-    if (c < C && (v[j] > mx || j == 0)) { mx = v[j]; cm = c; }
+    if (c == 0 || v[j] > mx) { mx = v[j]; cm = c; }
   }
 #pragma unroll
   for (int o = 1; o < 3; ++o) {
@@ -338,6 +344,8 @@ __device__ __forceinline__ void ft_loss16(float* lg_rows, int pitch, int C, cons
     const int c2 = ft_xor(cm, o);
     if (m2 > mx || (m2 == mx && c2 < cm)) { mx = m2; cm = c2; }
   }
+  mx = ft_first(mx);
+  cm = ft_first(cm);
   float rest = 0.f, others = 0.f, ly = 0.f;
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
@@ -356,12 +364,12 @@ __device__ __forceinline__ void ft_loss16(float* lg_rows, int pitch, int C, cons
   }
   if (rowloss && q == 0) rowloss[r] = live ? log1pf(rest) + (mx - ly) : 0.f;
   if (grad) {
-    const float inv = 1.f / (1.f + rest);
+    const float inv = 1.f / (1.f + rest), top = 1.f + (mx - mx);   // (NaN for an infinite maximum, as exp(mx - mx) is)
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       if (4 * j >= C) break;
       const int c = q + 4 * j;
-      if (c < C) lg[c] = live ? (c == yb ? -others * inv : v[j] * inv) * gscale : 0.f;
+      if (c < C) lg[c] = live ? (c == yb ? -others * inv : (c == cm ? top : v[j]) * inv) * gscale : 0.f;
     }
   }
 }

@@ -41,3 +41,50 @@ def test_step_and_score_against_the_oracle(dims, batch, n_eval, act, opt):
     assert np.all(pair.gpu.get(binding.ARR_T) == 3)
     pair.gpu.eval(pair.d_eval)
     assert pair.scalar_errors(pair.gpu.get(binding.ARR_SCORE), pair.eval_ref(), 1e-2) <= tol
+
+
+@pytest.mark.parametrize("label", [0, 1])
+@pytest.mark.parametrize("C", [2, 3, 4, 5, 7, 10])
+def test_a_logit_that_is_nan_marks_its_member(C, label):
+    """Member i's output i is NaN in every row (its bias is), the last member is sound.  The softmax of such a row is NaN throughout,
+    also where no label names the class: the loss, every gradient and the score of the member are NaN, whichever class it is."""
+    wl = W.MLP_SMALL.replace(P=C + 1, dims=[6, 20, C], batch=19, n_train=64, n_eval=70, n_trunc=0, n_classes=C)
+    rng = np.random.default_rng(C)
+    rows = lambda n: (rng.standard_normal((n, 6)).astype(np.float32), np.full(n, label, dtype=np.int32))  # noqa: E731
+    pair = Pair(wl, data=(rows(wl.n_train), rows(wl.n_eval)))
+    lay = pair.gpu.layout
+    for i in range(C):
+        theta = pair.gpu.get(binding.ARR_W32, i).reshape(-1)
+        theta[lay.b_off[1] + i] = np.nan
+        pair.gpu.set(binding.ARR_W32, theta, i)
+    pair.gpu.eval(pair.d_eval)
+    sc = pair.gpu.get(binding.ARR_SCORE)
+    assert np.all(np.isnan(sc[:C])) and np.isfinite(sc[C]), sc
+    pair.gpu.step(pair.d_train, 0)
+    loss, grad = pair.gpu.get(binding.ARR_LOSS).reshape(-1), pair.gpu.get(binding.ARR_GRAD)
+    assert np.all(np.isnan(loss[:C])) and np.isfinite(loss[C]), loss
+    for l, (fi, fo) in enumerate(((6, 20), (20, C))):
+        for off, n in ((lay.w_off[l], fi * fo), (lay.b_off[l], fo)):
+            g = grad[:, off:off + n]
+            if l == 1:
+                assert np.all(np.isnan(g[:C])), (l, off)
+            assert np.all(np.isfinite(g[C]))
+
+
+def test_a_logit_that_is_infinite_marks_its_member():
+    """Output i of member i is +infinity: exp(l - max) of that class is NaN, and with it its gradient (the labels name another)."""
+    C = 5
+    wl = W.MLP_SMALL.replace(P=C + 1, dims=[6, 20, C], batch=19, n_train=64, n_eval=70, n_trunc=0, n_classes=C)
+    rng = np.random.default_rng(1)
+    rows = lambda n: (rng.standard_normal((n, 6)).astype(np.float32), rng.integers(0, 1, n).astype(np.int32))  # noqa: E731
+    pair = Pair(wl, data=(rows(wl.n_train), rows(wl.n_eval)))
+    lay = pair.gpu.layout
+    for i in range(1, C):
+        theta = pair.gpu.get(binding.ARR_W32, i).reshape(-1)
+        theta[lay.b_off[1] + i] = np.inf
+        pair.gpu.set(binding.ARR_W32, theta, i)
+    pair.gpu.step(pair.d_train, 0)
+    loss, grad = pair.gpu.get(binding.ARR_LOSS).reshape(-1), pair.gpu.get(binding.ARR_GRAD)[:, lay.b_off[1]:lay.b_off[1] + C]
+    assert np.all(np.isposinf(loss[1:C])) and np.isfinite(loss[0]) and np.isfinite(loss[C])
+    for i in range(1, C):
+        assert np.isnan(grad[i, i]) and np.isclose(grad[i, 0], -1.0) and np.all(np.delete(grad[i], [0, i]) == 0)
