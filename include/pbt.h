@@ -253,9 +253,9 @@ pbt_status pbt_step(pbt_handle* h, const void* const* d_inputs, int32_t n_inputs
  * memory (the d_scratch of pbt_init: gradients, activations, per-row losses) taken from an array of
  * PBT_STATIC_SCRATCH_BYTES bytes that lives inside the library, one copy per GPU, held until the process
  * ends.  Same arguments, same kernels and bit-identical results as pbt_step; the population store stays
- * in the caller's d_state.  Calls no hipMalloc / hipFree and nothing that allocates.  PBT_ENOMEM when the
- * handle's configuration needs more working memory than the array holds (pbt_query_sizes reports the
- * need).  Every call on a GPU, from any handle, shares that GPU's array: it keeps the previous call's
+ * in the caller's d_state.  Calls no hipMalloc / hipFree and nothing that allocates.  PBT_ENOMEM when a
+ * step of the handle's configuration needs more working memory than the array holds (what pbt_query_sizes
+ * reports is an upper bound of that need: it includes the buffers of pbt_eval and pbt_exploit_explore).  Every call on a GPU, from any handle, shares that GPU's array: it keeps the previous call's
  * contents (the call clears the part that must start at zero, with a fill kernel), and calls that overlap
  * in time on one GPU race.  PBT_ARR_GRAD of the handle (which lives in d_scratch) is not written. */
 #define PBT_STATIC_SCRATCH_BYTES ((size_t)8 << 20)

@@ -200,6 +200,7 @@ pbt_status a2c_check_and_plan(const pbt_config* c, Plan* pl, Carver* w) {
     a.o_packed = w->take((size_t)(P * a2c_packed_elems(c)) * 2);
     a.o_draws = w->take((size_t)(P * a2c_draw_count(c)) * 8);
   }
+  pl->step_scratch_bytes = w->off;
   return PBT_OK;
 }
 

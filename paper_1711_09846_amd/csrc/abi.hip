@@ -183,18 +183,8 @@ pbt_status make_plan(const pbt_config* c, Plan* pl) {
 
   Carver w;
   pl->o_grad = w.take(pw * 4);
-  for (int k = 0; k < 6; ++k) pl->o_stage[k] = 0;
-  if (c->exploit_mode != PBT_EXPLOIT_TRUNCATION && !c->keep_weights) {
-    // a member can be donor and recipient: donor rows pass through these staging rows (same order as in pbt_exploit_explore)
-    int k = 0;
-    pl->o_stage[k++] = w.take(pw * 4);
-    pl->o_stage[k++] = w.take(pw * 4);
-    if (adam) pl->o_stage[k++] = w.take(pw * 4);
-    if (bf16) pl->o_stage[k++] = w.take(pw * 2);
-    if (c->workload == PBT_WL_A2C) pl->o_stage[k++] = w.take(P * 12 * 4);
-  }
+  // (every workload carves what its step uses first and sets step_scratch_bytes; the held-out pass's and the exploit pass's buffers follow)
   pl->fused_small = false;
-  pl->step_scratch_bytes = 0;
   pl->eval_chunk = 0;
   if (gan) {
     if (!bf16 || !adam) return fail(nullptr, PBT_EUNSUPPORTED, "the GAN workload is built for bf16 compute with Adam");
@@ -221,7 +211,7 @@ pbt_status make_plan(const pbt_config* c, Plan* pl) {
                   "fp32 compute is built only for networks whose weights, optimiser state and one mini-batch of "
                   "activations fit the 160 KB LDS of a compute unit; use bf16 compute for larger ones");
     pl->fused_small = true;
-    pl->step_scratch_bytes = w.off;   // (the score's partial sums are no part of a step's working memory)
+    pl->step_scratch_bytes = w.off;
     pl->o_evalrow = w.take((size_t)P * fused_small_eval_parts(c->n_eval) * 4);
   } else {
     for (int l = 0; l < L; ++l) {
@@ -240,6 +230,7 @@ pbt_status make_plan(const pbt_config* c, Plan* pl) {
         pl->o_dz[l] = w.take((size_t)P * B * c->dims[l + 1] * 2);  // gradient w.r.t. it
       }
     }
+    pl->step_scratch_bytes = w.off;
     // eval: held-out set in bf16 (shared), two ping-pong activation buffers per chunk, per-row losses
     int64_t maxh = 8;
     for (int l = 1; l < L; ++l) maxh = c->dims[l] > maxh ? c->dims[l] : maxh;
@@ -258,8 +249,17 @@ pbt_status make_plan(const pbt_config* c, Plan* pl) {
     pl->o_evala[1] = w.take((size_t)P * chunk * maxh * 2);
     pl->o_evalrow = w.take((size_t)P * c->n_eval * 4);
   }
+  for (int k = 0; k < 6; ++k) pl->o_stage[k] = 0;
+  if (c->exploit_mode != PBT_EXPLOIT_TRUNCATION && !c->keep_weights) {
+    // a member can be donor and recipient: donor rows pass through these staging rows (same order as in pbt_exploit_explore)
+    int k = 0;
+    pl->o_stage[k++] = w.take(pw * 4);
+    pl->o_stage[k++] = w.take(pw * 4);
+    if (adam) pl->o_stage[k++] = w.take(pw * 4);
+    if (bf16) pl->o_stage[k++] = w.take(pw * 2);
+    if (c->workload == PBT_WL_A2C) pl->o_stage[k++] = w.take(P * 12 * 4);
+  }
   pl->scratch_bytes = w.off;
-  if (!pl->step_scratch_bytes) pl->step_scratch_bytes = w.off;
   return PBT_OK;
 }
 

@@ -198,6 +198,7 @@ pbt_status gan_check_and_plan(const pbt_config* c, Plan* pl, Carver* w) {
     g.o_hout = w->take((size_t)P * R * 32 * 4);
     g.o_gin = w->take((size_t)P * B * D * 4);
   }
+  pl->step_scratch_bytes = w->off;
   // eval: latents, two ping-pong hidden buffers, generated rows, held-out rows (bf16), norms, partial sums
   int64_t maxh = 8;
   for (int l = 1; l < Lg; ++l) maxh = c->dims[l] > maxh ? c->dims[l] : maxh;

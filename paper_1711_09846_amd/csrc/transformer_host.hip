@@ -272,11 +272,12 @@ pbt_status tf_check_and_plan(const pbt_config* c, Plan* pl, Carver* w) {
   t.o_logits = w->take(P * n * D.V * 4);
   t.o_dlogits = w->take(P * n * D.V * 2);
   t.o_rowloss = w->take(P * n * 4);
-  t.o_evalrow = w->take(P * (size_t)c->n_eval * D.S * 4);
   t.o_tokstart = w->take(P * ((size_t)D.V + 1) * 4);
   t.o_tokcursor = w->take(P * (size_t)D.V * 4);
   t.o_tokorder = w->take(P * n * 4);
   t.o_lnpart = w->take(P * (size_t)(LN_FUSED_SLABS > LN_MAX_SLABS ? LN_FUSED_SLABS : LN_MAX_SLABS) * 2 * D.d * 4);
+  pl->step_scratch_bytes = w->off;
+  t.o_evalrow = w->take(P * (size_t)c->n_eval * D.S * 4);
   return PBT_OK;
 }
 

@@ -77,3 +77,29 @@ def test_static_step_rejects_what_does_not_fit():
         pop.step_static(d, 0)
     assert e.value.status == -2 and "static" in str(e.value)
     assert np.array_equal(pop.get(binding.ARR_T), before)
+
+
+def _static_against_step(wl, inputs, steps=2, **kw):
+    """Two populations of the same configuration, one stepped with each entry point: bit-identical stores.  Returns one of them."""
+    a, b = (binding.Population(binding.make_config(wl, 1, **kw)) for _ in range(2))
+    arrays = [binding.ARR_W32, binding.ARR_OPT0, binding.ARR_W16, binding.ARR_T, binding.ARR_LOSS]
+    if wl.optimizer == workloads.OPT_ADAM:
+        arrays.append(binding.ARR_OPT1)
+    for pop in (a, b):
+        pop.init_population(wl.priors)
+    inputs = [x.to(a.device) for x in inputs]
+    for s in range(steps):
+        a.step(inputs, s)
+        b.step_static(inputs, s)
+    for which in arrays:
+        assert a.get(which).tobytes() == b.get(which).tobytes(), which
+    assert np.all(np.isfinite(b.get(binding.ARR_LOSS)))
+    return b
+
+
+def test_static_step_does_not_count_the_held_out_pass():
+    """A held-out set whose buffers alone are larger than the static array: a step does not touch them."""
+    import torch
+    wl = workloads.GAN_MLP.replace(P=2, dims=[16, 32, 40], dims2=[40, 32, 1], batch=8, n_train=300, n_eval=20000, n_trunc=0)
+    assert binding.query_sizes(binding.make_config(wl, 1))[1] > binding.STATIC_SCRATCH_BYTES
+    _static_against_step(wl, [torch.randn(300, 40)])
