@@ -174,18 +174,20 @@ pbt_status a2c_check_and_plan(const pbt_config* c, Plan* pl, Carver* w) {
   if (!(c->gamma >= 0.f && c->gamma <= 1.f)) return fail(nullptr, PBT_EINVAL, "gamma outside [0, 1]");
   const int64_t P = c->P, R = (int64_t)c->batch * (c->unroll + 1);
   a.rows = (int)R;
-  for (int l = 0; l < L; ++l) {
-    a.o_a[l] = w->take((size_t)P * R * c->dims[l] * 2);
-    if (l < L - 1) {
-      a.o_z[l] = w->take((size_t)P * R * c->dims[l + 1] * 2);
-      a.o_dz[l] = w->take((size_t)P * R * c->dims[l + 1] * 2);
-    }
+  a.o_a[0] = w->take((size_t)P * R * c->dims[0] * 2);
+  a.o_act = w->take((size_t)P * c->batch * c->unroll * 4);
+  a.o_rew = w->take((size_t)P * c->batch * c->unroll * 4);
+  // what only the update uses, and over it what only the unroll ahead of the update uses
+  const Carver shared = *w;
+  for (int l = 0; l < L - 1; ++l) {
+    a.o_a[l + 1] = w->take((size_t)P * R * c->dims[l + 1] * 2);
+    a.o_z[l] = w->take((size_t)P * R * c->dims[l + 1] * 2);
+    a.o_dz[l] = w->take((size_t)P * R * c->dims[l + 1] * 2);
   }
   a.o_out = w->take((size_t)P * R * 32 * 4);
   a.o_dout = w->take((size_t)P * R * 32 * 2);
-  a.o_act = w->take((size_t)P * c->batch * c->unroll * 4);
-  a.o_rew = w->take((size_t)P * c->batch * c->unroll * 4);
-  a.o_lat = a.o_gout = 0;
+  a.o_lat = a.o_gout = a.o_packed = a.o_draws = 0;
+  a.one_kernel = a.packed_in_grad = false;
   if (c->on_policy) {
     if (c->latent_dim < 1 || c->latent_dim > 64) return fail(nullptr, PBT_EINVAL, "latent_dim outside 1..64");
     // (LDS of the generator's kernels: the latents of a member's trajectories, plus an action each in the transition
@@ -193,12 +195,33 @@ pbt_status a2c_check_and_plan(const pbt_config* c, Plan* pl, Carver* w) {
     if ((int64_t)c->batch * (c->latent_dim * 8 + 4) + (int64_t)c->latent_dim * 65 * 8 > 64 * 1024)
       return fail(nullptr, PBT_EUNSUPPORTED, "batch x latent_dim too large for the trajectory generator's LDS");
     if ((int64_t)R * c->dims[0] >= (1LL << 31)) return fail(nullptr, PBT_EUNSUPPORTED, "more than 2^31 observation elements per member");
-    a.o_lat = w->take((size_t)P * c->batch * c->latent_dim * 8);
-    for (int l = 1; l < L; ++l) a.o_ga[l] = w->take((size_t)P * c->batch * c->dims[l] * 2);
-    a.o_gout = w->take((size_t)P * c->batch * 32 * 4);
-    // the one-kernel unroll: weights as matrix fragments, draws made ahead
-    a.o_packed = w->take((size_t)(P * a2c_packed_elems(c)) * 2);
-    a.o_draws = w->take((size_t)(P * a2c_draw_count(c)) * 8);
+    // The one-kernel unroll: draws made ahead, weights as matrix fragments.  Many parameters and few rows make the fragments larger than
+    // the update's buffers; where that would push a step past the array of pbt_step_static, they lie over the gradients if they fit there, and if
+    // the step is past it even so, the kernels of one round each do the unroll, in memory that the update has anyway: whatever fits the
+    // array in one of these forms is run in it.  (22 members 320-128-256-3, 2 trajectories of 2 steps: 10.3 MB with fragments of their own.)
+    const size_t packed = (size_t)(P * a2c_packed_elems(c)) * 2;
+    auto carve = [&](bool one_kernel, bool in_grad) {
+      Carver u = shared;
+      a.one_kernel = one_kernel;
+      a.packed_in_grad = in_grad;
+      if (one_kernel) {
+        a.o_draws = u.take((size_t)(P * a2c_draw_count(c)) * 8);
+        a.o_packed = in_grad ? pl->o_grad : u.take(packed);
+      } else {
+        a.o_lat = u.take((size_t)P * c->batch * c->latent_dim * 8);
+        for (int l = 1; l < L; ++l) a.o_ga[l] = u.take((size_t)P * c->batch * c->dims[l] * 2);
+        a.o_gout = u.take((size_t)P * c->batch * 32 * 4);
+      }
+      return u.off > w->off ? u.off : w->off;
+    };
+    const bool covered = packed > 0, fits_grad = packed <= (size_t)P * pl->lay.stride * 4;
+    size_t end = carve(covered, false);
+    if (covered && end > PBT_STATIC_SCRATCH_BYTES) {
+      if (fits_grad) end = carve(true, true);
+      if (end > PBT_STATIC_SCRATCH_BYTES) end = carve(false, false);
+      if (end > PBT_STATIC_SCRATCH_BYTES) end = carve(true, false);
+    }
+    w->off = end;
   }
   pl->step_scratch_bytes = w->off;
   return PBT_OK;
@@ -925,7 +948,8 @@ pbt_status a2c_step_on_policy(pbt_handle* h, const A2CEnv& env, uint32_t step, h
   float* gout = h->sc<float>(a.o_gout);
   EnvArgs ea{env, c.latent_dim, C - 1, d, B, T, R, step, (uint32_t)c.seed, (uint32_t)(c.seed >> 32), h->sc<double>(a.o_lat), gout,
              h->sc<int32_t>(a.o_act), h->sc<float>(a.o_rew), obs, h->st<int32_t>(p.o_t)};
-  if (const RoCut cut = rollout_cut(c); cut.parts) {
+  if (a.one_kernel) {
+    const RoCut cut = rollout_cut(c);
     RolloutArgs ra{};
     ra.e = ea; ra.W16 = W16; ra.W32 = W32; ra.stride = S; ra.n_hidden = L - 1; ra.act = c.act; ra.rows = cut.rows;
     ra.packed = h->sc<bf16_t>(a.o_packed); ra.packed_stride = ro_packed_elems(c.dims, L); ra.draws = h->sc<double>(a.o_draws);
@@ -950,6 +974,8 @@ pbt_status a2c_step_on_policy(pbt_handle* h, const A2CEnv& env, uint32_t step, h
     if (cut.rows > 16) hipLaunchKernelGGL(a2c_rollout_kernel<2>, dim3(cut.parts, P), dim3(RO_THREADS), cut.lds, s, ra);
     else hipLaunchKernelGGL(a2c_rollout_kernel<1>, dim3(cut.parts, P), dim3(RO_THREADS), cut.lds, s, ra);
     PBT_HIP(h, hipGetLastError());
+    // (the gradients' padding has to be zero, and with the optimiser inside the weight-gradient products they are not all written)
+    if (a.packed_in_grad) PBT_HIP(h, fill_u32(h->sc<uint32_t>(a.o_packed), 0u, P * ra.packed_stride / 2, s));
     hipLaunchKernelGGL(a2c_push_return_kernel, dim3(P), dim3(64), 0, s, h->sc<float>(a.o_rew), B, T, h->st<float>(p.o_hist));
     PBT_HIP(h, hipGetLastError());
     return a2c_update(h, s);

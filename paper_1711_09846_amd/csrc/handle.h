@@ -47,6 +47,8 @@ struct A2CPlan {
   // head outputs for one time step ([P][batch][width])
   size_t o_lat, o_ga[PBT_MAX_DIMS], o_gout;
   size_t o_packed, o_draws;   // the one-kernel unroll's packed weights and the draws made ahead of it
+  bool one_kernel;            // the unroll runs in one kernel
+  bool packed_in_grad;        // its packed weights lie over the gradients, which are cleared again before the update
 };
 
 struct TfBlockOff { int64_t ln1g, ln1b, wqkv, bqkv, wo, bo, ln2g, ln2b, w1, b1, w2, b2; };

@@ -151,3 +151,14 @@ def test_beta1_column_needs_an_upper_clamp_below_one():
         with pytest.raises(binding.PbtError) as e:
             binding.query_sizes(binding.make_config(workloads.MLP_WIDE.replace(h_max=[math.inf, bad, math.inf]), 1))
         assert e.value.status == -1
+
+
+@pytest.mark.parametrize("P,dims,batch,unroll,latent", [
+    (6, [512, 256, 256, 19], 8, 5, 16), (22, [320, 128, 256, 3], 2, 2, 15), (240, [8, 200, 3], 2, 1, 3),
+    (16, [64, 64, 64, 9], 16, 20, 16), (3, [512, 256, 256, 3], 16, 20, 64),
+])
+def test_acting_agents_share_their_unrolls_memory(P, dims, batch, unroll, latent):
+    """What only the unroll needs (packed weights, draws, or latents and one round's activations) lies over what only the update
+    needs, or over the gradients, so that these populations fit the static array of pbt_step_static."""
+    wl = workloads.A2C_MLP.replace(P=P, dims=dims, n_actions=dims[-1] - 1, batch=batch, unroll=unroll, latent=latent, n_trunc=0, on_policy=1)
+    assert binding.query_sizes(binding.make_config(wl, 1))[1] <= binding.STATIC_SCRATCH_BYTES

@@ -239,6 +239,7 @@ def test_a2c_on_policy_full_size_steps():
     (2, [64, 24, 200, 136, 5], 33, 4, 1),      # three hidden layers of ragged widths, nine workgroups of four and fewer
     (130, [512, 256, 256, 19], 32, 2, 16),     # one workgroup of 32 per member
     (2, [512, 256, 256, 3], 32, 3, 64),        # the largest latent system
+    (22, [320, 128, 256, 3], 2, 2, 15),        # packed weights over the gradients
 ])
 def test_a2c_unroll_at_the_edges_of_its_kernels(P, dims, batch, unroll, latent):
     """The unroll where its cut into workgroups, row blocks and fragments has remainders: observations and rewards

@@ -94,7 +94,11 @@ def _static_against_step(wl, inputs, steps=2, **kw):
     for which in arrays:
         assert a.get(which).tobytes() == b.get(which).tobytes(), which
     assert np.all(np.isfinite(b.get(binding.ARR_LOSS)))
-    return b
+    used = np.zeros(b.layout.stride, dtype=bool)
+    for j in range(b.layout.n_seg):
+        used[b.layout.seg_off[j]:b.layout.seg_off[j] + b.layout.seg_len[j]] = True
+    assert not np.any(b.get(binding.ARR_W32)[:, ~used])
+    return a
 
 
 def test_static_step_does_not_count_the_held_out_pass():
@@ -103,3 +107,32 @@ def test_static_step_does_not_count_the_held_out_pass():
     wl = workloads.GAN_MLP.replace(P=2, dims=[16, 32, 40], dims2=[40, 32, 1], batch=8, n_train=300, n_eval=20000, n_trunc=0)
     assert binding.query_sizes(binding.make_config(wl, 1))[1] > binding.STATIC_SCRATCH_BYTES
     _static_against_step(wl, [torch.randn(300, 40)])
+
+
+def _acting(P, dims, batch, unroll, latent):
+    return workloads.A2C_MLP.replace(P=P, dims=dims, n_actions=dims[-1] - 1, batch=batch, unroll=unroll, latent=latent, n_trunc=0, on_policy=1)
+
+
+@pytest.mark.parametrize("fused", [0, 1])
+@pytest.mark.parametrize("wl,launches", [
+    (_acting(6, [512, 256, 256, 19], 8, 5, 16), 0),    # packed weights and draws over the update's buffers
+    (_acting(22, [320, 128, 256, 3], 2, 2, 15), 0),    # too large for those: the packed weights over the gradients
+    (_acting(240, [8, 200, 3], 2, 1, 3), 2),           # larger than the gradients too: the kernels of one round each, two products per round
+], ids=["over the update", "over the gradients", "in rounds"])
+def test_static_step_of_acting_agents(wl, launches, fused):
+    """Actor-critic populations whose packed weights, in memory of their own, are larger than what is left of the static array."""
+    import torch
+    noise = np.array([1.0, 0.1, 0.1])
+    inputs = [torch.from_numpy(np.ascontiguousarray(x, dtype=np.float64)) for x in (*workloads.latent_system(wl), noise)]
+    pop = _static_against_step(wl, inputs, steps=3, fuse_optimizer=fused)
+    # which form of the unroll it was: the one-kernel form has no launches of the fetch class
+    pop.timing_enable(binding.K_FETCH, 64)
+    pop.step([x.to(pop.device) for x in inputs], 3)
+    assert pop.timing_read()[1] == launches
+    # gradients that no launch writes, and their padding, are zero
+    grad, lay = pop.get(binding.ARR_GRAD), pop.layout
+    written = np.zeros(lay.stride, dtype=bool)
+    for j in range(lay.n_seg):
+        if not fused or j % 2 or j == lay.n_seg - 2:
+            written[lay.seg_off[j]:lay.seg_off[j] + lay.seg_len[j]] = True
+    assert not np.any(grad[:, ~written]) and np.any(grad[:, written])
