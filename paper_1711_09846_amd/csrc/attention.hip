@@ -159,14 +159,15 @@ __device__ __forceinline__ void store_rows(const acc_t* acc, bf16_t* region, int
 
 struct AttnDims { int d, H, S, Bc; float scale; };
 
-// Record of the keep bits: one 32-bit word per (member, sequence, head, query, key block); bit k = key
-// 32 kb + k of that query kept.  Words of key blocks past the query's own are never written or read.
+// Record of the keep bits: one 32-bit word per (member, sequence, head, query, key block), for the S queries and ceil(S / 32) key blocks that
+// exist (so that it is never larger than the bf16 arrays of S x S scores that products of their own would need); bit k = key
+// 32 kb + k of that query kept.  Words of key blocks past the query's own are not written, and what is read of them is not used.
 __device__ __forceinline__ int64_t record_index(const AttnDims& a, int member, int b, int h, int t, int kb) {
-  return ((((int64_t)member * a.Bc + b) * a.H + h) * SMAX + t) * 4 + kb;
+  return ((((int64_t)member * a.Bc + b) * a.H + h) * a.S + t) * ((a.S + 31) / 32) + kb;
 }
-// row statistics: [member][sequence][head][3][SMAX] floats
+// row statistics: [member][sequence][head][3][S] floats
 __device__ __forceinline__ int64_t stat_index(const AttnDims& a, int member, int b, int h) {
-  return (((int64_t)member * a.Bc + b) * a.H + h) * 3 * SMAX;
+  return (((int64_t)member * a.Bc + b) * a.H + h) * 3 * a.S;
 }
 // x where bit k of word is set, else 0
 __device__ __forceinline__ float keep_or_zero(uint32_t word, int k, float x) {
@@ -257,7 +258,7 @@ __global__ __launch_bounds__(256) void attention_fwd_kernel(const bf16_t* __rest
     }
     if (record) {
       const uint32_t full = (word << (4 * hf)) | (__shfl_xor(word, 32) << (4 * (1 - hf)));
-      if (hf == 0) record[record_index(a, member, b, h, t, kb)] = full;
+      if (hf == 0 && t < a.S) record[record_index(a, member, b, h, t, kb)] = full;
     }
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
@@ -300,7 +301,7 @@ __global__ __launch_bounds__(256, 3) void attention_bwd_dq_kernel(const bf16_t* 
   }
   const DropRate rate = drop_rate(dr.H, dr.n_hyper, dr.col, member, dr.active);
   uint32_t words[4] = {0u, 0u, 0u, 0u};
-  if (w < NB) {
+  if (t < a.S) {
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb)
       if (kb <= w) words[kb] = record[record_index(a, member, b, h, t, kb)] >> (4 * hf);   // bit 8 g + j: this lane's key 8 g + 4 hf + j
@@ -340,9 +341,9 @@ __global__ __launch_bounds__(256, 3) void attention_bwd_dq_kernel(const bf16_t* 
     }
   }
   dot += __shfl_xor(dot, 32);
-  if (hf == 0) {
+  if (hf == 0 && t < a.S) {
     float* st = stats + stat_index(a, member, b, h);
-    st[t] = mx; st[SMAX + t] = inv; st[2 * SMAX + t] = dot;
+    st[t] = mx; st[a.S + t] = inv; st[2 * a.S + t] = dot;
   }
   acc_t dq[W / 32];
 #pragma unroll
@@ -394,11 +395,16 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dkv_kernel(const bf16_t*
     fetch_rows(Q + a.d, pitch, a.S, k);
     fetch_rows(Q + 2 * a.d, pitch, a.S, v);
     fetch_rows(dOh, a.d, a.S, g);
-    // (3 * SMAX floats and SMAX * 4 words: 16 bytes per thread for the first 96 and the first 128 threads)
-    if (threadIdx.x < 3 * SMAX / 4)
-      reinterpret_cast<float4*>(st)[threadIdx.x] = reinterpret_cast<const float4*>(stats + stat_index(a, member, b, h))[threadIdx.x];
-    if (threadIdx.x < SMAX)
-      reinterpret_cast<uint4*>(rec)[threadIdx.x] = reinterpret_cast<const uint4*>(record + record_index(a, member, b, h, 0, 0))[threadIdx.x];
+    // (a query per thread; those past the sequence get zeros, which make their probabilities and ds zero)
+    if (threadIdx.x < SMAX) {
+      const int tq = threadIdx.x;
+      const float* __restrict__ sp = stats + stat_index(a, member, b, h);
+      const uint32_t* __restrict__ rp = record + record_index(a, member, b, h, min(tq, a.S - 1), 0);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) st[k * SMAX + tq] = tq < a.S ? sp[k * a.S + tq] : 0.f;
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) rec[tq * 4 + kb] = tq < a.S && kb < NB ? rp[kb] : 0u;
+    }
     put_rows(q, 32 * NB, Xr);
     put_rows(k, 32 * NB, Yr);
     put_transposed(q, 32 * NB, Qt);
@@ -470,8 +476,8 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dkv_kernel(const bf16_t*
 bool attention_fused_applies(int d_model, int heads, int seq) {
   return heads > 0 && d_model % heads == 0 && (d_model / heads == 64 || d_model / heads == 32) && seq % 8 == 0 && seq >= 8 && seq <= SMAX;
 }
-size_t attention_record_bytes(int P, int Bc, int heads) { return (size_t)P * Bc * heads * SMAX * 4 * 4; }
-size_t attention_stats_bytes(int P, int Bc, int heads) { return (size_t)P * Bc * heads * 3 * SMAX * 4; }
+size_t attention_record_bytes(int P, int Bc, int heads, int seq) { return (size_t)P * Bc * heads * seq * ((seq + 31) / 32) * 4; }
+size_t attention_stats_bytes(int P, int Bc, int heads, int seq) { return (size_t)P * Bc * heads * 3 * seq * 4; }
 
 hipError_t attention_fwd(const bf16_t* qkv, int P, int Bc, int S, int d, int H, float scale, const DropArgs& dr, int site, bf16_t* o,
                          uint32_t* record, hipStream_t s) {

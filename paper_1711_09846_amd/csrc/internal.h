@@ -174,8 +174,8 @@ hipError_t wgrad_combine(const float* part, const float* colpart, int n_parts, i
 // wanted); the backward pass (two kernels: dQ, then dK and dV) needs them and attention_stats_bytes of scratch.
 constexpr int ATTN_FUSED_MAX_SEQ = 128;
 bool attention_fused_applies(int d_model, int heads, int seq);
-size_t attention_record_bytes(int P, int Bc, int heads);
-size_t attention_stats_bytes(int P, int Bc, int heads);
+size_t attention_record_bytes(int P, int Bc, int heads, int seq);
+size_t attention_stats_bytes(int P, int Bc, int heads, int seq);
 hipError_t attention_fwd(const bf16_t* qkv, int P, int Bc, int S, int d, int H, float scale, const DropArgs& dr, int site, bf16_t* o,
                          uint32_t* record, hipStream_t s);
 hipError_t attention_bwd(const bf16_t* qkv, const bf16_t* dO, int P, int Bc, int S, int d, int H, float scale, const DropArgs& dr,

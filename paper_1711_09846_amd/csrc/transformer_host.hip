@@ -237,7 +237,7 @@ pbt_status tf_check_and_plan(const pbt_config* c, Plan* pl, Carver* w) {
     t.o_mean2[l] = w->take(P * n * 4); t.o_rstd2[l] = w->take(P * n * 4);
     t.o_u[l] = w->take(nd); t.o_qkv[l] = w->take(3 * nd); t.o_o[l] = w->take(nd);
     if (t.fused_attn) {
-      t.o_keep[l] = w->take(attention_record_bytes((int)P, c->batch, D.H));
+      t.o_keep[l] = w->take(attention_record_bytes((int)P, c->batch, D.H, D.S));
       t.o_pq[l] = t.o_pd[l] = 0;
     } else {
       t.o_pq[l] = w->take(ns); t.o_pd[l] = w->take(ns);
@@ -250,7 +250,7 @@ pbt_status tf_check_and_plan(const pbt_config* c, Plan* pl, Carver* w) {
   }
   t.o_meanf = w->take(P * n * 4); t.o_rstdf = w->take(P * n * 4);
   t.o_score = t.fused_attn ? 0 : w->take(ns);
-  t.o_attn_stats = t.fused_attn ? w->take(attention_stats_bytes((int)P, c->batch, D.H)) : 0;
+  t.o_attn_stats = t.fused_attn ? w->take(attention_stats_bytes((int)P, c->batch, D.H, D.S)) : 0;
   t.o_wpart = t.o_wcolpart = 0;
   t.wpart_elems = t.wcol_elems = 0;
   {

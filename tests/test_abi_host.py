@@ -162,3 +162,14 @@ def test_acting_agents_share_their_unrolls_memory(P, dims, batch, unroll, latent
     needs, or over the gradients, so that these populations fit the static array of pbt_step_static."""
     wl = workloads.A2C_MLP.replace(P=P, dims=dims, n_actions=dims[-1] - 1, batch=batch, unroll=unroll, latent=latent, n_trunc=0, on_policy=1)
     assert binding.query_sizes(binding.make_config(wl, 1))[1] <= binding.STATIC_SCRATCH_BYTES
+
+
+@pytest.mark.parametrize("P,vocab,d_model,heads,d_ff,blocks,seq,batch", [
+    (5, 120, 32, 1, 16, 4, 8, 45),
+])
+def test_small_transformers_fit_the_static_array(P, vocab, d_model, heads, d_ff, blocks, seq, batch):
+    """The attention's keep bits and statistics are those of the positions that exist.  (The last array of the held-out pass, 4 bytes per position, is no part of a step.)"""
+    wl = workloads.TRANSFORMER.replace(P=P, vocab=vocab, d_model=d_model, heads=heads, d_ff=d_ff, n_blocks=blocks, seq=seq, batch=batch,
+                                       n_eval=batch, n_trunc=0)
+    scratch = binding.query_sizes(binding.make_config(wl, 1))[1]
+    assert scratch - -(-P * batch * seq * 4 // 256) * 256 <= binding.STATIC_SCRATCH_BYTES

@@ -136,3 +136,14 @@ def test_static_step_of_acting_agents(wl, launches, fused):
         if not fused or j % 2 or j == lay.n_seg - 2:
             written[lay.seg_off[j]:lay.seg_off[j] + lay.seg_len[j]] = True
     assert not np.any(grad[:, ~written]) and np.any(grad[:, written])
+
+
+@pytest.mark.parametrize("P,vocab,d_model,heads,d_ff,blocks,seq,batch", [
+    (5, 120, 32, 1, 16, 4, 8, 45),       # short sequences: keep bits of the positions that exist
+])
+def test_static_step_of_small_transformers(P, vocab, d_model, heads, d_ff, blocks, seq, batch):
+    import torch
+    wl = workloads.TRANSFORMER.replace(P=P, vocab=vocab, d_model=d_model, heads=heads, d_ff=d_ff, n_blocks=blocks, seq=seq, batch=batch,
+                                       n_train=60, n_eval=batch, n_trunc=0)
+    tokens = torch.from_numpy(np.random.default_rng(3).integers(0, vocab, (60, seq + 1)).astype(np.int32))
+    _static_against_step(wl, [tokens])
