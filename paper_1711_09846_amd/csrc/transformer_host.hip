@@ -45,11 +45,13 @@ bool wgrad_in_parts(int P, int rows, int K, int N) {
   return (int64_t)((K + 255) / 256) * ((N + 255) / 256) * P <= 64 && K >= 256 && N >= 256 &&
          rows % (WGRAD_PARTS * 64) == 0 && rows / WGRAD_PARTS >= 1024;
 }
+// working memory of one such product: the pieces of the matrix, then those of the column sums
+size_t wgrad_parts_bytes(int P, int K, int N) { return (size_t)P * WGRAD_PARTS * ((size_t)K * N + N) * 4; }
 // G[w] = in^T dout, G[b] = column sums of dout
 pbt_status wgrad(const Ctx& x, const bf16_t* in, int K, const bf16_t* dout, int N, int64_t w, int64_t b) {
-  if ((int64_t)K * N <= x.h->plan.tf.wpart_elems && N <= x.h->plan.tf.wcol_elems && wgrad_in_parts(x.P, x.n, K, N)) {
-    float* part = x.sc<float>(x.h->plan.tf.o_wpart);
-    float* colpart = x.sc<float>(x.h->plan.tf.o_wcolpart);
+  if (wgrad_in_parts(x.P, x.n, K, N) && wgrad_parts_bytes(x.P, K, N) <= x.h->plan.tf.logits_bytes) {
+    float* part = x.sc<float>(x.h->plan.tf.o_logits);   // (the logits are dead once their gradient is taken)
+    float* colpart = part + (int64_t)x.P * WGRAD_PARTS * K * N;
     const int rows = x.n / WGRAD_PARTS;
     GemmOperands o{in, K, (int64_t)x.n * K, true, dout, N, (int64_t)x.n * N, false, K, N, rows, x.P * WGRAD_PARTS};
     o.inner = WGRAD_PARTS; o.sa_in = (int64_t)rows * K; o.sb_in = (int64_t)rows * N;
@@ -251,31 +253,30 @@ pbt_status tf_check_and_plan(const pbt_config* c, Plan* pl, Carver* w) {
   t.o_meanf = w->take(P * n * 4); t.o_rstdf = w->take(P * n * 4);
   t.o_score = t.fused_attn ? 0 : w->take(ns);
   t.o_attn_stats = t.fused_attn ? w->take(attention_stats_bytes((int)P, c->batch, D.H, D.S)) : 0;
-  t.o_wpart = t.o_wcolpart = 0;
-  t.wpart_elems = t.wcol_elems = 0;
-  {
-    const int shapes[5][2] = {{D.d, 3 * D.d}, {D.d, D.d}, {D.d, D.f}, {D.f, D.d}, {D.d, D.V}};   // (rows in, columns out) of every weight matrix
-    for (const auto& sh : shapes)
-      if (wgrad_in_parts((int)P, (int)n, sh[0], sh[1])) {
-        t.wpart_elems = std::max<int64_t>(t.wpart_elems, (int64_t)sh[0] * sh[1]);
-        t.wcol_elems = std::max<int64_t>(t.wcol_elems, sh[1]);
-      }
-    if (t.wpart_elems) {
-      t.o_wpart = w->take(P * WGRAD_PARTS * (size_t)t.wpart_elems * 4);
-      t.o_wcolpart = w->take(P * WGRAD_PARTS * (size_t)t.wcol_elems * 4);
-    }
-  }
   for (int k = 0; k < 3; ++k) t.o_tmp_d[k] = w->take(nd);
   for (int k = 0; k < 2; ++k) t.o_tmp_f[k] = w->take(nf);
   t.o_dqkv = w->take(3 * nd);
   t.o_uf = w->take(nd);
-  t.o_logits = w->take(P * n * D.V * 4);
   t.o_dlogits = w->take(P * n * D.V * 2);
   t.o_rowloss = w->take(P * n * 4);
   t.o_tokstart = w->take(P * ((size_t)D.V + 1) * 4);
   t.o_tokcursor = w->take(P * (size_t)D.V * 4);
   t.o_tokorder = w->take(P * n * 4);
   t.o_lnpart = w->take(P * (size_t)(LN_FUSED_SLABS > LN_MAX_SLABS ? LN_FUSED_SLABS : LN_MAX_SLABS) * 2 * D.d * 4);
+  // The logits, and over them the pieces of the weight gradients that are formed in parts: room for the largest, but where that would
+  // push a step past the array of pbt_step_static, only for those that fit it (the others are formed whole; 1 member, d_model 256, d_ff 512,
+  // vocabulary 96, 4 x 64 positions: 8.7 MB with room for all).
+  t.logits_bytes = P * n * D.V * 4;
+  const int shapes[5][2] = {{D.d, 3 * D.d}, {D.d, D.d}, {D.d, D.f}, {D.f, D.d}, {D.d, D.V}};   // (rows in, columns out) of every weight matrix
+  size_t largest = t.logits_bytes, fitting = t.logits_bytes;
+  for (const auto& sh : shapes) {
+    if (!wgrad_in_parts((int)P, (int)n, sh[0], sh[1])) continue;
+    const size_t bytes = wgrad_parts_bytes((int)P, sh[0], sh[1]);
+    largest = std::max(largest, bytes);
+    if (w->off + round_up(bytes, BUF_ALIGN) <= PBT_STATIC_SCRATCH_BYTES) fitting = std::max(fitting, bytes);
+  }
+  t.logits_bytes = w->off + round_up(t.logits_bytes, BUF_ALIGN) <= PBT_STATIC_SCRATCH_BYTES ? fitting : largest;
+  t.o_logits = w->take(t.logits_bytes);
   pl->step_scratch_bytes = w->off;
   t.o_evalrow = w->take(P * (size_t)c->n_eval * D.S * 4);
   return PBT_OK;

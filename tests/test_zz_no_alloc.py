@@ -139,7 +139,11 @@ def test_static_step_of_acting_agents(wl, launches, fused):
 
 
 @pytest.mark.parametrize("P,vocab,d_model,heads,d_ff,blocks,seq,batch", [
+    (2, 256, 128, 2, 512, 1, 32, 8),     # pieces of every weight gradient would not fit beside the rest
+    (2, 512, 128, 2, 512, 1, 32, 8),
+    (1, 96, 256, 4, 512, 1, 64, 4),
     (5, 120, 32, 1, 16, 4, 8, 45),       # short sequences: keep bits of the positions that exist
+    (1, 40, 384, 6, 16, 1, 56, 6),
 ])
 def test_static_step_of_small_transformers(P, vocab, d_model, heads, d_ff, blocks, seq, batch):
     import torch
