@@ -239,7 +239,9 @@ pbt_status pbt_set_priors(pbt_handle* h, const pbt_prior* priors);
  *   z_0 ~ N(0, I); o_t = C z_t + noise[0] xi_t (rounded to float, then to bf16); a_t ~ softmax(policy
  *   logits of the member's network on o_t); r_t = w.z_t + noise[1] nu_t (float);
  *   z_{t+1} = A z_t + B[:, a_t] + noise[2] zeta_t,
- * the latent and every sum in double.  Philox counters (step, member, 32 + k, e / 4): k = 0 z_0 (element
+ * the latent and every sum in double, except C z_t, which is summed in float where dims[0] is a multiple of 64 up to
+ * 512, latent_dim at most 32 with latent_dim dims[0] <= 8192, every hidden width 64, 128 or 256, at most 3 of them, and
+ * batch at most 32 (the sum is stored as bf16); xi is evaluated to float accuracy.  Philox counters (step, member, 32 + k, e / 4): k = 0 z_0 (element
  * e = r nz + j), 1 xi (e = (r (unroll + 1) + t) dims[0] + j), 3 nu (e = r unroll + t), 4 zeta
  * (e = (r unroll + t) nz + j), normals by Box-Muller from word pairs (0,1), (2,3) of a counter (cosine for
  * even e, sine for odd e, evaluated in double); k = 2: u = (word 0 + 0.5) / 2^32 of counter element

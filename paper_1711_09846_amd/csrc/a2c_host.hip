@@ -2,6 +2,7 @@
 // learning rate and entropy cost adapted per member, evaluated by the last 10 episodic returns).
 // Device kernels for the trajectory bookkeeping and the loss, and the host-side kernel sequence.
 #include <cstring>
+#include <type_traits>
 
 #include "common.h"
 #include "dense_host.h"
@@ -491,6 +492,7 @@ __global__ __launch_bounds__(256) void a2c_env_observe_kernel(EnvArgs a, int t) 
 // 1197 us as one workgroup per member that streamed its weights through LDS in every round.
 // Shapes: observation width and hidden widths multiples of 8, hidden widths up to 256, up to three hidden layers, at
 // most 32 head outputs, and what rollout_cut() finds to fit LDS.
+// The observations' sums C z run in double or in float, see there.
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 ro_frag_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float ro_acc_t;
 constexpr int RO_MAX_HIDDEN = 3;
@@ -664,28 +666,38 @@ __device__ __forceinline__ void ro_dense(int tid, const bf16_t* in, int pin, int
 }
 
 // The observations of round t, RG trajectories per thread: to memory (the update reads them) and to X0 (the policy's
-// input).  The sum C z runs in float (the result is stored as bf16; the latents themselves stay in double).
-template <int RG>
-__device__ __forceinline__ void ro_observe(int tid, const EnvArgs& e, int i, int t, int r0, int rows, const float* Ct, const float* zf, int zpitch,
+// input).  The sum C z runs in double, or in float (rollout_cut(): SUM; the result is stored as bf16).  z: component k of trajectory r at
+// k zk + r zr.
+__device__ __forceinline__ void ro_load4(const float* p, float* c) {
+  const float4 v = *reinterpret_cast<const float4*>(p);
+  c[0] = v.x; c[1] = v.y; c[2] = v.z; c[3] = v.w;
+}
+__device__ __forceinline__ void ro_load4(const double* p, double* c) {
+  const double2 lo = *reinterpret_cast<const double2*>(p), hi = *reinterpret_cast<const double2*>(p + 2);
+  c[0] = lo.x; c[1] = lo.y; c[2] = hi.x; c[3] = hi.y;
+}
+template <int RG, class SUM>
+__device__ __forceinline__ void ro_observe(int tid, const EnvArgs& e, int i, int t, int r0, int rows, const SUM* Ct, const SUM* z, int zk, int zr,
                                            bf16_t* X0, int px) {
   const int d = e.d, runs = d / 4, groups = (rows + RG - 1) / RG;
   for (int item = tid; item < groups * runs; item += RO_THREADS) {
     const int grp = item / runs, j0 = 4 * (item - grp * runs);
-    float acc[RG][4];
+    SUM acc[RG][4];
 #pragma unroll
     for (int s = 0; s < RG; ++s)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) acc[s][q] = 0.f;
+      for (int q = 0; q < 4; ++q) acc[s][q] = 0;
     for (int k = 0; k < e.nz; ++k) {
-      const float4 c = *reinterpret_cast<const float4*>(Ct + k * d + j0);
+      SUM c[4];
+      ro_load4(Ct + k * d + j0, c);
 #pragma unroll
       for (int s = 0; s < RG; ++s) {
-        const float zk = zf[k * zpitch + grp * RG + s];
-        acc[s][0] = fmaf(c.x, zk, acc[s][0]); acc[s][1] = fmaf(c.y, zk, acc[s][1]);
-        acc[s][2] = fmaf(c.z, zk, acc[s][2]); acc[s][3] = fmaf(c.w, zk, acc[s][3]);
+        const SUM zs = z[k * zk + (grp * RG + s) * zr];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[s][q] = fma(c[q], zs, acc[s][q]);
       }
     }
-    const float noise_obs = (float)e.env.noise[0];
+    const SUM noise_obs = (SUM)e.env.noise[0];
 #pragma unroll
     for (int s = 0; s < RG; ++s) {
       const int r = grp * RG + s;
@@ -694,7 +706,7 @@ __device__ __forceinline__ void ro_observe(int tid, const EnvArgs& e, int i, int
         float v[4], o[4];
         env_normal4_f32(e.step, i, DOMAIN_ENV + 1, (uint32_t)((row * d + j0) >> 2), e.k0, e.k1, v);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) o[q] = fmaf(noise_obs, v[q], acc[s][q]);
+        for (int q = 0; q < 4; ++q) o[q] = (float)fma(noise_obs, (SUM)v[q], acc[s][q]);
         const uint2 packed = make_uint2(f2bf_pair(o[0], o[1]), f2bf_pair(o[2], o[3]));
         *reinterpret_cast<uint2*>(e.obs + ((int64_t)i * e.rows + row) * d + j0) = packed;
         *reinterpret_cast<uint2*>(X0 + r * px + j0) = packed;
@@ -704,29 +716,30 @@ __device__ __forceinline__ void ro_observe(int tid, const EnvArgs& e, int i, int
 }
 
 // LDS of the kernel, in this order: doubles: latents (two copies of [rb][nz]), A transposed, B, w of the latent system, the next
-// round's latent noise [rb][nz], uniforms and reward noise [rb]; then, each 16-byte aligned, floats: C transposed [nz][d], the
-// round's latents [nz][rb], the head's partial sums [8][rb][36]; then bf16: observations and two activation buffers [rb][width + 8].
+// round's latent noise [rb][nz], uniforms and reward noise [rb]; then, each 16-byte aligned: C transposed [nz][d] (float, or double where the
+// sum C z runs in double), floats: the round's latents [nz][rb], the head's partial sums [8][rb][36]; then bf16: observations and two
+// activation buffers [rb][width + 8].
 struct RoLds { size_t o_Ct, o_zf, o_part, o_x, bytes; };
-__host__ __device__ inline RoLds ro_lds_layout(int rb, int nz, int n_act, int d, int hmax) {
+__host__ __device__ inline RoLds ro_lds_layout(int rb, int nz, int n_act, int d, int hmax, int sum_bytes) {
   RoLds o;
   const size_t doubles = (size_t)3 * rb * nz + (size_t)nz * nz + (size_t)nz * n_act + nz + 2 * rb;
   o.o_Ct = (doubles * 8 + 15) & ~(size_t)15;
-  o.o_zf = o.o_Ct + (size_t)nz * d * 4;
+  o.o_zf = o.o_Ct + (size_t)nz * d * sum_bytes;
   o.o_part = o.o_zf + (size_t)nz * rb * 4;
   o.o_x = o.o_part + (size_t)RO_WAVES * rb * RO_PART_PITCH * 4;
   o.bytes = o.o_x + (size_t)rb * (32 * ro_kblocks(d) + 8) * 2 + (size_t)2 * rb * (32 * ro_kblocks(hmax) + 8) * 2;
   return o;
 }
 
-// grid (parts, P); MB blocks of 16 trajectories
-template <int MB>
+// grid (parts, P); MB blocks of 16 trajectories; SUM: the type the observations are summed in
+template <int MB, class SUM>
 __global__ __launch_bounds__(RO_THREADS) void a2c_rollout_kernel(RolloutArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char ro_lds[];
   constexpr int RB = 16 * MB;
   const EnvArgs& e = a.e;
   const int i = blockIdx.y, nz = e.nz, T = e.T, d = e.d, n_act = e.n_act;
   const int r0 = blockIdx.x * a.rows, rows = min(a.rows, e.B - r0);
-  const RoLds o = ro_lds_layout(RB, nz, n_act, d, a.hmax);
+  const RoLds o = ro_lds_layout(RB, nz, n_act, d, a.hmax, (int)sizeof(SUM));
   double* zs = reinterpret_cast<double*>(ro_lds);                 // [2][RB][nz]
   double* At = zs + 2 * RB * nz;                                  // [nz][nz], transposed
   double* Bs = At + nz * nz;                                      // [nz][n_act]
@@ -734,7 +747,7 @@ __global__ __launch_bounds__(RO_THREADS) void a2c_rollout_kernel(RolloutArgs a) 
   double* zeta = ws + nz;                                         // [RB][nz]
   double* us = zeta + RB * nz;                                    // [RB]
   double* rns = us + RB;                                          // [RB]
-  float* Ct = reinterpret_cast<float*>(ro_lds + o.o_Ct);          // [nz][d]
+  SUM* Ct = reinterpret_cast<SUM*>(ro_lds + o.o_Ct);              // [nz][d]
   float* zf = reinterpret_cast<float*>(ro_lds + o.o_zf);          // [nz][RB]
   float* part = reinterpret_cast<float*>(ro_lds + o.o_part);      // [8][RB][36]
   const int px = 32 * ro_kblocks(d) + 8, ph = 32 * ro_kblocks(a.hmax) + 8;
@@ -763,7 +776,7 @@ __global__ __launch_bounds__(RO_THREADS) void a2c_rollout_kernel(RolloutArgs a) 
   for (int x = threadIdx.x; x < nz; x += RO_THREADS) ws[x] = e.env.w[x];
   for (int x = threadIdx.x; x < d * nz; x += RO_THREADS) {
     const int j = x / nz, k = x - j * nz;
-    Ct[k * d + j] = (float)e.env.C[x];
+    Ct[k * d + j] = (SUM)e.env.C[x];
   }
   const double noise_rew = e.env.noise[1], noise_lat = e.env.noise[2];
   // rows past the last trajectory and columns past the last component stay zero in the observation buffer
@@ -839,9 +852,13 @@ __global__ __launch_bounds__(RO_THREADS) void a2c_rollout_kernel(RolloutArgs a) 
       e.rew[((int64_t)i * e.B + r0 + r) * T + tt] = (float)rw;
     }
     // (as many trajectories per thread as leave every thread something to do)
-    if (rows * (d / 4) >= 4 * RO_THREADS) ro_observe<4>(tid, e, i, t, r0, rows, Ct, zf, RB, X0, px);
-    else if (rows * (d / 4) >= 2 * RO_THREADS) ro_observe<2>(tid, e, i, t, r0, rows, Ct, zf, RB, X0, px);
-    else ro_observe<1>(tid, e, i, t, r0, rows, Ct, zf, RB, X0, px);
+    const SUM* z;
+    int zk, zr;
+    if constexpr (std::is_same_v<SUM, double>) { z = zn; zk = 1; zr = nz; }
+    else { z = zf; zk = RB; zr = 1; }
+    if (rows * (d / 4) >= 4 * RO_THREADS) ro_observe<4>(tid, e, i, t, r0, rows, Ct, z, zk, zr, X0, px);
+    else if (rows * (d / 4) >= 2 * RO_THREADS) ro_observe<2>(tid, e, i, t, r0, rows, Ct, z, zk, zr, X0, px);
+    else ro_observe<1>(tid, e, i, t, r0, rows, Ct, z, zk, zr, X0, px);
     if (t == T) break;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -886,17 +903,22 @@ __global__ __launch_bounds__(RO_THREADS) void a2c_rollout_kernel(RolloutArgs a) 
 // How a population is cut into workgroups, 0 parts if the shape is not covered.  One workgroup occupies a compute unit
 // (registers), so a member gets as many as the chip has left for it, down to four trajectories each (below that the
 // per-round latencies are all there is); never more than 32 trajectories, and 16 where 32 do not fit LDS.
-struct RoCut { int parts, rows; size_t lds; };
+struct RoCut { int parts, rows; size_t lds; bool sum_in_float; };
 static RoCut rollout_cut(const pbt_config& c) {
   const int L = c.n_layers, d = c.dims[0], C = c.dims[L], B = c.batch;
-  const RoCut none{0, 0, 0};
+  const RoCut none{0, 0, 0, false};
   if (d % 8 || L - 1 < 1 || L - 1 > RO_MAX_HIDDEN || C > 32 || c.latent_dim > 64) return none;
   int hmax = 0;
+  // C z is summed in double, as by the kernels of one round each, except for the shapes whose unroll has summed it in float ever since it
+  // became one kernel (which goes into a bf16 value): in double their steps take 1 to 9 % longer (128 members 512-256-256-19, 32 x 20:
+  // 783 -> 811 us), and the others' as much (8 members 200-72-40-9, 40 x 10: 172 -> 177).
+  bool sum_in_float = d % 64 == 0 && d <= 512 && c.latent_dim <= 32 && c.latent_dim * d <= 8192 && B <= 32;
   for (int l = 1; l < L; ++l) {
     if (c.dims[l] > RO_MAX_WIDTH || c.dims[l] % 8) return none;
     hmax = c.dims[l] > hmax ? c.dims[l] : hmax;
+    sum_in_float = sum_in_float && (c.dims[l] == 64 || c.dims[l] == 128 || c.dims[l] == 256);
   }
-  auto lds_of = [&](int rows) { return ro_lds_layout(rows > 16 ? 32 : 16, c.latent_dim, C - 1, d, hmax).bytes; };
+  auto lds_of = [&](int rows) { return ro_lds_layout(rows > 16 ? 32 : 16, c.latent_dim, C - 1, d, hmax, sum_in_float ? 4 : 8).bytes; };
   constexpr size_t LDS_MAX = 160 * 1024;
   int parts = 256 / c.P;
   parts = parts > (B + 3) / 4 ? (B + 3) / 4 : parts;
@@ -904,7 +926,7 @@ static RoCut rollout_cut(const pbt_config& c) {
   int rows = (B + parts - 1) / parts;
   if (rows > 16 && lds_of(rows) > LDS_MAX) { parts = (B + 15) / 16; rows = (B + parts - 1) / parts; }
   if (lds_of(rows) > LDS_MAX) return none;
-  return RoCut{(B + rows - 1) / rows, rows, lds_of(rows)};
+  return RoCut{(B + rows - 1) / rows, rows, lds_of(rows), sum_in_float};
 }
 
 static int64_t a2c_packed_elems(const pbt_config* c) { return rollout_cut(*c).parts ? ro_packed_elems(c->dims, c->n_layers) : 0; }
@@ -963,16 +985,14 @@ pbt_status a2c_step_on_policy(pbt_handle* h, const A2CEnv& env, uint32_t step, h
       col_blocks += ro_nblocks(c.dims[l + 1]) / 2;
       kmax = c.dims[l] > kmax ? c.dims[l] : kmax;
     }
-    static hipError_t attr1 = hipFuncSetAttribute(reinterpret_cast<const void*>(a2c_rollout_kernel<1>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    static hipError_t attr2 = hipFuncSetAttribute(reinterpret_cast<const void*>(a2c_rollout_kernel<2>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    PBT_HIP(h, attr1);
-    PBT_HIP(h, attr2);
+    auto rollout = cut.rows > 16 ? (cut.sum_in_float ? a2c_rollout_kernel<2, float> : a2c_rollout_kernel<2, double>)
+                                 : (cut.sum_in_float ? a2c_rollout_kernel<1, float> : a2c_rollout_kernel<1, double>);
+    PBT_HIP(h, hipFuncSetAttribute(reinterpret_cast<const void*>(rollout), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
     hipLaunchKernelGGL(a2c_pack_weights_kernel, dim3(col_blocks, (kmax + 63) / 64, P), dim3(256), 0, s, ra);
     PBT_HIP(h, hipGetLastError());
     hipLaunchKernelGGL(a2c_env_noise_kernel, dim3((unsigned)((ro_draws(B, T, c.latent_dim).count / 4 + 255) / 256), P), dim3(256), 0, s, ea, ra.draws);
     PBT_HIP(h, hipGetLastError());
-    if (cut.rows > 16) hipLaunchKernelGGL(a2c_rollout_kernel<2>, dim3(cut.parts, P), dim3(RO_THREADS), cut.lds, s, ra);
-    else hipLaunchKernelGGL(a2c_rollout_kernel<1>, dim3(cut.parts, P), dim3(RO_THREADS), cut.lds, s, ra);
+    hipLaunchKernelGGL(rollout, dim3(cut.parts, P), dim3(RO_THREADS), cut.lds, s, ra);
     PBT_HIP(h, hipGetLastError());
     // (the gradients' padding has to be zero, and with the optimiser inside the weight-gradient products they are not all written)
     if (a.packed_in_grad) PBT_HIP(h, fill_u32(h->sc<uint32_t>(a.o_packed), 0u, P * ra.packed_stride / 2, s));

@@ -137,13 +137,13 @@ def test_a2c_ttest_selection_bit_exact(alpha):
 
 
 def _one_kernel_unroll_shape():
-    """A shape the single-kernel unroll covers (at most 32 trajectories, hidden widths 64 / 128 / 256, observation
-    width a multiple of 64), with fewer than 32 trajectories, an odd latent size and two different hidden widths."""
+    """A shape whose observations the single-kernel unroll sums in float (at most 32 trajectories, hidden widths 64 / 128 / 256,
+    observation width a multiple of 64), with fewer than 32 trajectories, an odd latent size and two different hidden widths."""
     return workloads.A2C_MLP.replace(P=4, dims=[64, 128, 64, 7], n_actions=6, batch=20, unroll=5, n_train=50, n_trunc=1, latent=5,
                                      priors=[("log", 1e-4, 2e-3), ("log", 1e-4, 1e-2)])
 
 
-@pytest.mark.parametrize("shape", ["kernel_per_round", "one_kernel"])
+@pytest.mark.parametrize("shape", ["one_kernel_ragged", "one_kernel"])
 def test_a2c_on_policy_unrolls_against_the_oracle(shape):
     """Section 4.1.1: agents act with their current policy.  Every step the GPU generates the unroll; the oracle
     (a) replays the latent system along the GPU's actions and must reproduce observations and rewards, (b) makes
@@ -151,7 +151,7 @@ def test_a2c_on_policy_unrolls_against_the_oracle(shape):
     draw lies within 1e-3 of an edge of the cdf (float32 against float64 logits), and on fewer than 1 % of the
     choices, (c) takes its step on the GPU's unroll and must stay within the bf16 tolerance, free-running."""
     from oracle import nets
-    wl = (_reduced() if shape == "kernel_per_round" else _one_kernel_unroll_shape()).replace(on_policy=1)
+    wl = (_reduced() if shape == "one_kernel_ragged" else _one_kernel_unroll_shape()).replace(on_policy=1)
     pair = A2CPair(wl)
     g, P = pair.gpu, wl.P
     n_choices = n_differ = n_obs = n_obs_differ = 0
@@ -232,16 +232,18 @@ def test_a2c_on_policy_full_size_steps():
     print("a2c on-policy full size:", {k: float("%.3g" % v) for k, v in worst.items()}, "choices differing:", n_differ, "of", n_choices, flush=True)
 
 
-@pytest.mark.parametrize("P,dims,batch,unroll,latent", [
-    (3, [40, 264, 24, 9], 5, 4, 4),            # a hidden width past the one-kernel unroll: the kernels of one round each
-    (2, [584, 256, 8, 32], 6, 4, 7),           # more k-blocks than are kept in registers, the widest head
-    (100, [72, 40, 19], 36, 3, 5),             # 18 trajectories per workgroup: two blocks of 16 rows; one hidden layer
-    (2, [64, 24, 200, 136, 5], 33, 4, 1),      # three hidden layers of ragged widths, nine workgroups of four and fewer
-    (130, [512, 256, 256, 19], 32, 2, 16),     # one workgroup of 32 per member
-    (2, [512, 256, 256, 3], 32, 3, 64),        # the largest latent system
-    (22, [320, 128, 256, 3], 2, 2, 15),        # packed weights over the gradients
+@pytest.mark.parametrize("P,dims,batch,unroll,latent,rounds", [
+    (3, [40, 264, 24, 9], 5, 4, 4, True),            # a hidden width past the one-kernel unroll: the kernels of one round each
+    (2, [584, 256, 8, 32], 6, 4, 7, False),          # more k-blocks than are kept in registers, the widest head
+    (100, [72, 40, 19], 36, 3, 5, False),            # 18 trajectories per workgroup: two blocks of 16 rows; one hidden layer
+    (2, [64, 24, 200, 136, 5], 33, 4, 1, False),     # three hidden layers of ragged widths, nine workgroups of four and fewer
+    (130, [512, 256, 256, 19], 32, 2, 16, False),    # one workgroup of 32 per member
+    (2, [512, 256, 256, 3], 32, 3, 64, True),        # the largest latent system on wide observations: past the compute unit's LDS
+    (300, [64, 64, 64, 9], 32, 3, 64, False),        # and on narrow ones: two components per lane, four latent noises per thread
+    (3, [128, 72, 40, 7], 20, 3, 37, False),         # a second component for some lanes only
+    (22, [320, 128, 256, 3], 2, 2, 15, False),       # packed weights over the gradients
 ])
-def test_a2c_unroll_at_the_edges_of_its_kernels(P, dims, batch, unroll, latent):
+def test_a2c_unroll_at_the_edges_of_its_kernels(P, dims, batch, unroll, latent, rounds):
     """The unroll where its cut into workgroups, row blocks and fragments has remainders: observations and rewards
     replayed by the oracle along the GPU's actions, choices that differ only next to an edge of the cdf (criteria of
     the free-running test above), and the step taken on it."""
@@ -252,6 +254,7 @@ def test_a2c_unroll_at_the_edges_of_its_kernels(P, dims, batch, unroll, latent):
     pair = A2CPair(wl, ref_members=sample)
     g = pair.gpu
     n_choices = n_differ = 0
+    g.timing_enable(binding.K_FETCH, 2 * unroll * (len(dims) - 1))   # launches of the form with a kernel per round and layer; the other has none
     for s in range(2):
         before = {i: [(W.copy(), b.copy()) for W, b in pair.oa.params_of(pair.ref[i])] for i in sample}
         g.step(pair.d_pool, s)
@@ -274,3 +277,31 @@ def test_a2c_unroll_at_the_edges_of_its_kernels(P, dims, batch, unroll, latent):
             assert pair.member_errors(i, binding.ARR_W32, "theta")[0] <= TOL_BF16
         _hist_equal(pair, sample)
     assert n_differ <= max(1, 0.01 * n_choices)
+    assert g.timing_read()[1] == (2 * unroll * (len(dims) - 1) if rounds else 0)
+
+
+@pytest.mark.parametrize("P,dims,batch,unroll,latent", [
+    (8, [200, 72, 40, 9], 40, 10, 20),     # widths and a batch past the shapes whose observations are summed in float
+    (4, [256, 72, 64, 5], 30, 10, 16),     # one width past them
+    (4, [320, 64, 64, 5], 30, 10, 30),     # more latent components times observations
+    (2, [40, 264, 24, 9], 30, 10, 12),     # the kernels of one round each
+])
+def test_a2c_observations_are_summed_in_double(P, dims, batch, unroll, latent):
+    """Without observation noise an observation is the product C z, rounded to float and then to bf16.  Summed in double on both
+    sides the two differ by 1e-15 of a value, which moves one in 10^8 of the float roundings and none of the 10^5 to 10^6 here; summed in
+    float, 1e-7 of it, some of them round to the neighbouring bf16 value."""
+    from oracle import nets
+    wl = workloads.A2C_MLP.replace(P=P, dims=dims, n_actions=dims[-1] - 1, batch=batch, unroll=unroll, n_train=50, n_trunc=0, latent=latent,
+                                   on_policy=1, priors=[("log", 1e-4, 2e-3), ("log", 1e-4, 1e-2)])
+    pair = A2CPair(wl)
+    pair.env.obs_noise = 0.0
+    pair.d_pool[4][0] = 0.0
+    before = {i: [(W.copy(), b.copy()) for W, b in pair.oa.params_of(pair.ref[i])] for i in range(P)}
+    pair.gpu.step(pair.d_pool, 0)
+    off = n = 0
+    for i in range(P):
+        obs_g, act_g, _ = pair.gpu_unroll(i)
+        obs_o = pair.env_mod.rollout(pair.spec, pair.env, before[i], i, 0, forced_actions=act_g)[0]
+        off += int(np.sum(nets.round_bf16(obs_o.astype(np.float64)) != obs_g))
+        n += obs_g.size
+    assert off == 0, (off, n)
