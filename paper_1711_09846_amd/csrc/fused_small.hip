@@ -6,6 +6,8 @@
 //
 // Row pitches in LDS are (width + 1) floats so that both "lanes along the batch" and "lanes
 // along the features" access patterns are free of bank conflicts.
+#include <algorithm>
+
 #include "common.h"
 #include "internal.h"
 #include "optim_math.h"
@@ -227,8 +229,6 @@ __global__ __launch_bounds__(FS_THREADS) void fused_small_step_kernel(FusedSmall
 __host__ __device__ inline int fs_pad(int w) { return (w + 15) & ~15; }
 __host__ __device__ inline int fs_pitch(int w) { return fs_pad(w) + 4; }
 
-constexpr int FT_WAVES = 8, FT_LOADERS = 4;   // wavefronts that compute, wavefronts that fetch
-constexpr int FT_THREADS = (FT_WAVES + FT_LOADERS) * 64;
 constexpr int FT_EVAL_ROWS = 64;    // held-out rows per workgroup: four wavefronts of 16 rows each
 
 size_t fused_tiled_plan(FusedSmallArgs& a, bool for_eval) {
@@ -377,7 +377,8 @@ __device__ __forceinline__ void ft_loss16(float* lg_rows, int pitch, int C, cons
 // e / d for 0 <= e < 65536, inv = ceil(2^32 / d) (d > 1; 2^32 / 1 does not fit and is taken as 0)
 __device__ __forceinline__ int ft_div(int e, uint32_t inv) { return inv ? (int)__umulhi((uint32_t)e, inv) : e; }
 
-// Block numbers wave, wave + FT_WAVES, ... of a grid with `rows` block rows, as (row, column)
+// Block numbers wave, wave + WAVES, ... of a grid with `rows` block rows, as (row, column)
+template <int WAVES>
 struct FtWalk {
   int row, col, rows;
   __device__ __forceinline__ void start(int first, int n) {
@@ -385,7 +386,7 @@ struct FtWalk {
     settle();
   }
   __device__ __forceinline__ void settle() { while (row >= rows) { row -= rows; ++col; } }
-  __device__ __forceinline__ void next() { row += FT_WAVES; settle(); }
+  __device__ __forceinline__ void next() { row += WAVES; settle(); }
 };
 
 __device__ __forceinline__ void ft_act4(float* v, int kind) {
@@ -434,11 +435,12 @@ __device__ __forceinline__ void ft_act4_bwd(float* v, int kind) {
   }
 }
 
-// Rows and labels of one step's mini-batch (Philox domain 1) into LDS, by the FT_LOADERS wavefronts: each takes its share of
+// Rows and labels of one step's mini-batch (Philox domain 1) into LDS, by the LOADERS wavefronts: each takes its share of
 // the rows, a lane draws the number of one row, then all lanes run over the rows' elements, eight loads at a time.
+template <int LOADERS>
 __device__ __forceinline__ void ft_load_batch(const FusedSmallArgs& a, int member, uint32_t step, float* X, int px, int* y, int loader) {
   const int lane = threadIdx.x & 63, B = a.B, d0 = a.dims[0];
-  const int share = (B + FT_LOADERS - 1) / FT_LOADERS, rbeg = loader * share, rend = min(B, rbeg + share);
+  const int share = (B + LOADERS - 1) / LOADERS, rbeg = loader * share, rend = min(B, rbeg + share);
   for (int r0 = rbeg; r0 < rend; r0 += 64) {
     const int rows = min(64, rend - r0), n = rows * d0;
     int src = 0;
@@ -461,10 +463,13 @@ __device__ __forceinline__ void ft_load_batch(const FusedSmallArgs& a, int membe
   }
 }
 
+// WAVES wavefronts compute and LOADERS fetch.  A block of a contraction is formed by one wavefront in the same order whatever their
+// number, so results do not depend on it.
 // NL: number of layers when it is known (its loops are unrolled and what they read of the argument block stays in scalar
 // registers), 0: any.  OPT: optimiser.
-template <int NL, int OPT>
-__global__ __launch_bounds__(FT_THREADS) void fused_tiled_step_kernel(FusedSmallArgs a) {
+template <int NL, int OPT, int WAVES, int LOADERS>
+__global__ __launch_bounds__((WAVES + LOADERS) * 64) void fused_tiled_step_kernel(FusedSmallArgs a) {
+  constexpr int FT_THREADS = (WAVES + LOADERS) * 64;
   extern __shared__ float lds[];
   const int i = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int fr = lane & 15, fg = lane >> 4;   // fragment row / column, group of four rows (or k offset)
@@ -493,15 +498,15 @@ __global__ __launch_bounds__(FT_THREADS) void fused_tiled_step_kernel(FusedSmall
   const float gscale = 1.f / (float)B;
   float last_loss = 0.f;
 
-  if (wave >= FT_WAVES) {
+  if (wave >= WAVES) {
     // the fetching wavefronts: step s + 1's rows, labels and bias corrections go into the half of the double buffers that
     // step s does not read; they meet the others at every barrier
     for (int s = -1; s < a.n_steps; ++s) {
       const int nxt = (s + 1) & 1;
       if (s + 1 < a.n_steps) {
-        if (OPT == OPT_ADAM && tid - FT_WAVES * 64 < 2)   // 1 / (1 - beta^t)
+        if (OPT == OPT_ADAM && tid - WAVES * 64 < 2)   // 1 / (1 - beta^t)
           lds[a.lt_sc + 2 * nxt + lane] = 1.f / (1.f - powf(lane == 0 ? b1 : a.c1, (float)(t0 + s + 2)));
-        ft_load_batch(a, i, a.step0 + (uint32_t)(s + 1), lds + a.lt_x[nxt], px, ytab + nxt * RB * 16, wave - FT_WAVES);
+        ft_load_batch<LOADERS>(a, i, a.step0 + (uint32_t)(s + 1), lds + a.lt_x[nxt], px, ytab + nxt * RB * 16, wave - WAVES);
       }
       if (s < 0) __syncthreads();
       else
@@ -561,7 +566,7 @@ __global__ __launch_bounds__(FT_THREADS) void fused_tiled_step_kernel(FusedSmall
       const bool last = s == a.n_steps - 1;
       const float* X = lds + a.lt_x[cur];
       const float* sc = lds + a.lt_sc + 2 * cur;
-      FtWalk w;
+      FtWalk<WAVES> w;
 #pragma unroll
       for (int l = 0; l < L; ++l) {
         const int KP = fs_pad(a.dims[l]), N = a.dims[l + 1], pk = fs_pitch(a.dims[l]), pn = fs_pitch(N), NB = fs_pad(N) / 16;
@@ -583,7 +588,7 @@ __global__ __launch_bounds__(FT_THREADS) void fused_tiled_step_kernel(FusedSmall
             for (int e = 0; e < 4; ++e) lds[a.lt_a[l + 1] + o + e * pn] = v[e];
           }
         } else {
-          for (int rb = wave; rb < RB; rb += FT_WAVES) {
+          for (int rb = wave; rb < RB; rb += WAVES) {
             for (int nb = 0; nb < NB; ++nb) {
               const int n = nb * 16 + fr, o = (rb * 16 + 4 * fg) * pn + n;
               const float bias = lds[a.lt_b[l] + n];
@@ -619,13 +624,13 @@ __global__ __launch_bounds__(FT_THREADS) void fused_tiled_step_kernel(FusedSmall
             ft_act4_bwd(v, a.act);
 #pragma unroll
             for (int e = 0; e < 4; ++e) d[e * pk] = acc[e] * v[e];
-            left += FT_WAVES;
+            left += WAVES;
           }
           left -= RB * KB;
         }
         if (l + 1 < L) {
           const int NB = fs_pad(a.dims[l + 2]) / 16, KB = fs_pad(a.dims[l + 1]) / 16;
-          for (w.start(left, NB); w.col < KB; w.next()) { weight_unit(l + 1, w.col, w.row, lds + a.lt_a[l + 1], fs_pitch(a.dims[l + 1]), sc, last); left += FT_WAVES; }
+          for (w.start(left, NB); w.col < KB; w.next()) { weight_unit(l + 1, w.col, w.row, lds + a.lt_a[l + 1], fs_pitch(a.dims[l + 1]), sc, last); left += WAVES; }
           left -= NB * KB;
         }
         if (l == 0) {
@@ -655,9 +660,21 @@ __global__ __launch_bounds__(FT_THREADS) void fused_tiled_step_kernel(FusedSmall
   }
 }
 
-template <int OPT>
+// The three sizes of the step's workgroup.  Eight and four wavefronts are fastest for a member by itself, but a compute unit holds one or
+// two of them (registers); populations of more members than that take four and two, or three and one, of which it holds two and four.
+constexpr struct { int waves, loaders; } FT_SIZES[3] = {{8, 4}, {4, 2}, {3, 1}};
+template <int OPT, int SIZE>
 static void (*ft_step_kernel(int n_layers))(FusedSmallArgs) {
-  return n_layers == 2 ? fused_tiled_step_kernel<2, OPT> : n_layers == 3 ? fused_tiled_step_kernel<3, OPT> : fused_tiled_step_kernel<0, OPT>;
+  constexpr int W = FT_SIZES[SIZE].waves, LD = FT_SIZES[SIZE].loaders;
+  return n_layers == 2 ? fused_tiled_step_kernel<2, OPT, W, LD> : n_layers == 3 ? fused_tiled_step_kernel<3, OPT, W, LD> : fused_tiled_step_kernel<0, OPT, W, LD>;
+}
+template <int OPT>
+static void (*ft_step_kernel(int n_layers, int size))(FusedSmallArgs) {
+  return size == 0 ? ft_step_kernel<OPT, 0>(n_layers) : size == 1 ? ft_step_kernel<OPT, 1>(n_layers) : ft_step_kernel<OPT, 2>(n_layers);
+}
+static void (*ft_step_kernel(int optimizer, int n_layers, int size))(FusedSmallArgs) {
+  return optimizer == OPT_SGD_MOMENTUM ? ft_step_kernel<OPT_SGD_MOMENTUM>(n_layers, size)
+         : optimizer == OPT_ADAM ? ft_step_kernel<OPT_ADAM>(n_layers, size) : ft_step_kernel<OPT_RMSPROP>(n_layers, size);
 }
 
 // (1024 rows x 8 members: 506 -> 18 us with the sum over workgroups, against one workgroup per member that walks all rows.)
@@ -717,19 +734,65 @@ static hipError_t set_lds(const void* kernel, size_t bytes) {
   return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-// The tiled form whenever its padded arrays fit a compute unit; the plain form (no padding, no double buffers) is left for
-// networks that fill the LDS nearly to the last byte.
+constexpr int FS_CUS = 256;
+// How often the compute units are filled when each holds up to `resident` workgroups of a kernel that needs `lds` bytes.
+static int fs_rounds(int P, size_t lds, int resident) {
+  const int each = std::max(1, std::min(resident, (int)(FUSED_SMALL_MAX_LDS / lds)));
+  return (P + FS_CUS * each - 1) / (FS_CUS * each);
+}
+
+// Networks for which the plain form is faster although the tiled one fits.  The tiled form pads batches and widths to 16, which costs
+// nothing while there is a compute unit for every member; with more members the padded arrays of a mini-batch of a few rows can take a
+// second round where the plain ones take one (1024 members 24-24-24-24-3, Adam, one row: 17 us against 39 per step), and four or more layers of a
+// handful of units are a serial chain that 16 x 16 blocks only lengthen (8 members 8-8-8-8-8-2, one row, one step per call: 14 us against 17).
+// From the configuration alone: how an interval is divided into calls does not change a result.
+static bool fs_plain_is_faster(const FusedSmallArgs& a, size_t tiled, size_t plain) {
+  int widest = 0;
+  for (int l = 0; l <= a.n_layers; ++l) widest = std::max(widest, a.dims[l]);
+  const bool fewer_rounds = fs_rounds(a.P, plain, 8) < fs_rounds(a.P, tiled, 4);
+  if (a.B <= 8 && widest <= 32 && fewer_rounds) return true;
+  return a.n_layers > 3 && widest <= 8 && a.B <= (fewer_rounds ? 32 : 4);
+}
+
+// The size that fills the compute units the fewest times, the larger of two that are equal.  20 steps a call, us per step of the largest
+// size only, now, and in the plain form: 1024 members 4-8-2, Adam, 16 rows: 17.6, 5.1, 10.0; 512 members 8-8-8-2, momentum, 16 rows: 9.8, 5.2,
+// 9.8; 1024 members 32-64-4, Adam, 16 rows: 22.9, 15.8, 48.1.  The smallest only where no phase of a step has more than eight 16 x 16
+// blocks: with more its three wavefronts become the bound (768 members 32-64-4, 32 rows: 11.4 us in two rounds of the largest, 15.6 in one
+// of the smallest), and with a mini-batch of more than 2048 values the one that fetches (768 members 64-10, 64 rows: 8.2 and 9.8).
+static int ft_size(const FusedSmallArgs& a, size_t tiled) {
+  if (a.P <= FS_CUS) return 0;
+  const int RB = fs_pad(a.B) / 16;
+  auto blocks = [&](int l) { return fs_pad(a.dims[l]) / 16; };
+  int most = 0;
+  for (int l = 0; l < a.n_layers; ++l) {
+    most = std::max(most, l + 1 < a.n_layers ? RB * blocks(l + 1) : RB);
+    most = std::max(most, (l > 0 ? RB * blocks(l) : blocks(0) * blocks(1)) + (l + 1 < a.n_layers ? blocks(l + 1) * blocks(l + 2) : 0));
+  }
+  int held = 1;   // workgroups of the largest size that a compute unit's registers hold
+  const auto largest = ft_step_kernel(a.optimizer, a.n_layers, 0);
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&held, reinterpret_cast<const void*>(largest), (FT_SIZES[0].waves + FT_SIZES[0].loaders) * 64, 0) != hipSuccess) {
+    (void)hipGetLastError();
+    held = 1;
+  }
+  const int rounds[3] = {fs_rounds(a.P, tiled, held), fs_rounds(a.P, tiled, 2), fs_rounds(a.P, tiled, 4)};
+  int size = 0;
+  if (rounds[1] < rounds[size]) size = 1;
+  if (rounds[2] < rounds[size] && most <= 8 && a.B * a.dims[0] <= 2048) size = 2;
+  return size;
+}
+
+// The tiled form whenever its padded arrays fit a compute unit and fs_plain_is_faster() knows nothing better; the plain form (no padding,
+// no double buffers) is left for those and for networks that fill the LDS nearly to the last byte.
 hipError_t fused_small_step(FusedSmallArgs a, hipStream_t s) {
-  const size_t tiled = fused_tiled_plan(a, false);
-  if (tiled <= FUSED_SMALL_MAX_LDS) {
-    auto kernel = a.optimizer == OPT_SGD_MOMENTUM ? ft_step_kernel<OPT_SGD_MOMENTUM>(a.n_layers)
-                  : a.optimizer == OPT_ADAM ? ft_step_kernel<OPT_ADAM>(a.n_layers) : ft_step_kernel<OPT_RMSPROP>(a.n_layers);
+  const size_t tiled = fused_tiled_plan(a, false), bytes = fused_small_plan(a, false);
+  if (tiled <= FUSED_SMALL_MAX_LDS && !fs_plain_is_faster(a, tiled, bytes)) {
+    const int size = ft_size(a, tiled);
+    const auto kernel = ft_step_kernel(a.optimizer, a.n_layers, size);
     hipError_t e = set_lds(reinterpret_cast<const void*>(kernel), tiled);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kernel, dim3(a.P), dim3(FT_THREADS), tiled, s, a);
+    hipLaunchKernelGGL(kernel, dim3(a.P), dim3((FT_SIZES[size].waves + FT_SIZES[size].loaders) * 64), tiled, s, a);
     return hipGetLastError();
   }
-  const size_t bytes = fused_small_plan(a, false);
   hipError_t e = set_lds(reinterpret_cast<const void*>(fused_small_step_kernel), bytes);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(fused_small_step_kernel, dim3(a.P), dim3(FS_THREADS), bytes, s, a);

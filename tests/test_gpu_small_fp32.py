@@ -88,3 +88,28 @@ def test_a_logit_that_is_infinite_marks_its_member():
     assert np.all(np.isposinf(loss[1:C])) and np.isfinite(loss[0]) and np.isfinite(loss[C])
     for i in range(1, C):
         assert np.isnan(grad[i, i]) and np.isclose(grad[i, 0], -1.0) and np.all(np.delete(grad[i], [0, i]) == 0)
+
+
+@pytest.mark.parametrize("opt", [SGD, ADAM, RMS])
+@pytest.mark.parametrize("dims,batch", [([20, 40, 5], 19), ([11, 24, 17, 6], 33), ([13, 9, 10, 8, 7], 40), ([50, 5], 70)], ids=lambda v: str(v))
+def test_results_do_not_depend_on_the_size_of_the_population(dims, batch, opt):
+    """More members than compute units take smaller workgroups (300: two to a compute unit, 1000: four).  A member's draws
+    depend on its number alone, so the first eight are bit for bit those of a population of eight."""
+    import torch
+    rng = np.random.default_rng(2)
+    x, y = rng.standard_normal((400, dims[0])).astype(np.float32), rng.integers(0, dims[-1], 400).astype(np.int32)
+    arrays = [binding.ARR_W32, binding.ARR_OPT0, binding.ARR_GRAD, binding.ARR_LOSS, binding.ARR_T] + ([binding.ARR_OPT1] if opt == ADAM else [])
+    got = {}
+    for P in (8, 300, 1000):
+        wl = W.MLP_SMALL.replace(P=P, dims=dims, batch=batch, n_eval=50, n_train=400, n_trunc=0, act=W.ACT_GELU, optimizer=opt, n_classes=dims[-1],
+                                 opt_const=CONST[opt], priors=[("log", 1e-3, 1e-2)])
+        pop = binding.Population(binding.make_config(wl, 7))
+        pop.init_population(wl.priors)
+        data = [torch.from_numpy(x).to(pop.device), torch.from_numpy(y).to(pop.device)]
+        pop.step(data, 0, n_steps=3)
+        pop.step(data, 3)
+        got[P] = [pop.get(w) for w in arrays]
+        assert np.all(np.isfinite(got[P][0])) and np.any(got[P][2][P - 1])
+    for P in (300, 1000):
+        for which, a, b in zip(arrays, got[8], got[P]):
+            assert a.tobytes() == b[:8].tobytes(), (P, which)
