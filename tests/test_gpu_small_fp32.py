@@ -27,6 +27,10 @@ def test_step_and_score_against_the_oracle(dims, batch, n_eval, act, opt):
     """Three steps from the same start, then the score.  fp32 sums of at most 128 products of O(1) terms: 128 x 2^-24 = 8e-6
     at worst per sum, a few 1e-7 as a rule; 2e-5 leaves room for three chained layers and steps.  Adam and RMSProp divide by
     the root of near-zero mean squares in the first steps: 2e-4 there.  Losses near 1: same bound."""
+    _step_and_score(dims, batch, n_eval, act, opt)
+
+
+def _step_and_score(dims, batch, n_eval, act, opt):
     wl = W.MLP_SMALL.replace(P=3, dims=dims, batch=batch, n_eval=n_eval, n_train=500, n_trunc=1, act=act, optimizer=opt, n_classes=dims[-1],
                              opt_const=CONST[opt], priors=[("log", 1e-3, 1e-2)])
     pair = Pair(wl)
@@ -38,9 +42,55 @@ def test_step_and_score_against_the_oracle(dims, batch, n_eval, act, opt):
     assert pair.scalar_errors(pair.gpu.get(binding.ARR_LOSS), loss, 1e-2) <= tol
     assert pair.tensor_errors(binding.ARR_W32, "theta") <= tol
     assert pair.tensor_errors(binding.ARR_OPT0, "s0") <= tol
+    if opt == ADAM:
+        assert pair.tensor_errors(binding.ARR_OPT1, "s1") <= tol
     assert np.all(pair.gpu.get(binding.ARR_T) == 3)
     pair.gpu.eval(pair.d_eval)
     assert pair.scalar_errors(pair.gpu.get(binding.ARR_SCORE), pair.eval_ref(), 1e-2) <= tol
+
+
+def _padded(w):
+    return -(-w // 16) * 16
+
+
+def _step_fits_padded(dims, batch, opt):
+    """Whether the step's arrays fit a compute unit's 160 KB when widths and rows are padded to 16 (and pitches by 4)."""
+    pairs, rows = list(zip(dims[:-1], dims[1:])), _padded(batch)
+    params = 0
+    for fi, fo in pairs:
+        params = -(-(params + fi * fo) // 64) * 64
+        params = -(-(params + fo) // 64) * 64
+    params = -(-params // 256) * 256
+    floats = sum(_padded(fi) * (_padded(fo) + 4) + _padded(fo) for fi, fo in pairs) + params * (2 if opt == ADAM else 1)
+    floats += rows * (2 * (_padded(dims[0]) + 4) + sum(_padded(w) + 4 for w in dims[1:-1]) + sum(_padded(w) + 4 for w in dims[1:])) + 3 * rows + 4
+    return floats * 4 <= 160 * 1024
+
+
+def _score_fits_padded(dims):
+    """The same for the score: the parameters and two buffers of 64 rows of the widest layer, beside 1 KB."""
+    floats = sum(_padded(fi) * (_padded(fo) + 4) + _padded(fo) for fi, fo in zip(dims[:-1], dims[1:])) + 2 * 64 * (_padded(max(dims)) + 4)
+    return floats * 4 <= 159 * 1024
+
+
+@pytest.mark.parametrize("dims,batch,n_eval,act,opt,plain", [
+    ([40, 50, 17], 100, 200, W.ACT_GELU, ADAM, "step"),
+    ([40, 50, 17], 128, 40, W.ACT_TANH, RMS, "step"),
+    ([100, 66, 5], 33, 70, W.ACT_LEAKY_RELU, ADAM, "step"),
+    ([8, 7, 6, 8, 5, 2], 3, 20, W.ACT_LEAKY_RELU, RMS, "chain"),
+    ([32, 256, 4], 8, 150, W.ACT_RELU, SGD, "score"),
+    ([16, 256, 10], 16, 17, W.ACT_GELU, RMS, "score"),
+    ([320, 32, 10], 16, 33, W.ACT_TANH, SGD, "score"),
+], ids=lambda v: str(v))
+def test_plain_form_against_the_oracle(dims, batch, n_eval, act, opt, plain):
+    """The form without padding: the step of networks whose padded arrays do not fit, the step of a chain of small layers, the score
+    of networks whose 64 padded rows do not fit (their step does).  Bounds as above, for sums of up to 320 products."""
+    if plain == "step":
+        assert not _step_fits_padded(dims, batch, opt)
+    elif plain == "chain":
+        assert len(dims) > 4 and max(dims) <= 8 and batch <= 4
+    else:
+        assert _step_fits_padded(dims, batch, opt) and not _score_fits_padded(dims)
+    _step_and_score(dims, batch, n_eval, act, opt)
 
 
 @pytest.mark.parametrize("label", [0, 1])

@@ -79,6 +79,19 @@ def test_transformer_reduced_ragged_shapes():
     print("transformer ragged:", {k: float("%.3g" % v) for k, v in worst.items()}, flush=True)
 
 
+def test_transformer_rows_wider_than_the_fused_kernels():
+    """Rows of more than 2048 values do not fit the registers of the kernels that join residual, dropout and LayerNorm: the separate
+    kernels of both passes, with the ragged last slab that 2056 leaves."""
+    wl = _reduced(P=1, vocab=24, d_model=2056, heads=1, d_ff=24, n_blocks=1, seq=8, batch=2, n_train=16, n_eval=2, n_trunc=0)
+    pair = TransformerPair(wl, H=np.array([[1e-3, 0.2, 0.1]], dtype=np.float32))
+    # (the bounds of the one-kernel attention test below, for its reason)
+    worst = _teacher_forced(pair, range(2), range(1), tol_grad=2 * TOL_GRAD_SMALL, tol_w=2 * TOL_GRAD_SMALL)
+    pair.gpu.eval(pair.d_eval)
+    sc, sc_ref = pair.gpu.get(binding.ARR_SCORE), pair.eval_ref()
+    assert np.max(np.abs(sc - sc_ref) / np.abs(sc_ref)) <= TOL_BF16, (sc, sc_ref)
+    print("transformer wide rows:", {k: float("%.3g" % v) for k, v in worst.items()}, flush=True)
+
+
 @pytest.mark.parametrize("seq,batch", [(96, 2), (128, 2), (64, 2), (32, 3)])
 def test_transformer_reduced_one_kernel_attention(seq, batch):
     """Heads of width 64 and sequences of 32, 96 and 128 positions take the attention kernels that keep the
