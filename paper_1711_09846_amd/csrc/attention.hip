@@ -395,15 +395,18 @@ __global__ __launch_bounds__(256, 2) void attention_bwd_dkv_kernel(const bf16_t*
     fetch_rows(Q + a.d, pitch, a.S, k);
     fetch_rows(Q + 2 * a.d, pitch, a.S, v);
     fetch_rows(dOh, a.d, a.S, g);
-    // (a query per thread; those past the sequence get zeros, which make their probabilities and ds zero)
+    // (a query per thread; those past the sequence get zeros, which make their probabilities and ds zero.  Clamped addresses and a
+    // selection: guarded loads would be waited for one at a time.)
     if (threadIdx.x < SMAX) {
-      const int tq = threadIdx.x;
-      const float* __restrict__ sp = stats + stat_index(a, member, b, h);
-      const uint32_t* __restrict__ rp = record + record_index(a, member, b, h, min(tq, a.S - 1), 0);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) st[k * SMAX + tq] = tq < a.S ? sp[k * a.S + tq] : 0.f;
-#pragma unroll
-      for (int kb = 0; kb < 4; ++kb) rec[tq * 4 + kb] = tq < a.S && kb < NB ? rp[kb] : 0u;
+      const int tq = threadIdx.x, in = min(tq, a.S - 1);
+      const float* __restrict__ sp = stats + stat_index(a, member, b, h) + in;
+      const uint32_t* __restrict__ rp = record + record_index(a, member, b, h, in, 0);
+      const float s0 = sp[0], s1 = sp[a.S], s2 = sp[2 * a.S];
+      const uint32_t r0 = rp[0], r1 = rp[min(1, NB - 1)], r2 = rp[min(2, NB - 1)], r3 = rp[min(3, NB - 1)];   // (words past the last block are not used)
+      st[tq] = tq < a.S ? s0 : 0.f;
+      st[SMAX + tq] = tq < a.S ? s1 : 0.f;
+      st[2 * SMAX + tq] = tq < a.S ? s2 : 0.f;
+      reinterpret_cast<uint4*>(rec)[tq] = make_uint4(r0, r1, r2, r3);
     }
     put_rows(q, 32 * NB, Xr);
     put_rows(k, 32 * NB, Yr);
