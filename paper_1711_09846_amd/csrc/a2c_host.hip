@@ -488,7 +488,7 @@ __global__ __launch_bounds__(256) void a2c_env_observe_kernel(EnvArgs a, int t) 
 //    once for all of them (16 bytes per lane; read 4 bytes at a time at a stride of 16 it was the LDS that bounded this).
 //  - the action draw and the latent transition of a trajectory belong to one half-wavefront (lane = action, then latent
 //    component): exchanges instead of barriers.
-// 128 members, 32 trajectories of 20 steps, 512-256-256-19: 356 us, and 31 (2-byte loads; less now) + 9 for the packing and the draws ahead, against
+// 128 members, 32 trajectories of 20 steps, 512-256-256-19: 353 us, and 26 + 9 for the packing and the draws ahead, against
 // 1197 us as one workgroup per member that streamed its weights through LDS in every round.
 // Shapes: observation width and hidden widths multiples of 8, hidden widths up to 256, up to three hidden layers, at
 // most 32 head outputs, and what rollout_cut() finds to fit LDS.
@@ -510,7 +510,7 @@ inline int64_t ro_packed_elems(const int32_t* dims, int L) {
   for (int l = 0; l < L; ++l) n += (int64_t)ro_nblocks(dims[l + 1]) * ro_kblocks(dims[l]) * 512;
   return n;
 }
-// draws made ahead, in doubles per member: latent noise [T][B][nz] in stream order, z_0, reward noise, uniforms
+// draws made ahead, in doubles per member: latent noise [B][T][nz] (the order of its stream), z_0 [B][nz], reward noise [B][T], uniforms [B][T]
 struct RoDraws { int64_t o_zeta, o_z0, o_rew, o_u, count; };
 __host__ __device__ inline RoDraws ro_draws(int B, int T, int nz) {
   RoDraws d;

@@ -216,10 +216,10 @@ __global__ __launch_bounds__(FS_THREADS) void fused_small_step_kernel(FusedSmall
 
 // ---- tiled form ------------------------------------------------------------------------------------------------
 // The same step with every contraction on the matrix cores (v_mfma_f32_16x16x4_f32: fp32 operands and accumulation).
-// What bounds the plain form below is LDS reads (two per multiply-add) and wavefronts that wait for each other's and the
+// What bounds the plain form above is LDS reads (two per multiply-add) and wavefronts that wait for each other's and the
 // data rows' latencies: 63 us per step of a 32-64-4 network with 64 rows.  Here an operand is read once per 16
-// multiply-adds, every array is padded to whole 16 x 16 blocks (so no loop has a remainder), four wavefronts of their own
-// fetch the rows of step s + 1 while the other eight compute step s, and phases that do not depend on each other share a
+// multiply-adds, every array is padded to whole 16 x 16 blocks (so no loop has a remainder), wavefronts of their own
+// fetch the rows of step s + 1 while the others compute step s (four and eight of them, fewer in large populations: ft_size()), and phases that do not depend on each other share a
 // barrier interval: 2 L barriers per step of an L-layer network.  6.3 us per step (50 steps in one launch: 3.13 -> 0.31 ms);
 // what is left is instruction issue and LDS latency of the chain fragment -> MFMA -> activation -> fragment of each
 // interval.  The optimiser and the number of layers are template parameters: as branches inside the element loops they cost

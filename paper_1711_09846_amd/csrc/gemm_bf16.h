@@ -850,7 +850,7 @@ struct EpiOptimizer {
 
 // Tile shapes.  128x128 tiles (four wavefronts, three workgroups per compute unit) unless that leaves
 // the 256 compute units with fewer than four workgroups each to hide latency with; then 128x64.
-// Products of at most 64 rows, or with too few of those for the compute units, take 64x64 tiles.
+// Products of at most 64 rows, or with fewer than two of those per compute unit, take 64x64 tiles.
 // Long contractions of large matrices take 256x256 tiles (eight wavefronts of 128x64, LDS slabs
 // double-buffered, one workgroup per compute unit): the L2 -> LDS traffic per flop halves, which
 // lifts the steady-state rate from about 880 to 1100 TFLOP/s (measured, 4096 x 2048 x K, batch 16);
@@ -877,7 +877,7 @@ inline GemmTile choose_tile(int M, int N, int K, int batch) {
   if (K >= 1024 && M > 128 && N > 128 && tile_count(M, N, batch, 256, 256) >= CUS * 3 / 4) return TILE_256x256;
   // (double-buffered 128x128 and 128x64 variants were tried for the long, narrow weight gradients (K >= 2048 with at
   // most two tiles per compute unit) and for all 128x128 launches: no change for the former, 3 % slower for the latter)
-  // Half a 128-row tile would be clamped rows (a GAN's 64-row batches), or its tiles are fewer than two per compute unit: the GAN step
+  // Half a 128-row tile would be clamped rows (a GAN's 64-row batches), or the 128x64 tiles are fewer than two per compute unit: the GAN step
   // 525 -> 487 us (500 with the line at one per compute unit), 21 members with batches of 75 and ragged widths 129 -> 116, six small
   // transformers 620 -> 584 (602); populations of the wide MLP and the actor-critic lie above the line.
   if (M <= 64 || tile_count(M, N, batch, 128, 64) < 2 * CUS) return TILE_64x64;

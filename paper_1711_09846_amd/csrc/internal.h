@@ -167,8 +167,8 @@ hipError_t residual_dropout_layernorm(const bf16_t* x, const bf16_t* res, int P,
 // of a contraction that was cut into pieces, in piece order, into G at w_off (b_off)
 hipError_t wgrad_combine(const float* part, const float* colpart, int n_parts, int P, int64_t count, int N, float* G, int64_t stride,
                          int64_t w_off, int64_t b_off, hipStream_t s);
-// Attention of one (member, sequence, head) per workgroup without score or probability arrays in memory, for
-// 64-wide heads and sequences of 32, 64, 96 or 128 positions (attention_fused_applies).  qkv: [P][Bc*S][3d]
+// Attention of one (member, sequence, head) per workgroup without score or probability arrays in memory, for heads 64 or 32
+// wide and sequences of at most 128 positions, a multiple of 8 (attention_fused_applies).  qkv: [P][Bc*S][3d]
 // (queries, keys, values side by side, heads side by side inside each); o, dO: [P][Bc*S][d]; dqkv like qkv.
 // The forward pass leaves the keep bits of its dropout site in `record` (attention_record_bytes; null = not
 // wanted); the backward pass (two kernels: dQ, then dK and dV) needs them and attention_stats_bytes of scratch.
