@@ -1,55 +1,16 @@
-// Population-batched GEMM on the gfx950 matrix cores: bf16 operands, fp32
-// accumulate, one output tile per workgroup, member index = batch dimension.
+// The population-batched GEMM that stages its operands through registers: for weight gradients dW = X^T dY with the optimiser in
+// the epilogue (its loads of theta and the optimiser state are what the launch waits for, and half of the first strip's go out ahead of the
+// K loop), and for rows too long for the direct-to-LDS kernel's buffer offsets (gemm_lds.h, which everything else takes).
 //
-// This is the dense contraction of `step` (Section 3, Eq. 2 of the PBT paper):
-// forward Y = X W, input gradient dX = dY W^T and weight gradient dW = X^T dY
-// for every member of the population in one launch.
-//
-// Tiling (wave64): a workgroup of WM x WN wavefronts owns a BM x BN tile of C;
-// each wavefront owns a (BM/WM) x (BN/WN) sub-tile made of 32x32 accumulator
-// blocks fed by v_mfma_f32_32x32x16_bf16.  The K loop moves BK wide slabs of A
-// and B from HBM into registers (16-byte loads), then into LDS in a
-// "K-contiguous" layout, so that every MFMA operand is one 16-byte LDS read.
-// Operands whose memory layout is contiguous along M or N instead of K (W in
-// the forward pass, X and dY in the weight gradient) are transposed in
-// registers on their way into LDS.  The loads of slab k+1 (k+2 with two LDS
-// buffers) are in flight while slab k is multiplied.
-//
-// The epilogue is a functor applied to runs of 8 consecutive columns; it fuses
-// bias + activation (forward) or the activation derivative (input gradient).
+// Tiling (wave64): a workgroup of WM x WN wavefronts owns a BM x BN tile of C; each wavefront owns a (BM/WM) x (BN/WN) sub-tile made of 32x32
+// accumulator blocks fed by v_mfma_f32_32x32x16_bf16.  The K loop moves BK wide slabs of A and B from HBM into registers (16-byte loads), then
+// into LDS in a "K-contiguous" layout, so that every MFMA operand is one 16-byte LDS read.  Operands whose memory layout is contiguous along M or
+// N instead of K (X and dY in the weight gradient) are transposed in registers on their way into LDS.  The loads of slab k+1 (k+2 with two
+// LDS buffers) are in flight while slab k is multiplied.
 #pragma once
-#include <type_traits>
-
-#include "common.h"
-#include "dropout.h"
-#include "optim_math.h"
+#include "gemm_epilogues.h"
 
 namespace pbt {
-
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
-
-struct GemmArgs {
-  const bf16_t* A;
-  int64_t lda, sa;
-  const bf16_t* B;
-  int64_t ldb, sb;
-  int M, N, K, batch;
-  int tiles_m, tiles_n;
-  // two-level batch index (attention: outer = sequence, inner = head): the operand of batch element b
-  // starts at (b / inner) * s? + (b % inner) * s?_in
-  int inner;
-  int64_t sa_in, sb_in;
-  // optional by-product: colsum[b * colsum_stride + n] = sum_k B[k][n] (float), written by the first tile
-  // row of every batch element from the B slabs it stages anyway (the bias gradient of a weight-gradient
-  // contraction, whose B operand is dZ); null = not wanted
-  float* colsum = nullptr;
-  int64_t colsum_stride = 0;
-  int colsum_k = 0;   // the column sums run over k < colsum_k (the launcher sets K when the caller gives no limit)
-  int upper = 0;      // EpiRbfSum only: C is symmetric, only the tiles that reach the diagonal or lie right of it are computed
-  int tiles = 0;      // tiles per batch element (set by the launcher)
-  int b_cols = 0;     // columns of an N-contiguous B that may be read (N, or more where the rows are padded with zeros)
-};
 
 // LDS row pitch in elements for a slab width BK: +8 keeps 16-byte alignment and skews the banks
 constexpr int gemm_pitch(int bk) { return bk + 8; }
@@ -185,32 +146,6 @@ struct TileLoader {
   }
 };
 
-// Workgroups are handed to the 8 XCDs round-robin by linear id.  Remap the id
-// so that each XCD works on a contiguous run of tiles (neighbouring tiles
-// share an A or B slab, which then stays in that XCD's L2).
-__device__ __forceinline__ int xcd_remap(int id, int total) {
-  constexpr int XCDS = 8;
-  const int per = total / XCDS;
-  if (id >= per * XCDS) return id;  // ragged tail keeps its place
-  return (id % XCDS) * per + id / XCDS;
-}
-
-// Tile order inside one batch element: tiles are numbered down groups of GROUP_M tile rows, so that the
-// workgroups resident on an XCD at one time (consecutive numbers) form a block of tiles that shares
-// few A and B slabs and keeps them in that XCD's L2.
-constexpr int GROUP_M = 8;
-
-// Tile row tm of a symmetric product starts at column tile (BM / BN) tm.
-template <int BM, int BN>
-__host__ __device__ inline int upper_tiles(int tiles_m, int tiles_n) {
-  int n = 0;
-  for (int tm = 0; tm < tiles_m; ++tm) n += tiles_n - BM / BN * tm;
-  return n;
-}
-
-struct EpiRbfSum;
-struct EpiHeadStats;
-
 template <int BM, int BN, int GEMM_BK, int WM, int WN, bool A_MCONTIG, bool B_KCONTIG, bool DOUBLE_BUF, class Epilogue>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, Epilogue epi) {
   constexpr int THREADS = WM * WN * 64;
@@ -225,19 +160,12 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, Epi
   const int per_member = g.tiles;
   const int member = id / per_member;
   id -= member * per_member;
-  const int tile = id;
-  int tm, tn;
-  if (std::is_same_v<Epilogue, EpiRbfSum> && g.upper) {
-    for (tm = 0; id >= g.tiles_n - BM / BN * tm; ++tm) id -= g.tiles_n - BM / BN * tm;
-    tn = BM / BN * tm + id;
-  } else {
-    const int group = id / (GROUP_M * g.tiles_n);
-    const int first_m = group * GROUP_M;
-    const int rows_in_group = g.tiles_m - first_m < GROUP_M ? g.tiles_m - first_m : GROUP_M;
-    id -= group * GROUP_M * g.tiles_n;
-    tm = first_m + id % rows_in_group;
-    tn = id / rows_in_group;
-  }
+  const int group = id / (GROUP_M * g.tiles_n);
+  const int first_m = group * GROUP_M;
+  const int rows_in_group = g.tiles_m - first_m < GROUP_M ? g.tiles_m - first_m : GROUP_M;
+  id -= group * GROUP_M * g.tiles_n;
+  const int tm = first_m + id % rows_in_group;
+  const int tn = id / rows_in_group;
   const int m0 = tm * BM, n0 = tn * BN;
 
   const bf16_t* __restrict__ A = g.A + (int64_t)(member / g.inner) * g.sa + (int64_t)(member % g.inner) * g.sa_in;
@@ -264,7 +192,6 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, Epi
   // strip's while the one before it is applied.
   constexpr int WCOLS = BN / WN, RUNS4 = WCOLS / 4, NQ4 = 32 * RUNS4 / 64;
   epi.begin(member);
-  if constexpr (std::is_same_v<Epilogue, EpiRbfSum>) epi.region = !g.upper ? 0 : n0 < m0 + BM ? 1 : 2;
 
   // (half of the first strip goes out ahead of the K loop so that memory is never left idle while the
   // workgroups of a compute unit are all busy with their operands; all of it would cost an occupancy step)
@@ -389,13 +316,6 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, Epi
   static_assert(WM * WN * 32 * CPITCH * 4 <= SLAB * 2, "C strips must fit the slab LDS");
   float* const Cw = reinterpret_cast<float*>(smem) + wave * 32 * CPITCH;
   fetch_first_strip(EARLY_RUNS, NQ4);
-  // A lane handles the same eight columns in every run, so what a functor needs per column (the bias) is
-  // read once, here: read inside the runs, after the stores of the run before, each run paid a memory
-  // latency of its own (more than half of a K = 512 tile's lifetime).  (Ahead of the K loop the eight
-  // registers would cost the 128x128 kernel its third workgroup per compute unit.)
-  static_assert(64 % RUNS == 0, "a lane's runs must share their columns");
-  float colv[8];
-  if constexpr (Epilogue::HAS_COLS) epi.load_cols(n0 + wn * WCOLS + (lane % RUNS) * 8, g.N, colv);
   __syncthreads();  // every wavefront is done with the slabs
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
@@ -425,16 +345,6 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, Epi
         if (i + 1 < TM && m + 32 < g.M && n < g.N) pre[q] = epi.fetch(m + 32, n, g.N - n < 4 ? g.N - n : 4);
       }
     } else {
-      typename Epilogue::RunData rund[32 * RUNS / 64];
-      if constexpr (Epilogue::HAS_RUNDATA) {
-#pragma unroll
-        for (int q = 0; q < 32 * RUNS / 64; ++q) {
-          const int run = q * 64 + lane;
-          const int m = m0 + wm * (BM / WM) + i * 32 + run / RUNS, n = n0 + wn * WCOLS + (run % RUNS) * 8;
-          rund[q] = typename Epilogue::RunData{};
-          if (m < g.M && n < g.N) rund[q] = epi.load_run(m, n, g.N - n < 8 ? g.N - n : 8);
-        }
-      }
 #pragma unroll
       for (int q = 0; q < 32 * RUNS / 64; ++q) {
         const int run = q * 64 + lane;
@@ -442,14 +352,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, Epi
         const int m = m0 + wm * (BM / WM) + i * 32 + row, n = n0 + wn * WCOLS + col;
         const float4 lo = *reinterpret_cast<const float4*>(Cw + row * CPITCH + col);
         const float4 hi = *reinterpret_cast<const float4*>(Cw + row * CPITCH + col + 4);
-        if constexpr (std::is_same_v<Epilogue, EpiHeadStats>) {
+        if (m < g.M && n < g.N) {
           const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-          epi.template apply_row<RUNS>(m, n, v, m < g.M ? min(max(g.N - n, 0), 8) : 0, colv);
-        } else if (m < g.M && n < g.N) {
-          const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-          if constexpr (Epilogue::HAS_COLS) epi.apply8(member, m, n, v, g.N - n < 8 ? g.N - n : 8, colv);
-          else if constexpr (Epilogue::HAS_RUNDATA) epi.apply8(member, m, n, v, g.N - n < 8 ? g.N - n : 8, rund[q]);
-          else epi.apply8(member, m, n, v, g.N - n < 8 ? g.N - n : 8);
+          const float none[1] = {0.f};
+          epi.template put<false>(m, n, (int64_t)m * epi.pitch() + n, v, g.N - n < 8 ? g.N - n : 8, none, NoData{});
         }
       }
     }
@@ -457,334 +363,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, Epi
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
-  if constexpr (Epilogue::HAS_FINISH) epi.finish(member, tile, g.tiles);
 }
-
-// ---- epilogues ------------------------------------------------------------------------------
-
-// Every epilogue receives runs of up to 8 consecutive columns of one row: v[0..count-1] are the
-// accumulator values of C[m][n .. n+count-1].  Full, 16-byte aligned runs use vector accesses.
-
-__device__ __forceinline__ uint4 pack_bf16x8(const float* v) {
-  return make_uint4(f2bf_pair(v[0], v[1]), f2bf_pair(v[2], v[3]), f2bf_pair(v[4], v[5]), f2bf_pair(v[6], v[7]));
-}
-__device__ __forceinline__ void unpack_bf16x8(uint4 p, float* v) {
-  const uint32_t w[4] = {p.x, p.y, p.z, p.w};
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    v[2 * q] = __uint_as_float(w[q] << 16);
-    v[2 * q + 1] = __uint_as_float(w[q] & 0xffff0000u);
-  }
-}
-__device__ __forceinline__ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-
-__device__ __forceinline__ void store_bf16_run(bf16_t* dst, const float* v, int count) {
-  if (count == 8 && aligned16(dst)) {
-    *reinterpret_cast<uint4*>(dst) = pack_bf16x8(v);
-  } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-      if (e < count) dst[e] = f2bf(v[e]);
-  }
-}
-
-// Every functor's begin(member) moves its pointers to the member's arrays once, so that apply8 is
-// left with m * pitch + n.
-struct EpiStoreF32 {
-  static constexpr bool HAS_FINISH = false;
-  static constexpr bool PREFETCH = false;
-  static constexpr bool COLSUM = true;   // weight gradients: the bias gradient can ride along
-  static constexpr bool HAS_COLS = false;
-  static constexpr bool HAS_RUNDATA = false;
-  static constexpr int LAYOUTS = 15;
-  struct Fetched {};
-  struct RunData {};
-  float* C;
-  int64_t ldc, sc;
-  __device__ __forceinline__ void begin(int member) { C += (int64_t)member * sc; }
-  __device__ __forceinline__ void apply8(int, int m, int n, const float* v, int count) const {
-    float* dst = C + (int64_t)m * ldc + n;
-    if (count == 8 && aligned16(dst)) {
-      *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
-      *reinterpret_cast<float4*>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
-    } else {
-      for (int e = 0; e < count; ++e) dst[e] = v[e];
-    }
-  }
-};
-
-struct EpiStoreBF16 {
-  static constexpr bool HAS_FINISH = false;
-  static constexpr bool PREFETCH = false;
-  static constexpr bool COLSUM = false;
-  static constexpr bool HAS_COLS = false;
-  static constexpr bool HAS_RUNDATA = false;
-  static constexpr int LAYOUTS = 15;
-  struct Fetched {};
-  struct RunData {};
-  bf16_t* C;
-  int64_t ldc, sc;
-  int inner = 1;       // two-level batch index as in GemmArgs
-  int64_t sc_in = 0;
-  __device__ __forceinline__ void begin(int member) { C += (int64_t)(member / inner) * sc + (int64_t)(member % inner) * sc_in; }
-  __device__ __forceinline__ void apply8(int, int m, int n, const float* v, int count) const {
-    store_bf16_run(C + (int64_t)m * ldc + n, v, count);
-  }
-};
-
-// Output layer over a large vocabulary: logits = acc + b[n], kept in float.  (Streaming stores for the logits made
-// this launch 4 % faster and the two that follow it slower by more: plain stores.)
-struct EpiBiasF32 {
-  static constexpr bool HAS_FINISH = false;
-  static constexpr bool PREFETCH = false;
-  static constexpr bool COLSUM = false;
-  static constexpr bool HAS_COLS = true;
-  static constexpr bool HAS_RUNDATA = false;
-  static constexpr int LAYOUTS = 1;
-  struct Fetched {};
-  struct RunData {};
-  const float* bias;
-  int64_t sbias;
-  float* C;
-  int64_t ldc, sc;
-  __device__ __forceinline__ void begin(int member) { bias += (int64_t)member * sbias; C += (int64_t)member * sc; }
-  // the eight biases of the lane's columns (the same for every run the lane handles), zero past N
-  __device__ __forceinline__ void load_cols(int n, int N, float* b) const {
-    if (n + 8 <= N && aligned16(bias + n)) {
-      const float4 lo = *reinterpret_cast<const float4*>(bias + n), hi = *reinterpret_cast<const float4*>(bias + n + 4);
-      b[0] = lo.x; b[1] = lo.y; b[2] = lo.z; b[3] = lo.w; b[4] = hi.x; b[5] = hi.y; b[6] = hi.z; b[7] = hi.w;
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) b[e] = n + e < N ? bias[n + e] : 0.f;
-    }
-  }
-  __device__ __forceinline__ void apply8(int, int m, int n, const float* v, int count, const float* b) const {
-    float* dst = C + (int64_t)m * ldc + n;
-    if (count == 8 && aligned16(dst)) {
-      *reinterpret_cast<float4*>(dst) = make_float4(v[0] + b[0], v[1] + b[1], v[2] + b[2], v[3] + b[3]);
-      *reinterpret_cast<float4*>(dst + 4) = make_float4(v[4] + b[4], v[5] + b[5], v[6] + b[6], v[7] + b[7]);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (e < count) dst[e] = v[e] + b[e];
-    }
-  }
-};
-
-// The same output layer where only the cross-entropy is wanted (held-out loss): the float logits stay in registers.  Of every row
-// and piece of 8 RUNS columns (64, or 32 with the narrow tile) the largest logit m and the sum of exp(logit - m) go to
-// stats[row][piece], the target's logit to target_logit[row]; a later pass puts a row's pieces together.  16 members x 4096 rows x 8192
-// logits: writing and re-reading 2.1 GB of logits cost 1161 + 388 us per
-// chunk, this 940 + 25.
-struct EpiHeadStats {
-  static constexpr bool HAS_FINISH = false;
-  static constexpr bool PREFETCH = false;
-  static constexpr bool COLSUM = false;
-  static constexpr bool HAS_COLS = true;
-  static constexpr bool HAS_RUNDATA = false;
-  static constexpr int LAYOUTS = 1;
-  struct Fetched {};
-  struct RunData {};
-  const float* bias;
-  int64_t sbias;
-  const int32_t* targets;   // [batch][M]
-  float2* stats;            // [batch][M][pieces]
-  float* target_logit;      // [batch][M]
-  int M, pieces;
-  __device__ __forceinline__ void begin(int member) {
-    bias += (int64_t)member * sbias;
-    targets += (int64_t)member * M;
-    stats += (int64_t)member * M * pieces;
-    target_logit += (int64_t)member * M;
-  }
-  __device__ __forceinline__ void load_cols(int n, int N, float* b) const {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) b[e] = n + e < N ? bias[n + e] : 0.f;
-  }
-  // every lane of the wavefront, RUNS neighbouring lanes on one row; count 0: nothing of this run lies inside C
-  template <int RUNS>
-  __device__ __forceinline__ void apply_row(int m, int n, const float* v, int count, const float* b) const {
-    float l[8], mx = -INFINITY;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      l[e] = v[e] + b[e];
-      if (e < count) mx = fmaxf(mx, l[e]);
-    }
-#pragma unroll
-    for (int off = 1; off < RUNS; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    const float base = mx == -INFINITY ? 0.f : mx;   // (a piece of nothing but -inf has the sum 0)
-    float se = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) se += e < count ? expf(l[e] - base) : 0.f;
-#pragma unroll
-    for (int off = 1; off < RUNS; off <<= 1) se += __shfl_xor(se, off, 64);
-    if (count > 0) {
-      const int y = targets[m] - n;
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (y == e && e < count) target_logit[m] = l[e];
-      if (n % (8 * RUNS) == 0) stats[(int64_t)m * pieces + n / (8 * RUNS)] = make_float2(mx, se);
-    }
-  }
-};
-
-// Forward layer: z = acc + b[n]; stores z (for the backward pass, may be null) and act(z), both bf16.
-struct EpiBiasAct {
-  static constexpr bool HAS_FINISH = false;
-  static constexpr bool PREFETCH = false;
-  static constexpr bool COLSUM = false;
-  static constexpr bool HAS_COLS = true;
-  static constexpr bool HAS_RUNDATA = false;
-  static constexpr int LAYOUTS = 1;
-  struct Fetched {};
-  struct RunData {};
-  const float* bias;  // + member * sbias + n
-  int64_t sbias;
-  bf16_t* Z;
-  bf16_t* Aout;
-  int64_t ld, so;
-  int act;
-  __device__ __forceinline__ void begin(int member) {
-    bias += (int64_t)member * sbias;
-    if (Z) Z += (int64_t)member * so;
-    Aout += (int64_t)member * so;
-  }
-  // the eight biases of the lane's columns (the same for every run the lane handles), zero past N
-  __device__ __forceinline__ void load_cols(int n, int N, float* b) const {
-    if (n + 8 <= N && aligned16(bias + n)) {
-      const float4 lo = *reinterpret_cast<const float4*>(bias + n), hi = *reinterpret_cast<const float4*>(bias + n + 4);
-      b[0] = lo.x; b[1] = lo.y; b[2] = lo.z; b[3] = lo.w; b[4] = hi.x; b[5] = hi.y; b[6] = hi.z; b[7] = hi.w;
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) b[e] = n + e < N ? bias[n + e] : 0.f;
-    }
-  }
-  __device__ __forceinline__ void apply8(int, int m, int n, const float* v, int count, const float* b) const {
-    float z[8], a[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) z[e] = e < count ? v[e] + b[e] : 0.f;
-    act_fwd8(z, a, act);
-    const int64_t o = (int64_t)m * ld + n;
-    if (Z) store_bf16_run(Z + o, z, count);
-    store_bf16_run(Aout + o, a, count);
-  }
-};
-
-// Forward layer followed by a dropout site: the stored activation is act(acc + b[n]), rounded, times the keep factor
-// of its element (Philox block (m ld + n) / 4 of the site, as the stand-alone dropout kernel draws it), rounded
-// again; the keep bits go to the site's record (bit e % 8 of byte e / 8 of the member's [rows][ld] array).  N and ld
-// are multiples of 8.  (A functor of its own: inside EpiBiasAct the extra state cost the 256x256 kernel its
-// registers, 156 -> 860 us per launch.)
-struct EpiBiasActDrop {
-  static constexpr bool HAS_FINISH = false;
-  static constexpr bool PREFETCH = false;
-  static constexpr bool COLSUM = false;
-  static constexpr bool HAS_COLS = true;
-  static constexpr bool HAS_RUNDATA = false;
-  static constexpr int LAYOUTS = 1;
-  struct Fetched {};
-  struct RunData {};
-  const float* bias;
-  int64_t sbias;
-  bf16_t* Aout;
-  int64_t ld, so;
-  int act;
-  uint8_t* rec;
-  int64_t rec_stride;   // bytes of record per member
-  DropArgs drop;
-  int site;
-  int member_ = 0;
-  DropRate rate = {0u, 1.f};
-  __device__ __forceinline__ void begin(int member) {
-    bias += (int64_t)member * sbias;
-    Aout += (int64_t)member * so;
-    rec += (int64_t)member * rec_stride;
-    rate = drop_rate(drop.H, drop.n_hyper, drop.col, member, drop.active);
-    member_ = member;
-  }
-  __device__ __forceinline__ void load_cols(int n, int N, float* b) const {
-    const float4 lo = *reinterpret_cast<const float4*>(bias + n), hi = *reinterpret_cast<const float4*>(bias + n + 4);
-    b[0] = lo.x; b[1] = lo.y; b[2] = lo.z; b[3] = lo.w; b[4] = hi.x; b[5] = hi.y; b[6] = hi.z; b[7] = hi.w;
-  }
-  __device__ __forceinline__ void apply8(int, int m, int n, const float* v, int, const float* b) const {
-    float z[8], a[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) z[e] = v[e] + b[e];
-    act_fwd8(z, a, act);
-    const int64_t o = (int64_t)m * ld + n;
-    const uint32_t b0 = drop_bits4(drop, rate, member_, site, (uint32_t)(o >> 2)), b1 = drop_bits4(drop, rate, member_, site, (uint32_t)(o >> 2) + 1u);
-    const uint32_t bits = b0 | (b1 << 4);
-    bf16_t out[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) out[e] = (bits >> e) & 1u ? bf16_times_float(f2bf(a[e]), rate.scale) : (bf16_t)(f2bf(a[e]) & 0x8000u);
-    *reinterpret_cast<uint4*>(Aout + o) = make_uint4(out[0] | ((uint32_t)out[1] << 16), out[2] | ((uint32_t)out[3] << 16),
-                                                     out[4] | ((uint32_t)out[5] << 16), out[6] | ((uint32_t)out[7] << 16));
-    rec[o >> 3] = (uint8_t)bits;
-  }
-};
-
-// Input gradient: dz_prev = acc * act'(z_prev), bf16.  With a dropout record (mask != null) the result is then
-// multiplied by the keep factor of the site that followed the activation in the forward pass: the value is
-// rounded to bf16, multiplied by 0 or by the member's scale (the float nearest 1 / (1 - p), p from column col
-// of H) in double, and rounded once more.  The record holds one bit per element of the member's [rows][ld]
-// array (bit e % 8 of byte e / 8), as the forward pass of that site left it.
-struct EpiDgradAct {
-  static constexpr bool HAS_FINISH = false;
-  static constexpr bool PREFETCH = false;
-  static constexpr bool COLSUM = false;
-  static constexpr bool HAS_COLS = false;
-  static constexpr bool HAS_RUNDATA = true;
-  static constexpr int LAYOUTS = 3;
-  struct Fetched {};
-  struct RunData { uint4 z = {0u, 0u, 0u, 0u}; uint32_t bits = 0u; };
-  const bf16_t* Zprev;
-  bf16_t* dZ;
-  int64_t ld, so;
-  int act;
-  const uint8_t* mask = nullptr;
-  int64_t mask_stride = 0;       // bytes of record per member
-  const float* H = nullptr;
-  int n_hyper = 0, col = -1;
-  float scale = 1.f;
-  __device__ __forceinline__ void begin(int member) {
-    Zprev += (int64_t)member * so; dZ += (int64_t)member * so;
-    if (mask) {
-      mask += (int64_t)member * mask_stride;
-      const float p = col >= 0 ? H[(int64_t)member * n_hyper + col] : 0.f;
-      scale = p > 0.f ? (float)(1.0 / (1.0 - (double)p)) : 1.f;
-    }
-  }
-  // the run of z the result is scaled by (and the run's eight record bits): requested for all runs of a strip
-  // before the first is applied (read inside apply8, after the store of the run before, every run paid a memory
-  // latency of its own)
-  __device__ __forceinline__ RunData load_run(int m, int n, int count) const {
-    const int64_t o = (int64_t)m * ld + n;
-    RunData r;
-    r.bits = mask ? mask[o >> 3] : 0u;   // (the launcher only attaches a record to arrays whose rows are whole runs of eight)
-    if (count == 8 && aligned16(Zprev + o)) { r.z = *reinterpret_cast<const uint4*>(Zprev + o); return r; }
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-      if (e < count) w[e >> 1] |= (uint32_t)Zprev[o + e] << (16 * (e & 1));
-    r.z = make_uint4(w[0], w[1], w[2], w[3]);
-    return r;
-  }
-  __device__ __forceinline__ void apply8(int, int m, int n, const float* v, int count, const RunData& run) const {
-    const int64_t o = (int64_t)m * ld + n;
-    float z[8], d[8];
-    unpack_bf16x8(run.z, z);
-    act_bwd_scale8(v, z, d, act);
-    if (mask) {
-      bf16_t out[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) out[e] = (run.bits >> e) & 1u ? bf16_times_float(f2bf(d[e]), scale) : (bf16_t)(f2bf(d[e]) & 0x8000u);  // x * 0 keeps the sign
-      *reinterpret_cast<uint4*>(dZ + o) = make_uint4(out[0] | ((uint32_t)out[1] << 16), out[2] | ((uint32_t)out[3] << 16),
-                                                     out[4] | ((uint32_t)out[5] << 16), out[6] | ((uint32_t)out[7] << 16));
-      return;
-    }
-    store_bf16_run(dZ + o, d, count);
-  }
-};
 
 // Weight gradient with the optimiser applied in place: v = dW[m][n .. n+3] never goes to memory;
 // the run of theta, its optimiser state and the bf16 shadow is read, updated and written back
@@ -792,14 +371,10 @@ struct EpiDgradAct {
 // parameter and step).  The layer's input-gradient GEMM must already have read the bf16 shadow.
 template <int OPT>
 struct EpiOptimizer {
-  static constexpr bool HAS_FINISH = false;
   static constexpr bool PREFETCH = true;
   static constexpr bool COLSUM = true;
-  static constexpr bool HAS_COLS = false;
-  static constexpr bool HAS_RUNDATA = false;
   static constexpr int LAYOUTS = 4;
   struct Fetched { float w[4], s0[4], s1[4]; };  // one run of theta and its state, read ahead of use
-  struct RunData {};
   float* W32; float* S0; float* S1; bf16_t* W16;
   int64_t stride, off, ldc;   // member stride, offset of the matrix in the member's vector, row pitch
   OptHyper hy;
@@ -857,16 +432,6 @@ struct EpiOptimizer {
 // a tile's fixed cost (first loads, epilogue) is no longer hidden by other workgroups on the compute
 // unit, so short contractions stay with 128x128.
 enum GemmTile { TILE_128x64 = 0, TILE_128x128, TILE_256x256, TILE_64x64 };
-struct TileShape { int bm, bn; };
-inline TileShape tile_shape(GemmTile t) {
-  switch (t) {
-    case TILE_64x64: return {64, 64};
-    case TILE_128x64: return {128, 64};
-    case TILE_256x256: return {256, 256};
-    default: return {128, 128};
-  }
-}
-inline int64_t tile_count(int M, int N, int batch, int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * batch; }
 inline GemmTile choose_tile(int M, int N, int K, int batch) {
   constexpr int CUS = 256;
   // (three quarters of the compute units busy with 256x256 tiles still beat all of them on smaller ones)
@@ -906,8 +471,7 @@ hipError_t launch_gemm_tile(const GemmArgs& g0, bool a_m_contig, bool b_k_contig
   GemmArgs g = g0;
   g.tiles_m = (g.M + BM - 1) / BM;
   g.tiles_n = (g.N + BN - 1) / BN;
-  if (g.upper && (!std::is_same_v<Epilogue, EpiRbfSum> || g.M != g.N)) return hipErrorInvalidValue;
-  g.tiles = g.upper ? upper_tiles<BM, BN>(g.tiles_m, g.tiles_n) : g.tiles_m * g.tiles_n;
+  g.tiles = g.tiles_m * g.tiles_n;
   const int64_t total = (int64_t)g.tiles * g.batch;
   if (total <= 0 || total > 0x7fffffff) return hipErrorInvalidValue;
   // operand layouts as bits of Epilogue::LAYOUTS: 1 both row-major, 2 B K-contiguous, 4 A M-contiguous, 8 both (only those a caller uses
@@ -920,74 +484,11 @@ hipError_t launch_gemm_tile(const GemmArgs& g0, bool a_m_contig, bool b_k_contig
   return hipErrorInvalidValue;
 }
 
-// Sum over the tile of exp(-(|a_m|^2 + |b_n|^2 - 2 a_m.b_n) / (2 d)): the RBF kernel of the MMD
-// score evaluated on the Gram tile while it is still in the accumulators.  Every thread adds its
-// elements in a fixed order, the wavefront and then the wavefronts are combined in a fixed
-// order, and the tile's sum goes to partial[member][tile]; a later pass adds the tiles.
-// Of a symmetric product (a = b) only the tiles at and right of the diagonal are computed: an element right of the diagonal counts
-// twice, one left of it (inside a tile on the diagonal) not at all.  32 members of 2048 x 784: 397 us as all 256 tiles, 205 as
-// the 136 that reach the diagonal.
-struct EpiRbfSum {
-  static constexpr bool HAS_FINISH = true;
-  static constexpr bool PREFETCH = false;
-  static constexpr bool COLSUM = false;
-  static constexpr bool HAS_COLS = true;
-  static constexpr bool HAS_RUNDATA = false;
-  static constexpr int LAYOUTS = 2;
-  struct Fetched {};
-  struct RunData {};
-  __device__ __forceinline__ void begin(int member) { na += (int64_t)member * sna; nb += (int64_t)member * snb; }
-  const float* na;  // squared norms of the A rows, + member * sna
-  int64_t sna;
-  const float* nb;
-  int64_t snb;
-  float inv2d;
-  float* partial;
-  float sum;
-  int region;         // 0: every element once, 1: tile on the diagonal of a symmetric product, 2: right of it
-  __device__ __forceinline__ void load_cols(int n, int N, float* b) const {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) b[e] = n + e < N ? nb[n + e] : 0.f;
-  }
-  __device__ __forceinline__ void apply8(int, int m, int n, const float* v, int count, const float* b) {
-    const float nam = na[m];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float k = expf(-(nam + b[e] - 2.f * v[e]) * inv2d);
-      const float weight = region == 0 ? 1.f : region == 2 || n + e > m ? 2.f : n + e == m ? 1.f : 0.f;
-      if (e < count && weight != 0.f) sum = fmaf(weight, k, sum);
-    }
-  }
-  __device__ __forceinline__ void finish(int member, int tile, int tiles) {
-    __shared__ float wsum[8];
-    const float w = wave_sum(sum);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = w;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      float t = wsum[0];
-      for (unsigned k = 1; k < blockDim.x / 64; ++k) t += wsum[k];
-      partial[(int64_t)member * tiles + tile] = t;
-    }
-  }
-};
-
 // Host-side launcher.  Caller guarantees 16-byte alignment of pitches / strides / bases.
 template <class Epilogue>
-hipError_t launch_gemm_bf16(const bf16_t* A, int64_t lda, int64_t sa, bool a_m_contig, const bf16_t* B, int64_t ldb,
-                            int64_t sb, bool b_k_contig, int M, int N, int K, int batch, const Epilogue& epi,
-                            hipStream_t stream, int inner = 1, int64_t sa_in = 0, int64_t sb_in = 0, float* colsum = nullptr,
-                            int64_t colsum_stride = 0, int colsum_k = -1, int b_cols = 0, int upper = 0) {
-  GemmArgs g;
-  g.upper = upper;
-  g.A = A; g.lda = lda; g.sa = sa;
-  g.B = B; g.ldb = ldb; g.sb = sb;
-  g.M = M; g.N = N; g.K = K; g.batch = batch;
-  g.tiles_m = g.tiles_n = 0;
-  g.inner = inner < 1 ? 1 : inner; g.sa_in = sa_in; g.sb_in = sb_in;
-  g.colsum = colsum; g.colsum_stride = colsum_stride; g.colsum_k = colsum_k < 0 ? K : colsum_k;
-  g.b_cols = b_cols > N ? b_cols : N;
-  switch (choose_tile(M, N, K, batch)) {
+hipError_t launch_gemm_bf16(const GemmArgs& g, bool a_m_contig, bool b_k_contig, const Epilogue& epi, hipStream_t stream) {
+  if constexpr (!Epilogue::PREFETCH) return launch_gemm_tile<64, 64, 64, 2, 2, false, Epilogue>(g, a_m_contig, b_k_contig, epi, stream);
+  else switch (choose_tile(g.M, g.N, g.K, g.batch)) {
     case TILE_256x256: return launch_gemm_tile<256, 256, 64, 2, 4, true, Epilogue>(g, a_m_contig, b_k_contig, epi, stream);
     case TILE_64x64: return launch_gemm_tile<64, 64, 64, 2, 2, false, Epilogue>(g, a_m_contig, b_k_contig, epi, stream);
     case TILE_128x64: return launch_gemm_tile<128, 64, 64, 2, 2, false, Epilogue>(g, a_m_contig, b_k_contig, epi, stream);

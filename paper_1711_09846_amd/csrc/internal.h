@@ -9,7 +9,7 @@ namespace pbt {
 
 typedef uint16_t bf16_t;
 
-// ---- gemm.hip: population-batched bf16 MFMA GEMM with fused epilogues ------------------------
+// ---- gemm_*.hip: population-batched bf16 MFMA GEMM with fused epilogues ------------------------
 struct GemmOperands {
   const bf16_t* A; int64_t lda, sa; bool a_m_contig;
   const bf16_t* B; int64_t ldb, sb; bool b_k_contig;

@@ -57,6 +57,29 @@ def test_batched_gemm(M, N, K, batch, a_m_contig, b_k_contig, out_bf16):
     assert np.max(np.abs(got[:, :, :N] - ref) / (scale + 1e-30)) <= tol
 
 
+@pytest.mark.parametrize("M,N,K,batch", [(64, 64, 8, 3), (65, 72, 63, 5), (1, 1, 1, 2), (128, 136, 33, 300),   # one element past a tile, a K inside one chunk
+                                         (512, 512, 60, 128),      # 256x256 tiles, two per workgroup, one slab that ends inside a chunk
+                                         (512, 256, 1092, 130)])   # the same with many slabs
+@pytest.mark.parametrize("a_m_contig,b_k_contig,out_bf16", [(0, 0, True), (0, 1, True), (1, 0, False), (1, 1, False)])
+def test_tile_and_slab_edges(M, N, K, batch, a_m_contig, b_k_contig, out_bf16):
+    test_batched_gemm(M, N, K, batch, a_m_contig, b_k_contig, out_bf16)
+
+
+def test_rows_longer_than_a_buffer_offset():
+    """Pitches of 2^22 and 2^24 elements: 64-row tiles, then the kernel that stages through registers."""
+    import torch
+    from paper_1711_09846_amd import binding
+    rng = np.random.default_rng(4)
+    for pitch in (1 << 22, 1 << 24):
+        A, B = _bf16_round(rng.standard_normal((70, 64))), _bf16_round(rng.standard_normal((64, 72)))
+        a = torch.zeros(70, pitch, dtype=torch.bfloat16, device="cuda")
+        a[:, :64] = A.cuda()
+        c = torch.zeros(70, 72, dtype=torch.float32, device="cuda")
+        binding.batched_gemm_bf16(a, B.cuda(), c, 70, 72, 64, 1, pitch, 0, 0, 72, 0, 0, 72, 0)
+        ref = np.matmul(A.to(torch.float64).numpy(), B.to(torch.float64).numpy())
+        assert np.max(np.abs(c.cpu().numpy() - ref)) < 1e-4
+
+
 def test_shared_operand_stride_zero():
     import torch
     from paper_1711_09846_amd import binding
