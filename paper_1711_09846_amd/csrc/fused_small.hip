@@ -219,8 +219,8 @@ __global__ __launch_bounds__(FS_THREADS) void fused_small_step_kernel(FusedSmall
 // What bounds the plain form above is LDS reads (two per multiply-add) and wavefronts that wait for each other's and the
 // data rows' latencies: 63 us per step of a 32-64-4 network with 64 rows.  Here an operand is read once per 16
 // multiply-adds, every array is padded to whole 16 x 16 blocks (so no loop has a remainder), wavefronts of their own
-// fetch the rows of step s + 1 while the others compute step s (four and eight of them, fewer in large populations: ft_size()), and phases that do not depend on each other share a
-// barrier interval: 2 L barriers per step of an L-layer network.  6.3 us per step (50 steps in one launch: 3.13 -> 0.31 ms);
+// fetch the rows of step s + 1 while the others compute step s (four and twelve of them, fewer in large populations: ft_size()), and phases that do not depend on each other share a
+// barrier interval: 2 L barriers per step of an L-layer network.  5.3 us per step (50 steps in one launch: 3.13 -> 0.27 ms);
 // what is left is instruction issue and LDS latency of the chain fragment -> MFMA -> activation -> fragment of each
 // interval.  The optimiser and the number of layers are template parameters: as branches inside the element loops they cost
 // a third of the time, and with the rows' loads in the computing wavefronts every loop waited for them.
@@ -267,43 +267,61 @@ size_t fused_tiled_plan(FusedSmallArgs& a, bool for_eval) {
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 // One 16 x 16 block of A B over k < KP (a multiple of 16: the padding is zero in at least one operand).  pa / pb point at
-// the lane's first element (row or column lane % 16, k = lane / 16); sa / sb are the steps along k.  Result: column
+// the lane's row or column (lane % 16) of the operand at k = 0; sa / sb are the steps along k (AC / BC: 1, and 16-byte aligned).  Result: column
 // lane % 16, rows 4 (lane / 16) + e.
-// colsum: sums of B's columns as a by-product.  The operands of the next 16 k are on their way while one 16 is multiplied (past the end the last ones again: loads that
-// are issued always let the compiler wait for the older ones only).
-template <bool COLSUM>
-__device__ __forceinline__ f32x4_t ft_block(const float* pa, int sa, const float* pb, int sb, int KP, f32x4_t& colsum) {
-  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-  float x[2][4], y[2][4];
-  auto fetch = [&](int q, int k) {
-    k = min(k, KP - 16);
+// The j-th MFMA of 16 k takes k = 4 (lane / 16) + j from every lane: a lane's four k are neighbours, one 16-byte read where k is contiguous, and where it is not
+// the four groups of lanes are four rows apart, which with pitches of 4 mod 16 floats are different banks (with k = lane / 16 + 4 j neighbouring rows: four
+// runs of 16 banks on top of each other).  
+// colsum: the sum of the lane's column of B.
+template <bool AC, bool BC, bool COLSUM>
+__device__ __forceinline__ f32x4_t ft_block(int fg, const float* pa, int sa, const float* pb, int sb, int KP, float& colsum) {
+  const int kg = 4 * fg;
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f}, x[2], y[2];
+  float sum = 0.f;
+  pa += kg * (AC ? 1 : sa);
+  pb += kg * (BC ? 1 : sb);
+  auto fetch = [&](int q) {
+    if constexpr (AC) x[q] = *reinterpret_cast<const f32x4_t*>(pa);
+    else
 #pragma unroll
-    for (int j = 0; j < 4; ++j) { x[q][j] = pa[(k + 4 * j) * sa]; y[q][j] = pb[(k + 4 * j) * sb]; }
+      for (int j = 0; j < 4; ++j) x[q][j] = pa[j * sa];
+    if constexpr (BC) y[q] = *reinterpret_cast<const f32x4_t*>(pb);
+    else
+#pragma unroll
+      for (int j = 0; j < 4; ++j) y[q][j] = pb[j * sb];
+    pa += 16 * (AC ? 1 : sa);
+    pb += 16 * (BC ? 1 : sb);
   };
   auto multiply = [&](int q) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[q][j], y[q][j], acc, 0, 0, 0);
-    if (COLSUM) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) colsum = __builtin_amdgcn_mfma_f32_16x16x4f32(1.f, y[q][j], colsum, 0, 0, 0);
-    }
+    if (COLSUM) sum += (y[q][0] + y[q][1]) + (y[q][2] + y[q][3]);
   };
-  fetch(0, 0);
-  for (int k = 0;;) {
-    fetch(1, k + 16);
+  // the operands of the next 16 k are on their way while one 16 is multiplied
+  fetch(0);
+  for (int left = KP >> 4;;) {
+    if (left > 1) fetch(1);
     __builtin_amdgcn_sched_barrier(0);
     multiply(0);
-    if ((k += 16) >= KP) break;
-    fetch(0, k + 16);
+    if (--left == 0) break;
+    if (left > 1) fetch(0);
     __builtin_amdgcn_sched_barrier(0);
     multiply(1);
-    if ((k += 16) >= KP) break;
+    if (--left == 0) break;
+  }
+  if (COLSUM) {   // the four groups' parts
+    const uint32_t u = __float_as_uint(sum);
+    const auto h = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    const uint32_t v = __float_as_uint(__uint_as_float(h[0]) + __uint_as_float(h[1]));
+    const auto g = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    colsum = __uint_as_float(g[0]) + __uint_as_float(g[1]);
   }
   return acc;
 }
-__device__ __forceinline__ f32x4_t ft_block(const float* pa, int sa, const float* pb, int sb, int KP) {
-  f32x4_t unused = {0.f, 0.f, 0.f, 0.f};
-  return ft_block<false>(pa, sa, pb, sb, KP, unused);
+template <bool AC, bool BC>
+__device__ __forceinline__ f32x4_t ft_block(int fg, const float* pa, int sa, const float* pb, int sb, int KP) {
+  float unused;
+  return ft_block<AC, BC, false>(fg, pa, sa, pb, sb, KP, unused);
 }
 // LDS written before is visible behind it; loads from memory stay in flight (a __syncthreads would wait for them)
 __device__ __forceinline__ void ft_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -435,33 +453,57 @@ __device__ __forceinline__ void ft_act4_bwd(float* v, int kind) {
   }
 }
 
-// Rows and labels of one step's mini-batch (Philox domain 1) into LDS, by the LOADERS wavefronts: each takes its share of
-// the rows, a lane draws the number of one row, then all lanes run over the rows' elements, eight loads at a time.
-template <int LOADERS>
-__device__ __forceinline__ void ft_load_batch(const FusedSmallArgs& a, int member, uint32_t step, float* X, int px, int* y, int loader) {
-  const int lane = threadIdx.x & 63, B = a.B, d0 = a.dims[0];
-  const int share = (B + LOADERS - 1) / LOADERS, rbeg = loader * share, rend = min(B, rbeg + share);
-  for (int r0 = rbeg; r0 < rend; r0 += 64) {
-    const int rows = min(64, rend - r0), n = rows * d0;
-    int src = 0;
-    if (lane < rows) {
-      src = (int)philox_bounded(philox4x32_10(step, (uint32_t)member, DOMAIN_BATCH, (uint32_t)(r0 + lane), (uint32_t)a.seed, (uint32_t)(a.seed >> 32)).x, (uint32_t)a.n_rows);
-      y[r0 + lane] = a.y[src];
+// Rows and labels of the steps' mini-batches (Philox domain 1) into LDS, by the LOADERS wavefronts: each takes its share of the rows, 64 at a time (a lane draws
+// the number of one row), in pieces of 512 elements.  A piece is requested one barrier interval or more before it is put into LDS: fetched and stored in
+// one go, its latency held everybody at the first barrier of a step (900 of 14900 cycles).
+struct FtLoader {
+  const FusedSmallArgs& a;
+  int member, rbeg, rend, px, lane;
+  float* lds;
+  int* ytab;
+  int yhalf;             // labels per half of the double buffer
+  int step = 0, r0, e0 = 0, src = 0, yv = 0;
+  float v[8];
+  int at[8];
+  __device__ __forceinline__ FtLoader(const FusedSmallArgs& args, int m, int loader, int loaders, float* l, int* y, int half, int pitch)
+      : a(args), member(m), px(pitch), lane(threadIdx.x & 63), lds(l), ytab(y), yhalf(half) {
+    const int share = (a.B + loaders - 1) / loaders;
+    rbeg = loader * share;
+    rend = min(a.B, rbeg + share);
+    r0 = rbeg;
+  }
+  __device__ __forceinline__ int rows() const { return min(64, rend - r0); }
+  __device__ __forceinline__ int pieces() const {   // per step
+    const int n = rend - rbeg;
+    return n <= 0 ? 0 : n / 64 * ((64 * a.dims[0] + 511) / 512) + (n % 64 * a.dims[0] + 511) / 512;
+  }
+  __device__ __forceinline__ void request() {
+    if (step >= a.n_steps) return;
+    if (e0 == 0 && lane < rows()) {
+      src = (int)philox_bounded(philox4x32_10(a.step0 + (uint32_t)step, (uint32_t)member, DOMAIN_BATCH, (uint32_t)(r0 + lane), (uint32_t)a.seed, (uint32_t)(a.seed >> 32)).x, (uint32_t)a.n_rows);
+      yv = a.y[src];
     }
-    for (int e0 = 0; e0 < n; e0 += 512) {
-      float v[8];
-      int at[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int e = min(e0 + 64 * j + lane, n - 1), r = ft_div(e, a.lt_inv_d0), c = e - r * d0;   // (past the end: the last element again)
-        at[j] = (r0 + r) * px + c;
-        v[j] = a.x[(int64_t)__shfl(src, r) * d0 + c];
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) X[at[j]] = v[j];
+    for (int j = 0; j < 8; ++j) {
+      const int e = min(e0 + 64 * j + lane, rows() * a.dims[0] - 1), r = ft_div(e, a.lt_inv_d0), c = e - r * a.dims[0];   // (past the end: the last element again)
+      at[j] = (r0 + r) * px + c;
+      v[j] = a.x[(int64_t)__shfl(src, r) * a.dims[0] + c];
     }
   }
-}
+  __device__ __forceinline__ void store() {   // and move on to the next piece
+    float* X = lds + a.lt_x[step & 1];
+    if (e0 == 0 && lane < rows()) ytab[(step & 1) * yhalf + r0 + lane] = yv;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) X[at[j]] = v[j];
+    e0 += 512;
+    if (e0 < rows() * a.dims[0]) return;
+    e0 = 0;
+    r0 += 64;
+    if (r0 < rend) return;
+    r0 = rbeg;
+    ++step;
+  }
+};
 
 // WAVES wavefronts compute and LOADERS fetch.  A block of a contraction is formed by one wavefront in the same order whatever their
 // number, so results do not depend on it.
@@ -472,7 +514,7 @@ __global__ __launch_bounds__((WAVES + LOADERS) * 64) void fused_tiled_step_kerne
   constexpr int FT_THREADS = (WAVES + LOADERS) * 64;
   extern __shared__ float lds[];
   const int i = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int fr = lane & 15, fg = lane >> 4;   // fragment row / column, group of four rows (or k offset)
+  const int fr = lane & 15, fg = lane >> 4;   // fragment row / column, group of four rows (or of four k)
   const int64_t base = (int64_t)i * a.stride;
   const int L = NL ? NL : a.n_layers, B = a.B, d0 = a.dims[0], RB = fs_pad(B) / 16, px = fs_pitch(d0);
   int* const ytab = reinterpret_cast<int*>(lds + a.lt_y);
@@ -501,64 +543,105 @@ __global__ __launch_bounds__((WAVES + LOADERS) * 64) void fused_tiled_step_kerne
   if (wave >= WAVES) {
     // the fetching wavefronts: step s + 1's rows, labels and bias corrections go into the half of the double buffers that
     // step s does not read; they meet the others at every barrier
-    for (int s = -1; s < a.n_steps; ++s) {
-      const int nxt = (s + 1) & 1;
-      if (s + 1 < a.n_steps) {
-        if (OPT == OPT_ADAM && tid - WAVES * 64 < 2)   // 1 / (1 - beta^t)
-          lds[a.lt_sc + 2 * nxt + lane] = 1.f / (1.f - powf(lane == 0 ? b1 : a.c1, (float)(t0 + s + 2)));
-        ft_load_batch<LOADERS>(a, i, a.step0 + (uint32_t)(s + 1), lds + a.lt_x[nxt], px, ytab + nxt * RB * 16, wave - WAVES);
+    FtLoader ld(a, i, wave - WAVES, LOADERS, lds, ytab, RB * 16, px);
+    const int pieces = ld.pieces(), share = (pieces + 2 * L - 1) / (2 * L);
+    auto corrections = [&](int s) {   // 1 / (1 - beta^t)
+      if (OPT == OPT_ADAM && tid - WAVES * 64 < 2 && s < a.n_steps) lds[a.lt_sc + 2 * (s & 1) + lane] = 1.f / (1.f - powf(lane == 0 ? b1 : a.c1, (float)(t0 + s + 1)));
+    };
+    corrections(0);
+    if (pieces > 0) ld.request();
+    for (int q = 0; q < pieces; ++q) {
+      ld.store();
+      ld.request();
+    }
+    __syncthreads();
+    for (int s = 0; s < a.n_steps; ++s) {
+      corrections(s + 1);
+      int left = s + 1 < a.n_steps ? pieces : 0;
+      for (int k = 0; k < 2 * L; ++k) {
+        for (int q = 0; q < share && left > 0; ++q, --left) {
+          ld.store();
+          ld.request();
+        }
+        ft_barrier();
       }
-      if (s < 0) __syncthreads();
-      else
-        for (int k = 0; k < 2 * L; ++k) ft_barrier();
     }
   } else {
-    // optimiser on n (at most 4) parameters: w[e * wp] in LDS, p + e * pp in the member's vector
-    auto update4 = [&](float* w, int wp, int p, int pp, const f32x4_t g, int n, const float* sc, bool last) {
-      float wv[4], s0[4], s1[4];
-      float* const S0 = lds + a.lt_s0 + p;
-      float* const S1 = lds + a.lt_s1 + p;
-      // (parameters past the n-th are read, inside the workgroup's LDS, and not written)
+    // A run of up to 4 parameters, w + e * wp in LDS and p + e * pp in the member's vector: theta and the optimiser's state are read before the
+    // gradient is formed.  (Parameters past the n-th are read, inside the workgroup's LDS, and not written.)
+    struct Run { float w[4], s0[4], s1[4]; };
+    auto read_run = [&](Run& r, const float* w, int wp, int p, int pp) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        wv[e] = w[e * wp];
-        s0[e] = S0[e * pp];
-        if (OPT == OPT_ADAM) s1[e] = S1[e * pp];
+        r.w[e] = w[e * wp];
+        r.s0[e] = lds[a.lt_s0 + p + e * pp];
+        if (OPT == OPT_ADAM) r.s1[e] = lds[a.lt_s1 + p + e * pp];
       }
+    };
+    // (the fused multiply-adds are written out: the sizes of workgroups must round alike)
+    auto update = [&](float& w, float& s0, float& s1, float g, float bc1, float bc2) {
+      if (OPT == OPT_SGD_MOMENTUM) {
+        s0 = fmaf(a.c0, s0, g);
+        w = fmaf(-lr, s0, w);
+      } else if (OPT == OPT_ADAM) {
+        s0 = fmaf(b1, s0, (1.f - b1) * g);
+        s1 = fmaf(a.c1, s1, (1.f - a.c1) * g * g);
+        w = fmaf(-lr, fmaf(wd, w, (s0 * bc1) / (sqrtf(s1 * bc2) + a.c2)), w);
+      } else {
+        s0 = fmaf(a.c0, s0, (1.f - a.c0) * g * g);
+        w = w - lr * g / sqrtf(s0 + a.c1);
+      }
+    };
+    auto write_run = [&](Run& r, float* w, int wp, int p, int pp, const f32x4_t g, int n, const float* sc, bool last) {
       const float bc1 = OPT == OPT_ADAM ? sc[0] : 1.f, bc2 = OPT == OPT_ADAM ? sc[1] : 1.f;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (OPT == OPT_SGD_MOMENTUM) {
-          s0[e] = a.c0 * s0[e] + g[e];
-          wv[e] = wv[e] - lr * s0[e];
-        } else if (OPT == OPT_ADAM) {
-          s0[e] = b1 * s0[e] + (1.f - b1) * g[e];
-          s1[e] = a.c1 * s1[e] + (1.f - a.c1) * g[e] * g[e];
-          wv[e] = wv[e] - lr * ((s0[e] * bc1) / (sqrtf(s1[e] * bc2) + a.c2) + wd * wv[e]);
-        } else {
-          s0[e] = a.c0 * s0[e] + (1.f - a.c0) * g[e] * g[e];
-          wv[e] = wv[e] - lr * g[e] / sqrtf(s0[e] + a.c1);
-        }
-      }
+      for (int e = 0; e < 4; ++e) update(r.w[e], r.s0[e], r.s1[e], g[e], bc1, bc2);
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         if (e < n) {
-          w[e * wp] = wv[e];
-          S0[e * pp] = s0[e];
-          if (OPT == OPT_ADAM) S1[e * pp] = s1[e];
-          if (last) a.G[base + p + e * pp] = g[e];
+          w[e * wp] = r.w[e];
+          lds[a.lt_s0 + p + e * pp] = r.s0[e];
+          if (OPT == OPT_ADAM) lds[a.lt_s1 + p + e * pp] = r.s1[e];
         }
+      if (last)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (e < n) a.G[base + p + e * pp] = g[e];
     };
     // gradient and update of a 16 x 16 block of W_l; the blocks of the first block row also form the bias gradient of their
-    // columns (column sums of dz: a product with ones, from the operands that are there anyway)
+    // columns (column sums of dz, from the operands that are there anyway)
     auto weight_unit = [&](int l, int kb, int nb, const float* in, int pin, const float* sc, bool last) {
       const int K = a.dims[l], N = a.dims[l + 1], pn = fs_pitch(N), n = nb * 16 + fr, k = kb * 16 + 4 * fg;
-      f32x4_t bsum = {0.f, 0.f, 0.f, 0.f};
-      const float* const pa = in + fg * pin + kb * 16 + fr;
-      const float* const pb = lds + a.lt_d[l] + fg * pn + n;
-      const f32x4_t acc = kb == 0 ? ft_block<true>(pa, pin, pb, pn, RB * 16, bsum) : ft_block(pa, pin, pb, pn, RB * 16);
-      if (k < K && n < N) update4(lds + a.lt_w[l] + k * pn + n, pn, a.w_off[l] + k * N + n, N, acc, K - k, sc, last);
-      if (kb == 0 && fg == 0 && n < N) update4(lds + a.lt_b[l] + n, 0, a.b_off[l] + n, 0, bsum, 1, sc, last);
+      const bool inside = k < K && n < N, bias = kb == 0 && fg == 0 && n < N;
+      float* const w = lds + a.lt_w[l] + k * pn + n;
+      const int p = a.w_off[l] + k * N + n;
+      Run r;
+      float bw = 0.f, bs0 = 0.f, bs1 = 0.f, bsum = 0.f;
+      // (ahead of the product, whose time hides their latency; where several members share a compute unit the registers are worth more)
+      constexpr bool AHEAD = WAVES > 8;
+      if (AHEAD && inside) read_run(r, w, pn, p, N);
+      if (AHEAD && bias) {
+        bw = lds[a.lt_b[l] + n];
+        bs0 = lds[a.lt_s0 + a.b_off[l] + n];
+        if (OPT == OPT_ADAM) bs1 = lds[a.lt_s1 + a.b_off[l] + n];
+      }
+      const float* const pa = in + kb * 16 + fr;
+      const float* const pb = lds + a.lt_d[l] + n;
+      const f32x4_t acc = kb == 0 ? ft_block<false, false, true>(fg, pa, pin, pb, pn, RB * 16, bsum) : ft_block<false, false>(fg, pa, pin, pb, pn, RB * 16);
+      if (!AHEAD && inside) read_run(r, w, pn, p, N);
+      if (inside) write_run(r, w, pn, p, N, acc, K - k, sc, last);
+      if (bias) {
+        if (!AHEAD) {
+          bw = lds[a.lt_b[l] + n];
+          bs0 = lds[a.lt_s0 + a.b_off[l] + n];
+          if (OPT == OPT_ADAM) bs1 = lds[a.lt_s1 + a.b_off[l] + n];
+        }
+        update(bw, bs0, bs1, bsum, OPT == OPT_ADAM ? sc[0] : 1.f, OPT == OPT_ADAM ? sc[1] : 1.f);
+        lds[a.lt_b[l] + n] = bw;
+        lds[a.lt_s0 + a.b_off[l] + n] = bs0;
+        if (OPT == OPT_ADAM) lds[a.lt_s1 + a.b_off[l] + n] = bs1;
+        if (last) a.G[base + a.b_off[l] + n] = bsum;
+      }
     };
     __syncthreads();
     for (int s = 0; s < a.n_steps; ++s) {
@@ -575,7 +658,7 @@ __global__ __launch_bounds__((WAVES + LOADERS) * 64) void fused_tiled_step_kerne
           for (w.start(wave, RB); w.col < NB; w.next()) {
             const int n = w.col * 16 + fr, o = (w.row * 16 + 4 * fg) * pn + n;
             const float bias = lds[a.lt_b[l] + n];
-            const f32x4_t acc = ft_block(in + (w.row * 16 + fr) * pk + fg, 1, lds + a.lt_w[l] + fg * pn + n, pn, KP);
+            const f32x4_t acc = ft_block<true, false>(fg, in + (w.row * 16 + fr) * pk, 1, lds + a.lt_w[l] + n, pn, KP);
             float v[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = acc[e] + bias;
@@ -592,7 +675,7 @@ __global__ __launch_bounds__((WAVES + LOADERS) * 64) void fused_tiled_step_kerne
             for (int nb = 0; nb < NB; ++nb) {
               const int n = nb * 16 + fr, o = (rb * 16 + 4 * fg) * pn + n;
               const float bias = lds[a.lt_b[l] + n];
-              const f32x4_t acc = ft_block(in + (rb * 16 + fr) * pk + fg, 1, lds + a.lt_w[l] + fg * pn + n, pn, KP);
+              const f32x4_t acc = ft_block<true, false>(fg, in + (rb * 16 + fr) * pk, 1, lds + a.lt_w[l] + n, pn, KP);
 #pragma unroll
               for (int e = 0; e < 4; ++e) lds[a.lt_d[l] + o + e * pn] = acc[e] + bias;
             }
@@ -620,7 +703,7 @@ __global__ __launch_bounds__((WAVES + LOADERS) * 64) void fused_tiled_step_kerne
             float v[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = from[e * pk];
-            const f32x4_t acc = ft_block(lds + a.lt_d[l] + (w.row * 16 + fr) * pn + fg, 1, lds + a.lt_w[l] + (w.col * 16 + fr) * pn + fg, 1, fs_pad(N));
+            const f32x4_t acc = ft_block<true, true>(fg, lds + a.lt_d[l] + (w.row * 16 + fr) * pn, 1, lds + a.lt_w[l] + (w.col * 16 + fr) * pn, 1, fs_pad(N));
             ft_act4_bwd(v, a.act);
 #pragma unroll
             for (int e = 0; e < 4; ++e) d[e * pk] = acc[e] * v[e];
@@ -660,9 +743,11 @@ __global__ __launch_bounds__((WAVES + LOADERS) * 64) void fused_tiled_step_kerne
   }
 }
 
-// The three sizes of the step's workgroup.  Eight and four wavefronts are fastest for a member by itself, but a compute unit holds one or
-// two of them (registers); populations of more members than that take four and two, or three and one, of which it holds two and four.
-constexpr struct { int waves, loaders; } FT_SIZES[3] = {{8, 4}, {4, 2}, {3, 1}};
+// The sizes of the step's workgroup.  Twelve and four wavefronts are fastest for a member by itself (32-64-4, 64 rows: 5.5 us per step, 5.9 with eight and
+// four), but a compute unit holds one of them; populations of more members than that take eight and four, of which it holds one or two (registers), four and
+// two, or three and one, of which it holds two and four.
+constexpr int FT_N_SIZES = 4;
+constexpr struct { int waves, loaders; } FT_SIZES[FT_N_SIZES] = {{12, 4}, {8, 4}, {4, 2}, {3, 1}};
 template <int OPT, int SIZE>
 static void (*ft_step_kernel(int n_layers))(FusedSmallArgs) {
   constexpr int W = FT_SIZES[SIZE].waves, LD = FT_SIZES[SIZE].loaders;
@@ -670,7 +755,7 @@ static void (*ft_step_kernel(int n_layers))(FusedSmallArgs) {
 }
 template <int OPT>
 static void (*ft_step_kernel(int n_layers, int size))(FusedSmallArgs) {
-  return size == 0 ? ft_step_kernel<OPT, 0>(n_layers) : size == 1 ? ft_step_kernel<OPT, 1>(n_layers) : ft_step_kernel<OPT, 2>(n_layers);
+  return size == 0 ? ft_step_kernel<OPT, 0>(n_layers) : size == 1 ? ft_step_kernel<OPT, 1>(n_layers) : size == 2 ? ft_step_kernel<OPT, 2>(n_layers) : ft_step_kernel<OPT, 3>(n_layers);
 }
 static void (*ft_step_kernel(int optimizer, int n_layers, int size))(FusedSmallArgs) {
   return optimizer == OPT_SGD_MOMENTUM ? ft_step_kernel<OPT_SGD_MOMENTUM>(n_layers, size)
@@ -709,7 +794,7 @@ __global__ __launch_bounds__(256) void fused_tiled_eval_kernel(FusedSmallArgs a,
     float* out = lds + a.lt_a[(l + 1) & 1] + wave * 16 * p;
     for (int nb = 0; nb < NB; ++nb) {
       const int n = nb * 16 + fr;
-      const f32x4_t acc = ft_block(in + fr * p + fg, 1, lds + a.lt_w[l] + fg * pn + n, pn, KP);
+      const f32x4_t acc = ft_block<true, false>(fg, in + fr * p, 1, lds + a.lt_w[l] + n, pn, KP);
       const float bias = lds[a.lt_b[l] + n];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -754,13 +839,12 @@ static bool fs_plain_is_faster(const FusedSmallArgs& a, size_t tiled, size_t pla
   return a.n_layers > 3 && widest <= 8 && a.B <= (fewer_rounds ? 32 : 4);
 }
 
-// The size that fills the compute units the fewest times, the larger of two that are equal.  20 steps a call, us per step of the largest
-// size only, now, and in the plain form: 1024 members 4-8-2, Adam, 16 rows: 17.6, 5.1, 10.0; 512 members 8-8-8-2, momentum, 16 rows: 9.8, 5.2,
+// The size that fills the compute units the fewest times, the larger of two that are equal.  20 steps a call, us per step of eight and four wavefronts
+// only, with the smaller sizes, and in the plain form: 1024 members 4-8-2, Adam, 16 rows: 17.6, 5.1, 10.0; 512 members 8-8-8-2, momentum, 16 rows: 9.8, 5.2,
 // 9.8; 1024 members 32-64-4, Adam, 16 rows: 22.9, 15.8, 48.1.  The smallest only where no phase of a step has more than eight 16 x 16
 // blocks: with more its three wavefronts become the bound (768 members 32-64-4, 32 rows: 11.4 us in two rounds of the largest, 15.6 in one
 // of the smallest), and with a mini-batch of more than 2048 values the one that fetches (768 members 64-10, 64 rows: 8.2 and 9.8).
 static int ft_size(const FusedSmallArgs& a, size_t tiled) {
-  if (a.P <= FS_CUS) return 0;
   const int RB = fs_pad(a.B) / 16;
   auto blocks = [&](int l) { return fs_pad(a.dims[l]) / 16; };
   int most = 0;
@@ -768,16 +852,24 @@ static int ft_size(const FusedSmallArgs& a, size_t tiled) {
     most = std::max(most, l + 1 < a.n_layers ? RB * blocks(l + 1) : RB);
     most = std::max(most, (l > 0 ? RB * blocks(l) : blocks(0) * blocks(1)) + (l + 1 < a.n_layers ? blocks(l + 1) * blocks(l + 2) : 0));
   }
-  int held = 1;   // workgroups of the largest size that a compute unit's registers hold
-  const auto largest = ft_step_kernel(a.optimizer, a.n_layers, 0);
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&held, reinterpret_cast<const void*>(largest), (FT_SIZES[0].waves + FT_SIZES[0].loaders) * 64, 0) != hipSuccess) {
-    (void)hipGetLastError();
-    held = 1;
-  }
-  const int rounds[3] = {fs_rounds(a.P, tiled, held), fs_rounds(a.P, tiled, 2), fs_rounds(a.P, tiled, 4)};
-  int size = 0;
+  // (more than eight wavefronts have nothing to do where no phase has more than eight blocks, and cost a launch of one step up to 9 %)
+  const int largest = most > 8 ? 0 : 1;
+  if (a.P <= FS_CUS) return largest;
+  // workgroups of a size that a compute unit's registers hold
+  auto held = [&](int size) {
+    int n = 1;
+    const auto kernel = ft_step_kernel(a.optimizer, a.n_layers, size);
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void*>(kernel), (FT_SIZES[size].waves + FT_SIZES[size].loaders) * 64, 0) != hipSuccess) {
+      (void)hipGetLastError();
+      n = 1;
+    }
+    return n;
+  };
+  const int rounds[FT_N_SIZES] = {fs_rounds(a.P, tiled, 1), fs_rounds(a.P, tiled, held(1)), fs_rounds(a.P, tiled, 2), fs_rounds(a.P, tiled, 4)};
+  int size = largest;
   if (rounds[1] < rounds[size]) size = 1;
-  if (rounds[2] < rounds[size] && most <= 8 && a.B * a.dims[0] <= 2048) size = 2;
+  if (rounds[2] < rounds[size]) size = 2;
+  if (rounds[3] < rounds[size] && most <= 8 && a.B * a.dims[0] <= 2048) size = 3;
   return size;
 }
 
