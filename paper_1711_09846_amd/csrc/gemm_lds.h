@@ -149,6 +149,14 @@ struct GlTile {
   static constexpr bool PERSISTENT = PERSISTENT_;
   static constexpr int WAVES = WM * WN, THREADS = WAVES * 64;
   static constexpr int LDS_BYTES = (BM * NA + BN * NB) * BK * 2;
+  static constexpr int STRIP_BYTES = WAVES * 32 * (BN / WN) * 4;   // the epilogue's strips
+  // what a launch over K needs
+  static int lds_bytes(int K) {
+    const int slabs = (K + BK - 1) / BK;
+    if (PERSISTENT || NA != NB || slabs >= NA) return LDS_BYTES;
+    const int bytes = slabs * (BM + BN) * BK * 2;
+    return bytes > STRIP_BYTES ? bytes : STRIP_BYTES;
+  }
   static constexpr int PER_CU = PERSISTENT ? 1 : (160 * 1024) / LDS_BYTES;   // workgroups per compute unit that LDS admits
   static constexpr int WAVES_PER_SIMD = PER_CU * WAVES / 4 < 1 ? 1 : PER_CU * WAVES / 4 > 4 ? 4 : PER_CU * WAVES / 4;
   static_assert(NA == NB || NA == NB + 1, "the wait counts below are written for these");
@@ -169,7 +177,9 @@ __global__ __launch_bounds__(T::THREADS, T::WAVES_PER_SIMD) void gemm_lds_kernel
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
   lds_bf16_t* const lds = (lds_bf16_t*)smem;
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
-  constexpr uint32_t B_RING = NA * SideA::SLOT;   // byte offset of the B ring
+  // Rings of equal depth lie slab by slab (a launch with fewer slabs than slots needs only theirs), otherwise B's behind A's.
+  constexpr uint32_t A_STEP = SideA::SLOT + (NA == NB ? SideB::SLOT : 0), A_END = NA * A_STEP;
+  constexpr uint32_t B_BASE = NA == NB ? SideA::SLOT : A_END, B_STEP = SideB::SLOT + (NA == NB ? SideA::SLOT : 0), B_END = B_BASE + NB * B_STEP;
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WN, wn = wave % WN;
@@ -214,7 +224,7 @@ __global__ __launch_bounds__(T::THREADS, T::WAVES_PER_SIMD) void gemm_lds_kernel
   SideA la;
   SideB lb;
   int ta = t, ka = 0, tb = t, kb = 0;
-  uint32_t slot_a = 0, slot_b = B_RING;
+  uint32_t slot_a = 0, slot_b = B_BASE;
   auto set_a = [&]() {
     int member, tile, m0, n0;
     locate(ta, member, tile, m0, n0);
@@ -225,12 +235,14 @@ __global__ __launch_bounds__(T::THREADS, T::WAVES_PER_SIMD) void gemm_lds_kernel
     locate(tb, member, tile, m0, n0);
     lb.set_tile(g.B + (int64_t)(member / g.inner) * g.sb + (int64_t)(member % g.inner) * g.sb_in, g.ldb, n0, B_KC ? g.N : g.b_cols, K, wave, lane);
   };
+  auto after_a = [](uint32_t slot) { return slot + A_STEP == A_END ? 0u : slot + A_STEP; };
+  auto after_b = [](uint32_t slot) { return slot + B_STEP == B_END ? B_BASE : slot + B_STEP; };
   // load j of the next slab (the last one moves on); nothing when the work is done
   auto issue_a = [&](int j) {
     if (ta >= t_end) return;
     la.issue(lds0 + slot_a, ka, K, wave, j);
     if (j + 1 < SideA::LOADS) return;
-    slot_a = slot_a + SideA::SLOT == B_RING ? 0u : slot_a + SideA::SLOT;
+    slot_a = after_a(slot_a);
     ka += BK;
     if (ka >= K) {
       ka = 0;
@@ -242,7 +254,7 @@ __global__ __launch_bounds__(T::THREADS, T::WAVES_PER_SIMD) void gemm_lds_kernel
     if (tb >= t_end) return;
     lb.issue(lds0 + slot_b, kb, K, wave, j);
     if (j + 1 < SideB::LOADS) return;
-    slot_b = slot_b + SideB::SLOT == B_RING + NB * SideB::SLOT ? B_RING : slot_b + SideB::SLOT;
+    slot_b = after_b(slot_b);
     kb += BK;
     if (kb >= K) {
       kb = 0;
@@ -263,15 +275,13 @@ __global__ __launch_bounds__(T::THREADS, T::WAVES_PER_SIMD) void gemm_lds_kernel
   GlFrag<BN, BK, B_KC, TN> frb;
   fra.init(wm * (BM / WM), lane);
   frb.init(wn * (BN / WN), lane);
-  uint32_t ra = 0, rb = B_RING;   // slots that are being read
+  uint32_t ra = 0, rb = B_BASE;   // slots that are being read
   bf16x8_t fa[2][TM], fb[2][TN];
   auto read_step = [&](int st) {
     fra.read(fa[st & 1], lds, ra, st);
     frb.read(fb[st & 1], lds, rb, st);
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto after_a = [](uint32_t slot) { return slot + SideA::SLOT == B_RING ? 0u : slot + SideA::SLOT; };
-  auto after_b = [](uint32_t slot) { return slot + SideB::SLOT == B_RING + NB * SideB::SLOT ? B_RING : slot + SideB::SLOT; };
   auto next_slots = [&]() {
     ra = after_a(ra);
     rb = after_b(rb);
@@ -538,34 +548,38 @@ __global__ __launch_bounds__(T::THREADS, T::WAVES_PER_SIMD) void gemm_lds_kernel
 }
 
 // Tile shapes.  256x256: eight wavefronts, one persistent workgroup per compute unit with 160 KB of LDS; its epilogue has the compute unit to itself.  128x128
-// and 64x64: four wavefronts, three workgroups per compute unit, one's epilogue beside the others' products.
+// and 64x64: four wavefronts, three workgroups per compute unit (128x64: two), one's epilogue beside the others' products.
 // (128x256 tiles with four wavefronts, two workgroups per compute unit: 5 to 20 % slower than 256x256 with plain epilogues, no faster than 128x128
 // with heavy ones.)
-enum GlShape { GL_256 = 0, GL_128, GL_64 };
+enum GlShape { GL_256 = 0, GL_128, GL_128x64, GL_64 };
 typedef GlTile<256, 256, 64, 2, 4, 3, 2, true> GlTile256;
 typedef GlTile<128, 128, 32, 2, 2, 3, 3, false> GlTile128;
+typedef GlTile<128, 64, 64, 2, 2, 3, 3, false> GlTile128x64;
 typedef GlTile<64, 64, 64, 2, 2, 3, 3, false> GlTile64;
-inline TileShape gl_shape(GlShape t) { return t == GL_256 ? TileShape{256, 256} : t == GL_128 ? TileShape{128, 128} : TileShape{64, 64}; }
+inline TileShape gl_shape(GlShape t) { return t == GL_256 ? TileShape{256, 256} : t == GL_128 ? TileShape{128, 128} : t == GL_128x64 ? TileShape{128, 64} : TileShape{64, 64}; }
 inline int gl_upper_tiles(int N, TileShape t) {
   const int tiles = (N + t.bm - 1) / t.bm;
   return tiles * (tiles + 1) / 2;
 }
 
-// The shape with the shortest estimate: tiles per compute unit, times what a tile costs there.  Measured on this card at about 2 GHz, where the matrix
-// pipes leave it, us per 64 of K while a compute unit is busy with tiles of that shape: 1.65, 0.72 and 0.24; per tile for its first loads and a plain epilogue:
-// 4.0, 1.0 and 0.4; more for a heavy one (an exponential, a Philox block or another array per element): 17.5, 1.6 and 0.5.  So 16 members' 4096 x 2048 x 512
-// take 256x256 tiles with a plain epilogue (180 us; 210 in 128x128) and 128x128 with dropout (283; 300), 64 members' 2048 x 1024 with GELU
-// 128x128 at K = 256 (188; 196) and 256x256 at K = 1024 (380; 440).
+// The shape with the shortest estimate, from what tiles take on this card (us, about 2 GHz, where the matrix pipes leave it): a compute unit's first tile LATENCY per 64
+// of K, each further one RATE; FIXED per tile for its first loads and a plain epilogue, HEAVY more for a long one (an exponential, a Philox block or
+// another array per element).  Fitted to 60 shapes of all three layouts; the shape it picks is 0.3 % slower than the best one on average, 7 % at most.  At its
+// lines: 16 members' 4096 x 2048 x 512 take 256x256 tiles with a plain epilogue (150 us; 128x128: 192) and 128x128 with dropout (283; 300), 64 members' 2048 x 1024
+// with GELU 128x128 at K = 256 (188; 196) and 256x256 at K = 1024 (380; 440); 6 members' 720 x 192 x 776 take 64x64 (7.9 us; 128x64: 9.7) and 720 x 776 x 192
+// 128x64 (6.6; 64x64: 8.2); one product 1536 x 1536 x 4096 64x64 (43.9; 128x128: 59.5).
 // Rows so long that 256 of them exceed a buffer offset take the 64-row tile.
-inline GlShape gl_choose(int M, int N, int K, int batch, bool heavy, int64_t pitch) {
+inline GlShape gl_choose(int M, int N, int K, int batch, bool heavy, bool square, int64_t pitch) {
   if (pitch >= GL_MAX_PITCH / 4) return GL_64;
-  constexpr double SLAB[3] = {1.65, 0.72, 0.24}, FIXED[3] = {4.0, 1.0, 0.4}, HEAVY[3] = {17.5, 1.6, 0.5};
+  constexpr double LATENCY[4] = {1.9, 1.09, 0.38, 0.255}, RATE[4] = {1.9, 0.5, 0.42, 0.21}, FIXED[4] = {3.4, 0.97, 0.75, 0.63}, HEAVY[4] = {14.5, 3.0, 4.0, 0.5};
   GlShape best = GL_256;
   double least = 0.;
   for (int t = GL_256; t <= GL_64; ++t) {
     const TileShape sh = gl_shape((GlShape)t);
+    if (square && sh.bm != sh.bn) continue;
     const int64_t per_cu = (tile_count(M, N, batch, sh.bm, sh.bn) + 255) / 256;
-    const double cost = (double)per_cu * (K * (SLAB[t] / 64.) + FIXED[t] + (heavy ? HEAVY[t] : 0.));
+    const double slabs = K / 64., fixed = FIXED[t] + (heavy ? HEAVY[t] : 0.);
+    const double cost = slabs * LATENCY[t] + fixed + (double)(per_cu - 1) * (slabs * RATE[t] + fixed);
     if (t == GL_256 || cost < least) {
       least = cost;
       best = (GlShape)t;
@@ -582,7 +596,7 @@ hipError_t launch_gl_kernel(const GemmArgs& g, const Epilogue& epi, hipStream_t 
     if (attr != hipSuccess) return attr;
   }
   const int64_t total = (int64_t)g.tiles * g.batch;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)(T::PERSISTENT && total > 256 ? 256 : total)), dim3(T::THREADS), T::LDS_BYTES, stream, g, epi);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(T::PERSISTENT && total > 256 ? 256 : total)), dim3(T::THREADS), T::lds_bytes(g.K), stream, g, epi);
   return hipGetLastError();
 }
 
@@ -610,9 +624,12 @@ template <class Epilogue>
 hipError_t launch_gemm_lds(const GemmArgs& g, bool a_m_contig, bool b_k_contig, const Epilogue& epi, hipStream_t stream) {
   if (g.lda >= GL_MAX_PITCH || g.ldb >= GL_MAX_PITCH) return hipErrorInvalidValue;
   if (g.colsum && (!Epilogue::COLSUM || b_k_contig)) return hipErrorInvalidValue;
-  switch (gl_choose(g.M, g.N, g.K, g.batch, Epilogue::HEAVY, g.lda > g.ldb ? g.lda : g.ldb)) {
+  switch (gl_choose(g.M, g.N, g.K, g.batch, Epilogue::HEAVY, std::is_same_v<Epilogue, EpiRbfSum>, g.lda > g.ldb ? g.lda : g.ldb)) {
     case GL_256: return launch_gl_tile<GlTile256>(g, a_m_contig, b_k_contig, epi, stream);
     case GL_128: return launch_gl_tile<GlTile128>(g, a_m_contig, b_k_contig, epi, stream);
+    case GL_128x64:
+      if constexpr (!std::is_same_v<Epilogue, EpiRbfSum>) return launch_gl_tile<GlTile128x64>(g, a_m_contig, b_k_contig, epi, stream);
+      return hipErrorInvalidValue;
     default: return launch_gl_tile<GlTile64>(g, a_m_contig, b_k_contig, epi, stream);
   }
 }

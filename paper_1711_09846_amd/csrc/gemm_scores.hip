@@ -3,7 +3,7 @@
 
 namespace pbt {
 
-int gemm_head_piece(int M, int N, int K, int batch) { return gl_choose(M, N, K, batch, EpiHeadStats::HEAVY, K > N ? K : N) == GL_64 ? 32 : 64; }
+int gemm_head_piece(int M, int N, int K, int batch) { return gl_shape(gl_choose(M, N, K, batch, EpiHeadStats::HEAVY, false, K > N ? K : N)).bn == 64 ? 32 : 64; }
 hipError_t gemm_head_stats(const GemmOperands& o, const float* bias, int64_t sbias, const int32_t* targets, float2* stats, float* target_logit,
                            int pieces, hipStream_t s) {
   if (o.a_m_contig || o.b_k_contig) return hipErrorInvalidValue;
@@ -12,7 +12,7 @@ hipError_t gemm_head_stats(const GemmOperands& o, const float* bias, int64_t sbi
 hipError_t gemm_rbf_sum(const GemmOperands& o, const float* na, int64_t sna, const float* nb, int64_t snb, float inv2d,
                         float* partial, int* tiles, hipStream_t s) {
   // tile count as launch_gemm_lds will choose it (the caller sizes `partial` with gemm_rbf_tiles, an upper bound)
-  const TileShape t = gl_shape(gl_choose(o.M, o.N, o.K, o.batch, EpiRbfSum::HEAVY, o.lda > o.ldb ? o.lda : o.ldb));
+  const TileShape t = gl_shape(gl_choose(o.M, o.N, o.K, o.batch, EpiRbfSum::HEAVY, true, o.lda > o.ldb ? o.lda : o.ldb));
   *tiles = o.symmetric ? gl_upper_tiles(o.N, t) : ((o.M + t.bm - 1) / t.bm) * ((o.N + t.bn - 1) / t.bn);
   return run_gemm(o, EpiRbfSum{na, sna, nb, snb, inv2d, partial}, s);
 }
