@@ -36,12 +36,10 @@ pbt_status dense(const Ctx& x, const bf16_t* in, int K, int N, int64_t w, int64_
 // A small weight matrix over many rows (the attention output projection: 512 x 512 from 4096 rows) gives 256 x 256 tiles
 // to a quarter of the compute units, and smaller tiles spend the long contraction on loop overhead (12 % of the MFMA peak):
 // its contraction is cut into WGRAD_PARTS pieces, each a tile of its own, and the pieces are added up in order afterwards.
-// The same where the whole population's 128 x 64 tiles do not fill the compute units once (small models: 6 members, 192 x 776 from
-// 720 rows): a tile there is one serial chain of slabs, 21 us, and a quarter of the chain plus the addition is 13.
+// (Not for small models: with slabs that go straight into LDS 6 members' 192 x 776 from 720 rows take 14.5 us whole, 12.3 + 4.6 in pieces.)
 constexpr int WGRAD_PARTS = 4;
 bool wgrad_in_parts(int P, int rows, int K, int N) {
   if (N % 4 || ((int64_t)K * N) % 4) return false;
-  if ((int64_t)((K + 127) / 128) * ((N + 63) / 64) * P <= 256) return rows % WGRAD_PARTS == 0 && rows >= WGRAD_PARTS * 64;
   return (int64_t)((K + 255) / 256) * ((N + 255) / 256) * P <= 64 && K >= 256 && N >= 256 &&
          rows % (WGRAD_PARTS * 64) == 0 && rows / WGRAD_PARTS >= 1024;
 }
