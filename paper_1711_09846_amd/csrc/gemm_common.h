@@ -11,6 +11,21 @@ namespace pbt {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 
+// n / d for 0 <= n < 2^31 and a d >= 1 that is known at the launch: with l = ceil(log2 d) and mul = floor(2^(31 + l) / d) + 1, which is below 2^32,
+// n * mul exceeds n * 2^(31 + l) / d by at most n * 2^l / d < 2^(31 + l) / d.  (A division by a kernel argument is 25 dependent scalar instructions; a tile
+// needs four before its first load.)
+struct Divisor {
+  uint32_t mul = 0x80000001u, shift = 31;
+  Divisor() = default;
+  explicit Divisor(int d) {
+    int l = 0;
+    while ((int64_t)1 << l < d) ++l;
+    shift = (uint32_t)(31 + l);
+    mul = (uint32_t)((((uint64_t)1 << shift) / (uint32_t)d) + 1);
+  }
+  __device__ __forceinline__ int divide(int n) const { return (int)(((uint64_t)(uint32_t)n * mul) >> shift); }
+};
+
 struct GemmArgs {
   const bf16_t* A;
   int64_t lda, sa;
@@ -30,6 +45,8 @@ struct GemmArgs {
   int colsum_k = 0;   // the column sums run over k < colsum_k (the launcher sets K when the caller gives no limit)
   int upper = 0;      // RBF sums only: C is symmetric, only the tiles that reach the diagonal or lie right of it are computed
   int tiles = 0;      // tiles per batch element (set by the launcher)
+  // (set by the launcher) by tiles, by the tiles of a group of tile rows, by the rows of the last group, by inner
+  Divisor by_tiles, by_group, by_last, by_inner;
   int b_cols = 0;     // columns of an N-contiguous B that may be read (N, or more where the rows are padded with zeros)
 };
 

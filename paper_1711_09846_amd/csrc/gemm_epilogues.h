@@ -106,7 +106,10 @@ struct EpiStoreBF16 : EpiPlain {
   int inner;       // two-level batch index as in GemmArgs
   int64_t sc_in;
   __host__ __device__ EpiStoreBF16(bf16_t* c, int64_t l, int64_t s, int in = 1, int64_t s_in = 0) : C(c), ldc(l), sc(s), inner(in), sc_in(s_in) {}
-  __device__ __forceinline__ void begin(int member) { C += (int64_t)(member / inner) * sc + (int64_t)(member % inner) * sc_in; }
+  __device__ __forceinline__ void begin(int member) {
+    if (inner == 1) C += (int64_t)member * sc;
+    else C += (int64_t)(member / inner) * sc + (int64_t)(member % inner) * sc_in;
+  }
   __device__ __forceinline__ int64_t pitch() const { return ldc; }
   __device__ __forceinline__ bool vectors() const { return aligned16(C) && ldc % 8 == 0; }
   template <bool FULL>

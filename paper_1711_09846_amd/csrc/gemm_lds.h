@@ -201,7 +201,7 @@ __global__ __launch_bounds__(T::THREADS, T::WAVES_PER_SIMD) void gemm_lds_kernel
   if (t >= t_end) return;
 
   auto locate = [&](int id, int& member, int& tile, int& m0, int& n0) {
-    member = id / g.tiles;
+    member = g.by_tiles.divide(id);
     id -= member * g.tiles;
     tile = id;
     if (std::is_same_v<Epilogue, EpiRbfSum> && g.upper) {
@@ -212,12 +212,12 @@ __global__ __launch_bounds__(T::THREADS, T::WAVES_PER_SIMD) void gemm_lds_kernel
       n0 = (tm + id) * BN;
       return;
     }
-    const int group = id / (GROUP_M * g.tiles_n);
-    const int first_m = group * GROUP_M;
-    const int rows_in_group = g.tiles_m - first_m < GROUP_M ? g.tiles_m - first_m : GROUP_M;
-    id -= group * GROUP_M * g.tiles_n;
-    m0 = (first_m + id % rows_in_group) * BM;
-    n0 = id / rows_in_group * BN;
+    const int group = g.by_group.divide(id), first_m = group * GROUP_M;
+    id -= first_m * g.tiles_n;
+    const bool last = g.tiles_m - first_m < GROUP_M;
+    const int col = last ? g.by_last.divide(id) : id / GROUP_M;
+    m0 = (first_m + id - col * (last ? g.tiles_m - first_m : GROUP_M)) * BM;
+    n0 = col * BN;
   };
 
   // where the next slab of either operand comes from and goes to
@@ -225,15 +225,25 @@ __global__ __launch_bounds__(T::THREADS, T::WAVES_PER_SIMD) void gemm_lds_kernel
   SideB lb;
   int ta = t, ka = 0, tb = t, kb = 0;
   uint32_t slot_a = 0, slot_b = B_BASE;
+  // (a batch element's operand begins at outer * s + rest * s_in)
+  auto outer = [&](int member, int& rest) {
+    const int q = g.by_inner.divide(member);
+    rest = member - q * g.inner;
+    return q;
+  };
   auto set_a = [&]() {
     int member, tile, m0, n0;
     locate(ta, member, tile, m0, n0);
-    la.set_tile(g.A + (int64_t)(member / g.inner) * g.sa + (int64_t)(member % g.inner) * g.sa_in, g.lda, m0, g.M, K, wave, lane);
+    int rest;
+    const int q = outer(member, rest);
+    la.set_tile(g.A + (int64_t)q * g.sa + (int64_t)rest * g.sa_in, g.lda, m0, g.M, K, wave, lane);
   };
   auto set_b = [&]() {
     int member, tile, m0, n0;
     locate(tb, member, tile, m0, n0);
-    lb.set_tile(g.B + (int64_t)(member / g.inner) * g.sb + (int64_t)(member % g.inner) * g.sb_in, g.ldb, n0, B_KC ? g.N : g.b_cols, K, wave, lane);
+    int rest;
+    const int q = outer(member, rest);
+    lb.set_tile(g.B + (int64_t)q * g.sb + (int64_t)rest * g.sb_in, g.ldb, n0, B_KC ? g.N : g.b_cols, K, wave, lane);
   };
   auto after_a = [](uint32_t slot) { return slot + A_STEP == A_END ? 0u : slot + A_STEP; };
   auto after_b = [](uint32_t slot) { return slot + B_STEP == B_END ? B_BASE : slot + B_STEP; };
@@ -296,19 +306,25 @@ __global__ __launch_bounds__(T::THREADS, T::WAVES_PER_SIMD) void gemm_lds_kernel
   int cs_k = 0;   // k of the slab being multiplied
   auto colsum_step = [&](int st) {
     if constexpr (COLSUM) if (want_colsum) {
-      const int left = g.colsum_k - (cs_k + st * 16 + 8 * (lane >> 5));
-      const bool whole = cs_k + BK <= g.colsum_k;
+      // (a slab that reaches past colsum_k, which is rare, masks the fragment; doing that to every slab took as long as the loads: 14.4 us for six
+      // members' 192 x 192 from 720 rows, 11.0 so)
+      const bool whole = g.colsum_k >= K || cs_k + BK <= g.colsum_k;
 #pragma unroll
       for (int b = 0; b < CS_BLOCKS; ++b)
 #pragma unroll
         for (int w = 0; w < WM; ++w)
           if (w == wm && b * WM + w < TN) {
-            const u32x4_t v = __builtin_bit_cast(u32x4_t, fb[st & 1][b * WM + w < TN ? b * WM + w : 0]);
+            u32x4_t v = __builtin_bit_cast(u32x4_t, fb[st & 1][b * WM + w < TN ? b * WM + w : 0]);
+            if (__builtin_expect(!whole, 0)) {
+              const int left = g.colsum_k - (cs_k + st * 16 + 8 * (lane >> 5));
+#pragma unroll
+              for (int q = 0; q < 4; ++q) v[q] &= 2 * q + 1 < left ? 0xffffffffu : 2 * q < left ? 0xffffu : 0u;
+            }
             float f[8];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              f[2 * q] = whole || 2 * q < left ? __uint_as_float(v[q] << 16) : 0.f;
-              f[2 * q + 1] = whole || 2 * q + 1 < left ? __uint_as_float(v[q] & 0xffff0000u) : 0.f;
+              f[2 * q] = __uint_as_float(v[q] << 16);
+              f[2 * q + 1] = __uint_as_float(v[q] & 0xffff0000u);
             }
             csum[b] += ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
           }
@@ -589,13 +605,17 @@ inline GlShape gl_choose(int M, int N, int K, int batch, bool heavy, bool square
 }
 
 template <class T, bool A_KC, bool B_KC, class Epilogue>
-hipError_t launch_gl_kernel(const GemmArgs& g, const Epilogue& epi, hipStream_t stream) {
+hipError_t launch_gl_kernel(GemmArgs g, const Epilogue& epi, hipStream_t stream) {
   auto kernel = gemm_lds_kernel<T, A_KC, B_KC, Epilogue>;
   if constexpr (T::LDS_BYTES > 64 * 1024) {
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
     if (attr != hipSuccess) return attr;
   }
   const int64_t total = (int64_t)g.tiles * g.batch;
+  g.by_tiles = Divisor(g.tiles);
+  g.by_group = Divisor(GROUP_M * g.tiles_n);
+  g.by_last = Divisor(g.tiles_m % GROUP_M ? g.tiles_m % GROUP_M : 1);
+  g.by_inner = Divisor(g.inner);
   hipLaunchKernelGGL(kernel, dim3((unsigned)(T::PERSISTENT && total > 256 ? 256 : total)), dim3(T::THREADS), T::lds_bytes(g.K), stream, g, epi);
   return hipGetLastError();
 }
