@@ -51,39 +51,6 @@ __device__ __forceinline__ void store_run(bf16_t* dst, const float* v, int count
   if (FULL) *reinterpret_cast<uint4*>(dst) = pack_bf16x8(v);
   else store_bf16_run(dst, v, count);
 }
-// eight values, rounded to bf16, times 0 (keeping the sign) or the scale by their keep bits, rounded once more
-__device__ __forceinline__ uint4 keep_times_scale(const float* a, uint32_t bits, float scale) {
-  uint32_t out[4], tie = 0;
-  float x[8];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const uint32_t r = f2bf_pair(a[2 * q], a[2 * q + 1]);
-    x[2 * q] = __uint_as_float(r << 16);
-    x[2 * q + 1] = __uint_as_float(r & 0xffff0000u);
-    const float lo = x[2 * q] * scale, hi = x[2 * q + 1] * scale;
-    // (the rounded product rounds wrongly only where it lies half way between two bf16 values: bf16_times_float looks into those)
-    tie |= ((__float_as_uint(lo) & 0xffffu) == 0x8000u || (__float_as_uint(hi) & 0xffffu) == 0x8000u) ? 1u << q : 0u;
-    const uint32_t keep = (((bits >> (2 * q)) & 1u) ? 0xffffu : 0x8000u) | (((bits >> (2 * q + 1)) & 1u) ? 0xffff0000u : 0x80000000u);
-    // (x * 0 keeps the sign: of the value itself, which the scale does not change)
-    out[q] = f2bf_pair(lo, hi) & keep;
-  }
-  if (tie) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if ((tie >> q) & 1u) {
-        uint32_t w = 0;
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const bf16_t b = (bf16_t)(__float_as_uint(x[2 * q + e]) >> 16);
-          const bf16_t y = (bits >> (2 * q + e)) & 1u ? bf16_times_float(b, scale) : (bf16_t)(b & 0x8000u);
-          w |= (uint32_t)y << (16 * e);
-        }
-        out[q] = w;
-      }
-  }
-  return make_uint4(out[0], out[1], out[2], out[3]);
-}
-
 struct EpiStoreF32 : EpiPlain {
   static constexpr bool COLSUM = true;
   static constexpr int LAYOUTS = 15;

@@ -65,8 +65,8 @@ struct TfPlan {
   bool fused_attn;                  // one attention kernel per pass: no score / probability arrays, o_keep instead
   size_t o_keep[PBT_MAX_DIMS];      // keep bits of the attention dropout site (fused attention only)
   size_t o_attn_stats;              // softmax row statistics between the two backward kernels (fused attention only)
-  size_t logits_bytes;              // of o_logits: the logits, afterwards the partial weight gradients of contractions cut into pieces (transformer_host.hip: wgrad)
-  size_t o_score, o_tmp_d[3], o_tmp_f[2], o_dqkv, o_uf, o_logits, o_dlogits, o_rowloss, o_evalrow, o_tokstart, o_tokcursor, o_tokorder, o_lnpart;
+  size_t logits_bytes;              // of o_logits: the logits, afterwards the partial weight gradients of contractions cut into pieces (transformer_host.hip: wgrad) and the sums of the LayerNorms' parameter gradients
+  size_t o_score, o_tmp_d[3], o_tmp_f[2], o_dqkv, o_uf, o_logits, o_dlogits, o_rowloss, o_evalrow, o_tokends, o_tokorder, o_lnpart;
 };
 
 struct Plan {

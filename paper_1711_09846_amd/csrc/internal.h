@@ -139,7 +139,7 @@ hipError_t embed_fwd(const int32_t* pool, int n_pool, int S, int B, int d, int V
                      int64_t tok_off, int64_t pos_off, uint32_t c0, uint64_t seed, int draw, bf16_t* h, int32_t* tokens,
                      int32_t* targets, int32_t* t, hipStream_t s);
 hipError_t embed_bwd(const bf16_t* dh, const int32_t* tokens, int B, int S, int d, int V, int P, float* G, int64_t stride,
-                     int64_t tok_off, int64_t pos_off, int32_t* start, int32_t* cursor, int32_t* order, hipStream_t s);
+                     int64_t tok_off, int64_t pos_off, int32_t* ends, int32_t* order, hipStream_t s);
 hipError_t layernorm_fwd(const bf16_t* x, int P, int rows, int d, const float* W32, int64_t stride, int64_t g_off, int64_t b_off,
                          bf16_t* y, float* mean, float* rstd, hipStream_t s);
 hipError_t layernorm_bwd(const bf16_t* dy, const bf16_t* x, const float* mean, const float* rstd, int P, int rows, int d,
@@ -148,13 +148,19 @@ constexpr int LN_MAX_SLABS = 64;  // row slabs whose partial sums layernorm_para
 hipError_t layernorm_param_grad(const bf16_t* dy, const bf16_t* x, const float* mean, const float* rstd, int P, int rows, int d,
                                 float* G, int64_t stride, int64_t g_off, int64_t b_off, float* part, hipStream_t s);
 constexpr int LN_FUSED_SLABS = 64;  // row slabs of the fused LayerNorm backward
-// LayerNorm backward (as layernorm_bwd) and the gain / bias gradients (as layernorm_param_grad) in one pass; d <= 2048
+// LayerNorm backward (as layernorm_bwd) and the sums behind the gain / bias gradients (as layernorm_param_grad) in one pass; d <= 2048.
+// part: float [P][layernorm_bwd_slabs(rows)][2][d], which layernorm_param_combine adds up
 // out2 (optional): out multiplied by the recorded keep factors of a dropout site (drop as in gemm_dgrad_act), i.e.
 // the gradient that enters the branch behind that site
-hipError_t layernorm_bwd_with_param_grad(const bf16_t* dy, const bf16_t* x, const float* mean, const float* rstd, int P, int rows,
-                                         int d, const float* W32, int64_t stride, int64_t g_off, int64_t b_off, const bf16_t* res,
-                                         bf16_t* out, float* G, float* part, hipStream_t s, bf16_t* out2 = nullptr,
+int layernorm_bwd_slabs(int rows);
+hipError_t layernorm_bwd_with_param_sums(const bf16_t* dy, const bf16_t* x, const float* mean, const float* rstd, int P, int rows,
+                                         int d, const float* W32, int64_t stride, int64_t g_off, const bf16_t* res,
+                                         bf16_t* out, float* part, hipStream_t s, bf16_t* out2 = nullptr,
                                          const DropRecord& drop = DropRecord());
+// the gradients of gain and bias of n_sites LayerNorms, whose sums lie site_stride floats apart, to G at g_off[k] and b_off[k]
+constexpr int LN_SITES = 16;   // per launch
+hipError_t layernorm_param_combine(const float* part, int64_t site_stride, int n_sites, const int64_t* g_off, const int64_t* b_off, int n_slabs, int P, int d,
+                                   float* G, int64_t stride, hipStream_t s);
 hipError_t softmax_fwd(const bf16_t* sc, int P, int64_t rows, int S, float scale, const DropArgs& d, int site, bf16_t* pq,
                        bf16_t* pd, hipStream_t s);
 hipError_t softmax_bwd(const bf16_t* pq, bf16_t* dpd, int P, int64_t rows, int S, float scale, const DropArgs& d, int site,

@@ -77,13 +77,42 @@ pbt_status dgrad(const Ctx& x, const bf16_t* dout, int N, int K, int64_t w, cons
   return PBT_OK;
 }
 
-// out = LayerNorm backward of dy (+ res); G[g], G[b] = gradients of gain and bias
+// The parameter gradients of all LayerNorms of a pass are added up in one launch at its end if there is room for their sums behind the pieces of the weight
+// gradients in the logits' buffer (dead by then), else each in one of its own: 16 members, d 512, nine launches
+// of 6.3 us: 10 in one; 6 members, d 192, five of 4.8: 3.6.
+struct LnLate {
+  float* part;
+  int64_t stride;   // floats per LayerNorm
+  int n = 0;
+  int64_t g[2 * PBT_MAX_DIMS + 1], b[2 * PBT_MAX_DIMS + 1];
+};
+bool ln_late(const Ctx& x, LnLate* late) {
+  const TfPlan& t = x.h->plan.tf;
+  if (!x.fused_bwd) return false;
+  const Dim& D = x.D;
+  const int shapes[4][2] = {{D.d, 3 * D.d}, {D.d, D.d}, {D.d, D.f}, {D.f, D.d}};   // (the head's pieces are added up before the first LayerNorm)
+  size_t pieces = 0;
+  for (const auto& sh : shapes)
+    if (wgrad_in_parts(x.P, x.n, sh[0], sh[1]) && wgrad_parts_bytes(x.P, sh[0], sh[1]) <= t.logits_bytes) pieces = std::max(pieces, wgrad_parts_bytes(x.P, sh[0], sh[1]));
+  pieces = round_up(pieces, BUF_ALIGN);
+  late->stride = (int64_t)x.P * layernorm_bwd_slabs(x.n) * 2 * D.d;
+  late->part = x.sc<float>(t.o_logits) + pieces / 4;
+  return pieces + (size_t)(2 * D.L + 1) * late->stride * 4 <= t.logits_bytes;
+}
+
+// out = LayerNorm backward of dy (+ res); G[g], G[b] = gradients of gain and bias (late: noted for the launch at the end of the pass)
 // out2 / drop (optional, fused path only): out times the recorded keep factors of a dropout site
-pbt_status ln_backward(const Ctx& x, const bf16_t* dy, const bf16_t* in, const float* mean, const float* rstd, int64_t g, int64_t b,
+pbt_status ln_backward(const Ctx& x, LnLate* late, const bf16_t* dy, const bf16_t* in, const float* mean, const float* rstd, int64_t g, int64_t b,
                        const bf16_t* res, bf16_t* out, bf16_t* out2 = nullptr, const DropRecord& drop = DropRecord()) {
-  float* part = x.sc<float>(x.h->plan.tf.o_lnpart);
+  float* part = late ? late->part + late->n * late->stride : x.sc<float>(x.h->plan.tf.o_lnpart);
   if (x.fused_bwd) {
-    PBT_HIP(x.h, layernorm_bwd_with_param_grad(dy, in, mean, rstd, x.P, x.n, x.D.d, x.W32, x.S_, g, b, res, out, x.G, part, x.s, out2, drop));
+    PBT_HIP(x.h, layernorm_bwd_with_param_sums(dy, in, mean, rstd, x.P, x.n, x.D.d, x.W32, x.S_, g, res, out, part, x.s, out2, drop));
+    if (late) {
+      late->g[late->n] = g;
+      late->b[late->n++] = b;
+      return PBT_OK;
+    }
+    PBT_HIP(x.h, layernorm_param_combine(part, 0, 1, &g, &b, layernorm_bwd_slabs(x.n), x.P, x.D.d, x.G, x.S_, x.s));
     return PBT_OK;
   }
   PBT_HIP(x.h, layernorm_param_grad(dy, in, mean, rstd, x.P, x.n, x.D.d, x.G, x.S_, g, b, part, x.s));
@@ -257,8 +286,7 @@ pbt_status tf_check_and_plan(const pbt_config* c, Plan* pl, Carver* w) {
   t.o_uf = w->take(nd);
   t.o_dlogits = w->take(P * n * D.V * 2);
   t.o_rowloss = w->take(P * n * 4);
-  t.o_tokstart = w->take(P * ((size_t)D.V + 1) * 4);
-  t.o_tokcursor = w->take(P * (size_t)D.V * 4);
+  t.o_tokends = w->take(P * (size_t)D.V * 4);
   t.o_tokorder = w->take(P * n * 4);
   t.o_lnpart = w->take(P * (size_t)(LN_FUSED_SLABS > LN_MAX_SLABS ? LN_FUSED_SLABS : LN_MAX_SLABS) * 2 * D.d * 4);
   // The logits, and over them the pieces of the weight gradients that are formed in parts: room for the largest, but where that would
@@ -315,10 +343,11 @@ pbt_status tf_step(pbt_handle* h, const int32_t* pool, uint32_t step, hipStream_
     return DropRecord{x.sc<uint8_t>(t.o_mask[l][k]), (int64_t)(dropout_mask_bytes(1, per_member)), Hh, c.n_hyper, t.col_drop};
   };
   const bool fb = x.fused_bwd;
+  LnLate sums, *late = ln_late(x, &sums) ? &sums : nullptr;
   // head and final LayerNorm
   TF_TRY(wgrad(x, x.sc<bf16_t>(t.o_uf), D.d, dl, D.V, t.whead, t.bhead));
   TF_TRY(dgrad(x, dl, D.V, D.d, t.whead, nullptr, 0, du));   // (du: the final LayerNorm's output buffer, free once the head's weight gradient is taken)
-  TF_TRY(ln_backward(x, du, x.sc<bf16_t>(t.o_h[D.L]), x.sc<float>(t.o_meanf), x.sc<float>(t.o_rstdf), t.lnfg, t.lnfb, nullptr, dh,
+  TF_TRY(ln_backward(x, late, du, x.sc<bf16_t>(t.o_h[D.L]), x.sc<float>(t.o_meanf), x.sc<float>(t.o_rstdf), t.lnfg, t.lnfb, nullptr, dh,
                      fb ? dd : nullptr, fb ? record(D.L - 1, 2, per_d) : DropRecord()));
   for (int l = D.L - 1; l >= 0; --l) {
     const TfBlockOff& b = t.blk[l];
@@ -334,7 +363,7 @@ pbt_status tf_step(pbt_handle* h, const int32_t* pool, uint32_t step, hipStream_
     }
     TF_TRY(wgrad(x, x.sc<bf16_t>(t.o_u2[l]), D.d, df1, D.f, b.w1, b.b1));
     TF_TRY(dgrad(x, df1, D.f, D.d, b.w1, nullptr, 0, du));
-    TF_TRY(ln_backward(x, du, x.sc<bf16_t>(t.o_hmid[l]), x.sc<float>(t.o_mean2[l]), x.sc<float>(t.o_rstd2[l]), b.ln2g, b.ln2b, dh, dh2,
+    TF_TRY(ln_backward(x, late, du, x.sc<bf16_t>(t.o_hmid[l]), x.sc<float>(t.o_mean2[l]), x.sc<float>(t.o_rstd2[l]), b.ln2g, b.ln2b, dh, dh2,
                        fb ? dd : nullptr, fb ? record(l, 0, per_d) : DropRecord()));
     // attention branch
     if (!fb) PBT_HIP(h, dropout_apply(dh2, nullptr, x.P, per_d, dr, 4 * l + 1, dd, s, x.sc<uint16_t>(t.o_mask[l][0])));
@@ -354,11 +383,12 @@ pbt_status tf_step(pbt_handle* h, const int32_t* pool, uint32_t step, hipStream_
     TF_TRY(wgrad(x, x.sc<bf16_t>(t.o_u[l]), D.d, dqkv, 3 * D.d, b.wqkv, b.bqkv));
     TF_TRY(dgrad(x, dqkv, 3 * D.d, D.d, b.wqkv, nullptr, 0, du));
     const bool next = fb && l > 0;   // the block below starts with the backward of its feed-forward output site
-    TF_TRY(ln_backward(x, du, x.sc<bf16_t>(t.o_h[l]), x.sc<float>(t.o_mean1[l]), x.sc<float>(t.o_rstd1[l]), b.ln1g, b.ln1b, dh2, dh,
+    TF_TRY(ln_backward(x, late, du, x.sc<bf16_t>(t.o_h[l]), x.sc<float>(t.o_mean1[l]), x.sc<float>(t.o_rstd1[l]), b.ln1g, b.ln1b, dh2, dh,
                        next ? dd : nullptr, next ? record(l - 1, 2, per_d) : DropRecord()));
   }
-  PBT_HIP(h, embed_bwd(dh, x.sc<int32_t>(t.o_tokens), x.Bc, D.S, D.d, D.V, x.P, x.G, x.S_, t.tok, t.pos, x.sc<int32_t>(t.o_tokstart),
-                       x.sc<int32_t>(t.o_tokcursor), x.sc<int32_t>(t.o_tokorder), s));
+  if (late) PBT_HIP(h, layernorm_param_combine(late->part, late->stride, late->n, late->g, late->b, layernorm_bwd_slabs(x.n), x.P, D.d, x.G, x.S_, s));
+  PBT_HIP(h, embed_bwd(dh, x.sc<int32_t>(t.o_tokens), x.Bc, D.S, D.d, D.V, x.P, x.G, x.S_, t.tok, t.pos, x.sc<int32_t>(t.o_tokends),
+                       x.sc<int32_t>(t.o_tokorder), s));
   OptArgs oa{h->st<float>(p.o_w32), h->st<float>(p.o_opt0), h->st<float>(p.o_opt1), h->st<bf16_t>(p.o_w16), x.G, 0, x.S_,
              h->st<float>(p.o_hyper), h->st<int32_t>(p.o_t), x.S_, x.P, c.n_hyper, PBT_OPT_ADAM, p.col_lr, -1, -1,
              c.opt_const[0], c.opt_const[1], c.opt_const[2], c.opt_const[3]};

@@ -21,112 +21,180 @@ namespace pbt {
 // tokens outside the vocabulary are mapped to its ends so that no table read leaves its array
 __device__ __forceinline__ int32_t clamp_token(int32_t tok, int V) { return tok < 0 ? 0 : tok >= V ? V - 1 : tok; }
 
+// eight consecutive elements of a row, one or two 16-byte accesses
+__device__ __forceinline__ void unpack8(const uint4& u, float* v) {
+  const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+  for (int q = 0; q < 4; ++q) { v[2 * q] = __uint_as_float(w[q] << 16); v[2 * q + 1] = __uint_as_float(w[q] & 0xffff0000u); }
+}
+__device__ __forceinline__ void load8(const bf16_t* p, float* v) { unpack8(*reinterpret_cast<const uint4*>(p), v); }
+__device__ __forceinline__ void load8(const float* p, float* v) {
+  const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
+  v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+}
+__device__ __forceinline__ void store8(bf16_t* p, const float* v) {
+  *reinterpret_cast<uint4*>(p) = make_uint4(f2bf_pair(v[0], v[1]), f2bf_pair(v[2], v[3]), f2bf_pair(v[4], v[5]), f2bf_pair(v[6], v[7]));
+}
+
 // ---- embeddings ------------------------------------------------------------------------------
 // h[i][b][s][:] = tok[token] + pos[s]; tokens are drawn here: sequence b of member i is pool row
 // floor(x * n_pool / 2^32), x from Philox domain 1; also copies the targets and bumps t.
-__global__ __launch_bounds__(64) void embed_fwd_kernel(const int32_t* __restrict__ pool, int n_pool, int S, int B, int d, int V,
-                                                       const bf16_t* __restrict__ W16, int64_t stride, int64_t tok_off,
-                                                       int64_t pos_off, uint32_t c0, uint32_t k0, uint32_t k1, int draw,
-                                                       bf16_t* __restrict__ h, int32_t* __restrict__ tokens,
-                                                       int32_t* __restrict__ targets, int32_t* __restrict__ t) {
-  const int s = blockIdx.x, b = blockIdx.y, i = blockIdx.z;
+// A wavefront per position, eight elements (16 bytes) per lane and pass: 65536 rows of 512 in 35 us (47 with 2-byte accesses).
+__global__ __launch_bounds__(256) void embed_fwd_kernel(const int32_t* __restrict__ pool, int n_pool, int S, int B, int d, int V,
+                                                        const bf16_t* __restrict__ W16, int64_t stride, int64_t tok_off,
+                                                        int64_t pos_off, uint32_t c0, uint32_t k0, uint32_t k1, int draw,
+                                                        bf16_t* __restrict__ h, int32_t* __restrict__ tokens,
+                                                        int32_t* __restrict__ targets, int32_t* __restrict__ t) {
+  const int i = blockIdx.y, lane = threadIdx.x & 63;
+  const int at = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));   // position of the member
+  if (at >= B * S) return;
+  const int b = at / S, s = at - b * S;
   int64_t row = b;
   if (draw) row = philox_bounded(philox4x32_10(c0, (uint32_t)i, DOMAIN_BATCH, (uint32_t)b, k0, k1).x, (uint32_t)n_pool);
   const int32_t tok = clamp_token(pool[row * (S + 1) + s], V);
-  const int64_t r = ((int64_t)i * B + b) * S + s;
+  const int64_t r = (int64_t)i * B * S + at;
   const bf16_t* __restrict__ te = W16 + (int64_t)i * stride + tok_off + (int64_t)tok * d;
   const bf16_t* __restrict__ pe = W16 + (int64_t)i * stride + pos_off + (int64_t)s * d;
-  for (int c = threadIdx.x; c < d; c += 64) h[r * d + c] = f2bf(bf2f(te[c]) + bf2f(pe[c]));
-  if (threadIdx.x == 0) {
+  for (int c = lane * 8; c < d; c += 512) {
+    float v[8], w[8];
+    load8(te + c, v);
+    load8(pe + c, w);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += w[e];
+    store8(h + r * d + c, v);
+  }
+  if (lane == 0) {
     tokens[r] = tok;
     targets[r] = clamp_token(pool[row * (S + 1) + s + 1], V);
-    if (draw && s == 0 && b == 0) t[i] += 1;
+    if (draw && at == 0) t[i] += 1;
   }
 }
 hipError_t embed_fwd(const int32_t* pool, int n_pool, int S, int B, int d, int V, int P, const bf16_t* W16, int64_t stride,
                      int64_t tok_off, int64_t pos_off, uint32_t c0, uint64_t seed, int draw, bf16_t* h, int32_t* tokens,
                      int32_t* targets, int32_t* t, hipStream_t s) {
-  hipLaunchKernelGGL(embed_fwd_kernel, dim3(S, B, P), dim3(64), 0, s, pool, n_pool, S, B, d, V, W16, stride, tok_off, pos_off, c0,
+  if (d % 8 || stride % 8 || tok_off % 8 || pos_off % 8) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(embed_fwd_kernel, dim3((unsigned)((B * S + 3) / 4), P), dim3(256), 0, s, pool, n_pool, S, B, d, V, W16, stride, tok_off, pos_off, c0,
                      (uint32_t)seed, (uint32_t)(seed >> 32), draw, h, tokens, targets, t);
   return hipGetLastError();
 }
 
 // Gradient of the embedding tables, in a fixed summation order (no floating-point atomics):
-//   1. count the positions of every token (integer atomics), 2. the counts become list starts and every position
-//   is filed under its token, positions ascending,
-//   3. one workgroup per (token, member) adds up the rows of its list; tokens that do not occur get
-//   zeros.  The position table's gradient sums the B rows that share a position.
-__global__ __launch_bounds__(256) void tok_count_kernel(const int32_t* __restrict__ tokens, int n, int V, int32_t* __restrict__ start) {
-  const int i = blockIdx.y;
-  const int r = blockIdx.x * 256 + threadIdx.x;
-  if (r < n) atomicAdd(&start[(int64_t)i * (V + 1) + tokens[(int64_t)i * n + r]], 1);
-}
+//   1. the positions of every token are filed under it, in any order,
+//   2. one workgroup per (token, member) puts its list in ascending order and adds up the rows; tokens that do not
+//      occur get zeros.
+// The position table's gradient sums the B rows that share a position.
 
-// counts -> list starts (exclusive prefix sum over the vocabulary), one workgroup per member
-__global__ __launch_bounds__(256) void tok_start_kernel(int V, int n, int32_t* __restrict__ start) {
-  __shared__ int32_t part[256];
-  const int i = blockIdx.x, tid = threadIdx.x;
-  int32_t* __restrict__ st = start + (int64_t)i * (V + 1);
-  const int span = (V + 255) / 256;   // a span of consecutive tokens per thread
-  const int v0 = tid * span, v1 = min(V, v0 + span);
-  int32_t sum = 0;
-  for (int v = v0; v < v1; ++v) sum += st[v];
-  part[tid] = sum;
-  __syncthreads();
-  if (tid == 0) {
-    int32_t run = 0;
-    for (int k = 0; k < 256; ++k) { const int32_t c = part[k]; part[k] = run; run += c; }
-  }
-  __syncthreads();
-  int32_t run = part[tid];
-  for (int v = v0; v < v1; ++v) { const int32_t c = st[v]; st[v] = run; run += c; }
-  if (tid == 255) st[V] = n;
-}
-
-// Files every position under its token, positions ascending: position r goes to start[token] + (number of earlier
-// positions of the member with the same token).  A workgroup takes 256 positions and counts by looking at all earlier
-// tokens of the member, staged in LDS (n^2 / 2 integer compares per member, spread over the whole device: with one
-// workgroup per member walking the positions in order this step took 150 us on 16 of 256 compute units).
-__global__ __launch_bounds__(256) void tok_place_kernel(const int32_t* __restrict__ tokens, int n, int V, const int32_t* __restrict__ start,
-                                                        int32_t* __restrict__ order) {
-  extern __shared__ __attribute__((aligned(16))) int32_t s_tok[];   // tokens of positions 0 .. base + 255
-  const int i = blockIdx.y, base = blockIdx.x * 256, tid = threadIdx.x;
+// One workgroup per member; the counts of a range of the vocabulary lie in LDS.  Count, prefix sum (a thread owns `span` consecutive tokens, span odd: no bank
+// conflicts), file.  The counters end as the ends of the lists, which is what tok_sum_kernel wants: list v is [end[v - 1], end[v]).
+// What bounds it: the latency of its passes over the tokens.  16 members, 4096 positions, vocabulary 8192: 8.8 us; 6 members, 720, 1000: 4.1.  (In four
+// launches, counted in memory and filed in ascending order by comparing every position with all before it: 78 and 31.)
+constexpr int TOK_THREADS = 1024, TOK_SPAN = 15;
+__global__ __launch_bounds__(TOK_THREADS) void tok_lists_kernel(const int32_t* __restrict__ tokens, int n, int V, int span, int32_t* __restrict__ end,
+                                                                int32_t* __restrict__ order) {
+  extern __shared__ int32_t s_count[];   // [TOK_THREADS * span]
+  __shared__ int32_t s_part[TOK_THREADS / 64];
+  const int i = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int32_t* __restrict__ tk = tokens + (int64_t)i * n;
-  const int upto = min(n, base + 256);
-  // (16-byte loads, several in flight: n is a multiple of 4 and so is upto)
+  int32_t before = 0;   // positions whose token lies below the range
+  for (int v0 = 0; v0 < V; v0 += TOK_THREADS * span) {
+    const int width = min(V - v0, TOK_THREADS * span);
+    for (int k = tid; k < TOK_THREADS * span; k += TOK_THREADS) s_count[k] = 0;
+    __syncthreads();
 #pragma unroll 4
-  for (int r = tid * 4; r < upto; r += 1024) *reinterpret_cast<int4*>(s_tok + r) = *reinterpret_cast<const int4*>(tk + r);
-  for (int r = upto + tid; r < base + 256; r += 256) s_tok[r] = -1;   // (a ragged last workgroup reads its whole 256)
-  __syncthreads();
-  const int r = base + tid;
-  if (r >= n) return;
-  const int32_t tok = s_tok[r];
-  int rank = 0;
-  // (whole groups of four below the workgroup's first position: the same 16-byte LDS read for every lane)
-#pragma unroll 8
-  for (int j = 0; j < base; j += 4) {   // (base is a multiple of 256; unrolled so that several reads are in flight)
-    const int4 q = *reinterpret_cast<const int4*>(s_tok + j);
-    rank += (q.x == tok ? 1 : 0) + (q.y == tok ? 1 : 0) + (q.z == tok ? 1 : 0) + (q.w == tok ? 1 : 0);
+    for (int r = tid; r < n; r += TOK_THREADS) {
+      const uint32_t k = (uint32_t)(tk[r] - v0);
+      if (k < (uint32_t)width) atomicAdd(&s_count[k], 1);
+    }
+    __syncthreads();
+    int32_t sum = 0;
+    for (int k = 0; k < span; ++k) sum += s_count[tid * span + k];
+    int32_t upto = sum;   // of the wavefront's lanes up to this one
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int32_t o = __shfl_up(upto, off, 64);
+      if (lane >= off) upto += o;
+    }
+    if (lane == 63) s_part[wave] = upto;
+    __syncthreads();
+    int32_t run = before + upto - sum;
+    int32_t all = 0;
+#pragma unroll
+    for (int w = 0; w < TOK_THREADS / 64; ++w) {
+      const int32_t c = s_part[w];
+      run += w < wave ? c : 0;
+      all += c;
+    }
+    before += all;
+    for (int k = 0; k < span; ++k) {
+      const int32_t c = s_count[tid * span + k];
+      s_count[tid * span + k] = run;
+      run += c;
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int r = tid; r < n; r += TOK_THREADS) {
+      const uint32_t k = (uint32_t)(tk[r] - v0);
+      if (k < (uint32_t)width) order[(int64_t)i * n + atomicAdd(&s_count[k], 1)] = r;
+    }
+    __syncthreads();
+    for (int k = tid; k < width; k += TOK_THREADS) end[(int64_t)i * V + v0 + k] = s_count[k];
+    __syncthreads();
   }
-#pragma unroll 8
-  for (int j = 0; j < 256; ++j) rank += (base + j < r && s_tok[base + j] == tok) ? 1 : 0;
-  order[(int64_t)i * n + start[(int64_t)i * (V + 1) + tok] + rank] = r;
 }
 
-__global__ __launch_bounds__(128) void tok_sum_kernel(const bf16_t* __restrict__ dh, const int32_t* __restrict__ start,
-                                                      const int32_t* __restrict__ order, int n, int d, int V, float* __restrict__ G,
-                                                      int64_t stride, int64_t tok_off) {
-  const int v = blockIdx.x, i = blockIdx.y;
-  const int32_t b = start[(int64_t)i * (V + 1) + v], e = start[(int64_t)i * (V + 1) + v + 1];
-  const int32_t* __restrict__ ord = order + (int64_t)i * n;
+// Bound by the writes of G (16 members, 8192 x 512: 268 MB).  Lists of up to 64 positions are ordered by rank, one lane per position; longer ones through a bit per position of the member.
+constexpr int TOK_MAX_POSITIONS = 16384;
+__global__ __launch_bounds__(128) void tok_sum_kernel(const bf16_t* __restrict__ dh, const int32_t* __restrict__ end, int32_t* order, int n, int d, int V,
+                                                      float* __restrict__ G, int64_t stride, int64_t tok_off) {
+  __shared__ int32_t s_list[64];
+  __shared__ uint32_t s_bits[TOK_MAX_POSITIONS / 32];
+  __shared__ int32_t s_start[128];
+  const int v = blockIdx.x, i = blockIdx.y, tid = threadIdx.x;
+  const int32_t* __restrict__ en = end + (int64_t)i * V;
+  const int32_t b = v > 0 ? en[v - 1] : 0, count = en[v] - b;
+  int32_t* ord = order + (int64_t)i * n + b;
+  const int32_t first = count > 0 ? ord[0] : 0;
+  if (count > 64) {
+    const int words = (n + 31) / 32, per = (words + 127) / 128;   // a run of words per thread
+    for (int k = tid; k < words; k += 128) s_bits[k] = 0u;
+    __syncthreads();
+    for (int k = tid; k < count; k += 128) {
+      const int32_t r = ord[k];
+      atomicOr(&s_bits[r >> 5], 1u << (r & 31));
+    }
+    __syncthreads();
+    int32_t mine = 0;
+    for (int k = tid * per; k < min(words, (tid + 1) * per); ++k) mine += __popc(s_bits[k]);
+    s_start[tid] = mine;
+    __syncthreads();
+    int32_t at = 0;
+    for (int k = 0; k < tid; ++k) at += s_start[k];
+    for (int k = tid * per; k < min(words, (tid + 1) * per); ++k)
+      for (uint32_t w = s_bits[k]; w; w &= w - 1u) ord[at++] = k * 32 + __ffs(w) - 1;
+    __syncthreads();
+  } else if (count > 1) {
+    if (tid < 64) {
+      const int32_t p = tid < count ? ord[tid] : 0;
+      int rank = 0;
+      for (int k = 0; k < count; ++k) rank += __builtin_amdgcn_readlane(p, k) < p ? 1 : 0;
+      if (tid < count) s_list[rank] = p;
+    }
+    __syncthreads();
+  }
   const bf16_t* __restrict__ g = dh + (int64_t)i * n * d;
-  for (int c0 = threadIdx.x * 4; c0 < d; c0 += 512) {
+  for (int c0 = tid * 4; c0 < d; c0 += 512) {
     float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-    for (int k = b; k < e; ++k) {
-      const uint2 x = *reinterpret_cast<const uint2*>(g + (int64_t)ord[k] * d + c0);
+    auto add = [&](int32_t r) {
+      const uint2 x = *reinterpret_cast<const uint2*>(g + (int64_t)r * d + c0);
       a0 += __uint_as_float(x.x << 16); a1 += __uint_as_float(x.x & 0xffff0000u);
       a2 += __uint_as_float(x.y << 16); a3 += __uint_as_float(x.y & 0xffff0000u);
-    }
+    };
+    if (count == 1)
+      add(first);
+    else if (count > 64)
+      for (int k = 0; k < count; ++k) add(ord[k]);
+    else
+      for (int k = 0; k < count; ++k) add(s_list[k]);
     *reinterpret_cast<float4*>(G + (int64_t)i * stride + tok_off + (int64_t)v * d + c0) = make_float4(a0, a1, a2, a3);
   }
 }
@@ -146,19 +214,14 @@ __global__ __launch_bounds__(128) void pos_sum_kernel(const bf16_t* __restrict__
   }
 }
 
-// start: int32 [P][V + 1], cursor: int32 [P][V], order: int32 [P][B * S] (scratch)
+// ends: int32 [P][V], order: int32 [P][B * S] (scratch)
 hipError_t embed_bwd(const bf16_t* dh, const int32_t* tokens, int B, int S, int d, int V, int P, float* G, int64_t stride,
-                     int64_t tok_off, int64_t pos_off, int32_t* start, int32_t* cursor, int32_t* order, hipStream_t s) {
+                     int64_t tok_off, int64_t pos_off, int32_t* ends, int32_t* order, hipStream_t s) {
   const int n = B * S;
-  if (d % 4) return hipErrorInvalidValue;
-  hipError_t e = fill_u32(reinterpret_cast<uint32_t*>(start), 0u, (int64_t)P * (V + 1), s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(tok_count_kernel, dim3((n + 255) / 256, P), dim3(256), 0, s, tokens, n, V, start);
-  (void)cursor;
-  if ((size_t)(n + 255) * sizeof(int32_t) > 64 * 1024 || n % 4) return hipErrorInvalidValue;   // (a member's tokens are staged in LDS)
-  hipLaunchKernelGGL(tok_start_kernel, dim3(P), dim3(256), 0, s, V, n, start);
-  hipLaunchKernelGGL(tok_place_kernel, dim3((n + 255) / 256, P), dim3(256), (size_t)((n + 255) / 256 * 256) * sizeof(int32_t), s, tokens, n, V, start, order);
-  hipLaunchKernelGGL(tok_sum_kernel, dim3(V, P), dim3(128), 0, s, dh, start, order, n, d, V, G, stride, tok_off);
+  if (d % 4 || n > TOK_MAX_POSITIONS) return hipErrorInvalidValue;
+  const int per = (V + TOK_THREADS - 1) / TOK_THREADS, span = (per < TOK_SPAN ? per : TOK_SPAN) | 1;
+  hipLaunchKernelGGL(tok_lists_kernel, dim3(P), dim3(TOK_THREADS), (size_t)TOK_THREADS * span * sizeof(int32_t), s, tokens, n, V, span, ends, order);
+  hipLaunchKernelGGL(tok_sum_kernel, dim3(V, P), dim3(128), 0, s, dh, ends, order, n, d, V, G, stride, tok_off);
   hipLaunchKernelGGL(pos_sum_kernel, dim3(S, P), dim3(128), 0, s, dh, B, S, d, G, stride, pos_off);
   return hipGetLastError();
 }
@@ -168,19 +231,6 @@ hipError_t embed_bwd(const bf16_t* dh, const int32_t* tokens, int B, int S, int 
 // is at most a few KB, so the second and third pass over it are served by the caches.
 // y = (x - mean) * rstd * g + b, eps = 1e-5; mean and rstd are kept.
 constexpr float LN_EPS = 1e-5f;
-__device__ __forceinline__ void load8(const bf16_t* p, float* v) {
-  const uint4 u = *reinterpret_cast<const uint4*>(p);
-  const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-  for (int q = 0; q < 4; ++q) { v[2 * q] = __uint_as_float(w[q] << 16); v[2 * q + 1] = __uint_as_float(w[q] & 0xffff0000u); }
-}
-__device__ __forceinline__ void load8(const float* p, float* v) {
-  const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
-  v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-}
-__device__ __forceinline__ void store8(bf16_t* p, const float* v) {
-  *reinterpret_cast<uint4*>(p) = make_uint4(f2bf_pair(v[0], v[1]), f2bf_pair(v[2], v[3]), f2bf_pair(v[4], v[5]), f2bf_pair(v[6], v[7]));
-}
 
 __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const bf16_t* __restrict__ x, int rows_per_member, int d,
                                                             const float* __restrict__ W32, int64_t stride, int64_t g_off,
@@ -310,22 +360,42 @@ __global__ __launch_bounds__(256) void layernorm_param_grad_kernel(const bf16_t*
     out[d + c] = ((pb[0][cl] + pb[1][cl]) + pb[2][cl]) + pb[3][cl];
   }
 }
-// adds the slabs' partial sums in a fixed order: a workgroup covers 64 of the 2 d columns (gains, then biases), its
+// adds the slabs' partial sums in a fixed order: a workgroup covers 64 of the 2 d columns (gains, then biases) of a LayerNorm, its
 // four thread groups each add a quarter of the slabs in slab order, and the four results are added in group order
-__global__ __launch_bounds__(256) void layernorm_param_combine_kernel(const float* __restrict__ part, int n_slabs, int d,
-                                                                      float* __restrict__ G, int64_t stride, int64_t g_off, int64_t b_off) {
+struct LnSites { int64_t g[LN_SITES], b[LN_SITES]; };   // where the gradients of each go
+__global__ __launch_bounds__(256) void layernorm_param_combine_kernel(const float* __restrict__ part, int64_t site_stride, int n_slabs, int d,
+                                                                      float* __restrict__ G, int64_t stride, LnSites sites) {
   __shared__ float red[4][64];
-  const int i = blockIdx.y;
+  const int i = blockIdx.y, site = blockIdx.z;
   const int cl = threadIdx.x & 63, grp = threadIdx.x >> 6;
   const int c = blockIdx.x * 64 + cl;  // 0..2d-1
-  const int per = (n_slabs + 3) / 4;
+  const int per = (n_slabs + 3) / 4, k_end = min(n_slabs, (grp + 1) * per);
   float acc = 0.f;
-  if (c < 2 * d)
-    for (int k = grp * per; k < min(n_slabs, (grp + 1) * per); ++k) acc += part[((int64_t)i * n_slabs + k) * 2 * d + c];
+  if (c < 2 * d) {
+    const float* __restrict__ p = part + site * site_stride + (int64_t)i * n_slabs * 2 * d + c;
+    for (int k = grp * per; k < k_end; k += 8) {   // (eight loads on their way)
+      float v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = k + q < k_end ? p[(int64_t)(k + q) * 2 * d] : 0.f;
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (k + q < k_end) acc += v[q];
+    }
+  }
   red[grp][cl] = acc;
   __syncthreads();
   if (grp == 0 && c < 2 * d)
-    G[(int64_t)i * stride + (c < d ? g_off + c : b_off + c - d)] = ((red[0][cl] + red[1][cl]) + red[2][cl]) + red[3][cl];
+    G[(int64_t)i * stride + (c < d ? sites.g[site] + c : sites.b[site] + c - d)] = ((red[0][cl] + red[1][cl]) + red[2][cl]) + red[3][cl];
+}
+hipError_t layernorm_param_combine(const float* part, int64_t site_stride, int n_sites, const int64_t* g_off, const int64_t* b_off, int n_slabs, int P, int d,
+                                   float* G, int64_t stride, hipStream_t s) {
+  for (int k = 0; k < n_sites; k += LN_SITES) {
+    const int count = n_sites - k < LN_SITES ? n_sites - k : LN_SITES;
+    LnSites sites{};
+    for (int q = 0; q < count; ++q) { sites.g[q] = g_off[k + q]; sites.b[q] = b_off[k + q]; }
+    hipLaunchKernelGGL(layernorm_param_combine_kernel, dim3((2 * d + 63) / 64, P, count), dim3(256), 0, s, part + k * site_stride, site_stride, n_slabs, d, G, stride, sites);
+  }
+  return hipGetLastError();
 }
 // part: float [P][LN_MAX_SLABS][2][d] (scratch)
 hipError_t layernorm_param_grad(const bf16_t* dy, const bf16_t* x, const float* mean, const float* rstd, int P, int rows, int d,
@@ -335,16 +405,17 @@ hipError_t layernorm_param_grad(const bf16_t* dy, const bf16_t* x, const float* 
   const int rows_per_slab = (rows + n_slabs - 1) / n_slabs;
   hipLaunchKernelGGL(layernorm_param_grad_kernel, dim3((d + 63) / 64, n_slabs, P), dim3(256), 0, s, dy, x, mean, rstd, rows, d,
                      rows_per_slab, part);
-  hipLaunchKernelGGL(layernorm_param_combine_kernel, dim3((2 * d + 63) / 64, P), dim3(256), 0, s, part, n_slabs, d, G, stride, g_off, b_off);
-  return hipGetLastError();
+  return layernorm_param_combine(part, 0, 1, &g_off, &b_off, n_slabs, P, d, G, stride, s);
 }
 
-// LayerNorm backward and the gradients of its gain and bias in one pass over dy and x: a workgroup takes a slab
+// LayerNorm backward and the sums behind the gradients of its gain and bias in one pass over dy and x: a workgroup takes a slab
 // of rows (wavefront w the rows w, w + 4, ... of the slab), a lane owns the same 8 J columns in every row, so the
-// gain is read once, a row is read once (it stays in registers between the two reductions and the output) and
+// gain is read once, a row is read once (it stays in registers between the two reductions and the output, the next one's loads on their way) and
 // the per-column sums dg += dy xhat, db += dy accumulate in registers; the four wavefronts are combined through
 // LDS in wavefront order and the slab's partial sums go to `part`, which layernorm_param_combine_kernel adds in
 // slab order.  J = ceil(d / 512).
+// Bound by memory for large batches (16 members' 4096 x 512 with residual and dropout, 340 MB: 58 us, 66 without the loads ahead), by a row's latency
+// for small ones (6 members' 720 x 192: 8.4 us, 10.8).
 template <int J>
 __global__ __launch_bounds__(256) void layernorm_bwd_fused_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ x,
                                                                   const float* __restrict__ mean, const float* __restrict__ rstd,
@@ -370,17 +441,40 @@ __global__ __launch_bounds__(256) void layernorm_bwd_fused_kernel(const bf16_t* 
     if (c < d) load8(g + c, gv[j]);
   }
   const int r_end = min(rows_per_member, (slab + 1) * rows_per_slab);
-  for (int r = slab * rows_per_slab + wave; r < r_end; r += 4) {
+  struct Row { uint4 dy[J], x[J], res[J]; uint32_t bits[J]; float mu, rs; };
+  auto fetch = [&](int r) {
+    Row q;
     const int64_t row = (int64_t)i * rows_per_member + r;
-    const float mu = mean[row], rs = rstd[row];
+    q.mu = mean[row];
+    q.rs = rstd[row];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int c = lane * 8 + 512 * j;
+      if (c < d) {
+        q.dy[j] = *reinterpret_cast<const uint4*>(dy + row * d + c);
+        q.x[j] = *reinterpret_cast<const uint4*>(x + row * d + c);
+        if (res) q.res[j] = *reinterpret_cast<const uint4*>(res + row * d + c);
+        if (out2) q.bits[j] = drop.mask[(int64_t)i * drop.mask_stride + (((int64_t)r * d + c) >> 3)];
+      }
+    }
+    return q;
+  };
+  int r = slab * rows_per_slab + wave;
+  Row next{};
+  if (r < r_end) next = fetch(r);
+  for (; r < r_end; r += 4) {
+    const Row q = next;
+    if (r + 4 < r_end) next = fetch(r + 4);   // (on its way while this row is reduced)
+    const int64_t row = (int64_t)i * rows_per_member + r;
+    const float mu = q.mu, rs = q.rs;
     float dv[J][8], xv[J][8];
     float a = 0.f, b = 0.f;
 #pragma unroll
     for (int j = 0; j < J; ++j) {
       const int c = lane * 8 + 512 * j;
       if (c < d) {
-        load8(dy + row * d + c, dv[j]);
-        load8(x + row * d + c, xv[j]);
+        unpack8(q.dy[j], dv[j]);
+        unpack8(q.x[j], xv[j]);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const float dyg = dv[j][e] * gv[j][e];
@@ -405,20 +499,12 @@ __global__ __launch_bounds__(256) void layernorm_bwd_fused_kernel(const bf16_t* 
         }
         if (res) {
           float rv[8];
-          load8(res + row * d + c, rv);
+          unpack8(q.res[j], rv);
 #pragma unroll
           for (int e = 0; e < 8; ++e) o[e] += rv[e];
         }
         store8(out + row * d + c, o);
-        if (out2) {
-          // the stored (bf16) value times the recorded keep factor, rounded once more
-          const uint32_t bits = drop.mask[(int64_t)i * drop.mask_stride + (((int64_t)r * d + c) >> 3)];
-          bf16_t w[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) w[e] = (bits >> e) & 1u ? d2bf((double)bf2f(f2bf(o[e])) * (double)drop_scale) : (bf16_t)(f2bf(o[e]) & 0x8000u);  // x * 0 keeps the sign
-          *reinterpret_cast<uint4*>(out2 + row * d + c) = make_uint4(w[0] | ((uint32_t)w[1] << 16), w[2] | ((uint32_t)w[3] << 16),
-                                                                      w[4] | ((uint32_t)w[5] << 16), w[6] | ((uint32_t)w[7] << 16));
-        }
+        if (out2) *reinterpret_cast<uint4*>(out2 + row * d + c) = keep_times_scale(o, q.bits[j], drop_scale);   // (the stored value times the recorded keep factor)
       }
     }
   }
@@ -440,15 +526,18 @@ __global__ __launch_bounds__(256) void layernorm_bwd_fused_kernel(const bf16_t* 
     po[c] = ((red[(0 * 2 + which) * d + col] + red[(1 * 2 + which) * d + col]) + red[(2 * 2 + which) * d + col]) + red[(3 * 2 + which) * d + col];
   }
 }
-// out = LayerNorm backward of dy (+ res), G[g_off], G[b_off] = gradients of gain and bias; part: float
-// [P][LN_FUSED_SLABS][2][d] (scratch).  d <= 2048.
-hipError_t layernorm_bwd_with_param_grad(const bf16_t* dy, const bf16_t* x, const float* mean, const float* rstd, int P, int rows,
-                                         int d, const float* W32, int64_t stride, int64_t g_off, int64_t b_off, const bf16_t* res,
-                                         bf16_t* out, float* G, float* part, hipStream_t s, bf16_t* out2, const DropRecord& drop) {
-  if (d % 8 || g_off % 4 || b_off % 4 || stride % 4 || d > 2048) return hipErrorInvalidValue;
+int layernorm_bwd_slabs(int rows) {
+  const int n = (rows + 15) / 16;
+  return n < LN_FUSED_SLABS ? n : LN_FUSED_SLABS;
+}
+// out = LayerNorm backward of dy (+ res); part[P][layernorm_bwd_slabs(rows)][2][d]: what layernorm_param_combine adds up to the gradients of gain and bias.
+// d <= 2048.
+hipError_t layernorm_bwd_with_param_sums(const bf16_t* dy, const bf16_t* x, const float* mean, const float* rstd, int P, int rows,
+                                         int d, const float* W32, int64_t stride, int64_t g_off, const bf16_t* res,
+                                         bf16_t* out, float* part, hipStream_t s, bf16_t* out2, const DropRecord& drop) {
+  if (d % 8 || g_off % 4 || stride % 4 || d > 2048) return hipErrorInvalidValue;
   if (out2 && !drop.mask) return hipErrorInvalidValue;
-  int n_slabs = (rows + 15) / 16;
-  if (n_slabs > LN_FUSED_SLABS) n_slabs = LN_FUSED_SLABS;
+  const int n_slabs = layernorm_bwd_slabs(rows);
   const int rows_per_slab = (rows + n_slabs - 1) / n_slabs;
   const size_t lds = (size_t)8 * d * sizeof(float);
   const dim3 grid(n_slabs, P);
@@ -458,9 +547,6 @@ hipError_t layernorm_bwd_with_param_grad(const bf16_t* dy, const bf16_t* x, cons
     hipLaunchKernelGGL(layernorm_bwd_fused_kernel<2>, grid, dim3(256), lds, s, dy, x, mean, rstd, rows, d, rows_per_slab, W32, stride, g_off, res, out, part, out2, drop);
   else
     hipLaunchKernelGGL(layernorm_bwd_fused_kernel<4>, grid, dim3(256), lds, s, dy, x, mean, rstd, rows, d, rows_per_slab, W32, stride, g_off, res, out, part, out2, drop);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(layernorm_param_combine_kernel, dim3((2 * d + 63) / 64, P), dim3(256), 0, s, part, n_slabs, d, G, stride, g_off, b_off);
   return hipGetLastError();
 }
 

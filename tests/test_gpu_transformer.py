@@ -146,6 +146,16 @@ def test_transformer_one_kernel_attention_of_padded_sequences(width, seq):
     assert np.max(np.abs(sc - sc_ref) / np.abs(sc_ref)) <= TOL_BF16, (sc, sc_ref)
 
 
+@pytest.mark.parametrize("vocab,seq,batch", [(8, 128, 12), (64, 64, 66), (15368, 32, 4)])
+def test_transformer_embedding_gradient_lists(vocab, seq, batch):
+    """Lists of positions far longer than a wavefront, lists of about its length (either way of ordering them), and a
+    vocabulary eight tokens beyond what is counted at once."""
+    wl = _reduced(P=2, vocab=vocab, d_model=16, heads=2, d_ff=24, n_blocks=1, seq=seq, batch=batch, n_train=max(16, batch), n_eval=batch, n_trunc=0)
+    pair = TransformerPair(wl, H=np.array([[1e-3, 0.0, 0.0], [5e-4, 0.1, 0.05]], dtype=np.float32))
+    # (the bounds of the one-kernel attention test above, for its reason)
+    _teacher_forced(pair, range(2), range(2), tol_grad=2 * TOL_GRAD_SMALL, tol_w=2 * TOL_GRAD_SMALL)
+
+
 def test_transformer_free_running_eval_and_exploit():
     pair = TransformerPair(_reduced(P=4))
     g, P = pair.gpu, 4
