@@ -17,30 +17,49 @@ namespace {
 
 constexpr uint32_t DOMAIN_GP_EPS = 14;
 
-// Rows 2B .. 3B-1 of the critic's input buffer: xhat_r = eps_r x_r + (1 - eps_r) G(z)_r from the real rows
-// 0 .. B-1 and the generated rows B .. 2B-1 (both bf16 already), eps_r from Philox counter
-// (step, member, 14, counter0 + r); the sum is formed in double and rounded once.
-__global__ __launch_bounds__(256) void wgan_interpolate_kernel(bf16_t* __restrict__ X, int B, int D, uint32_t step, uint32_t counter0,
-                                                               uint32_t k0, uint32_t k1) {
+// The 3B rows of the critic's input buffer.  0 .. B-1: real rows x_r, drawn as gather_rows does (counter element counter0 + r; t[i] += 1 when bump_t).
+// B .. 2B-1: the generated rows G(z)_r, from gen[i][gen_rows][D] rows gen_row .. .  2B .. 3B-1: xhat_r = eps_r x_r + (1 - eps_r) G(z)_r from the rounded
+// values, eps_r from Philox counter (step, member, 14, counter0 + r); the sum is formed in double and rounded once.
+// Eight elements of the three rows per thread (D a multiple of 8); bound by the latency of a launch, 6.1 us for 32 members of 64 x 784 (a gathering and an
+// interpolating kernel with 2-byte accesses: 10.3).
+__global__ __launch_bounds__(128) void wgan_rows_kernel(const float* __restrict__ train_x, int n_train, const bf16_t* __restrict__ gen, int gen_rows, int gen_row,
+                                                        bf16_t* __restrict__ X, int B, int D, uint32_t step, uint32_t counter0, uint32_t k0, uint32_t k1,
+                                                        int bump_t, int32_t* __restrict__ t) {
   const int r = blockIdx.x, i = blockIdx.y;
+  const uint32_t x = philox4x32_10(step, (uint32_t)i, DOMAIN_BATCH, counter0 + (uint32_t)r, k0, k1).x;
   const double eps = philox_unit(philox4x32_10(step, (uint32_t)i, DOMAIN_GP_EPS, counter0 + (uint32_t)r, k0, k1).x);
-  bf16_t* __restrict__ base = X + (int64_t)i * 3 * B * D;
-  const bf16_t* __restrict__ xr = base + (int64_t)r * D;
-  const bf16_t* __restrict__ xf = base + (int64_t)(B + r) * D;
-  bf16_t* __restrict__ xh = base + (int64_t)(2 * B + r) * D;
-  for (int c = threadIdx.x; c < D; c += blockDim.x)
-    xh[c] = d2bf(eps * (double)bf2f(xr[c]) + (1.0 - eps) * (double)bf2f(xf[c]));
+  const float* __restrict__ row = train_x + (int64_t)philox_bounded(x, (uint32_t)n_train) * D;
+  const bf16_t* __restrict__ fake = gen + ((int64_t)i * gen_rows + gen_row + r) * D;
+  bf16_t* __restrict__ out = X + ((int64_t)i * 3 * B + r) * D;
+  for (int c = threadIdx.x * 8; c < D; c += 1024) {
+    const float4 lo = *reinterpret_cast<const float4*>(row + c), hi = *reinterpret_cast<const float4*>(row + c + 4);
+    const uint4 f = *reinterpret_cast<const uint4*>(fake + c);
+    const uint32_t xr[4] = {f2bf_pair(lo.x, lo.y), f2bf_pair(lo.z, lo.w), f2bf_pair(hi.x, hi.y), f2bf_pair(hi.z, hi.w)}, xf[4] = {f.x, f.y, f.z, f.w};
+    uint32_t xh[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const bf16_t l = d2bf(eps * (double)__uint_as_float(xr[q] << 16) + (1.0 - eps) * (double)__uint_as_float(xf[q] << 16));
+      const bf16_t h = d2bf(eps * (double)__uint_as_float(xr[q] & 0xffff0000u) + (1.0 - eps) * (double)__uint_as_float(xf[q] & 0xffff0000u));
+      xh[q] = (uint32_t)l | (uint32_t)h << 16;
+    }
+    *reinterpret_cast<uint4*>(out + c) = make_uint4(xr[0], xr[1], xr[2], xr[3]);
+    *reinterpret_cast<uint4*>(out + (int64_t)B * D + c) = f;
+    *reinterpret_cast<uint4*>(out + (int64_t)2 * B * D + c) = make_uint4(xh[0], xh[1], xh[2], xh[3]);
+  }
+  if (bump_t && threadIdx.x == 0 && r == 0) t[i] += 1;
 }
 
 // One workgroup per member.  out: the critic's outputs, float [P][rows][32], column 0.
-// critic (rows = 3B): loss[2 i] = mean out[B..2B) - mean out[0..B) (the penalty is added later), and the
+// critic (rows = 3B): loss[2 i] = mean out[B..2B) - mean out[0..B) (the penalty is added by the generator's launch), and the
 // gradient of the outputs: -1/B on the real rows, +1/B on the generated rows, 1 on the interpolated rows (which
-// starts the input-gradient pass).  generator (rows = B): loss[2 i + 1] = -mean out, gradient -1/B.
+// starts the input-gradient pass).  generator (rows = B): loss[2 i + 1] = -mean out, gradient -1/B; the last critic
+// update's penalty, the weight times the mean of its rows' dev[i][B] (added in row order), is added to loss[2 i].
 // The outputs are brought into LDS by all threads and added in row order from there: one thread that read them
 // from memory one after the other (128 bytes apart) was the whole kernel, 30 us for B = 64 against 5.
-__global__ __launch_bounds__(256) void wgan_head_kernel(const float* __restrict__ out, int B, int rows, int generator,
+__global__ __launch_bounds__(256) void wgan_head_kernel(const float* __restrict__ out, int B, int rows, int generator, const double* __restrict__ dev, float weight,
                                                         bf16_t* __restrict__ dlogits, float* __restrict__ loss) {
-  extern __shared__ float col[];  // [generator ? B : 2 B] the outputs that enter the loss
+  extern __shared__ double sq[];  // [B], generator: the deviations; critic: the outputs that enter the loss, [2 B]
+  float* col = reinterpret_cast<float*>(sq);
   const int i = blockIdx.x, n = generator ? B : 2 * B;
   const float* __restrict__ o = out + (int64_t)i * rows * 32;
   for (int r = threadIdx.x; r < n; r += blockDim.x) col[r] = o[(int64_t)r * 32];
@@ -63,23 +82,31 @@ __global__ __launch_bounds__(256) void wgan_head_kernel(const float* __restrict_
       loss[2 * i] = (float)(fake / (double)B - real / (double)B);
     }
   }
+  if (!generator) return;
+  __syncthreads();   // (the outputs have been read)
+  for (int r = threadIdx.x; r < B; r += blockDim.x) sq[r] = dev[(int64_t)i * B + r];
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double total = 0.0;
+#pragma unroll 8
+    for (int r = 0; r < B; ++r) total += sq[r];
+    loss[2 * i] = (float)((double)loss[2 * i] + (double)weight * total / (double)B);
+  }
 }
 
-// One workgroup per member, a wavefront per row.  g: the critic's input gradient on the interpolated rows, float
-// [P][B][D] (D a multiple of 8).  penalty = weight * mean_r (|g_r| - 1)^2 is added to loss[2 i];
+// A wavefront per row, four to a workgroup.  g: the critic's input gradient on the interpolated rows, float
+// [P][B][D] (D a multiple of 8).  dev[i][r] = (|g_r| - 1)^2, whose mean times the weight is the penalty;
 // c_r = (2 weight / B) (|g_r| - 1) / |g_r| g_r, the gradient of the penalty with respect to g_r, goes (bf16) to
 // rows 2B .. 3B-1 of the critic's input buffer, where the weight-gradient contraction of the first layer finds it.
-// Row norms are summed in double, lanes in a fixed butterfly order, rows in order.
+// Row norms are summed in double, lanes in a fixed butterfly order.
 // Bound by memory latency (6 MB in all for 32 members of 64 x 784): each wavefront reads its row once, as 16-byte
 // loads that are all in flight together, and keeps up to PEN_VEC * 256 elements in registers between the norm and
-// the scaling (longer rows read the rest again).  With four wavefronts per member, 4-byte loads and a second pass
-// over memory the kernel took 106 us at those sizes, now 15.
+// the scaling (longer rows read the rest again).  5.1 us at those sizes; one workgroup per member, which also added the penalty to the loss, took 15.
 constexpr int PEN_VEC = 4;
-__global__ __launch_bounds__(1024) void wgan_penalty_kernel(const float* __restrict__ g, int B, int D, float weight,
-                                                            bf16_t* __restrict__ X, float* __restrict__ loss) {
-  extern __shared__ double sq[];  // [B] squared deviations
-  const int i = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
-  for (int r = wave; r < B; r += waves) {
+__global__ __launch_bounds__(256) void wgan_penalty_kernel(const float* __restrict__ g, int B, int D, float weight,
+                                                           bf16_t* __restrict__ X, double* __restrict__ dev) {
+  const int i = blockIdx.y, lane = threadIdx.x & 63, r = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r < B) {
     const float* __restrict__ gr = g + ((int64_t)i * B + r) * D;
     float4 v[PEN_VEC];
 #pragma unroll
@@ -107,14 +134,7 @@ __global__ __launch_bounds__(1024) void wgan_penalty_kernel(const float* __restr
       }
     }
     for (int c = PEN_VEC * 256 + lane; c < D; c += 64) xr[c] = d2bf(scale * (double)gr[c]);
-    if (lane == 0) sq[r] = (norm - 1.0) * (norm - 1.0);
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double total = 0.0;
-#pragma unroll 8
-    for (int r = 0; r < B; ++r) total += sq[r];
-    loss[2 * i] = (float)((double)loss[2 * i] + (double)weight * total / (double)B);
+    if (lane == 0) dev[(int64_t)i * B + r] = (norm - 1.0) * (norm - 1.0);
   }
 }
 
@@ -179,25 +199,35 @@ pbt_status gan_check_and_plan(const pbt_config* c, Plan* pl, Carver* w) {
   if (wgan && 3 + c->n_critic > 10) return fail(nullptr, PBT_EUNSUPPORTED, "at most 7 critic updates per step (latent sub-streams 3 .. 9)");
   // critic buffers hold real + generated rows, and for WGAN-GP the interpolated rows behind them
   const int64_t P = c->P, B = c->batch, R = (wgan ? 3 : 2) * B, E = c->n_eval, D = c->dims2[0];
-  g.o_zin = w->take((size_t)P * B * c->dims[0] * 2);
-  for (int l = 0; l < Lg; ++l) {
-    g.o_ga[l] = w->take((size_t)P * B * c->dims[l + 1] * 2);
-    g.o_gz[l] = w->take((size_t)P * B * c->dims[l + 1] * 2);
-    g.o_gdz[l] = w->take((size_t)P * B * c->dims[l + 1] * 2);
-  }
-  g.o_dx = w->take((size_t)P * R * D * 2);
-  for (int l = 0; l < Ld - 1; ++l) {
-    g.o_da[l] = w->take((size_t)P * R * c->dims2[l + 1] * 2);
-    g.o_dz[l] = w->take((size_t)P * R * c->dims2[l + 1] * 2);
-    g.o_ddz[l] = w->take((size_t)P * R * c->dims2[l + 1] * 2);
-  }
-  g.o_dlogits = w->take((size_t)P * R * 32 * 2);
-  g.o_rowloss = w->take((size_t)P * R * 4);
-  g.o_hout = g.o_gin = 0;
-  if (wgan) {
-    g.o_hout = w->take((size_t)P * R * 32 * 4);
-    g.o_gin = w->take((size_t)P * B * D * 4);
-  }
+  // The generator is fixed while the critic is updated, so one forward pass forms the generated rows of all of a step's critic updates: more rows per launch
+  // (32 members, 5 updates of 64 rows, 100-256-512-784: 55 us instead of five passes of 24), and more scratch; where that would push a step past the
+  // array of pbt_step_static, a pass per update.
+  auto carve = [&](Carver* at, int n_ahead) {
+    g.n_ahead = n_ahead;
+    g.o_zin = at->take((size_t)P * n_ahead * B * c->dims[0] * 2);
+    for (int l = 0; l < Lg; ++l) {
+      g.o_ga[l] = at->take((size_t)P * n_ahead * B * c->dims[l + 1] * 2);
+      g.o_gz[l] = at->take((size_t)P * B * c->dims[l + 1] * 2);
+      g.o_gdz[l] = at->take((size_t)P * B * c->dims[l + 1] * 2);
+    }
+    g.o_dx = at->take((size_t)P * R * D * 2);
+    for (int l = 0; l < Ld - 1; ++l) {
+      g.o_da[l] = at->take((size_t)P * R * c->dims2[l + 1] * 2);
+      g.o_dz[l] = at->take((size_t)P * R * c->dims2[l + 1] * 2);
+      g.o_ddz[l] = at->take((size_t)P * R * c->dims2[l + 1] * 2);
+    }
+    g.o_dlogits = at->take((size_t)P * R * 32 * 2);
+    g.o_rowloss = at->take((size_t)P * R * 4);
+    g.o_hout = g.o_gin = 0;
+    if (wgan) {
+      g.o_hout = at->take((size_t)P * R * 32 * 4);
+      g.o_gin = at->take((size_t)P * B * D * 4);
+    }
+    return at->off;
+  };
+  Carver trial = *w;
+  const int n_ahead = wgan && (carve(&trial, c->n_critic) <= PBT_STATIC_SCRATCH_BYTES || carve(&(trial = *w), 1) > PBT_STATIC_SCRATCH_BYTES) ? c->n_critic : 1;
+  carve(w, n_ahead);
   pl->step_scratch_bytes = w->off;
   // eval: latents, two ping-pong hidden buffers, generated rows, held-out rows (bf16), norms, partial sums
   int64_t maxh = 8;
@@ -235,22 +265,24 @@ static pbt_status gan_step_wgan(pbt_handle* h, const float* train_x, uint32_t st
   bf16_t* dlogits = h->sc<bf16_t>(g.o_dlogits);
   float* hout = h->sc<float>(g.o_hout);
   float* gin = h->sc<float>(g.o_gin);
+  double* dev = h->sc<double>(g.o_rowloss);   // [P][B]: the rows' part in the penalty (the array has 3 B floats per member)
   float* loss = h->st<float>(p.o_loss);
   const int Ld = c.n_layers2, Kh = c.dims2[Ld - 1];
   const int first = c.n_layers, head = c.n_layers + Ld - 1;  // layout indices of the critic's first and output layer
   const uint32_t k0 = (uint32_t)c.seed, k1 = (uint32_t)(c.seed >> 32);
   pbt_status st;
   for (int k = 0; k < K; ++k) {
-    PBT_LAUNCH(h, PBT_K_FETCH, s, gather_rows(train_x, c.n_train, D, P, B, (int64_t)R * D, step, c.seed, b.dA[0], h->st<int32_t>(p.o_t), s,
-                                              (uint32_t)(k * B), k == 0));
-    PBT_LAUNCH(h, PBT_K_FETCH, s, latent_normal(b.gA[0], P, B, c.dims[0], step, 3 + k, c.seed, s));
-    if ((st = forward(h, gnet, gnet.L, B, b.gA, nullptr, b.dA[0] + (int64_t)B * D, (int64_t)R * D, s)) != PBT_OK) return st;
-    hipLaunchKernelGGL(wgan_interpolate_kernel, dim3(B, P), dim3(256), 0, s, b.dA[0], B, D, step, (uint32_t)(k * B), k0, k1);
+    if (k % g.n_ahead == 0) {
+      PBT_LAUNCH(h, PBT_K_FETCH, s, latent_normal(b.gA[0], P, B, c.dims[0], step, 3 + k, c.seed, s, g.n_ahead));
+      if ((st = forward(h, gnet, gnet.L, g.n_ahead * B, b.gA, nullptr, nullptr, 0, s)) != PBT_OK) return st;
+    }
+    hipLaunchKernelGGL(wgan_rows_kernel, dim3(B, P), dim3(128), 0, s, train_x, c.n_train, b.gA[gnet.L], g.n_ahead * B, k % g.n_ahead * B, b.dA[0], B, D, step,
+                       (uint32_t)(k * B), k0, k1, k == 0 ? 1 : 0, h->st<int32_t>(p.o_t));
     PBT_HIP(h, hipGetLastError());
     if ((st = forward(h, dnet, Ld - 1, R, b.dA, b.dZ, nullptr, 0, s)) != PBT_OK) return st;
     PBT_LAUNCH(h, PBT_K_HEAD, s, head_fwd_loss(b.dA[Ld - 1], (int64_t)R * Kh, W16 + p.lay.w_off[head], S, W32 + p.lay.b_off[head], S,
                                                nullptr, 0, P, R, Kh, 1, 0.f, -2, nullptr, hout, 0, s));
-    hipLaunchKernelGGL(wgan_head_kernel, dim3(P), dim3(256), (size_t)2 * B * sizeof(float), s, hout, B, R, 0, dlogits, loss);
+    hipLaunchKernelGGL(wgan_head_kernel, dim3(P), dim3(256), (size_t)2 * B * sizeof(float), s, hout, B, R, 0, dev, c.gp_weight, dlogits, loss);
     PBT_HIP(h, hipGetLastError());
     // input gradients of every layer on all 3B rows (no weight gradients yet), down to g = dz_0 W_0^T on the interpolated rows
     PBT_LAUNCH(h, PBT_K_HEAD, s, head_dgrad(dlogits, W16 + p.lay.w_off[head], S, b.dZ[Ld - 2], b.ddZ[Ld - 2], P, R, Kh, 1, dnet.hidden_act, s));
@@ -260,7 +292,7 @@ static pbt_status gan_step_wgan(pbt_handle* h, const float* train_x, uint32_t st
       GemmOperands o{b.ddZ[0] + (int64_t)2 * B * N0, N0, (int64_t)R * N0, false, W16 + p.lay.w_off[first], N0, S, true, B, D, N0, P};
       PBT_LAUNCH(h, PBT_K_GEMM_DGRAD, s, gemm_store_f32(o, gin, D, (int64_t)B * D, s));
     }
-    hipLaunchKernelGGL(wgan_penalty_kernel, dim3(P), dim3(1024), (size_t)B * sizeof(double), s, gin, B, D, c.gp_weight, b.dA[0], loss);
+    hipLaunchKernelGGL(wgan_penalty_kernel, dim3((B + 3) / 4, P), dim3(256), 0, s, gin, B, D, c.gp_weight, b.dA[0], dev);
     PBT_HIP(h, hipGetLastError());
     // c_{l+1} = (c_l W_l) * act'(z_l) on the interpolated rows, written over those rows of the next layer's input
     for (int l = 0; l < Ld - 1; ++l) {
@@ -295,7 +327,7 @@ static pbt_status gan_step_wgan(pbt_handle* h, const float* train_x, uint32_t st
   if ((st = forward(h, dnet, Ld - 1, B, dA, b.dZ, nullptr, 0, s)) != PBT_OK) return st;
   PBT_LAUNCH(h, PBT_K_HEAD, s, head_fwd_loss(dA[Ld - 1], (int64_t)B * Kh, W16 + p.lay.w_off[head], S, W32 + p.lay.b_off[head], S,
                                              nullptr, 0, P, B, Kh, 1, 0.f, -2, nullptr, hout, 0, s));
-  hipLaunchKernelGGL(wgan_head_kernel, dim3(P), dim3(256), (size_t)B * sizeof(float), s, hout, B, B, 1, dlogits, loss);
+  hipLaunchKernelGGL(wgan_head_kernel, dim3(P), dim3(256), (size_t)B * sizeof(double), s, hout, B, B, 1, dev, c.gp_weight, dlogits, loss);
   PBT_HIP(h, hipGetLastError());
   PBT_LAUNCH(h, PBT_K_HEAD, s, head_dgrad(dlogits, W16 + p.lay.w_off[head], S, b.dZ[Ld - 2], b.ddZ[Ld - 2], P, B, Kh, 1, dnet.hidden_act, s));
   if ((st = backward(h, dnet, Ld - 1, B, dA, b.dZ, b.ddZ, false, nullptr, b.gZ[gnet.L - 1], b.gdZ[gnet.L - 1], gnet.out_act, s)) != PBT_OK) return st;

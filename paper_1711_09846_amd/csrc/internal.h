@@ -122,14 +122,14 @@ hipError_t gemm_wgrad_optimizer(const GemmOperands& o, const OptArgs& a, int64_t
 
 // out[P][rows][d] (bf16) = standard normal latents: element e uses Philox counter
 // (c0, member, DOMAIN_LATENT + substream, e / 4); words (0,1) and (2,3) are one Box-Muller pair each
-// (cosine branch for even e, sine for odd), evaluated in double.
-hipError_t latent_normal(bf16_t* out, int P, int rows, int d, uint32_t c0, int substream, uint64_t seed, hipStream_t s);
+// (cosine branch for even e, sine for odd), evaluated in double.  n_sub > 1: out[P][n_sub][rows][d], sub-streams substream, substream + 1, ...
+hipError_t latent_normal(bf16_t* out, int P, int rows, int d, uint32_t c0, int substream, uint64_t seed, hipStream_t s, int n_sub = 1);
 // out[batch][rows] = sum_k X[batch][rows][d]^2 (float)
 hipError_t row_sqnorm(const bf16_t* X, int batch, int rows, int d, float* out, hipStream_t s);
 // gathers rows of a float data set into bf16 X[P][ld_rows][d] rows 0..B-1 (Philox domain 1, counter element
-// counter0 + r for row r); t[i] += 1 when bump_t
+// r for row r); t[i] += 1
 hipError_t gather_rows(const float* train_x, int n_train, int d, int P, int B, int64_t member_stride, uint32_t step,
-                       uint64_t seed, bf16_t* X16, int32_t* t, hipStream_t s, uint32_t counter0 = 0, bool bump_t = true);
+                       uint64_t seed, bf16_t* X16, int32_t* t, hipStream_t s);
 // score[i] = -( sxx[i] + syy[0] - 2 sxy[i] ) * inv_n2 where each s is the sum of `tiles` partials
 hipError_t mmd_combine(const float* pxx, int txx, const float* pyy, int tyy, const float* pxy, int txy, int P, float inv_n2,
                        float* score, hipStream_t s);

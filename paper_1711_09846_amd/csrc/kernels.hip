@@ -187,36 +187,37 @@ hipError_t optimizer_step(const OptArgs& a, hipStream_t s) {
 
 // ---- GAN workload: latents, real-row gather, squared norms, MMD combination -------------------
 
-__global__ __launch_bounds__(256) void latent_normal_kernel(bf16_t* __restrict__ out, int64_t per_member, uint32_t c0,
+// blockIdx.z: sub-streams side by side in a member's array
+__global__ __launch_bounds__(256) void latent_normal_kernel(bf16_t* __restrict__ out, int64_t count, uint32_t c0,
                                                             uint32_t domain, uint32_t k0, uint32_t k1) {
   const int i = blockIdx.y;
   const int64_t blk = (int64_t)blockIdx.x * 256 + threadIdx.x;  // block of 4 elements
-  if (blk * 4 >= per_member) return;
-  const u32x4 w = philox4x32_10(c0, (uint32_t)i, domain, (uint32_t)blk, k0, k1);
+  if (blk * 4 >= count) return;
+  const u32x4 w = philox4x32_10(c0, (uint32_t)i, domain + blockIdx.z, (uint32_t)blk, k0, k1);
   // (cos and sin of 2 pi u through sincospi(2 u): no reduction of a large argument modulo pi)
   const double r1 = sqrt(-2.0 * log(philox_unit(w.x))), r2 = sqrt(-2.0 * log(philox_unit(w.z)));
   double s1, c1, s2, c2;
   sincospi(2.0 * philox_unit(w.y), &s1, &c1);
   sincospi(2.0 * philox_unit(w.w), &s2, &c2);
   const double v[4] = {r1 * c1, r1 * s1, r2 * c2, r2 * s2};
-  bf16_t* __restrict__ o = out + (int64_t)i * per_member + blk * 4;
+  bf16_t* __restrict__ o = out + ((int64_t)i * gridDim.z + blockIdx.z) * count + blk * 4;
 #pragma unroll
   for (int e = 0; e < 4; ++e)
-    if (blk * 4 + e < per_member) o[e] = f2bf((float)v[e]);
+    if (blk * 4 + e < count) o[e] = f2bf((float)v[e]);
 }
-hipError_t latent_normal(bf16_t* out, int P, int rows, int d, uint32_t c0, int substream, uint64_t seed, hipStream_t s) {
-  const int64_t per_member = (int64_t)rows * d;
-  const int64_t blocks4 = (per_member + 3) / 4;
-  hipLaunchKernelGGL(latent_normal_kernel, dim3((unsigned)((blocks4 + 255) / 256), P), dim3(256), 0, s, out, per_member, c0,
+hipError_t latent_normal(bf16_t* out, int P, int rows, int d, uint32_t c0, int substream, uint64_t seed, hipStream_t s, int n_sub) {
+  const int64_t count = (int64_t)rows * d;
+  const int64_t blocks4 = (count + 3) / 4;
+  hipLaunchKernelGGL(latent_normal_kernel, dim3((unsigned)((blocks4 + 255) / 256), P, n_sub), dim3(256), 0, s, out, count, c0,
                      (uint32_t)(DOMAIN_LATENT + substream), (uint32_t)seed, (uint32_t)(seed >> 32));
   return hipGetLastError();
 }
 
 __global__ __launch_bounds__(256) void gather_rows_kernel(const float* __restrict__ train_x, int n_train, int d,
                                                           int64_t member_stride, uint32_t step, uint32_t k0, uint32_t k1,
-                                                          bf16_t* __restrict__ X16, int32_t* __restrict__ t, uint32_t counter0) {
+                                                          bf16_t* __restrict__ X16, int32_t* __restrict__ t) {
   const int r = blockIdx.x, i = blockIdx.y;
-  const uint32_t x = philox4x32_10(step, (uint32_t)i, DOMAIN_BATCH, counter0 + (uint32_t)r, k0, k1).x;
+  const uint32_t x = philox4x32_10(step, (uint32_t)i, DOMAIN_BATCH, (uint32_t)r, k0, k1).x;
   const float* __restrict__ row = train_x + (int64_t)philox_bounded(x, (uint32_t)n_train) * d;
   bf16_t* __restrict__ o = X16 + (int64_t)i * member_stride + (int64_t)r * d;
   if ((d & 3) == 0) {  // rows are 16-byte aligned: four floats in, four bf16 out per access
@@ -230,13 +231,13 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const float* __restric
   } else {
     for (int c = threadIdx.x; c < d; c += 256) o[c] = f2bf(row[c]);
   }
-  if (t != nullptr && threadIdx.x == 0 && r == 0) t[i] += 1;
+  if (threadIdx.x == 0 && r == 0) t[i] += 1;
 }
 hipError_t gather_rows(const float* train_x, int n_train, int d, int P, int B, int64_t member_stride, uint32_t step,
-                       uint64_t seed, bf16_t* X16, int32_t* t, hipStream_t s, uint32_t counter0, bool bump_t) {
+                       uint64_t seed, bf16_t* X16, int32_t* t, hipStream_t s) {
   if ((d & 3) == 0 && (member_stride & 3)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(gather_rows_kernel, dim3(B, P), dim3(256), 0, s, train_x, n_train, d, member_stride, step,
-                     (uint32_t)seed, (uint32_t)(seed >> 32), X16, bump_t ? t : nullptr, counter0);
+                     (uint32_t)seed, (uint32_t)(seed >> 32), X16, t);
   return hipGetLastError();
 }
 

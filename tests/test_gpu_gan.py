@@ -166,6 +166,21 @@ def test_wgan_gp_one_critic_step_gradient_against_the_oracle():
             assert np.linalg.norm(got_b - gb) <= TOL_BF16 * max(np.linalg.norm(gb), 1e-3), (i, l, "b")
 
 
+def test_wgan_gp_generator_pass_per_critic_update():
+    """A step whose scratch fits the library's static array (8 MiB) only with the generated rows of one critic update at a time: 7.0 MB so, 9.4 MB with those
+    of all seven.  It has to be accepted there, and both ways of calling it have to agree with the oracle."""
+    wl = _reduced(P=2).replace(objective="wgan_gp", n_critic=7, gp_weight=10.0, batch=768)
+    pair = GanPair(wl)
+    g = pair.gpu
+    for s, step in enumerate((g.step_static, g.step)):
+        step(pair.d_train, s)
+        loss_ref = pair.step_ref(s)
+        loss = g.get(binding.ARR_LOSS)
+        assert np.max(np.abs(loss - loss_ref) / np.maximum(np.abs(loss_ref), FLOOR_WGAN)) <= TOL_BF16, (s, loss, loss_ref)
+        for i in range(2):
+            assert pair.member_errors(i, binding.ARR_W32, "theta")[0] <= TOL_BF16, (s, i)
+
+
 def test_wgan_gp_full_size_steps():
     """P = 32 at the full shape with 5 critic updates per step: sampled members per step against the oracle."""
     wl = workloads.GAN_MLP_WGAN_GP
