@@ -347,7 +347,7 @@ pbt_status step_bf16(pbt_handle* h, const float* train_x, const int32_t* train_y
   PBT_LAUNCH(h, PBT_K_HEAD, s, head_fwd_loss(h->sc<bf16_t>(p.o_act[L - 1]), (int64_t)B * Kh, W16 + p.lay.w_off[L - 1], S,
                                              W32 + p.lay.b_off[L - 1], S, Y, B, P, B, Kh, C, 1.f / (float)B, -1, dlogits,
                                              rowloss, B, s));
-  PBT_LAUNCH(h, PBT_K_HEAD, s, row_reduce(rowloss, B, P, B, 1.f / (float)B, h->st<float>(p.o_loss), 1, s));
+  const HeadLoss loss{rowloss, 1.f / (float)B, h->st<float>(p.o_loss), 1};
   {
     // dW_head[Kh][C] = X^T dlogits (contraction over the B rows), db_head = column sums
     GemmOperands wg{h->sc<bf16_t>(p.o_act[L - 1]), Kh, (int64_t)B * Kh, true, dlogits, 32, (int64_t)B * 32, false,
@@ -358,7 +358,9 @@ pbt_status step_bf16(pbt_handle* h, const float* train_x, const int32_t* train_y
   }
   if (L >= 2)
     PBT_LAUNCH(h, PBT_K_HEAD, s, head_dgrad(dlogits, W16 + p.lay.w_off[L - 1], S, h->sc<bf16_t>(p.o_z[L - 2]),
-                                            h->sc<bf16_t>(p.o_dz[L - 2]), P, B, Kh, C, c.act, s));
+                                            h->sc<bf16_t>(p.o_dz[L - 2]), P, B, Kh, C, c.act, s, loss));
+  else
+    PBT_LAUNCH(h, PBT_K_HEAD, s, row_reduce(rowloss, B, P, B, loss.scale, loss.out, 1, s));
   OptArgs oa{W32, h->st<float>(p.o_opt0), c.optimizer == PBT_OPT_ADAM ? h->st<float>(p.o_opt1) : nullptr, W16, G,
              0, S, h->st<float>(p.o_hyper), h->st<int32_t>(p.o_t), S, P, c.n_hyper, c.optimizer, p.col_lr, p.col_beta1, p.col_wd,
              c.opt_const[0], c.opt_const[1], c.opt_const[2], c.opt_const[3]};

@@ -362,14 +362,14 @@ pbt_status gan_step(pbt_handle* h, const float* train_x, uint32_t step, hipStrea
   if ((st = forward(h, dnet, Ld - 1, R, b.dA, b.dZ, nullptr, 0, s)) != PBT_OK) return st;
   PBT_LAUNCH(h, PBT_K_HEAD, s, head_fwd_loss(b.dA[Ld - 1], (int64_t)R * Kh, W16 + p.lay.w_off[head], S, W32 + p.lay.b_off[head], S,
                                              nullptr, 0, P, R, Kh, 1, 1.f / (float)B, B, dlogits, rowloss, R, s));
-  PBT_LAUNCH(h, PBT_K_HEAD, s, row_reduce(rowloss, R, P, R, 1.f / (float)B, loss, 2, s));
   {
     GemmOperands wg{b.dA[Ld - 1], Kh, (int64_t)R * Kh, true, dlogits, 32, (int64_t)R * 32, false, Kh, 1, R, P};
     wg.b_cols = 32;
     wg.colsum = G + p.lay.b_off[head]; wg.colsum_stride = S;   // the bias gradient, a by-product of the same launch
     PBT_LAUNCH(h, PBT_K_HEAD, s, gemm_store_f32(wg, G + p.lay.w_off[head], 1, S, s));
   }
-  PBT_LAUNCH(h, PBT_K_HEAD, s, head_dgrad(dlogits, W16 + p.lay.w_off[head], S, b.dZ[Ld - 2], b.ddZ[Ld - 2], P, R, Kh, 1, dnet.hidden_act, s));
+  PBT_LAUNCH(h, PBT_K_HEAD, s, head_dgrad(dlogits, W16 + p.lay.w_off[head], S, b.dZ[Ld - 2], b.ddZ[Ld - 2], P, R, Kh, 1, dnet.hidden_act, s,
+                                            HeadLoss{rowloss, 1.f / (float)B, loss, 2}));
   const bool fused = c.fuse_optimizer != 0;
   const OptArgs oa_d = adam_args(h, g.d_begin, g.d_count, g.col_lr_d), oa_g = adam_args(h, 0, g.g_count, g.col_lr_g);
   if ((st = backward(h, dnet, Ld - 1, R, b.dA, b.dZ, b.ddZ, true, fused ? &oa_d : nullptr, nullptr, nullptr, 0, s)) != PBT_OK) return st;
@@ -389,8 +389,8 @@ pbt_status gan_step(pbt_handle* h, const float* train_x, uint32_t step, hipStrea
     if ((st = forward(h, dnet, Ld - 1, B, dA, b.dZ, nullptr, 0, s)) != PBT_OK) return st;
     PBT_LAUNCH(h, PBT_K_HEAD, s, head_fwd_loss(dA[Ld - 1], (int64_t)B * Kh, W16 + p.lay.w_off[head], S, W32 + p.lay.b_off[head], S,
                                                nullptr, 0, P, B, Kh, 1, 1.f / (float)B, B, dlogits, rowloss, B, s));
-    PBT_LAUNCH(h, PBT_K_HEAD, s, row_reduce(rowloss, B, P, B, 1.f / (float)B, loss + 1, 2, s));
-    PBT_LAUNCH(h, PBT_K_HEAD, s, head_dgrad(dlogits, W16 + p.lay.w_off[head], S, b.dZ[Ld - 2], b.ddZ[Ld - 2], P, B, Kh, 1, dnet.hidden_act, s));
+    PBT_LAUNCH(h, PBT_K_HEAD, s, head_dgrad(dlogits, W16 + p.lay.w_off[head], S, b.dZ[Ld - 2], b.ddZ[Ld - 2], P, B, Kh, 1, dnet.hidden_act, s,
+                                              HeadLoss{rowloss, 1.f / (float)B, loss + 1, 2}));
     // through the discriminator down to its input, no weight gradients; the input gradient is
     // multiplied by the derivative of the generator's output activation on the way
     if ((st = backward(h, dnet, Ld - 1, B, dA, b.dZ, b.ddZ, false, nullptr, b.gZ[gnet.L - 1], b.gdZ[gnet.L - 1], gnet.out_act, s)) != PBT_OK) return st;

@@ -13,6 +13,7 @@
 // of a row); the partial sums are added in wavefront order.  Backward: a wavefront owns 32 rows and
 // passes its 32x64 block through LDS so that memory sees 16-byte accesses of whole 128-byte rows.
 #include "common.h"
+#include "row_sum.h"
 #include "internal.h"
 
 namespace pbt {
@@ -218,7 +219,14 @@ constexpr int DG_PITCH = DG_COLS + 4;   // floats: 16-byte writes of a wavefront
 __global__ __launch_bounds__(256) void head_dgrad_kernel(const bf16_t* __restrict__ dlogits,
                                                          const bf16_t* __restrict__ W16, int64_t sw,
                                                          const bf16_t* __restrict__ Zprev, bf16_t* __restrict__ dZprev,
-                                                         int rows, int K, int C, int act) {
+                                                         int rows, int K, int C, int act, HeadLoss loss) {
+  if (loss.out && blockIdx.x == gridDim.x - 1) {
+    if (blockIdx.y == 0 && threadIdx.x < 64) {
+      const float sum = member_row_sum(loss.rowloss + (int64_t)blockIdx.z * rows, rows, nullptr, 64);
+      if (threadIdx.x == 0) loss.out[(int64_t)blockIdx.z * loss.out_stride] = sum * loss.scale;
+    }
+    return;
+  }
   __shared__ __attribute__((aligned(16))) bf16_t Ws[DG_COLS * 40];   // [64 columns k][32 classes + 8]
   __shared__ __attribute__((aligned(16))) float Cs[4 * 32 * DG_PITCH];  // one 32 x 64 strip per wavefront
   const int i = blockIdx.z;
@@ -308,10 +316,18 @@ __global__ __launch_bounds__(256) void head_dgrad_kernel(const bf16_t* __restric
 }
 
 hipError_t head_dgrad(const bf16_t* dlogits, const bf16_t* W16, int64_t sw, const bf16_t* Zprev, bf16_t* dZprev, int P,
-                      int rows, int K, int C, int act, hipStream_t s) {
+                      int rows, int K, int C, int act, hipStream_t s, const HeadLoss& loss) {
   if (C > HEAD_NP || C < 1) return hipErrorInvalidValue;
-  dim3 grid((K + DG_COLS - 1) / DG_COLS, (rows + HEAD_ROWS - 1) / HEAD_ROWS, P);
-  hipLaunchKernelGGL(head_dgrad_kernel, grid, dim3(256), 0, s, dlogits, W16, sw, Zprev, dZprev, rows, K, C, act);
+  // Up to 1024 rows, whose sum is one wavefront's work, a workgroup beside the others adds up the loss (a launch of 3.0 to 4.8 us for that: ragged
+  // networks' step 100.7 -> 99.2 us, GAN 458.5 -> 454.1).
+  HeadLoss beside = loss;
+  if (loss.out && row_sum_threads(rows) > 64) {
+    const hipError_t e = row_reduce(loss.rowloss, rows, P, rows, loss.scale, loss.out, loss.out_stride, s);
+    if (e != hipSuccess) return e;
+    beside.out = nullptr;
+  }
+  dim3 grid((K + DG_COLS - 1) / DG_COLS + (beside.out ? 1 : 0), (rows + HEAD_ROWS - 1) / HEAD_ROWS, P);
+  hipLaunchKernelGGL(head_dgrad_kernel, grid, dim3(256), 0, s, dlogits, W16, sw, Zprev, dZprev, rows, K, C, act, beside);
   return hipGetLastError();
 }
 

@@ -81,9 +81,15 @@ hipError_t gather_batch(const float* train_x, const int32_t* train_y, int n_trai
 hipError_t head_fwd_loss(const bf16_t* A, int64_t sa, const bf16_t* W16, int64_t sw, const float* bias, int64_t sbias,
                          const int32_t* labels, int64_t sy, int P, int rows, int K, int C, float gscale, int n_pos,
                          bf16_t* dlogits, float* rowloss, int64_t srowloss, hipStream_t s);
-// dZprev[P][rows][K] = (dlogits W^T) * act'(Zprev)
+// dZprev[P][rows][K] = (dlogits W^T) * act'(Zprev); with a loss, as row_reduce: out[i * out_stride] = scale * sum_r rowloss[i][r] over the rows
+struct HeadLoss {
+  const float* rowloss = nullptr;   // [P][rows]
+  float scale = 0.f;
+  float* out = nullptr;
+  int out_stride = 0;
+};
 hipError_t head_dgrad(const bf16_t* dlogits, const bf16_t* W16, int64_t sw, const bf16_t* Zprev, bf16_t* dZprev, int P,
-                      int rows, int K, int C, int act, hipStream_t s);
+                      int rows, int K, int C, int act, hipStream_t s, const HeadLoss& loss = HeadLoss());
 // out[i * out_stride] = scale * sum_r rowval[i][r]   (one wavefront per member, fixed order)
 hipError_t row_reduce(const float* rowval, int64_t srow, int P, int rows, float scale, float* out, int out_stride,
                       hipStream_t s);

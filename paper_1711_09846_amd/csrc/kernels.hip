@@ -111,7 +111,7 @@ __global__ __launch_bounds__(1024) void row_reduce_kernel(const float* __restric
                                                           float scale, float* __restrict__ out, int out_stride) {
   __shared__ float wsum[16];
   const int i = blockIdx.x;
-  const float acc = member_row_sum(rowval + (int64_t)i * srow, rows, wsum);
+  const float acc = member_row_sum(rowval + (int64_t)i * srow, rows, wsum, blockDim.x);
   if (threadIdx.x == 0) out[(int64_t)i * out_stride] = acc * scale;
 }
 hipError_t row_reduce(const float* rowval, int64_t srow, int P, int rows, float scale, float* out, int out_stride,

@@ -4,10 +4,10 @@
 
 namespace pbt {
 
-// Sum of p[0 .. rows) by one workgroup of row_sum_threads(rows) threads; the total is valid in thread 0.  wsum: 16 floats of LDS.
+// Sum of p[0 .. rows) by the first n = row_sum_threads(rows) threads of a workgroup (64, or all of it); the total is valid in thread 0.  wsum: 16 floats
+// of LDS.
 inline int row_sum_threads(int rows) { return rows > 1024 ? 1024 : 64; }
-__device__ __forceinline__ float member_row_sum(const float* __restrict__ p, int rows, float* wsum) {
-  const int n = blockDim.x;
+__device__ __forceinline__ float member_row_sum(const float* __restrict__ p, int rows, float* wsum, int n) {
   float acc = 0.f;
   int r = threadIdx.x;
   for (; r + 7 * n < rows; r += 8 * n) {

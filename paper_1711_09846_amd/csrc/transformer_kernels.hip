@@ -1033,7 +1033,7 @@ hipError_t xent_from_stats(const float2* stats, const float* target_logit, int P
 __global__ __launch_bounds__(1024) void perplexity_kernel(const float* __restrict__ rowloss, int rows, float* __restrict__ score) {
   __shared__ float wsum[16];
   const int i = blockIdx.x;
-  const float acc = member_row_sum(rowloss + (int64_t)i * rows, rows, wsum);
+  const float acc = member_row_sum(rowloss + (int64_t)i * rows, rows, wsum, blockDim.x);
   if (threadIdx.x == 0) score[i] = -expf(acc / (float)rows);
 }
 hipError_t perplexity_score(const float* rowloss, int P, int rows, float* score, hipStream_t s) {
