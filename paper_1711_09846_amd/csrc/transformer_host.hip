@@ -36,7 +36,7 @@ pbt_status dense(const Ctx& x, const bf16_t* in, int K, int N, int64_t w, int64_
 // A small weight matrix over many rows (the attention output projection: 512 x 512 from 4096 rows) gives 256 x 256 tiles
 // to a quarter of the compute units, and smaller tiles spend the long contraction on loop overhead (12 % of the MFMA peak):
 // its contraction is cut into WGRAD_PARTS pieces, each a tile of its own, and the pieces are added up in order afterwards.
-// (Not for small models: with slabs that go straight into LDS 6 members' 192 x 776 from 720 rows take 11.2 us whole, 12.3 + 4.6 in pieces.)
+// (Not for small models: with slabs that go straight into LDS 6 members' 192 x 776 from 720 rows take 10.2 us whole, 12.3 + 4.6 in pieces.)
 constexpr int WGRAD_PARTS = 4;
 bool wgrad_in_parts(int P, int rows, int K, int N) {
   if (N % 4 || ((int64_t)K * N) % 4) return false;
