@@ -1,6 +1,6 @@
 // The population-batched GEMM that stages its operands through registers: for weight gradients dW = X^T dY with the optimiser in
 // the epilogue (its loads of theta and the optimiser state are what the launch waits for, and half of the first strip's go out ahead of the
-// K loop), and for rows too long for the direct-to-LDS kernel's buffer offsets (gemm_lds.h, which everything else takes).
+// K loop), and, with every other functor, for rows too long for the direct-to-LDS kernel's buffer offsets (gemm_lds.h, which everything else takes).
 //
 // Tiling (wave64): a workgroup of WM x WN wavefronts owns a BM x BN tile of C; each wavefront owns a (BM/WM) x (BN/WN) sub-tile made of 32x32
 // accumulator blocks fed by v_mfma_f32_32x32x16_bf16.  The K loop moves BK wide slabs of A and B from HBM into registers (16-byte loads), then
@@ -160,6 +160,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, Epi
   const int per_member = g.tiles;
   const int member = id / per_member;
   id -= member * per_member;
+  const int tile = id;
   const int group = id / (GROUP_M * g.tiles_n);
   const int first_m = group * GROUP_M;
   const int rows_in_group = g.tiles_m - first_m < GROUP_M ? g.tiles_m - first_m : GROUP_M;
@@ -316,6 +317,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, Epi
   static_assert(WM * WN * 32 * CPITCH * 4 <= SLAB * 2, "C strips must fit the slab LDS");
   float* const Cw = reinterpret_cast<float*>(smem) + wave * 32 * CPITCH;
   fetch_first_strip(EARLY_RUNS, NQ4);
+  float colv[8];   // (a lane handles the same eight columns in every run)
+  if constexpr (!Epilogue::PREFETCH) if constexpr (Epilogue::HAS_COLS) {
+    static_assert(64 % RUNS == 0, "a lane's runs must share their columns");
+    epi.load_cols(n0 + wn * WCOLS + (lane % RUNS) * 8, g.N, colv);
+  }
   __syncthreads();  // every wavefront is done with the slabs
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
@@ -352,16 +358,23 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs g, Epi
         const int m = m0 + wm * (BM / WM) + i * 32 + row, n = n0 + wn * WCOLS + col;
         const float4 lo = *reinterpret_cast<const float4*>(Cw + row * CPITCH + col);
         const float4 hi = *reinterpret_cast<const float4*>(Cw + row * CPITCH + col + 4);
-        if (m < g.M && n < g.N) {
-          const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-          const float none[1] = {0.f};
-          epi.template put<false>(m, n, (int64_t)m * epi.pitch() + n, v, g.N - n < 8 ? g.N - n : 8, none, NoData{});
-        }
+        const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        const bool inside = m < g.M && n < g.N;
+        const int count = inside ? min(g.N - n, 8) : 0;
+        const int64_t o = (int64_t)m * epi.pitch() + n;
+        typename Epilogue::Data data{};
+        if constexpr (Epilogue::HAS_DATA) if (inside) data = epi.load_run(m, n, o, count);
+        if constexpr (Epilogue::ROWWISE) epi.template put_row<false, RUNS>(m, n, v, count, colv, data);
+        else if (inside) epi.template put<false>(m, n, o, v, count, colv, data);
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  if constexpr (!Epilogue::PREFETCH) if constexpr (Epilogue::HAS_FINISH) {
+    __syncthreads();   // (every wavefront is done with its strip)
+    epi.finish(member, tile, g.tiles, reinterpret_cast<float*>(smem));
   }
 }
 
@@ -469,6 +482,7 @@ hipError_t launch_gemm_kernel(const GemmArgs& g, const Epilogue& epi, hipStream_
 template <int BM, int BN, int BK, int WM, int WN, bool DOUBLE_BUF, class Epilogue>
 hipError_t launch_gemm_tile(const GemmArgs& g0, bool a_m_contig, bool b_k_contig, const Epilogue& epi, hipStream_t stream) {
   GemmArgs g = g0;
+  if (g.upper || (g.colsum && (!Epilogue::COLSUM || b_k_contig))) return hipErrorInvalidValue;
   g.tiles_m = (g.M + BM - 1) / BM;
   g.tiles_n = (g.N + BN - 1) / BN;
   g.tiles = g.tiles_m * g.tiles_n;
@@ -484,7 +498,8 @@ hipError_t launch_gemm_tile(const GemmArgs& g0, bool a_m_contig, bool b_k_contig
   return hipErrorInvalidValue;
 }
 
-// Host-side launcher.  Caller guarantees 16-byte alignment of pitches / strides / bases.
+// Host-side launcher.  Caller guarantees 16-byte alignment of pitches / strides / bases.  (Functors other than the optimiser come here for sizes that no
+// workload of this library's descriptions has: one tile shape serves them.)
 template <class Epilogue>
 hipError_t launch_gemm_bf16(const GemmArgs& g, bool a_m_contig, bool b_k_contig, const Epilogue& epi, hipStream_t stream) {
   if constexpr (!Epilogue::PREFETCH) return launch_gemm_tile<64, 64, 64, 2, 2, false, Epilogue>(g, a_m_contig, b_k_contig, epi, stream);

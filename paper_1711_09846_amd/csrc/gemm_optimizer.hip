@@ -1,5 +1,4 @@
 // The weight-gradient GEMM with the optimiser in its epilogue.
-#include "gemm_bf16.h"
 #include "gemm_run.h"
 
 namespace pbt {

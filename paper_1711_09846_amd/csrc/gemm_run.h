@@ -1,5 +1,6 @@
 // From the callers' operands to a kernel launch.
 #pragma once
+#include "gemm_bf16.h"
 #include "gemm_lds.h"
 #include "internal.h"
 
@@ -17,8 +18,11 @@ inline GemmArgs arguments(const GemmOperands& o) {
   g.b_cols = o.b_cols > o.N ? o.b_cols : o.N;
   return g;
 }
+// (rows of 16 million elements are past what a buffer offset spans)
+inline bool gemm_rows_fit_lds(const GemmOperands& o) { return o.lda < GL_MAX_PITCH && o.ldb < GL_MAX_PITCH; }
 template <class E>
 hipError_t run_gemm(const GemmOperands& o, const E& e, hipStream_t s) {
+  if (!gemm_rows_fit_lds(o)) return launch_gemm_bf16(arguments(o), o.a_m_contig, o.b_k_contig, e, s);
   return launch_gemm_lds(arguments(o), o.a_m_contig, o.b_k_contig, e, s);
 }
 
