@@ -868,6 +868,11 @@ static int ft_size(const FusedSmallArgs& a, size_t tiled) {
   const int rounds[FT_N_SIZES] = {fs_rounds(a.P, tiled, 1), fs_rounds(a.P, tiled, held(1)), fs_rounds(a.P, tiled, 2), fs_rounds(a.P, tiled, 4)};
   int size = largest;
   if (rounds[1] < rounds[size]) size = 1;
+  // (Four wavefronts have a block each where no phase has more than four, and a smaller workgroup starts and meets at barriers sooner; past 1024 values its
+  // two fetching wavefronts become the bound.  512 members, us per call with eight and four wavefronts and with four and two: 4-2, Adam, 4 rows, one
+  // step 9.4 and 9.1; 4-8-2, momentum, 16 rows, one step 9.7 and 8.9, 20 steps 77.7 and 70.8; 32-4, momentum, 32 rows, 20 steps 62.6 and 58.8; 64-4, Adam,
+  // 32 rows, one step 10.9 and 11.5.  With a compute unit per member the two are within 2 % of each other either way for one step.)
+  if (size == 1 && rounds[2] == rounds[1] && most <= 4 && a.B * a.dims[0] <= 1024) size = 2;
   if (rounds[2] < rounds[size]) size = 2;
   if (rounds[3] < rounds[size] && most <= 8 && a.B * a.dims[0] <= 2048) size = 3;
   return size;

@@ -141,7 +141,8 @@ def test_a_logit_that_is_infinite_marks_its_member():
 
 
 @pytest.mark.parametrize("opt", [SGD, ADAM, RMS])
-@pytest.mark.parametrize("dims,batch", [([20, 40, 5], 19), ([11, 24, 17, 6], 33), ([13, 9, 10, 8, 7], 40), ([50, 5], 70)], ids=lambda v: str(v))
+@pytest.mark.parametrize("dims,batch", [([20, 40, 5], 19), ([11, 24, 17, 6], 33), ([13, 9, 10, 8, 7], 40), ([50, 5], 70),
+                                        ([4, 8, 2], 16), ([32, 4], 32), ([32, 4], 33)], ids=lambda v: str(v))
 def test_results_do_not_depend_on_the_size_of_the_population(dims, batch, opt):
     """More members than compute units take smaller workgroups (300: two to a compute unit, 1000: four).  A member's draws
     depend on its number alone, so the first eight are bit for bit those of a population of eight."""
