@@ -45,6 +45,8 @@ constexpr int FS_THREADS = 256;
 
 // Forward through all layers for the B rows whose inputs sit in lds_a[0]; leaves logits in
 // lds_z[L-1] and per-row losses in lds_rowloss.
+// (The sums of the plain form are chains of two LDS reads and a multiply-add, in order.  Unrolled eight times the reads of several terms are on their way; as
+// loops of two terms they took 157 or 172 us per step of 8 members 40-50-17 with 128 rows, as the code around them shifted their alignment; 85 now.)
 __device__ __forceinline__ void fs_forward(const FusedSmallArgs& a, float* lds, int nrows) {
   const int tid = threadIdx.x;
   const float* W = lds + a.lds_w;
@@ -57,6 +59,7 @@ __device__ __forceinline__ void fs_forward(const FusedSmallArgs& a, float* lds, 
     for (int idx = tid; idx < nrows * N; idx += FS_THREADS) {
       const int b = idx / N, n = idx - b * N;
       float acc = 0.f;
+#pragma unroll 8
       for (int k = 0; k < K; ++k) acc = fmaf(in[b * (K + 1) + k], Wl[k * N + n], acc);
       acc += bl[n];
       z[b * (N + 1) + n] = acc;
@@ -162,6 +165,7 @@ __global__ __launch_bounds__(FS_THREADS) void fused_small_step_kernel(FusedSmall
         for (int idx = tid; idx < B * K; idx += FS_THREADS) {
           const int k = idx / B, b = idx - k * B;  // lanes along the batch
           float acc = 0.f;
+#pragma unroll 8
           for (int nn = 0; nn < N; ++nn) acc = fmaf(dz[b * (N + 1) + nn], Wl[k * N + nn], acc);
           dprev[b * (K + 1) + k] = acc * act_bwd(zp[b * (K + 1) + k], a.act);
         }
@@ -173,10 +177,12 @@ __global__ __launch_bounds__(FS_THREADS) void fused_small_step_kernel(FusedSmall
         int p;
         if (idx < K * N) {
           const int k = idx / N, nn = idx - k * N;
+#pragma unroll 8
           for (int b = 0; b < B; ++b) g = fmaf(in[b * (K + 1) + k], dz[b * (N + 1) + nn], g);
           p = a.w_off[l] + idx;
         } else {
           const int nn = idx - K * N;
+#pragma unroll 8
           for (int b = 0; b < B; ++b) g += dz[b * (N + 1) + nn];
           p = a.b_off[l] + nn;
         }
