@@ -595,17 +595,26 @@ inline int gl_upper_tiles(int N, TileShape t) {
 // with GELU 128x128 at K = 256 (188; 196) and 256x256 at K = 1024 (380; 440); 6 members' 720 x 192 x 776 take 64x64 (7.9 us; 128x64: 9.7) and 720 x 776 x 192
 // 128x64 (6.6; 64x64: 8.2); one product 1536 x 1536 x 4096 64x64 (43.9; 128x128: 59.5).
 // Rows so long that 256 of them exceed a buffer offset take the 64-row tile.
-inline GlShape gl_choose(int M, int N, int K, int batch, bool heavy, bool square, int64_t pitch) {
+// square: RBF sums, whose tiles are square and whose long epilogue has a slower path for tiles on the diagonal of a symmetric product (upper) and at a ragged
+// edge: GENERAL more for each of those that a compute unit gets.  Held-out passes of 6 members, 1500 rows of 256, with the tiles counted as if all
+// of a symmetric product were formed: 97.4 us, 82.7 now; 16 members, 1024 rows of 256: 93.1, 83.5; 8 members, 1024 rows of 64: 52.7, 48.3.
+inline GlShape gl_choose(int M, int N, int K, int batch, bool heavy, bool square, int64_t pitch, bool upper = false) {
   if (pitch >= GL_MAX_PITCH / 4) return GL_64;
   constexpr double LATENCY[4] = {1.9, 1.09, 0.38, 0.255}, RATE[4] = {1.9, 0.5, 0.42, 0.21}, FIXED[4] = {3.4, 0.97, 0.75, 0.63}, HEAVY[4] = {14.5, 3.0, 4.0, 0.5};
+  constexpr double RBF[4] = {14.5, 3.0, 0.0, 0.8}, GENERAL[4] = {6.0, 3.0, 0.0, 0.5};
   GlShape best = GL_256;
   double least = 0.;
   for (int t = GL_256; t <= GL_64; ++t) {
     const TileShape sh = gl_shape((GlShape)t);
     if (square && sh.bm != sh.bn) continue;
-    const int64_t per_cu = (tile_count(M, N, batch, sh.bm, sh.bn) + 255) / 256;
-    const double slabs = K / 64., fixed = FIXED[t] + (heavy ? HEAVY[t] : 0.);
-    const double cost = slabs * LATENCY[t] + fixed + (double)(per_cu - 1) * (slabs * RATE[t] + fixed);
+    const int64_t tiles_m = (M + sh.bm - 1) / sh.bm, tiles_n = (N + sh.bn - 1) / sh.bn;
+    const int64_t per_cu = ((upper ? gl_upper_tiles(N, sh) : tiles_m * tiles_n) * batch + 255) / 256;
+    const double slabs = K / 64., fixed = FIXED[t] + (square ? RBF[t] : heavy ? HEAVY[t] : 0.);
+    double cost = slabs * LATENCY[t] + fixed + (double)(per_cu - 1) * (slabs * RATE[t] + fixed);
+    if (square) {
+      const int64_t general = (upper ? tiles_n : 0) + (N % sh.bn ? tiles_m : 0) + (!upper && M % sh.bm ? tiles_n : 0);
+      cost += GENERAL[t] * (double)((general * batch + 255) / 256);
+    }
     if (t == GL_256 || cost < least) {
       least = cost;
       best = (GlShape)t;
@@ -654,7 +663,7 @@ template <class Epilogue>
 hipError_t launch_gemm_lds(const GemmArgs& g, bool a_m_contig, bool b_k_contig, const Epilogue& epi, hipStream_t stream) {
   if (g.lda >= GL_MAX_PITCH || g.ldb >= GL_MAX_PITCH) return hipErrorInvalidValue;
   if (g.colsum && (!Epilogue::COLSUM || b_k_contig)) return hipErrorInvalidValue;
-  switch (gl_choose(g.M, g.N, g.K, g.batch, Epilogue::HEAVY, std::is_same_v<Epilogue, EpiRbfSum>, g.lda > g.ldb ? g.lda : g.ldb)) {
+  switch (gl_choose(g.M, g.N, g.K, g.batch, Epilogue::HEAVY, std::is_same_v<Epilogue, EpiRbfSum>, g.lda > g.ldb ? g.lda : g.ldb, g.upper)) {
     case GL_256: return launch_gl_tile<GlTile256>(g, a_m_contig, b_k_contig, epi, stream);
     case GL_128: return launch_gl_tile<GlTile128>(g, a_m_contig, b_k_contig, epi, stream);
     case GL_128x64:

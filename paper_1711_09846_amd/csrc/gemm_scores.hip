@@ -14,7 +14,7 @@ hipError_t gemm_rbf_sum(const GemmOperands& o, const float* na, int64_t sna, con
   // tile count as the launch will choose it (the caller sizes `partial` with gemm_rbf_tiles, an upper bound)
   GemmOperands q = o;
   TileShape t{64, 64};   // of the kernel that takes longer rows, where a symmetric product is formed whole
-  if (gemm_rows_fit_lds(o)) t = gl_shape(gl_choose(o.M, o.N, o.K, o.batch, EpiRbfSum::HEAVY, true, o.lda > o.ldb ? o.lda : o.ldb));
+  if (gemm_rows_fit_lds(o)) t = gl_shape(gl_choose(o.M, o.N, o.K, o.batch, EpiRbfSum::HEAVY, true, o.lda > o.ldb ? o.lda : o.ldb, o.symmetric));
   else q.symmetric = 0;
   *tiles = q.symmetric ? gl_upper_tiles(o.N, t) : ((o.M + t.bm - 1) / t.bm) * ((o.N + t.bn - 1) / t.bn);
   return run_gemm(q, EpiRbfSum{na, sna, nb, snb, inv2d, partial}, s);
