@@ -4,6 +4,7 @@
 
 #include "common.h"
 #include "dropout.h"
+#include "gemm_choose.h"
 #include "optim_math.h"
 
 namespace pbt {
@@ -64,9 +65,6 @@ __device__ __forceinline__ int xcd_remap(int id, int total) {
 // workgroups resident on an XCD at one time (consecutive numbers) form a block of tiles that shares
 // few A and B slabs and keeps them in that XCD's L2.
 constexpr int GROUP_M = 8;
-
-struct TileShape { int bm, bn; };
-inline int64_t tile_count(int M, int N, int batch, int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * batch; }
 
 __device__ __forceinline__ uint4 pack_bf16x8(const float* v) {
   return make_uint4(f2bf_pair(v[0], v[1]), f2bf_pair(v[2], v[3]), f2bf_pair(v[4], v[5]), f2bf_pair(v[6], v[7]));

@@ -30,7 +30,6 @@ typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
 
 constexpr uint32_t GL_OUTSIDE = 0x80000000u;   // a byte offset past the end of every buffer
-constexpr int64_t GL_MAX_PITCH = 1 << 24;      // elements per row below which every offset inside a slab of 64 rows stays under it
 
 typedef __attribute__((address_space(3))) bf16_t lds_bf16_t;
 
@@ -577,51 +576,10 @@ __global__ __launch_bounds__(T::THREADS, T::WAVES_PER_SIMD) void gemm_lds_kernel
 // and 64x64: four wavefronts, three workgroups per compute unit (128x64: two), one's epilogue beside the others' products.
 // (128x256 tiles with four wavefronts, two workgroups per compute unit: 5 to 20 % slower than 256x256 with plain epilogues, no faster than 128x128
 // with heavy ones.)
-enum GlShape { GL_256 = 0, GL_128, GL_128x64, GL_64 };
 typedef GlTile<256, 256, 64, 2, 4, 3, 2, true> GlTile256;
 typedef GlTile<128, 128, 32, 2, 2, 3, 3, false> GlTile128;
 typedef GlTile<128, 64, 64, 2, 2, 3, 3, false> GlTile128x64;
 typedef GlTile<64, 64, 64, 2, 2, 3, 3, false> GlTile64;
-inline TileShape gl_shape(GlShape t) { return t == GL_256 ? TileShape{256, 256} : t == GL_128 ? TileShape{128, 128} : t == GL_128x64 ? TileShape{128, 64} : TileShape{64, 64}; }
-inline int gl_upper_tiles(int N, TileShape t) {
-  const int tiles = (N + t.bm - 1) / t.bm;
-  return tiles * (tiles + 1) / 2;
-}
-
-// The shape with the shortest estimate, from what tiles take on this card (us, about 2 GHz, where the matrix pipes leave it): a compute unit's first tile LATENCY per 64
-// of K, each further one RATE; FIXED per tile for its first loads and a plain epilogue, HEAVY more for a long one (an exponential, a Philox block or
-// another array per element).  Fitted to 60 shapes of all three layouts; the shape it picks is 0.3 % slower than the best one on average, 7 % at most.  At its
-// lines: 16 members' 4096 x 2048 x 512 take 256x256 tiles with a plain epilogue (150 us; 128x128: 192) and 128x128 with dropout (283; 300), 64 members' 2048 x 1024
-// with GELU 128x128 at K = 256 (188; 196) and 256x256 at K = 1024 (380; 440); 6 members' 720 x 192 x 776 take 64x64 (7.9 us; 128x64: 9.7) and 720 x 776 x 192
-// 128x64 (6.6; 64x64: 8.2); one product 1536 x 1536 x 4096 64x64 (43.9; 128x128: 59.5).
-// Rows so long that 256 of them exceed a buffer offset take the 64-row tile.
-// square: RBF sums, whose tiles are square and whose long epilogue has a slower path for tiles on the diagonal of a symmetric product (upper) and at a ragged
-// edge: GENERAL more for each of those that a compute unit gets.  Held-out passes of 6 members, 1500 rows of 256, with the tiles counted as if all
-// of a symmetric product were formed: 97.4 us, 82.7 now; 16 members, 1024 rows of 256: 93.1, 83.5; 8 members, 1024 rows of 64: 52.7, 48.3.
-inline GlShape gl_choose(int M, int N, int K, int batch, bool heavy, bool square, int64_t pitch, bool upper = false) {
-  if (pitch >= GL_MAX_PITCH / 4) return GL_64;
-  constexpr double LATENCY[4] = {1.9, 1.09, 0.38, 0.255}, RATE[4] = {1.9, 0.5, 0.42, 0.21}, FIXED[4] = {3.4, 0.97, 0.75, 0.63}, HEAVY[4] = {14.5, 3.0, 4.0, 0.5};
-  constexpr double RBF[4] = {14.5, 3.0, 0.0, 0.8}, GENERAL[4] = {6.0, 3.0, 0.0, 0.5};
-  GlShape best = GL_256;
-  double least = 0.;
-  for (int t = GL_256; t <= GL_64; ++t) {
-    const TileShape sh = gl_shape((GlShape)t);
-    if (square && sh.bm != sh.bn) continue;
-    const int64_t tiles_m = (M + sh.bm - 1) / sh.bm, tiles_n = (N + sh.bn - 1) / sh.bn;
-    const int64_t per_cu = ((upper ? gl_upper_tiles(N, sh) : tiles_m * tiles_n) * batch + 255) / 256;
-    const double slabs = K / 64., fixed = FIXED[t] + (square ? RBF[t] : heavy ? HEAVY[t] : 0.);
-    double cost = slabs * LATENCY[t] + fixed + (double)(per_cu - 1) * (slabs * RATE[t] + fixed);
-    if (square) {
-      const int64_t general = (upper ? tiles_n : 0) + (N % sh.bn ? tiles_m : 0) + (!upper && M % sh.bm ? tiles_n : 0);
-      cost += GENERAL[t] * (double)((general * batch + 255) / 256);
-    }
-    if (t == GL_256 || cost < least) {
-      least = cost;
-      best = (GlShape)t;
-    }
-  }
-  return best;
-}
 
 template <class T, bool A_KC, bool B_KC, class Epilogue>
 hipError_t launch_gl_kernel(GemmArgs g, const Epilogue& epi, hipStream_t stream) {

@@ -8,6 +8,7 @@
 #include <cstring>
 
 #include "dense_host.h"
+#include "gemm_choose.h"
 
 namespace pbt {
 
@@ -33,17 +34,7 @@ pbt_status dense(const Ctx& x, const bf16_t* in, int K, int N, int64_t w, int64_
   PBT_LAUNCH(x.h, PBT_K_GEMM_FWD, x.s, gemm_bias_act(o, x.W32 + b, x.S_, Z, out, N, (int64_t)x.n * N, act, x.s, site));
   return PBT_OK;
 }
-// A small weight matrix over many rows (the attention output projection: 512 x 512 from 4096 rows) gives 256 x 256 tiles
-// to a quarter of the compute units, and smaller tiles spend the long contraction on loop overhead (12 % of the MFMA peak):
-// its contraction is cut into WGRAD_PARTS pieces, each a tile of its own, and the pieces are added up in order afterwards.
-// (Not for small models: with slabs that go straight into LDS 6 members' 192 x 776 from 720 rows take 10.2 us whole, 12.3 + 4.6 in pieces.)
-constexpr int WGRAD_PARTS = 4;
-bool wgrad_in_parts(int P, int rows, int K, int N) {
-  if (N % 4 || ((int64_t)K * N) % 4) return false;
-  return (int64_t)((K + 255) / 256) * ((N + 255) / 256) * P <= 64 && K >= 256 && N >= 256 &&
-         rows % (WGRAD_PARTS * 64) == 0 && rows / WGRAD_PARTS >= 1024;
-}
-// working memory of one such product: the pieces of the matrix, then those of the column sums
+// working memory of a weight gradient in pieces (gemm_choose.h): the pieces of the matrix, then those of the column sums
 size_t wgrad_parts_bytes(int P, int K, int N) { return (size_t)P * WGRAD_PARTS * ((size_t)K * N + N) * 4; }
 // G[w] = in^T dout, G[b] = column sums of dout
 pbt_status wgrad(const Ctx& x, const bf16_t* in, int K, const bf16_t* dout, int N, int64_t w, int64_t b) {
@@ -58,9 +49,7 @@ pbt_status wgrad(const Ctx& x, const bf16_t* in, int K, const bf16_t* dout, int 
     PBT_HIP(x.h, wgrad_combine(part, colpart, WGRAD_PARTS, x.P, (int64_t)K * N, N, x.G, x.S_, w, b, x.s));
     return PBT_OK;
   }
-  // The column sums are a by-product of the GEMM (its first tile row adds up the dout slabs it stages anyway).
-  // That tile row finishes last and the launch takes 17 % longer (146 -> 171 us), which is still cheaper than a
-  // pass of its own over dout (41 us per layer): 16.78 -> 16.43 ms per population step.
+  // (the column sums are a by-product: the GEMM's first tile row adds up the dout fragments it multiplies anyway)
   GemmOperands o{in, K, (int64_t)x.n * K, true, dout, N, (int64_t)x.n * N, false, K, N, x.n, x.P};
   o.colsum = x.G + b; o.colsum_stride = x.S_;
   PBT_LAUNCH(x.h, PBT_K_GEMM_WGRAD, x.s, gemm_store_f32(o, x.G + w, N, x.S_, x.s));
@@ -289,19 +278,12 @@ pbt_status tf_check_and_plan(const pbt_config* c, Plan* pl, Carver* w) {
   t.o_tokends = w->take(P * (size_t)D.V * 4);
   t.o_tokorder = w->take(P * n * 4);
   t.o_lnpart = w->take(P * (size_t)(LN_FUSED_SLABS > LN_MAX_SLABS ? LN_FUSED_SLABS : LN_MAX_SLABS) * 2 * D.d * 4);
-  // The logits, and over them the pieces of the weight gradients that are formed in parts: room for the largest, but where that would
-  // push a step past the array of pbt_step_static, only for those that fit it (the others are formed whole; 1 member, d_model 256, d_ff 512,
-  // vocabulary 96, 4 x 64 positions: 8.7 MB with room for all).
+  // The logits, and over them the pieces of the weight gradients that are formed in parts: room for the largest of the large ones (whose steps are far
+  // past the array of pbt_step_static); the others' are formed in parts where they fit.
   t.logits_bytes = P * n * D.V * 4;
   const int shapes[5][2] = {{D.d, 3 * D.d}, {D.d, D.d}, {D.d, D.f}, {D.f, D.d}, {D.d, D.V}};   // (rows in, columns out) of every weight matrix
-  size_t largest = t.logits_bytes, fitting = t.logits_bytes;
-  for (const auto& sh : shapes) {
-    if (!wgrad_in_parts((int)P, (int)n, sh[0], sh[1])) continue;
-    const size_t bytes = wgrad_parts_bytes((int)P, sh[0], sh[1]);
-    largest = std::max(largest, bytes);
-    if (w->off + round_up(bytes, BUF_ALIGN) <= PBT_STATIC_SCRATCH_BYTES) fitting = std::max(fitting, bytes);
-  }
-  t.logits_bytes = w->off + round_up(t.logits_bytes, BUF_ALIGN) <= PBT_STATIC_SCRATCH_BYTES ? fitting : largest;
+  for (const auto& sh : shapes)
+    if (wgrad_large_pieces((int)P, (int)n, sh[0], sh[1])) t.logits_bytes = std::max(t.logits_bytes, wgrad_parts_bytes((int)P, sh[0], sh[1]));
   t.o_logits = w->take(t.logits_bytes);
   pl->step_scratch_bytes = w->off;
   t.o_evalrow = w->take(P * (size_t)c->n_eval * D.S * 4);

@@ -166,11 +166,11 @@ def test_acting_agents_share_their_unrolls_memory(P, dims, batch, unroll, latent
 
 @pytest.mark.parametrize("P,vocab,d_model,heads,d_ff,blocks,seq,batch", [
     (2, 256, 128, 2, 512, 1, 32, 8), (2, 512, 128, 2, 512, 1, 32, 8), (1, 96, 256, 4, 512, 1, 64, 4),
-    (5, 120, 32, 1, 16, 4, 8, 45), (1, 40, 384, 6, 16, 1, 56, 6),
+    (5, 120, 32, 1, 16, 4, 8, 45), (1, 40, 384, 6, 16, 1, 56, 6), (1, 16, 64, 2, 128, 1, 64, 32),
 ])
 def test_small_transformers_fit_the_static_array(P, vocab, d_model, heads, d_ff, blocks, seq, batch):
-    """Pieces of weight gradients lie over the logits, and are formed only where they fit; the attention's keep bits and statistics are
-    those of the positions that exist.  (The last array of the held-out pass, 4 bytes per position, is no part of a step.)"""
+    """Pieces of weight gradients need no memory of their own in models as small (they lie over the logits, where they fit); the attention's keep bits and
+    statistics are those of the positions that exist.  (The last array of the held-out pass, 4 bytes per position, is no part of a step.)"""
     wl = workloads.TRANSFORMER.replace(P=P, vocab=vocab, d_model=d_model, heads=heads, d_ff=d_ff, n_blocks=blocks, seq=seq, batch=batch,
                                        n_eval=batch, n_trunc=0)
     scratch = binding.query_sizes(binding.make_config(wl, 1))[1]

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from paper_1711_09846_amd import binding, workloads
+from tests import native
 from tests.harness import TransformerPair
 
 pytestmark = pytest.mark.gpu
@@ -119,16 +120,19 @@ def test_transformer_reduced_weight_gradient_in_parts():
     in four pieces of the contraction and added up (here the attention projections and, with d_ff = 256, the
     feed-forward matrices too)."""
     wl = _reduced(P=2, vocab=64, d_model=256, heads=4, d_ff=256, n_blocks=1, seq=128, batch=32, n_train=64, n_eval=32)
+    assert native.weight_gradient_in_parts(2, 4096, 256, 256)
     pair = TransformerPair(wl, H=np.array([[1e-3, 0.1, 0.05], [5e-4, 0.0, 0.0]], dtype=np.float32))
     worst = _teacher_forced(pair, range(2), range(2), tol_grad=2 * TOL_GRAD_SMALL, tol_w=2 * TOL_GRAD_SMALL)
     print("transformer weight gradient in parts:", {k: float("%.3g" % v) for k, v in worst.items()}, flush=True)
 
 
-@pytest.mark.parametrize("seq,batch", [(72, 10), (32, 8)])
-def test_transformer_small_population_weight_gradient_in_parts(seq, batch):
-    """Few small members: every weight gradient's contraction is cut in four (180 rows each, no whole slab among the
-    remainder; 64 rows each, the fewest), widths that are multiples of 8 and not of 16."""
+@pytest.mark.parametrize("seq,batch,parts", [(72, 10, False), (32, 8, False), (72, 56, True), (32, 128, True)])
+def test_transformer_small_population_weight_gradients(seq, batch, parts):
+    """Few small members, widths that are multiples of 8 and not of 16: every weight gradient as one product with its column sums (720 rows, no whole
+    slab at the end; 256), or its contraction in four pieces (1008 rows each, no whole slab at the end; 1024)."""
     wl = _reduced(P=2, vocab=136, d_model=40, heads=5, d_ff=104, n_blocks=1, seq=seq, batch=batch, n_train=16, n_eval=batch)
+    for K, N in ((40, 120), (40, 40), (40, 104), (104, 40), (40, 136)):
+        assert native.weight_gradient_in_parts(2, seq * batch, K, N) == parts
     pair = TransformerPair(wl, H=np.array([[1e-3, 0.1, 0.05], [5e-4, 0.0, 0.0]], dtype=np.float32))
     # (the bounds of the two tests above, for their reason)
     _teacher_forced(pair, range(2), range(2), tol_grad=2 * TOL_GRAD_SMALL, tol_w=2 * TOL_GRAD_SMALL)
