@@ -469,10 +469,10 @@ template <int BM, int BN, int BK, int WM, int WN, bool DOUBLE_BUF, bool A_M, boo
 hipError_t launch_gemm_kernel(const GemmArgs& g, const Epilogue& epi, hipStream_t stream) {
   constexpr int SLAB_BYTES = (BM + BN) * gemm_pitch(BK) * 2;
   constexpr int LDS_BYTES = SLAB_BYTES * (DOUBLE_BUF ? 2 : 1);
-  auto kernel = gemm_bf16_kernel<BM, BN, BK, WM, WN, A_M, B_K, DOUBLE_BUF, Epilogue>;
+  constexpr auto kernel = gemm_bf16_kernel<BM, BN, BK, WM, WN, A_M, B_K, DOUBLE_BUF, Epilogue>;
   if constexpr (LDS_BYTES > 64 * 1024) {
-    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
-    if (attr != hipSuccess) return attr;
+    const hipError_t e = allow_lds<kernel>(LDS_BYTES);
+    if (e != hipSuccess) return e;
   }
   const int64_t total = (int64_t)g.tiles * g.batch;
   hipLaunchKernelGGL(kernel, dim3((unsigned)total), dim3(WM * WN * 64), LDS_BYTES, stream, g, epi);

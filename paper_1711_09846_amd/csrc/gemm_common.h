@@ -6,6 +6,7 @@
 #include "dropout.h"
 #include "gemm_choose.h"
 #include "optim_math.h"
+#include "per_device.h"
 
 namespace pbt {
 
@@ -65,6 +66,16 @@ __device__ __forceinline__ int xcd_remap(int id, int total) {
 // workgroups resident on an XCD at one time (consecutive numbers) form a block of tiles that shares
 // few A and B slabs and keeps them in that XCD's L2.
 constexpr int GROUP_M = 8;
+
+// A kernel's permission to use more than 64 KB of LDS belongs to the device that is current when it is given.
+template <auto Kernel>
+hipError_t allow_lds(int bytes) {
+  static std::atomic<uint64_t> allowed{0};   // devices that have it
+  int device = 0;
+  const hipError_t e = hipGetDevice(&device);
+  if (e != hipSuccess) return e;
+  return once_per_device(allowed, device, [&] { return hipFuncSetAttribute(reinterpret_cast<const void*>(Kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
+}
 
 __device__ __forceinline__ uint4 pack_bf16x8(const float* v) {
   return make_uint4(f2bf_pair(v[0], v[1]), f2bf_pair(v[2], v[3]), f2bf_pair(v[4], v[5]), f2bf_pair(v[6], v[7]));

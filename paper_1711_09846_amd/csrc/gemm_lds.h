@@ -583,10 +583,10 @@ typedef GlTile<64, 64, 64, 2, 2, 3, 3, false> GlTile64;
 
 template <class T, bool A_KC, bool B_KC, class Epilogue>
 hipError_t launch_gl_kernel(GemmArgs g, const Epilogue& epi, hipStream_t stream) {
-  auto kernel = gemm_lds_kernel<T, A_KC, B_KC, Epilogue>;
+  constexpr auto kernel = gemm_lds_kernel<T, A_KC, B_KC, Epilogue>;
   if constexpr (T::LDS_BYTES > 64 * 1024) {
-    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
-    if (attr != hipSuccess) return attr;
+    const hipError_t e = allow_lds<kernel>(T::LDS_BYTES);
+    if (e != hipSuccess) return e;
   }
   const int64_t total = (int64_t)g.tiles * g.batch;
   g.by_tiles = Divisor(g.tiles);
