@@ -199,9 +199,10 @@ pbt_status gan_check_and_plan(const pbt_config* c, Plan* pl, Carver* w) {
   if (wgan && 3 + c->n_critic > 10) return fail(nullptr, PBT_EUNSUPPORTED, "at most 7 critic updates per step (latent sub-streams 3 .. 9)");
   // critic buffers hold real + generated rows, and for WGAN-GP the interpolated rows behind them
   const int64_t P = c->P, B = c->batch, R = (wgan ? 3 : 2) * B, E = c->n_eval, D = c->dims2[0];
-  // The generator is fixed while the critic is updated, so one forward pass forms the generated rows of all of a step's critic updates: more rows per launch
-  // (32 members, 5 updates of 64 rows, 100-256-512-784: 55 us instead of five passes of 24), and more scratch; where that would push a step past the
-  // array of pbt_step_static, a pass per update.
+  // The generator is fixed while the critic is updated, so one forward pass forms the generated rows of several of a step's critic updates: more rows per launch
+  // (32 members, 5 updates of 64 rows, 100-256-512-784: 55 us instead of five passes of 24), and more working memory: as many updates' as fit the memory
+  // of the held-out pass behind a step with a pass per update, and, where that step fits the array of pbt_step_static, the array too.  So no configuration
+  // needs more memory than with a pass per update.
   auto carve = [&](Carver* at, int n_ahead) {
     g.n_ahead = n_ahead;
     g.o_zin = at->take((size_t)P * n_ahead * B * c->dims[0] * 2);
@@ -225,23 +226,32 @@ pbt_status gan_check_and_plan(const pbt_config* c, Plan* pl, Carver* w) {
     }
     return at->off;
   };
-  Carver trial = *w;
-  const int n_ahead = wgan && (carve(&trial, c->n_critic) <= PBT_STATIC_SCRATCH_BYTES || carve(&(trial = *w), 1) > PBT_STATIC_SCRATCH_BYTES) ? c->n_critic : 1;
-  carve(w, n_ahead);
-  pl->step_scratch_bytes = w->off;
+  Carver held = *w;
+  const size_t one = carve(&held, 1);
   // eval: latents, two ping-pong hidden buffers, generated rows, held-out rows (bf16), norms, partial sums
   int64_t maxh = 8;
   for (int l = 1; l < Lg; ++l) maxh = c->dims[l] > maxh ? c->dims[l] : maxh;
-  g.o_ez = w->take((size_t)P * E * c->dims[0] * 2);
-  g.o_ea[0] = w->take((size_t)P * E * maxh * 2);
-  g.o_ea[1] = w->take((size_t)P * E * maxh * 2);
-  g.o_ex = w->take((size_t)P * E * D * 2);
-  g.o_ey = w->take((size_t)E * D * 2);
-  g.o_nx = w->take((size_t)P * E * 4);
-  g.o_ny = w->take((size_t)E * 4);
-  g.o_pxx = w->take((size_t)gemm_rbf_tiles((int)E, (int)E, (int)P) * P * 4);
-  g.o_pyy = w->take((size_t)gemm_rbf_tiles((int)E, (int)E, 1) * 4);
-  g.o_pxy = w->take((size_t)gemm_rbf_tiles((int)E, (int)E, (int)P) * P * 4);
+  g.o_ez = held.take((size_t)P * E * c->dims[0] * 2);
+  g.o_ea[0] = held.take((size_t)P * E * maxh * 2);
+  g.o_ea[1] = held.take((size_t)P * E * maxh * 2);
+  g.o_ex = held.take((size_t)P * E * D * 2);
+  g.o_ey = held.take((size_t)E * D * 2);
+  g.o_nx = held.take((size_t)P * E * 4);
+  g.o_ny = held.take((size_t)E * 4);
+  g.o_pxx = held.take((size_t)gemm_rbf_tiles((int)E, (int)E, (int)P) * P * 4);
+  g.o_pyy = held.take((size_t)gemm_rbf_tiles((int)E, (int)E, 1) * 4);
+  g.o_pxy = held.take((size_t)gemm_rbf_tiles((int)E, (int)E, (int)P) * P * 4);
+  // (a step and a held-out pass never run at the same time)
+  int n_ahead = wgan ? c->n_critic : 1;
+  auto fits = [&](int n) {
+    Carver trial = *w;
+    const size_t end = carve(&trial, n);
+    return end <= held.off && (one > PBT_STATIC_SCRATCH_BYTES || end <= PBT_STATIC_SCRATCH_BYTES);
+  };
+  while (n_ahead > 1 && !fits(n_ahead)) --n_ahead;
+  carve(w, n_ahead);
+  pl->step_scratch_bytes = w->off;
+  *w = held;
   return PBT_OK;
 }
 
@@ -271,12 +281,15 @@ static pbt_status gan_step_wgan(pbt_handle* h, const float* train_x, uint32_t st
   const int first = c.n_layers, head = c.n_layers + Ld - 1;  // layout indices of the critic's first and output layer
   const uint32_t k0 = (uint32_t)c.seed, k1 = (uint32_t)(c.seed >> 32);
   pbt_status st;
+  int formed = 0;
   for (int k = 0; k < K; ++k) {
-    if (k % g.n_ahead == 0) {
-      PBT_LAUNCH(h, PBT_K_FETCH, s, latent_normal(b.gA[0], P, B, c.dims[0], step, 3 + k, c.seed, s, g.n_ahead));
-      if ((st = forward(h, gnet, gnet.L, g.n_ahead * B, b.gA, nullptr, nullptr, 0, s)) != PBT_OK) return st;
+    const int at = k % g.n_ahead;   // of the updates whose rows are formed together
+    if (at == 0) {
+      formed = std::min(g.n_ahead, K - k);
+      PBT_LAUNCH(h, PBT_K_FETCH, s, latent_normal(b.gA[0], P, B, c.dims[0], step, 3 + k, c.seed, s, formed));
+      if ((st = forward(h, gnet, gnet.L, formed * B, b.gA, nullptr, nullptr, 0, s)) != PBT_OK) return st;
     }
-    hipLaunchKernelGGL(wgan_rows_kernel, dim3(B, P), dim3(128), 0, s, train_x, c.n_train, b.gA[gnet.L], g.n_ahead * B, k % g.n_ahead * B, b.dA[0], B, D, step,
+    hipLaunchKernelGGL(wgan_rows_kernel, dim3(B, P), dim3(128), 0, s, train_x, c.n_train, b.gA[gnet.L], formed * B, at * B, b.dA[0], B, D, step,
                        (uint32_t)(k * B), k0, k1, k == 0 ? 1 : 0, h->st<int32_t>(p.o_t));
     PBT_HIP(h, hipGetLastError());
     if ((st = forward(h, dnet, Ld - 1, R, b.dA, b.dZ, nullptr, 0, s)) != PBT_OK) return st;

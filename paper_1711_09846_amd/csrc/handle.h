@@ -32,7 +32,7 @@ struct GanPlan {
   int64_t g_count, d_begin, d_count;  // ranges of the flat parameter vector
   int col_lr_g, col_lr_d;
   int eval_rows;
-  int n_ahead;   // WGAN-GP: critic updates whose generated rows are formed in one forward pass of the generator (n_critic or 1)
+  int n_ahead;   // WGAN-GP: critic updates whose generated rows are formed in one forward pass of the generator (the last pass may form fewer)
   // scratch offsets (bytes)
   size_t o_zin, o_ga[PBT_MAX_DIMS], o_gz[PBT_MAX_DIMS], o_gdz[PBT_MAX_DIMS];
   size_t o_dx, o_da[PBT_MAX_DIMS], o_dz[PBT_MAX_DIMS], o_ddz[PBT_MAX_DIMS];

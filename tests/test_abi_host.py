@@ -175,3 +175,12 @@ def test_small_transformers_fit_the_static_array(P, vocab, d_model, heads, d_ff,
                                        n_eval=batch, n_trunc=0)
     scratch = binding.query_sizes(binding.make_config(wl, 1))[1]
     assert scratch - -(-P * batch * seq * 4 // 256) * 256 <= binding.STATIC_SCRATCH_BYTES
+
+
+@pytest.mark.parametrize("P,batch,n_eval", [(32, 64, 2048), (2, 64, 8), (4, 16, 200), (1, 768, 64)])
+def test_critic_updates_share_their_working_memory(P, batch, n_eval):
+    """The generated rows of several critic updates are formed together only where they lie in memory that a step with one update needs anyway (the
+    held-out pass's): a caller's buffer does not depend on n_critic."""
+    wl = workloads.GAN_MLP_WGAN_GP.replace(P=P, batch=batch, n_eval=n_eval, n_trunc=0)
+    sizes = {binding.query_sizes(binding.make_config(wl.replace(n_critic=k), 1))[:2] for k in range(1, 8)}
+    assert len(sizes) == 1, sizes

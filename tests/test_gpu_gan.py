@@ -166,10 +166,16 @@ def test_wgan_gp_one_critic_step_gradient_against_the_oracle():
             assert np.linalg.norm(got_b - gb) <= TOL_BF16 * max(np.linalg.norm(gb), 1e-3), (i, l, "b")
 
 
-def test_wgan_gp_generator_pass_per_critic_update():
-    """A step whose scratch fits the library's static array (8 MiB) only with the generated rows of one critic update at a time: 7.0 MB so, 9.4 MB with those
-    of all seven.  It has to be accepted there, and both ways of calling it have to agree with the oracle."""
-    wl = _reduced(P=2).replace(objective="wgan_gp", n_critic=7, gp_weight=10.0, batch=768)
+@pytest.mark.parametrize("batch,n_eval", [
+    (768, 4096),    # a step of 7.0 MB with the rows of one update, 9.4 MB with those of all seven: the static array (8 MiB) takes those of four
+    (48, 96),       # the memory of the held-out pass takes those of four
+    (64, 1),        # or of one
+    (24, 2048),     # or of all
+])
+def test_wgan_gp_generator_passes_of_a_step(batch, n_eval):
+    """Seven critic updates whose generated rows are formed one update, several (the last pass fewer) or all at a time.  The first step is taken in the
+    static array, and both ways of calling it have to agree with the oracle."""
+    wl = _reduced(P=2).replace(objective="wgan_gp", n_critic=7, gp_weight=10.0, batch=batch, n_eval=n_eval)
     pair = GanPair(wl)
     g = pair.gpu
     for s, step in enumerate((g.step_static, g.step)):
