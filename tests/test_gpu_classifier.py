@@ -240,3 +240,19 @@ def test_mlp_wide_bf16_full_size_window():
                     free[i] = copy.deepcopy(pair.ref[i])
     assert n_grad_checks >= 100, n_grad_checks
     print("mlp_wide_bf16 full size:", {k: float("%.3g" % v) for k, v in worst.items()}, "gradient checks:", n_grad_checks, flush=True)
+
+
+def test_input_gradient_on_persistent_tiles():
+    """256 x 256 tiles, several to a workgroup, ragged in every direction, with the derivative of the activation behind the products."""
+    from oracle import nets, classifier as oc
+    from tests import native
+    P, B, dims = 60, 500, [16, 1000, 520, 10]
+    assert native.tile(B, dims[1], dims[2], P, heavy=True) == native.TILE_256 and 2 * 4 * P > 256
+    pair = Pair(workloads.MLP_WIDE.replace(P=P, dims=dims, batch=B, n_train=2048, n_eval=64, n_trunc=0), ref_members=[0, P - 1])
+    pair.gpu.step(pair.d_train, 0)
+    loss = pair.gpu.get(binding.ARR_LOSS)
+    for i in pair.ref_ids:
+        rows = oc.batch_rows(pair.seed, 0, i, B, pair.wl.n_train)
+        loss_ref, grads = nets.classifier_loss_and_grads(oc.params_of(pair.ref[i]), pair.train_x[rows], pair.train_y[rows], pair.wl.act, pair.spec.q)
+        assert abs(loss[i] - loss_ref) <= TOL_BF16 * max(loss_ref, FLOOR_BF16), i
+        assert pair.member_errors(i, binding.ARR_GRAD, None, _flatten_grads(pair, grads))[0] <= TOL_BF16, i

@@ -140,11 +140,13 @@ def test_wgan_gp_reduced_free_running_window():
     print("wgan-gp reduced:", {k: float("%.3g" % v) for k, v in worst.items()}, flush=True)
 
 
-def test_wgan_gp_one_critic_step_gradient_against_the_oracle():
+@pytest.mark.parametrize("batch", [24, 32, 40])
+def test_wgan_gp_one_critic_step_gradient_against_the_oracle(batch):
     """One step with a single critic update and zero learning rates: the gradient buffer holds the critic's
-    gradient (Wasserstein terms + penalty) and then the generator's, compared array by array."""
+    gradient (Wasserstein terms + penalty) and then the generator's, compared array by array.  The critic's bias gradients
+    are column sums over two thirds of the rows: 48 of 72, inside the first slab of 64 and none of the second; 64, just the first; 80, inside the second."""
     from oracle import gan as og
-    wl = _reduced(P=3).replace(objective="wgan_gp", n_critic=1, gp_weight=10.0)
+    wl = _reduced(P=3).replace(objective="wgan_gp", n_critic=1, gp_weight=10.0, batch=batch)
     pair = GanPair(wl)
     g = pair.gpu
     g.set(binding.ARR_HYPER, np.zeros((3, 2), dtype=np.float32))

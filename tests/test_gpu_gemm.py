@@ -57,11 +57,21 @@ def test_batched_gemm(M, N, K, batch, a_m_contig, b_k_contig, out_bf16):
     assert np.max(np.abs(got[:, :, :N] - ref) / (scale + 1e-30)) <= tol
 
 
-@pytest.mark.parametrize("M,N,K,batch", [(64, 64, 8, 3), (65, 72, 63, 5), (1, 1, 1, 2), (128, 136, 33, 300),   # one element past a tile, a K inside one chunk
-                                         (512, 512, 60, 128),      # 256x256 tiles, two per workgroup, one slab that ends inside a chunk
-                                         (512, 256, 1092, 130)])   # the same with many slabs
+@pytest.mark.parametrize("M,N,K,batch", [(64, 64, 8, 3), (65, 72, 63, 5), (1, 1, 1, 2), (128, 136, 33, 300)])   # one element past a tile, a K inside one chunk
 @pytest.mark.parametrize("a_m_contig,b_k_contig,out_bf16", [(0, 0, True), (0, 1, True), (1, 0, False), (1, 1, False)])
 def test_tile_and_slab_edges(M, N, K, batch, a_m_contig, b_k_contig, out_bf16):
+    test_batched_gemm(M, N, K, batch, a_m_contig, b_k_contig, out_bf16)
+
+
+@pytest.mark.parametrize("M,N,K,batch", [(512, 512, 60, 128),      # one slab, which ends inside a chunk
+                                         (508, 508, 196, 128),     # four, ragged in every direction
+                                         (400, 400, 1092, 98)])    # eighteen
+@pytest.mark.parametrize("a_m_contig,b_k_contig,out_bf16", [(0, 0, True), (0, 1, True), (1, 0, False), (1, 1, False)])
+def test_persistent_workgroups_walk_over_several_tiles(M, N, K, batch, a_m_contig, b_k_contig, out_bf16):
+    """256 x 256 tiles, more than one for some workgroup: rings of slabs that go on from one tile to the next, waits behind an epilogue, strips in
+    any slot, the end of K cleared on later tiles."""
+    from tests import native
+    assert native.tile(M, N, K, batch) == native.TILE_256 and -(-M // 256) * -(-N // 256) * batch > 256
     test_batched_gemm(M, N, K, batch, a_m_contig, b_k_contig, out_bf16)
 
 

@@ -152,12 +152,32 @@ def test_transformer_one_kernel_attention_of_padded_sequences(width, seq):
 
 @pytest.mark.parametrize("vocab,seq,batch", [(8, 128, 12), (64, 64, 66), (15368, 32, 4)])
 def test_transformer_embedding_gradient_lists(vocab, seq, batch):
-    """Lists of positions far longer than a wavefront, lists of about its length (either way of ordering them), and a
-    vocabulary eight tokens beyond what is counted at once."""
+    """Lists of positions far longer than a wavefront, lists of about its length, and a vocabulary eight tokens beyond what is counted at once."""
     wl = _reduced(P=2, vocab=vocab, d_model=16, heads=2, d_ff=24, n_blocks=1, seq=seq, batch=batch, n_train=max(16, batch), n_eval=batch, n_trunc=0)
     pair = TransformerPair(wl, H=np.array([[1e-3, 0.0, 0.0], [5e-4, 0.1, 0.05]], dtype=np.float32))
     # (the bounds of the one-kernel attention test above, for its reason)
     _teacher_forced(pair, range(2), range(2), tol_grad=2 * TOL_GRAD_SMALL, tol_w=2 * TOL_GRAD_SMALL)
+
+
+@pytest.mark.parametrize("vocab,seq", [(16, 1024), (40, 128)])
+def test_transformer_embedding_gradient_adds_up_in_order(vocab, seq):
+    """Positions are filed under their tokens in any order; the rows of a token's list have to be added in ascending order all the same.  With
+    one sequence the position table's gradient is the rows themselves, so the token table's is known bit for bit: lists of one position,
+    of up to 64 and of more."""
+    wl = _reduced(P=2, vocab=vocab, d_model=16, heads=2, d_ff=24, n_blocks=1, seq=seq, batch=1, n_train=1, n_eval=1, n_trunc=0)
+    pair = TransformerPair(wl, H=np.array([[1e-3, 0.0, 0.0], [5e-4, 0.2, 0.05]], dtype=np.float32))
+    tokens = pair.pool[0][:seq]
+    counts = np.bincount(tokens, minlength=vocab)
+    assert np.any((counts > 1) & (counts <= 64)) and (seq < 1024 or counts.max() > 64)
+    pair.gpu.step(pair.d_pool, 0)
+    for i in range(2):
+        g = pair.gpu.get(binding.ARR_GRAD, i)
+        lay = pair.gpu.layout
+        table, rows = (g[lay.seg_off[k]:lay.seg_off[k] + lay.seg_len[k]].reshape(-1, 16) for k in range(2))
+        want = np.zeros_like(table)
+        for s in range(seq):
+            want[tokens[s]] += rows[s]
+        assert np.any(rows) and table.tobytes() == want.tobytes(), i
 
 
 def test_transformer_free_running_eval_and_exploit():
