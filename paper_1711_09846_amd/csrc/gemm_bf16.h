@@ -436,31 +436,24 @@ struct EpiOptimizer {
   }
 };
 
-// Tile shapes.  128x128 tiles (four wavefronts, three workgroups per compute unit) unless that leaves
-// the 256 compute units with fewer than four workgroups each to hide latency with; then 128x64.
-// Products of at most 64 rows, or with fewer than two of those per compute unit, take 64x64 tiles.
-// Long contractions of large matrices take 256x256 tiles (eight wavefronts of 128x64, LDS slabs
-// double-buffered, one workgroup per compute unit): the L2 -> LDS traffic per flop halves, which
-// lifts the steady-state rate from about 880 to 1100 TFLOP/s (measured, 4096 x 2048 x K, batch 16);
-// a tile's fixed cost (first loads, epilogue) is no longer hidden by other workgroups on the compute
-// unit, so short contractions stay with 128x128.
+// Tile shapes of the weight gradients with the optimiser in the epilogue: 128x128 (four wavefronts, three workgroups per compute unit) unless that leaves
+// the 256 compute units with fewer than four workgroups each to hide the optimiser's latency with; then 128x64; 64x64 for at most 64 rows or
+// where 128x64 tiles are fewer than two per compute unit; 256x256 (eight wavefronts, LDS slabs double-buffered) for contractions of at least 1024
+// over large matrices.  Per step with the rule, and with 64x64, 128x64, 128x128 and 256x256 tiles throughout (us, Adam):
+//   64 members 256-1024-1024-10, 128 rows     548    542   548   548   636
+//   the same, 1024 rows                      1244   1236  1217  1185  1242
+//   8 members 1024-2048-2048-10, 2048 rows    993   1048  1037   984   994
+//   21 members 200-712-360-7, 75 rows         132    131   132   127   205
+//   16 members 128-512-512-10, 64 rows         77     73    83    93   159
+//   64 members 64-64-64-4, 64 rows             48     48    54    64    82
+//   32 GANs 128-512-512-784, 64 rows          448    417   454   442   571
+//   128 agents 512-256-256-19, 672 rows       436    418   435   421   444
+// (64x64 tiles would take more of the short contractions than the rule gives them, 128x128 the long ones it gives to 256x256.)
 enum GemmTile { TILE_128x64 = 0, TILE_128x128, TILE_256x256, TILE_64x64 };
 inline GemmTile choose_tile(int M, int N, int K, int batch) {
   constexpr int CUS = 256;
-  // (three quarters of the compute units busy with 256x256 tiles still beat all of them on smaller ones)
-  // K = 512 stays with 128x128: timed alone, 256x256 tiles are 5-20 % faster there (4096 rows x 16 members,
-  // N = 512 ... 8192), but inside the transformer step, with the fused epilogues and whatever the previous kernel
-  // left in the caches, the same launches came out 9 % slower (forward class 206 -> 225 us, step +0.6 ms; for the
-  // feed-forward layers alone +0.8 ms, for the vocabulary head alone +0.15 ms).
   if (K >= 1024 && M > 128 && N > 128 && tile_count(M, N, batch, 256, 256) >= CUS * 3 / 4) return TILE_256x256;
-  // (double-buffered 128x128 and 128x64 variants were tried for the long, narrow weight gradients (K >= 2048 with at
-  // most two tiles per compute unit) and for all 128x128 launches: no change for the former, 3 % slower for the latter)
-  // Half a 128-row tile would be clamped rows (a GAN's 64-row batches), or the 128x64 tiles are fewer than two per compute unit: the GAN step
-  // 525 -> 487 us (500 with the line at one per compute unit), 21 members with batches of 75 and ragged widths 129 -> 116, six small
-  // transformers 620 -> 584 (602); populations of the wide MLP and the actor-critic lie above the line.
   if (M <= 64 || tile_count(M, N, batch, 128, 64) < 2 * CUS) return TILE_64x64;
-  // (a column or ten of them, the output layers' weight gradients, waste less of 64 columns than of 128: 15.4 -> 8.4 us for 21 members
-  // with this and the 64-row tile)
   if (tile_count(M, N, batch, 128, 128) < 4 * CUS || N <= 64) return TILE_128x64;
   return TILE_128x128;
 }
@@ -498,8 +491,8 @@ hipError_t launch_gemm_tile(const GemmArgs& g0, bool a_m_contig, bool b_k_contig
   return hipErrorInvalidValue;
 }
 
-// Host-side launcher.  Caller guarantees 16-byte alignment of pitches / strides / bases.  (Functors other than the optimiser come here for sizes that no
-// workload of this library's descriptions has: one tile shape serves them.)
+// Host-side launcher.  Caller guarantees 16-byte alignment of pitches / strides / bases.  (Functors other than the optimiser come here for rows of 2^24
+// elements or more only: one tile shape serves them.)
 template <class Epilogue>
 hipError_t launch_gemm_bf16(const GemmArgs& g, bool a_m_contig, bool b_k_contig, const Epilogue& epi, hipStream_t stream) {
   if constexpr (!Epilogue::PREFETCH) return launch_gemm_tile<64, 64, 64, 2, 2, false, Epilogue>(g, a_m_contig, b_k_contig, epi, stream);
